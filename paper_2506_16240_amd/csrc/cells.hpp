@@ -1,0 +1,607 @@
+// Cell sweeps: MicSA on bit planes with a row's 32 sites of one parity in
+// one register, several sweeps per launch, the neighbours exchanged through
+// LDS.  One form serves a whole small lattice per work-group (any number of
+// sweeps per launch) and tiles of a large one (T sweeps per launch, rings
+// recomputed), for any row length.
+//
+// Planes (per lattice; cell = row * W + w, row = y + Ly z, W = ceil(Kx / 32)
+// words per row and parity; bit b of word w is site k = 32 w + b of the
+// row's parity-p sites, x = 2k + ((p + y + z) & 1)):
+//   spin[l][p][cell]         dem0/dem1[l][p][cell]  the daemon level's bits
+//   bond[l / bdiv][d][cell]  coupling of the even site's bond in direction d
+// With Lx a multiple of 128 these are the multispin planes (msc_kernels.hpp)
+// read as 32-bit words.
+//
+// A thread owns NR cells for the whole launch: both parities' spins, the
+// level bits and all twelve coupling words (six of the even sites, six of
+// the odd ones, gathered once) stay in registers.  A half sweep reads four
+// LDS words (the rows y +- 1 and z +- 1 of the other parity; the x
+// neighbours are the thread's own word and the same word rotated, or one
+// more LDS word where a row has several), runs the bit-sliced Creutz move
+// (24 three-input operations for 32 sites) and publishes one word; one
+// barrier per half sweep.
+//
+// Tiles.  A work-group owns TY rows x TZ planes and computes on EY x EZ,
+// GY = 2T (or 0: the whole side, periodic) more rows on each side and GZ
+// planes likewise: half sweep h of the launch is right on all but the outer
+// h + 1 rows and planes, so the owned ones are right after 2T.  Rows and
+// planes at the edge read themselves in place of a neighbour they do not
+// have; nobody uses what that gives.
+//
+// Refresh levels (Sec. 2.7) depend on the refresh index and temperature
+// only: k_cells_draw draws those of many refreshes in one launch on the
+// whole device, and the sweep reads them (loaded a refresh ahead).
+//
+// Bound: instruction issue where the device is full (a half of 32 sites is
+// about 36 VALU instructions per wave, 24 of them the move), else the chain
+// of one half: LDS reads, the move, the write, a barrier, 0.12 us with one
+// wave and 0.25 us with sixteen.  Measured against the byte-wise LDS sweeps
+// this replaced (us per sweep, refreshes left out, one MI355X): 8^3 0.24
+// (4.5), 16^3 0.30 (4.2 with a logged row), 64 x 32^3 0.51 (9.9), 256 x 64^3
+// 2.0 = 33700 updates/ns; against one or two byte sweeps per launch: 64^3 x 2
+// 1.4 (3.6), 104 x 90 x 70 x 4 2.8 (10.5).
+#pragma once
+#include "bitplane_kernels.hpp"
+#include "byte_kernels.hpp"
+
+namespace micsa {
+
+constexpr int kCellLanes = 1024;   // work-group size at most
+constexpr int kCellMaxNR = 4;      // cells per thread at most
+
+struct CellGeom {
+    Geom g;
+    int32_t W;      // words per row and parity
+    int32_t bdiv;   // lattices that share one set of coupling planes (consecutive ones)
+    int64_t plane;  // cells = rows * W
+};
+
+__device__ __forceinline__ uint32_t cell_mask(int nv) { return nv >= 32 ? 0xFFFFFFFFu : (1u << nv) - 1u; }
+
+// ------------------------------------------------------ 32-site Creutz move
+__device__ __forceinline__ uint32_t maj32(uint32_t a, uint32_t b, uint32_t c)
+{
+    return __builtin_amdgcn_bitop3_b32(a, b, c, 0xE8);
+}
+
+// The move of msc_move_fused on 32 sites: u[0..5] are the unsatisfied-bond
+// bits; returns the accepted flips and updates the level bits.
+__device__ __forceinline__ uint32_t cell_move(const uint32_t (&u)[6], uint32_t& m0, uint32_t& m1)
+{
+    const uint32_t s1 = xor3(u[0], u[1], u[2]), c1 = maj32(u[0], u[1], u[2]);
+    const uint32_t s2 = xor3(u[3], u[4], u[5]), c2 = maj32(u[3], u[4], u[5]);
+    const uint32_t k0 = s1 & s2;
+    const uint32_t u1 = xor3(c1, c2, k0), u2 = maj32(c1, c2, k0);
+    const uint32_t x0 = __builtin_amdgcn_bitop3_b32(s1, m0, s2, 0x69);   // ~(m0 ^ s1 ^ s2) = ~w0
+    const uint32_t cw0 = __builtin_amdgcn_bitop3_b32(s1, m0, s2, 0x48);  // m0 & (s1 ^ s2)
+    const uint32_t w1 = xor3(m1, u1, cw0), cw1 = maj32(m1, u1, cw0);
+    const uint32_t p = w1 & ~x0, r = w1 | ~x0;                               // w1 & w0, w1 | w0
+    const uint32_t acc = __builtin_amdgcn_bitop3_b32(u2, p, cw1, 0x16);  // ~(u2 & cw1) & (u2 ^ cw1 ^ p)
+    const uint32_t v = __builtin_amdgcn_bitop3_b32(u2, r, cw1, 0x48);    // (u2 ^ cw1) & r
+    m0 = (acc & x0) | (~acc & m0);
+    m1 = (acc & v) | (~acc & m1);
+    return acc;
+}
+
+// ------------------------------------------------------------------- draws
+// Both parities' levels of word w of a row: 32 sites of each, 16 Philox
+// calls (nv / 2 for a shorter word).  The bits enter from the top word's end,
+// one add-with-carry each.
+__device__ __forceinline__ void cell_draw(const Geom& g, int row, int w, int nv, uint32_t fam_off, uint32_t rho,
+                                          uint32_t r, uint32_t sw, uint32_t t0, uint32_t t1, uint32_t t2,
+                                          uint32_t (&d0)[2], uint32_t (&d1)[2])
+{
+    const uint32_t base = (uint32_t)(((int64_t)g.Lx * row) >> 2) + fam_off + 16u * (uint32_t)w;
+    uint32_t a0 = 0, a1 = 0, b0 = 0, b1 = 0;  // even-x and odd-x sites
+    auto push = [&](uint32_t& l0, uint32_t& l1, uint32_t u) {
+        const bool p0 = u > t0, p1 = u > t1, p2 = u > t2;
+        l1 = l1 + l1 + (p1 ? 1u : 0u);
+        l0 = l0 + l0 + ((p0 ^ p1 ^ p2) ? 1u : 0u);
+    };
+    for (int c = (nv >> 1) - 1; c >= 0; --c) {
+        const u32x4 o = philox10(base + (uint32_t)c, rho, r, sw, g.key0, g.key1);
+        push(a0, a1, o.v2);
+        push(b0, b1, o.v3);
+        push(a0, a1, o.v0);
+        push(b0, b1, o.v1);
+    }
+    const int y = row % g.Ly, z = row / g.Ly;
+    const bool q = (y + z) & 1;  // parity of the row's even-x sites
+    d0[0] = q ? b0 : a0;
+    d1[0] = q ? b1 : a1;
+    d0[1] = q ? a0 : b0;
+    d1[1] = q ? a1 : b1;
+}
+
+// A slice of drawn refreshes: refresh j of the slice (index rho0 + j) has its
+// level planes at dr0 / dr1 + j * stride words, laid out [lattice][p][cell].
+struct CellDraw {
+    CellGeom cg;
+    uint32_t *dr0, *dr1;
+    const DaemonThresholds* dth;  // the schedule's table
+    int64_t rho0, stride;
+    int32_t n, L;
+};
+
+// Thread per (refresh, cell) of lattice l, grid-stride.  Bound: the Philox
+// multiplications (quarter rate).
+__device__ __forceinline__ void cells_draw_body(const CellDraw& D, int l, int64_t first, int64_t step)
+{
+    const CellGeom& cg = D.cg;
+    const int64_t total = (int64_t)D.n * cg.plane;
+    for (int64_t i = first; i < total; i += step) {
+        const int j = (int)(i / cg.plane);
+        const int64_t cell = i - (int64_t)j * cg.plane;
+        const int row = (int)(cell / cg.W), w = (int)(cell - (int64_t)row * cg.W);
+        const DaemonThresholds th = D.dth[D.rho0 + j];
+        uint32_t d0[2], d1[2];
+        cell_draw(cg.g, row, w, min(32, cg.g.Kx - 32 * w), 0u, (uint32_t)(D.rho0 + j), (uint32_t)(l % cg.g.R),
+                  stream_word(kStreamDaemon, (uint32_t)(l / cg.g.R)), (uint32_t)(th.t0 - 1u), (uint32_t)(th.t1 - 1u),
+                  (uint32_t)(th.t2 - 1u), d0, d1);
+        const int64_t at = (int64_t)j * D.stride + (int64_t)l * 2 * cg.plane + cell;
+        D.dr0[at] = d0[0];
+        D.dr1[at] = d1[0];
+        D.dr0[at + cg.plane] = d0[1];
+        D.dr1[at + cg.plane] = d1[1];
+    }
+}
+
+__global__ void __launch_bounds__(256) k_cells_draw(CellDraw D)
+{
+    cells_draw_body(D, blockIdx.y, (int64_t)blockIdx.x * blockDim.x + threadIdx.x, (int64_t)gridDim.x * blockDim.x);
+}
+
+// ------------------------------------------------------------------ sweeps
+struct CellTile {
+    int32_t TY, TZ;    // owned rows and planes
+    int32_t GY, GZ;    // ring rows and planes on each side (0: the whole side, periodic)
+    int32_t EY, EZ;    // rows and planes computed on
+    int32_t nty, ntz;  // tiles
+    float inv_EYW, inv_W, inv_Ly, inv_Lz;  // reciprocals of EY W, W, Ly, Lz
+};
+
+// a / n for 0 <= a < 2^22 with inv = 1.0f / n: the product is off by less
+// than one, put right by a step either way.
+__device__ __forceinline__ int cell_div(int a, int n, float inv)
+{
+    int q = (int)((float)a * inv);
+    const int r = a - q * n;
+    q += r >= n ? 1 : 0;
+    return r < 0 ? q - 1 : q;
+}
+
+// v mod n for |v| < 2^22.
+__device__ __forceinline__ int cell_wrap(int v, int n, float inv)
+{
+    int r = v - (int)floorf((float)v * inv) * n;
+    r += r < 0 ? n : 0;
+    return r >= n ? r - n : r;
+}
+
+
+struct CellSweep {
+    CellGeom cg;
+    CellTile f;
+    const uint32_t *s_in, *d0_in, *d1_in, *bond;
+    uint32_t *s_out, *d0_out, *d1_out;  // may be the inputs where a tile is a whole lattice
+    const uint32_t *dr0, *dr1;          // drawn levels of the launch's first refresh
+    int64_t dr_stride;              // words from one refresh's levels to the next's
+    unsigned long long* tally;
+    long long* log;      // [row][lattices][2]: unsatisfied bonds and level sum, or null
+    int64_t log_row0;
+    int64_t k0;          // first sweep index
+    int32_t n;           // sweeps
+    int32_t ref0;        // first refresh sweep of the launch, counted from k0 (>= n: none)
+    int32_t period;      // refresh period, 0: before sweeps k with k + 1 a power of two
+    int32_t log_stride;  // sweeps between logged rows
+    int32_t log_first;   // sweeps until the launch's first one
+    int32_t lattices;
+    float inv_bdiv;      // 1 / cg.bdiv
+};
+
+// Sweeps from one refresh (at k) to the next.
+__device__ __forceinline__ int64_t cell_refresh_gap(int64_t k, int32_t P) { return P >= 1 ? P : k + 1; }
+
+// Sum over a wave, in lane 63 (DPP: shifts by 1, 2, 4, 8 within rows of 16,
+// then the rows' totals broadcast upwards).
+__device__ __forceinline__ uint32_t wave_sum_dpp(uint32_t v)
+{
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xF, 0xF, true);
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xF, 0xF, true);
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xF, 0xF, true);
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xF, 0xF, true);
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xA, 0xF, true);  // row 0 -> 1, 2 -> 3
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xC, 0xF, true);  // rows 0, 1 -> 2, 3
+    return v;
+}
+
+// XM: how a row's x neighbours are found.  0: the row is one word (rotate
+// within its Kx bits); 1: several full words (funnel shift with the next or
+// previous one); 2: several words, the last one short.
+template <int NR, int XM>
+__device__ __forceinline__ void cells_body(const CellSweep& J, int l, int ty, int tz, uint32_t* lds, uint32_t* red)
+{
+    constexpr int CAP = NR * kCellLanes;  // LDS words of one parity's plane
+    const CellGeom& cg = J.cg;
+    const Geom& g = cg.g;
+    const CellTile& f = J.f;
+    const int W = XM == 0 ? 1 : cg.W;
+    const int t = threadIdx.x, B = blockDim.x;
+    const int y0 = ty * f.TY, z0 = tz * f.TZ;
+    const int EYW = f.EY * W, C = EYW * f.EZ;
+    const int ownY = min(f.TY, g.Ly - y0), ownZ = min(f.TZ, g.Lz - z0);
+
+    uint32_t s[2][NR], m0[2][NR], m1[2][NR];  // by parity
+    uint32_t j[2][NR][6];                     // couplings: x same k, x shifted, y + 1, y - 1, z + 1, z - 1
+    int iyp[NR], iym[NR], izp[NR], izm[NR];   // LDS words of the neighbours
+    int adj[2][NR];                           // XM > 0: the other x word of each parity's sites
+    uint32_t sa[NR], sb[NR], sc[2][NR], sd[2][NR], nvs[NR];
+    bool qq[NR];
+    uint32_t gi[NR];                          // byte offset of the cell in a plane (fewer than 2^30 cells)
+    uint32_t own = 0, valid = 0;              // bit i: cell i is owned / exists
+    // uniform plane addresses; a lane adds a 32-bit byte offset
+    const int64_t lp = (int64_t)l * 2 * cg.plane;
+    auto at = [](const uint32_t* base, uint32_t off) {
+        return *reinterpret_cast<const uint32_t*>(reinterpret_cast<const char*>(base) + off);
+    };
+    auto put = [](uint32_t* base, uint32_t off, uint32_t v) {
+        *reinterpret_cast<uint32_t*>(reinterpret_cast<char*>(base) + off) = v;
+    };
+    const uint32_t* const bl = J.bond + (int64_t)cell_div(l, cg.bdiv, J.inv_bdiv) * 6 * cg.plane;
+#pragma unroll
+    for (int i = 0; i < NR; ++i) {
+        const int c = t + i * B;
+        const bool ok = c < C;
+        const int cc = ok ? c : 0;  // a lane without a cell reads cell 0's neighbours, writes its own word
+        const int ez = cell_div(cc, EYW, f.inv_EYW), rem = cc - ez * EYW;
+        const int ey = XM == 0 ? rem : cell_div(rem, W, f.inv_W), w = XM == 0 ? 0 : rem - ey * W;
+        const int y = cell_wrap(y0 - f.GY + ey, g.Ly, f.inv_Ly), z = cell_wrap(z0 - f.GZ + ez, g.Lz, f.inv_Lz);
+        iyp[i] = cc + (ey + 1 < f.EY ? W : (f.GY ? 0 : W - EYW));
+        iym[i] = cc + (ey > 0 ? -W : (f.GY ? 0 : EYW - W));
+        izp[i] = cc + (ez + 1 < f.EZ ? EYW : (f.GZ ? 0 : EYW - C));
+        izm[i] = cc + (ez > 0 ? -EYW : (f.GZ ? 0 : C - EYW));
+        const int wn = w + 1 == W ? 0 : w + 1, wp = w == 0 ? W - 1 : w - 1;
+        const int q = (y + z) & 1;
+        qq[i] = q;
+        const int nv = min(32, g.Kx - 32 * w), nvp = min(32, g.Kx - 32 * wp);
+        nvs[i] = (uint32_t)nv;
+        // the shifted x neighbour of a parity-p site is at k + 1 (q ^ p = 1) or k - 1
+        if (XM == 0) {
+            sa[i] = q ? 1u : (uint32_t)(g.Kx - 1);
+        } else {
+            adj[0][i] = cc + (q ? wn : wp) - w;
+            adj[1][i] = cc + (q ? wp : wn) - w;
+            sa[i] = q ? 1u : 0u;
+            sb[i] = 1u - sa[i];
+            sc[0][i] = q ? 0u : (uint32_t)(nvp - 1);
+            sd[0][i] = q ? (uint32_t)(nv - 1) : 0u;
+            sc[1][i] = q ? (uint32_t)(nvp - 1) : 0u;
+            sd[1][i] = q ? 0u : (uint32_t)(nv - 1);
+        }
+        const int ZS = g.Ly * W;  // cells of a plane z
+        const int me = z * ZS + y * W + w;
+        gi[i] = (uint32_t)me << 2;
+#pragma unroll
+        for (int p = 0; p < 2; ++p) {
+            s[p][i] = at(J.s_in + lp + p * cg.plane, gi[i]);
+            m0[p][i] = at(J.d0_in + lp + p * cg.plane, gi[i]);
+            m1[p][i] = at(J.d1_in + lp + p * cg.plane, gi[i]);
+        }
+        auto bd = [&](int d, int cell) { return at(bl + (int64_t)d * cg.plane, (uint32_t)cell << 2); };
+        const uint32_t jpx = bd(kPx, me), jmx = bd(kMx, me);
+        const uint32_t jA = q ? jmx : jpx, jB = q ? jpx : jmx;
+        j[0][i][0] = jA;
+        j[0][i][1] = jB;
+        j[0][i][2] = bd(kPy, me);
+        j[0][i][3] = bd(kMy, me);
+        j[0][i][4] = bd(kPz, me);
+        j[0][i][5] = bd(kMz, me);
+        // an odd site's coupling is its even neighbour's in the opposite direction
+        j[1][i][0] = jA;
+        {
+            uint32_t N = jB;
+            if (XM > 0) {
+                const uint32_t Np = bd(kPx, me + wp - w), Nm = bd(kMx, me + wn - w);
+                N = q ? Np : Nm;
+            }
+            j[1][i][1] = (q ? (jB << 1) | (N >> (nvp - 1)) : (jB >> 1) | (N << (nv - 1))) & cell_mask(nv);
+        }
+        j[1][i][2] = bd(kMy, me + (y + 1 == g.Ly ? W - ZS : W));
+        j[1][i][3] = bd(kPy, me + (y == 0 ? ZS - W : -W));
+        j[1][i][4] = bd(kMz, me + (z + 1 == g.Lz ? ZS - (int)cg.plane : ZS));
+        j[1][i][5] = bd(kPz, me + (z == 0 ? (int)cg.plane - ZS : -ZS));
+        const bool o = ok && (unsigned)(ey - f.GY) < (unsigned)ownY && (unsigned)(ez - f.GZ) < (unsigned)ownZ;
+        own |= (o ? 1u : 0u) << i;
+        valid |= (ok ? 1u : 0u) << i;
+        lds[c] = s[0][i];
+        lds[CAP + c] = s[1][i];
+    }
+    if (t < 4) red[t] = 0;
+    auto levels = [&]() {
+        int v = 0;
+#pragma unroll
+        for (int i = 0; i < NR; ++i) {
+            const int n = __popc(m0[0][i]) + __popc(m0[1][i]) + 2 * (__popc(m1[0][i]) + __popc(m1[1][i]));
+            v += (own >> i) & 1u ? n : 0;
+        }
+        return v;
+    };
+    // valid bits of cell i's word: the same for every cell unless the rows
+    // have a short last word
+    const uint32_t mask01 = XM == 0 ? cell_mask(g.Kx) : 0xFFFFFFFFu;
+    auto msk = [&](int i) { return XM == 2 ? cell_mask((int)nvs[i]) : mask01; };
+    // the levels of the next refresh, loaded ahead of it (with three or four
+    // cells per thread the registers are needed elsewhere: loaded at it)
+    constexpr bool AHEAD = NR <= 2;
+    uint32_t r0[2][NR], r1[2][NR];
+    int64_t dr = 0;
+    auto fetch = [&]() {
+#pragma unroll
+        for (int i = 0; i < NR; ++i)
+#pragma unroll
+            for (int p = 0; p < 2; ++p) {
+                r0[p][i] = at(J.dr0 + dr + lp + p * cg.plane, gi[i]);
+                r1[p][i] = at(J.dr1 + dr + lp + p * cg.plane, gi[i]);
+            }
+    };
+    int64_t ref = J.ref0;
+    if (AHEAD) fetch();  // (with no refresh in the launch the addresses are still good)
+    int taken = levels();  // levels in, minus levels out, of the owned sites
+    lds_barrier();
+
+    // the x neighbour word of parity p's sites other than the one at the same k
+    auto shifted = [&](int i, int p) -> uint32_t {
+        const uint32_t o = s[1 - p][i];
+        if (XM == 0) {
+            const uint32_t c = (uint32_t)g.Kx - sa[i], a = p ? c : sa[i], b = p ? sa[i] : c;
+            return ((o >> a) | (o << b)) & mask01;
+        }
+        const uint32_t N = lds[(1 - p) * CAP + adj[p][i]];
+        const bool up = p ? !qq[i] : qq[i];
+        if (XM == 1) return __builtin_amdgcn_alignbit(up ? N : o, up ? o : N, up ? 1u : 31u);
+        const uint32_t a = p ? sb[i] : sa[i], b = p ? sa[i] : sb[i];
+        return (((o >> a) << b) | ((N >> sc[p][i]) << sd[p][i])) & msk(i);
+    };
+    auto unsat = [&](int i, int p, uint32_t (&u)[6]) {
+        const uint32_t* oth = lds + (1 - p) * CAP;
+        const uint32_t S = s[p][i];
+        u[2] = xor3(S, oth[iyp[i]], j[p][i][2]);
+        u[3] = xor3(S, oth[iym[i]], j[p][i][3]);
+        u[4] = xor3(S, oth[izp[i]], j[p][i][4]);
+        u[5] = xor3(S, oth[izm[i]], j[p][i][5]);
+        u[0] = xor3(S, s[1 - p][i], j[p][i][0]);
+        u[1] = xor3(S, shifted(i, p), j[p][i][1]);
+    };
+    auto half = [&](auto pc) {
+        constexpr int p = decltype(pc)::value;
+#pragma unroll
+        for (int i = 0; i < NR; ++i) {
+            uint32_t u[6];
+            unsat(i, p, u);
+            s[p][i] ^= cell_move(u, m0[p][i], m1[p][i]);
+            lds[p * CAP + t + i * B] = s[p][i];
+        }
+        lds_barrier();
+    };
+    int64_t row = J.log_row0;
+    int pend = -1;  // buffer of `red` holding a logged row not yet written
+    auto flush = [&]() {
+        if (pend >= 0 && t == 0) {
+            J.log[(row * J.lattices + l) * 2 + 0] = (long long)red[2 * pend];
+            J.log[(row * J.lattices + l) * 2 + 1] = (long long)red[2 * pend + 1];
+            red[2 * pend] = red[2 * pend + 1] = 0;
+        }
+        if (pend >= 0) ++row;
+        pend = -1;
+    };
+    int to_log = J.log_first, buf = 0;
+    for (int it = 0; it < J.n; ++it) {
+        if (it == ref) {
+            taken -= levels();
+            if (!AHEAD) fetch();
+#pragma unroll
+            for (int i = 0; i < NR; ++i)
+#pragma unroll
+                for (int p = 0; p < 2; ++p) {
+                    m0[p][i] = r0[p][i];
+                    m1[p][i] = r1[p][i];
+                }
+            taken += levels();
+            ref += cell_refresh_gap(J.k0 + it, J.period);
+            // no branch around the loads: they stay in flight until the next refresh
+            dr += ref < J.n ? J.dr_stride : 0;
+            if (AHEAD) fetch();
+        }
+        half(std::integral_constant<int, 0>{});
+        flush();
+        half(std::integral_constant<int, 1>{});
+        if (J.log && --to_log == 0) {
+            to_log = J.log_stride;
+            // from-scratch energy (every bond once, at its even end) and the
+            // level sum; a wave's sums stay below 2^16
+            uint32_t U = 0, D0 = 0, D1 = 0;
+#pragma unroll
+            for (int i = 0; i < NR; ++i) {
+                uint32_t u[6];
+                unsat(i, 0, u);
+                uint32_t n = 0;
+#pragma unroll
+                for (int d = 0; d < 6; ++d) n += (uint32_t)__popc(u[d] & msk(i));
+                U += (valid >> i) & 1u ? n : 0u;
+                D0 += (valid >> i) & 1u ? (uint32_t)(__popc(m0[0][i]) + __popc(m0[1][i])) : 0u;
+                D1 += (valid >> i) & 1u ? (uint32_t)(__popc(m1[0][i]) + __popc(m1[1][i])) : 0u;
+            }
+            const uint32_t v = wave_sum_dpp(U | ((D0 + 2 * D1) << 16));
+            if ((t & 63) == 63) {
+                atomicAdd(&red[2 * buf], v & 0xFFFFu);
+                atomicAdd(&red[2 * buf + 1], v >> 16);
+            }
+            pend = buf;
+            buf ^= 1;
+        }
+    }
+    if (J.log) {
+        lds_barrier();
+        flush();
+    }
+    taken -= levels();
+#pragma unroll
+    for (int i = 0; i < NR; ++i) {
+        if (!((own >> i) & 1u)) continue;
+#pragma unroll
+        for (int p = 0; p < 2; ++p) {
+            put(J.s_out + lp + p * cg.plane, gi[i], s[p][i]);
+            put(J.d0_out + lp + p * cg.plane, gi[i], m0[p][i]);
+            put(J.d1_out + lp + p * cg.plane, gi[i], m1[p][i]);
+        }
+    }
+    // a wave's sum fits 32 bits (at most 64 lanes x 4 cells x 64 sites x 3, per refresh met)
+    const int sum = (int)wave_sum_dpp((uint32_t)taken);
+    if ((t & 63) == 63 && sum != 0)
+        atomicAdd(&J.tally[(int64_t)l * kSlots + ((ty + tz * f.nty + (t >> 6)) % kSlots)],
+                  (unsigned long long)(4ll * sum));
+}
+
+// Grid (tiles along y, tiles along z, lattices).
+template <int NR, int XM>
+__global__ void __launch_bounds__(kCellLanes) k_cells_sweep(CellSweep J)
+{
+    __shared__ uint32_t lds[2 * NR * kCellLanes];
+    __shared__ uint32_t red[4];
+    cells_body<NR, XM>(J, blockIdx.z, blockIdx.x, blockIdx.y, lds, red);
+}
+
+// ------------------------------------------------- planes <-> other layouts
+// Bit 0 of each byte of a word as four bits, and back.
+__device__ __forceinline__ uint32_t gather4(uint32_t w) { return ((w & 0x01010101u) * 0x01020408u) >> 24; }
+__device__ __forceinline__ uint32_t spread4(uint32_t n) { return ((n & 0xFu) * 0x00204081u) & 0x01010101u; }
+
+// Byte layout -> planes, thread per (lattice, cell): 32 bytes of each parity.
+// Coupling planes are written by the first lattice of each set.
+__global__ void __launch_bounds__(256) k_cells_pack(CellGeom cg, const uint8_t* __restrict__ spin_b,
+                                                    const uint8_t* __restrict__ dem_b, uint32_t* __restrict__ spin,
+                                                    uint32_t* __restrict__ d0, uint32_t* __restrict__ d1,
+                                                    uint32_t* __restrict__ bond)
+{
+    const Geom& g = cg.g;
+    const int64_t cell = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int l = blockIdx.y;
+    if (cell >= cg.plane) return;
+    const int64_t row = cell / cg.W;
+    const int w = (int)(cell - row * cg.W);
+    const int n4 = min(32, g.Kx - 32 * w) >> 2;
+    const int64_t h = row * g.Kx + 32 * w;
+    const uint32_t *ev = reinterpret_cast<const uint32_t*>(spin_b + (int64_t)l * 2 * g.Nh + h),
+                   *od = reinterpret_cast<const uint32_t*>(spin_b + ((int64_t)l * 2 + 1) * g.Nh + h),
+                   *me = reinterpret_cast<const uint32_t*>(dem_b + (int64_t)l * 2 * g.Nh + h),
+                   *mo = reinterpret_cast<const uint32_t*>(dem_b + ((int64_t)l * 2 + 1) * g.Nh + h);
+    uint32_t se = 0, so = 0, e0 = 0, e1 = 0, o0 = 0, o1 = 0, jb[6] = {0, 0, 0, 0, 0, 0};
+#pragma unroll
+    for (int v = 0; v < 8; ++v) {
+        if (v >= n4) break;
+        const uint32_t a = ev[v], b = od[v], c = me[v], d = mo[v];
+        se |= gather4(a) << (4 * v);
+        so |= gather4(b) << (4 * v);
+        e0 |= gather4(c) << (4 * v);
+        e1 |= gather4(c >> 1) << (4 * v);
+        o0 |= gather4(d) << (4 * v);
+        o1 |= gather4(d >> 1) << (4 * v);
+#pragma unroll
+        for (int k = 0; k < 6; ++k) jb[k] |= gather4(a >> (1 + k)) << (4 * v);
+    }
+    const int64_t at = (int64_t)l * 2 * cg.plane + cell;
+    spin[at] = se;
+    spin[at + cg.plane] = so;
+    d0[at] = e0;
+    d0[at + cg.plane] = o0;
+    d1[at] = e1;
+    d1[at + cg.plane] = o1;
+    if (l % cg.bdiv == 0)
+#pragma unroll
+        for (int k = 0; k < 6; ++k) bond[((int64_t)(l / cg.bdiv) * 6 + k) * cg.plane + cell] = jb[k];
+}
+
+__global__ void __launch_bounds__(256) k_cells_unpack(CellGeom cg, const uint32_t* __restrict__ spin,
+                                                      const uint32_t* __restrict__ d0, const uint32_t* __restrict__ d1,
+                                                      const uint32_t* __restrict__ bond, uint8_t* __restrict__ spin_b,
+                                                      uint8_t* __restrict__ dem_b)
+{
+    const Geom& g = cg.g;
+    const int64_t cell = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int l = blockIdx.y;
+    if (cell >= cg.plane) return;
+    const int64_t row = cell / cg.W;
+    const int w = (int)(cell - row * cg.W);
+    const int n4 = min(32, g.Kx - 32 * w) >> 2;
+    const int64_t h = row * g.Kx + 32 * w;
+    uint32_t *ev = reinterpret_cast<uint32_t*>(spin_b + (int64_t)l * 2 * g.Nh + h),
+             *od = reinterpret_cast<uint32_t*>(spin_b + ((int64_t)l * 2 + 1) * g.Nh + h),
+             *me = reinterpret_cast<uint32_t*>(dem_b + (int64_t)l * 2 * g.Nh + h),
+             *mo = reinterpret_cast<uint32_t*>(dem_b + ((int64_t)l * 2 + 1) * g.Nh + h);
+    const int64_t at = (int64_t)l * 2 * cg.plane + cell;
+    const uint32_t se = spin[at], so = spin[at + cg.plane];
+    const uint32_t e0 = d0[at], o0 = d0[at + cg.plane];
+    const uint32_t e1 = d1[at], o1 = d1[at + cg.plane];
+    uint32_t jb[6];
+#pragma unroll
+    for (int k = 0; k < 6; ++k) jb[k] = bond[((int64_t)(l / cg.bdiv) * 6 + k) * cg.plane + cell];
+#pragma unroll
+    for (int v = 0; v < 8; ++v) {
+        if (v >= n4) break;
+        uint32_t a = spread4(se >> (4 * v));
+#pragma unroll
+        for (int k = 0; k < 6; ++k) a |= spread4(jb[k] >> (4 * v)) << (1 + k);
+        ev[v] = a;
+        od[v] = spread4(so >> (4 * v));
+        me[v] = spread4(e0 >> (4 * v)) | (spread4(e1 >> (4 * v)) << 1);
+        mo[v] = spread4(o0 >> (4 * v)) | (spread4(o1 >> (4 * v)) << 1);
+    }
+}
+
+// -------------------------------------------------------------- reductions
+// KIND 0: unsatisfied bonds of lattice l (each at its even end); 1: level
+// sum; 2: sites where replicas a and b of sample blockIdx.y differ.  Grid
+// (blocks, lattices or samples), grid-stride over the cells.
+template <int KIND>
+__global__ void __launch_bounds__(256) k_cells_count(CellGeom cg, const uint32_t* __restrict__ spin,
+                                                     const uint32_t* __restrict__ d0, const uint32_t* __restrict__ d1,
+                                                     const uint32_t* __restrict__ bond, int a, int b,
+                                                     unsigned long long* __restrict__ out)
+{
+    const Geom& g = cg.g;
+    const int l = blockIdx.y;
+    const int64_t lp = (int64_t)l * 2 * cg.plane, lb = (int64_t)(l / cg.bdiv) * 6 * cg.plane;
+    const int64_t step = (int64_t)gridDim.x * blockDim.x;
+    int v = 0;
+    for (int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; c < cg.plane; c += step) {
+        if (KIND == 1) {
+            v += __popc(d0[lp + c]) + __popc(d0[lp + cg.plane + c]) +
+                 2 * (__popc(d1[lp + c]) + __popc(d1[lp + cg.plane + c]));
+        } else if (KIND == 2) {
+            const int64_t pa = ((int64_t)l * g.R + a) * 2 * cg.plane + c, pb = ((int64_t)l * g.R + b) * 2 * cg.plane + c;
+            v += __popc(spin[pa] ^ spin[pb]) +
+                 __popc(spin[pa + cg.plane] ^ spin[pb + cg.plane]);
+        } else {
+            const int row = (int)(c / cg.W), w = (int)(c - (int64_t)row * cg.W);
+            const int z = row / g.Ly, y = row - z * g.Ly, q = (y + z) & 1;
+            const int nv = min(32, g.Kx - 32 * w);
+            auto od = [&](int yy, int zz, int ww) {
+                return spin[lp + cg.plane + ((int64_t)zz * g.Ly + yy) * cg.W + ww];
+            };
+            auto bd = [&](int d) { return bond[lb + (int64_t)d * cg.plane + c]; };
+            const uint32_t S = spin[lp + c], O = od(y, z, w);
+            const int wn = w + 1 == cg.W ? 0 : w + 1, wp = w == 0 ? cg.W - 1 : w - 1;
+            const uint32_t N = od(y, z, q ? wn : wp);
+            const uint32_t X = q ? (O >> 1) | (N << (nv - 1)) : (O << 1) | (N >> (min(32, g.Kx - 32 * wp) - 1));
+            const uint32_t m = cell_mask(nv);
+            v += __popc((S ^ O ^ bd(q ? kMx : kPx)) & m) + __popc((S ^ X ^ bd(q ? kPx : kMx)) & m) +
+                 __popc((S ^ od(y + 1 == g.Ly ? 0 : y + 1, z, w) ^ bd(kPy)) & m) +
+                 __popc((S ^ od(y == 0 ? g.Ly - 1 : y - 1, z, w) ^ bd(kMy)) & m) +
+                 __popc((S ^ od(y, z + 1 == g.Lz ? 0 : z + 1, w) ^ bd(kPz)) & m) +
+                 __popc((S ^ od(y, z == 0 ? g.Lz - 1 : z - 1, w) ^ bd(kMz)) & m);
+        }
+    }
+    block_add(out + (int64_t)l * kSlots, v);
+}
+
+}  // namespace micsa

@@ -18,7 +18,7 @@
 
 #include "bitplane_kernels.hpp"
 #include "bitplane_sweep.hpp"
-#include "byte_slab.hpp"
+#include "cells.hpp"
 #include "fused_kernels.hpp"
 #include "fused2_kernels.hpp"
 #include "msc_kernels.hpp"
@@ -46,6 +46,16 @@ struct Schedule {
     std::vector<double> table;
 };
 
+// How the cell sweep runs a context's lattices.
+struct CellPlan {
+    bool ok = false;
+    CellTile f{};
+    int nr = 1, xm = 0;
+    unsigned block = 64;
+    int sweeps = 0;   // sweeps per launch of a tiled lattice; 0: the tile is the lattice, any number
+    double cost = 0;  // estimated cycles per sweep of every lattice
+};
+
 }  // namespace
 
 struct micsa_ctx {
@@ -61,10 +71,6 @@ struct micsa_ctx {
     uint8_t* spin = nullptr;  // [L][2][Nh] current
     uint8_t* dem = nullptr;   // [L][2][Nh] current
     uint8_t* spin_alt = nullptr;
-    // two-sweep slab launches: levels of later refreshes drawn ahead (shape of
-    // dem) and the sweep index each holds the levels of (-1: none)
-    uint8_t* sdr[2] = {nullptr, nullptr};
-    int64_t sdr_k[2] = {-1, -1};
     uint8_t* dem_alt = nullptr;
     // bit-plane layout (MICSA_LAYOUT_BITPLANE): 64 samples per word
     bool bit = false;
@@ -104,10 +110,18 @@ struct micsa_ctx {
     // walkers on the fused sweep: parity of a forward-X wandering the stored
     // daemons still owe (applied by the next fused sweep on load), or -1
     int32_t pend_wander = -1;
-    // the multispin planes hold the state and the byte arrays are stale (a
-    // multispin call leaves its planes live; whatever reads or writes the
-    // byte arrays unpacks them first)
-    bool msc_live = false;
+    // where the state is: in the layout's own arrays (home), in the bit planes
+    // (ms, md0, md1: multispin and cell sweeps leave it there), or in both.
+    // Whatever reads the home arrays unpacks the planes first, whatever
+    // writes them makes the planes stale.
+    bool home_ok = true, planes_ok = false;
+    // cell sweeps (cells.hpp): launch plan, planes in one allocation (null
+    // where the multispin sweep owns them), and the levels of cdr_n refreshes
+    // from index cdr_rho0 on, drawn ahead (room for cdr_cap of them)
+    CellPlan plan;
+    void* parena = nullptr;
+    uint32_t *cdr0 = nullptr, *cdr1 = nullptr;
+    int64_t cdr_rho0 = 0, cdr_n = 0, cdr_cap = 0;
     // refresh sweep whose levels the multispin draw planes hold, drawn during
     // an earlier call (-1: none)
     int64_t msc_drawn = -1;
@@ -145,7 +159,8 @@ int fail(micsa_ctx* c, int status, const std::string& msg)
     return status;
 }
 
-int settle_msc(micsa_ctx* c);
+int need_home(micsa_ctx* c);
+int own_home(micsa_ctx* c);
 
 #define HIP_TRY(ctx, call)                                                                       \
     do {                                                                                         \
@@ -562,8 +577,10 @@ bool use_msc(const micsa_ctx* c, int64_t n = kMscMinSweeps, int32_t algo = MICSA
     return c->kernel_opt == MICSA_KERNEL_AUTO && !use_resident(c) && n >= kMscMinSweeps;
 }
 
-// One launch per sweep with a z plane per work-group (byte_slab.hpp): a
-// plane's 4-site words fit one work-group.
+// The slab variant (a lattice too large for one work-group and too narrow
+// for the fused sweep) is asked for where a plane has at most this many
+// 4-site words.
+constexpr int kSlabLanes = 1024;
 bool slab_eligible(const micsa_ctx* c)
 {
     return !c->bit && c->gamma == 1 && (int64_t)c->p.Ly * (c->p.Lx / 8) <= kSlabLanes;
@@ -580,149 +597,11 @@ bool use_slab(const micsa_ctx* c)
     return c->kernel_opt == MICSA_KERNEL_AUTO && !use_resident(c) && !use_fused(c);
 }
 
-// One slab sweep.  refresh: draw the levels in the kernel; drawn (not
-// null): read them from levels drawn ahead in place of the stored daemons.
-int launch_slab_sweep(micsa_ctx* c, bool refresh, int64_t rho, double T, const uint8_t* drawn = nullptr)
-{
-    const int P = c->p.Ly * (c->p.Lx / 8);
-    const dim3 grid((unsigned)(c->L * c->p.Lz));
-    const unsigned block = (unsigned)((P + 63) / 64 * 64);
-    const size_t lds = (size_t)8 * P * 4;
-    const uint8_t* dem_in = drawn ? drawn : c->dem;
-    {
-        TimedLaunch t(c, kTimeSweep);
-        if (refresh && !drawn)
-            k_micsa_slab<true><<<grid, block, lds, c->stream>>>(c->g, c->spin, dem_in, c->spin_alt, c->dem_alt,
-                                                                c->tally, (uint32_t)rho, daemon_thresholds(T));
-        else
-            k_micsa_slab<false><<<grid, block, lds, c->stream>>>(c->g, c->spin, dem_in, c->spin_alt, c->dem_alt,
-                                                                 c->tally, 0u, DaemonThresholds{0, 0, 0});
-    }
-    const int st = check_launch(c, "k_micsa_slab");
-    if (st) return st;
-    std::swap(c->spin, c->spin_alt);
-    std::swap(c->dem, c->dem_alt);
-    return MICSA_OK;
-}
-
-// Sweeps k and k + 1 in one slab launch.  refreshA / refreshB: k / k + 1 are
-// refresh points whose levels the kernel draws; drawnA (not null): the
-// levels of sweep k, drawn ahead, read in place of the stored daemons;
-// next (not null, no refresh in the launch): also draw the levels of refresh
-// rhoN at temperature TN into next.
-int launch_slab_sweep2(micsa_ctx* c, bool refreshA, int64_t rhoA, double TA, bool refreshB, int64_t rhoB, double TB,
-                       const uint8_t* drawnA, uint8_t* next, int64_t rhoN, double TN)
-{
-    if (drawnA) refreshA = false;
-    if (refreshA || refreshB) next = nullptr;
-    const int P = c->p.Ly * (c->p.Lx / 8);
-    const dim3 grid((unsigned)(c->L * c->p.Lz));
-    const unsigned block = (unsigned)((P + 63) / 64 * 64);
-    const size_t lds = (size_t)24 * P * 4;
-    const SlabRefresh ra{(uint32_t)rhoA, refreshA ? daemon_thresholds(TA) : DaemonThresholds{0, 0, 0}};
-    const SlabRefresh rb{(uint32_t)rhoB, refreshB ? daemon_thresholds(TB) : DaemonThresholds{0, 0, 0}};
-    const SlabRefresh rn{(uint32_t)rhoN, next ? daemon_thresholds(TN) : DaemonThresholds{0, 0, 0}};
-    const auto kern = next ? k_micsa_slab2<false, false, true>
-                           : refreshA ? (refreshB ? k_micsa_slab2<true, true, false> : k_micsa_slab2<true, false, false>)
-                                      : (refreshB ? k_micsa_slab2<false, true, false> : k_micsa_slab2<false, false, false>);
-    if (lds > 64 * 1024 &&
-        hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
-        return fail(c, MICSA_EHIP, "k_micsa_slab2 LDS attribute");
-    {
-        TimedLaunch t(c, kTimeSweep);
-        kern<<<grid, block, lds, c->stream>>>(c->g, c->spin, drawnA ? drawnA : c->dem, c->spin_alt, c->dem_alt,
-                                              c->tally, ra, rb, rn, next);
-    }
-    const int st = check_launch(c, "k_micsa_slab2");
-    if (st) return st;
-    std::swap(c->spin, c->spin_alt);
-    std::swap(c->dem, c->dem_alt);
-    return MICSA_OK;
-}
-
-// Two sweeps per slab launch pay off while the one-sweep launch leaves
-// compute units idle (fewer planes than units, e.g. L = 64 with 2
-// replicas): they halve the launches on a latency-bound path, at twice the
-// arithmetic per sweep.  A full grid keeps one sweep per launch.
+// The slab variant's name (micsa_kernel_name): "2" while the lattices have
+// fewer planes than the device has compute units.  Both run the cell sweep.
 bool slab_pairs(const micsa_ctx* c)
 {
     return c->temporal == 2 && (int64_t)c->L * c->p.Lz < (c->cus > 0 ? c->cus : 256);
-}
-
-int64_t next_refresh(const micsa_ctx* c, int64_t from, int64_t end);
-
-constexpr int64_t kSlabDrawWindow = 1024;  // how far ahead a launch looks for the next refresh
-
-// The two buffers of levels drawn ahead for two-sweep slab launches.
-int slab_alloc(micsa_ctx* c)
-{
-    if (c->sdr[0]) return MICSA_OK;
-    const size_t bytes = (size_t)c->L * 2 * (size_t)c->g.Nh;
-    for (auto& q : c->sdr)
-        if (hipMalloc(&q, bytes) != hipSuccess) {
-            (void)hipGetLastError();
-            for (auto& f : c->sdr)
-                if (f) (void)hipFree(f);
-            c->sdr[0] = c->sdr[1] = nullptr;
-            return fail(c, MICSA_ENOMEM, "slab drawn levels");
-        }
-    c->sdr_k[0] = c->sdr_k[1] = -1;
-    return MICSA_OK;
-}
-
-// MicSA sweeps k .. k + n - 1 on the slab sweep (gamma = 1): two per launch
-// where slab_pairs() holds, else one.  With OPT_DRAW_AHEAD (default) a
-// two-sweep launch with no refresh of its own also draws the levels of the
-// next refresh of the schedule (each work-group its own plane) into one of
-// two buffers; the launch that starts at that refresh, in this call or a
-// later one, reads them, and the buffer it reads is never the one its own
-// draw writes.  Other refreshes are drawn inside the refresh launch.
-int sweep_slab(micsa_ctx* c, int64_t n)
-{
-    const int64_t k_end = c->k + n;
-    const bool pairs = slab_pairs(c);
-    const bool ahead = c->draw_ahead != 0 && pairs;
-    int st;
-    if (ahead && (st = slab_alloc(c))) return st;
-    while (c->k < k_end) {
-        const int64_t k = c->k;
-        const bool refresh = is_refresh(k, c->sched.period);
-        const int64_t rho = refresh_index(k, c->sched.period);
-        const double T = temperature(c->sched, rho);
-        if (!(T > 0.0) || !std::isfinite(T)) return fail(c, MICSA_ERANGE, "no temperature for this refresh");
-        int rd = -1;  // buffer holding this refresh's levels
-        if (refresh && ahead)
-            for (int b = 0; b < 2; ++b)
-                if (c->sdr_k[b] == k) rd = b;
-        const uint8_t* drawn = rd >= 0 ? c->sdr[rd] : nullptr;
-        if (pairs && k + 1 < k_end) {
-            const bool refreshB = is_refresh(k + 1, c->sched.period);
-            const int64_t rhoB = refresh_index(k + 1, c->sched.period);
-            const double TB = temperature(c->sched, rhoB);
-            if (!(TB > 0.0) || !std::isfinite(TB)) return fail(c, MICSA_ERANGE, "no temperature for this refresh");
-            // the next refresh after this pair, if no buffer holds it yet
-            uint8_t* next = nullptr;
-            int wb = -1;
-            int64_t kn = -1, rhoN = 0;
-            double TN = 0.0;
-            if (ahead && !(refresh && !drawn) && !refreshB &&
-                (kn = next_refresh(c, k + 2, std::min(c->sched.n_sweeps, k + 2 + kSlabDrawWindow))) >= 0 &&
-                c->sdr_k[0] != kn && c->sdr_k[1] != kn) {
-                wb = rd >= 0 ? 1 - rd : (c->sdr_k[0] < c->sdr_k[1] ? 0 : 1);
-                rhoN = refresh_index(kn, c->sched.period);
-                TN = temperature(c->sched, rhoN);
-                if (!(TN > 0.0) || !std::isfinite(TN)) return fail(c, MICSA_ERANGE, "no temperature for this refresh");
-                next = c->sdr[wb];
-            }
-            if ((st = launch_slab_sweep2(c, refresh, rho, T, refreshB, rhoB, TB, drawn, next, rhoN, TN))) return st;
-            if (next) c->sdr_k[wb] = kn;
-            c->k = k + 2;
-        } else {
-            if ((st = launch_slab_sweep(c, refresh, rho, T, drawn))) return st;
-            c->k = k + 1;
-        }
-    }
-    return MICSA_OK;
 }
 
 bool use_fused(const micsa_ctx* c)
@@ -768,8 +647,21 @@ FusedTile choose_tile(const micsa_ctx* c)
     return f;
 }
 
+void* dev_alloc(size_t bytes);
+
+// The alternate byte arrays (allocated with the context where a path that
+// needs them is the default, else by the first call that takes one).
+int need_alt(micsa_ctx* c)
+{
+    const size_t state = (size_t)c->L * 2 * (size_t)c->g.Nh;
+    if (!c->spin_alt) c->spin_alt = static_cast<uint8_t*>(dev_alloc(state));
+    if (!c->dem_alt) c->dem_alt = static_cast<uint8_t*>(dev_alloc(state * (size_t)c->gamma));
+    return c->spin_alt && c->dem_alt ? MICSA_OK : fail(c, MICSA_ENOMEM, "alternate state buffers");
+}
+
 int launch_fused_sweep(micsa_ctx* c, bool refresh, int64_t rho, double T, int wander = -1)
 {
+    if (int st = need_alt(c)) return st;
     const FusedTile f = choose_tile(c);
     const int lanes = (f.TY + 4) * f.NC;
     const int block = (lanes + 63) / 64 * 64;
@@ -815,6 +707,7 @@ bool sweep2_eligible(const micsa_ctx* c) { return kSweep2Lanes / (c->p.Lx / 32) 
 int launch_fused_sweep2(micsa_ctx* c, bool refreshA, int64_t rhoA, double TA, bool refreshB, int64_t rhoB, double TB,
                         bool walk = false, int wanderA = -1, int wanderAB = -1)
 {
+    if (int st = need_alt(c)) return st;
     const FusedTile f = choose_tile2(c);
     const int lanes = (f.TY + 8) * f.NC;
     const int block = (lanes + 63) / 64 * 64;
@@ -877,6 +770,7 @@ int launch_micsa_sweep(micsa_ctx* c, int fam)
 
 int launch_fused_canonical(micsa_ctx* c, int32_t algo, int64_t k, double T)
 {
+    if (int st = need_alt(c)) return st;
     const FusedTile f = choose_tile(c);
     const int lanes = (f.TY + 4) * f.NC;
     const int block = (lanes + 63) / 64 * 64;
@@ -937,13 +831,30 @@ int enqueue_bonds(micsa_ctx* c)
     return check_launch(c, "k_init_couplings");
 }
 
-// Enqueue: dst[l] = from-scratch H^EA of lattice l.
+// Count over the planes (k_cells_count) into the zeroed slots of n entities.
+CellGeom cell_geom(const micsa_ctx* c);
+template <int KIND>
+int enqueue_cells_count(micsa_ctx* c, int n, int a, int b, unsigned long long* dst)
+{
+    const CellGeom cg = cell_geom(c);
+    // a few words per thread, enough work-groups to fill the device
+    const int64_t blocks = std::max<int64_t>(1, std::min<int64_t>((cg.plane + 255) / 256, 4096 / std::max(1, n) + 1));
+    {
+        TimedLaunch t(c, kTimeReduce);
+        k_cells_count<KIND><<<dim3((unsigned)blocks, (unsigned)n), 256, 0, c->stream>>>(
+            cg, reinterpret_cast<const uint32_t*>(c->ms), reinterpret_cast<const uint32_t*>(c->md0),
+            reinterpret_cast<const uint32_t*>(c->md1), reinterpret_cast<const uint32_t*>(c->mb), a, b, dst);
+    }
+    return check_launch(c, "k_cells_count");
+}
+
+// Enqueue: dst[l] = unsatisfied bonds of lattice l, from scratch.
 int enqueue_energy(micsa_ctx* c, unsigned long long* dst)
 {
-    if (int st = settle_msc(c)) return st;
-    if (c->bit) return enqueue_lane_count<0>(c, dst, 0, 0);
+    if (c->bit && !c->planes_ok) return enqueue_lane_count<0>(c, dst, 0, 0);
     int st = zero_slots(c, dst, c->L);
     if (st) return st;
+    if (c->planes_ok) return enqueue_cells_count<0>(c, c->L, 0, 0, dst);
     TimedLaunch t(c, kTimeReduce);
     k_unsat_bonds<<<grid_for((int64_t)c->g.rows * c->g.Wr, c->L), kBlock, 0, c->stream>>>(c->g, c->spin,
                                                                                            dst);
@@ -952,10 +863,10 @@ int enqueue_energy(micsa_ctx* c, unsigned long long* dst)
 
 int enqueue_level_sum(micsa_ctx* c, unsigned long long* dst)
 {
-    if (int st = settle_msc(c)) return st;
-    if (c->bit) return enqueue_lane_count<1>(c, dst, 0, 0);
+    if (c->bit && !c->planes_ok) return enqueue_lane_count<1>(c, dst, 0, 0);
     int st = zero_slots(c, dst, c->L);
     if (st) return st;
+    if (c->planes_ok) return enqueue_cells_count<1>(c, c->L, 0, 0, dst);
     TimedLaunch t(c, kTimeReduce);
     const int64_t wpl = (int64_t)c->gamma * 2 * c->g.Nh / 4;  // every family of the lattice
     k_level_sum<<<grid_for(wpl, c->L), kBlock, 0, c->stream>>>(wpl, reinterpret_cast<const uint32_t*>(c->dem),
@@ -1125,6 +1036,7 @@ int check_sweep(micsa_ctx* c, int32_t algo, int64_t n)
 // family along its own direction, the half of the cycle given by t's parity).
 int launch_wander(micsa_ctx* c, int64_t t)
 {
+    if (int st = need_alt(c)) return st;
     const int64_t words = (int64_t)c->g.rows * c->g.Wr;
     {
         TimedLaunch tl(c, kTimeSweep);
@@ -1228,12 +1140,15 @@ int draw_levels(micsa_ctx* c, const MscGeom& m, int64_t kr, bool alone = false)
     return MICSA_OK;
 }
 
+// Sweep of refresh rho (gamma = 1).
+int64_t refresh_sweep(int64_t rho, int32_t P) { return P >= 1 ? rho * P : ((int64_t)1 << rho) - 1; }
+
 // First refresh sweep in [from, end), or -1.
 int64_t next_refresh(const micsa_ctx* c, int64_t from, int64_t end)
 {
-    for (int64_t k = from; k < end; ++k)
-        if (is_refresh(k, c->sched.period)) return k;
-    return -1;
+    const int32_t P = c->sched.period;
+    const int64_t k = is_refresh(from, P) ? from : refresh_sweep(refresh_index(from, P) + 1, P);
+    return k < end ? k : -1;
 }
 
 // MicSA sweeps k .. k + n - 1 on multispin planes: pack the byte state
@@ -1252,19 +1167,55 @@ MscGeom msc_geom(const micsa_ctx* c)
     return m;
 }
 
-// Unpack live multispin planes into the byte arrays (before anything reads
-// or writes those).
-int settle_msc(micsa_ctx* c)
+CellGeom cell_geom(const micsa_ctx* c)
 {
-    if (!c->msc_live) return MICSA_OK;
-    const MscGeom m = msc_geom(c);
-    const dim3 cgrid((unsigned)((2 * m.plane + 255) / 256), (unsigned)c->L);
+    CellGeom cg;
+    cg.g = c->g;
+    cg.W = (c->g.Kx + 31) / 32;
+    cg.bdiv = msc_eligible(c) ? 1 : c->g.R;  // the multispin kernels read a set of couplings per lattice
+    cg.plane = (int64_t)c->g.rows * cg.W;
+    return cg;
+}
+
+uint32_t* w32(uint64_t* p) { return reinterpret_cast<uint32_t*>(p); }
+
+// Unpack the planes into the layout's own arrays if those are stale (before
+// anything reads them).
+int need_home(micsa_ctx* c)
+{
+    if (c->home_ok) return MICSA_OK;
+    const CellGeom cg = cell_geom(c);
     {
         TimedLaunch t(c, kTimeReduce);
-        k_msc_unpack<<<cgrid, 256, 0, c->stream>>>(c->g, m, c->ms, c->md0, c->md1, c->mb, c->spin, c->dem);
+        k_cells_unpack<<<dim3((unsigned)((cg.plane + 255) / 256), (unsigned)c->L), 256, 0, c->stream>>>(
+            cg, w32(c->ms), w32(c->md0), w32(c->md1), w32(c->mb), c->spin, c->dem);
     }
-    const int st = check_launch(c, "k_msc_unpack");
-    if (!st) c->msc_live = false;
+    const int st = check_launch(c, "k_cells_unpack");
+    if (!st) c->home_ok = true;
+    return st;
+}
+
+// The same before something writes them.
+int own_home(micsa_ctx* c)
+{
+    const int st = need_home(c);
+    if (!st) c->planes_ok = false;
+    return st;
+}
+
+// Pack the planes if they are stale (before a sweep on them, which then owns
+// the state).
+int need_planes(micsa_ctx* c)
+{
+    if (c->planes_ok) return MICSA_OK;
+    const CellGeom cg = cell_geom(c);
+    {
+        TimedLaunch t(c, kTimeReduce);
+        k_cells_pack<<<dim3((unsigned)((cg.plane + 255) / 256), (unsigned)c->L), 256, 0, c->stream>>>(
+            cg, c->spin, c->dem, w32(c->ms), w32(c->md0), w32(c->md1), w32(c->mb));
+    }
+    const int st = check_launch(c, "k_cells_pack");
+    if (!st) c->planes_ok = true;
     return st;
 }
 
@@ -1319,7 +1270,6 @@ int sweep_msc(micsa_ctx* c, int64_t n, bool walkers = false)
     const bool ahead = one && c->draw_ahead;
     (void)words;
     if (int st = msc_alloc(c, one, ahead)) return st;
-    const dim3 cgrid((unsigned)((2 * m.plane + 255) / 256), (unsigned)c->L);
     int st = MICSA_OK;
     const int64_t k_end = c->k + n;
     int64_t drawn = -1;  // refresh sweep whose levels the draw planes hold (or are being drawn)
@@ -1332,13 +1282,8 @@ int sweep_msc(micsa_ctx* c, int64_t n, bool walkers = false)
         (st = draw_levels(c, m, drawn, drawn == c->k)))
         return st;
     c->msc_drawn = -1;
-    if (!c->msc_live) {
-        {
-            TimedLaunch t(c, kTimeReduce);
-            k_msc_pack<<<cgrid, 256, 0, c->stream>>>(c->g, m, c->spin, c->dem, c->ms, c->md0, c->md1, c->mb);
-        }
-        if ((st = check_launch(c, "k_msc_pack"))) return st;
-    }
+    if ((st = need_planes(c))) return st;
+    c->home_ok = false;
     const dim3 grid((unsigned)((m.plane + 255) / 256), (unsigned)c->L);
     const dim3 sgrid((unsigned)(f.nty * f.ntz), (unsigned)c->L);
     const unsigned sblock = (unsigned)((lanes + 63) / 64 * 64);
@@ -1496,10 +1441,9 @@ int sweep_msc(micsa_ctx* c, int64_t n, bool walkers = false)
         if ((st = check_launch(c, "k_msc_half<1>"))) return st;
         c->k = k + 1;
     }
-    // the planes stay live (unpacked when the byte arrays are next needed); a
-    // draw for a refresh after this call is joined into the library stream
-    // here and kept for the call that starts there
-    c->msc_live = true;
+    // the planes keep the state (unpacked when the byte arrays are next
+    // needed); a draw for a refresh after this call is joined into the library
+    // stream here and kept for the call that starts there
     if (ahead && drawn >= k_end) {
         HIP_TRY(c, hipStreamWaitEvent(c->stream, c->draw_done, 0));
         c->msc_drawn = drawn;
@@ -1511,10 +1455,307 @@ int sweep_msc(micsa_ctx* c, int64_t n, bool walkers = false)
 int settle_wander(micsa_ctx* c)
 {
     if (c->pend_wander < 0) return MICSA_OK;
-    if (int st = settle_msc(c)) return st;  // the wandering kernel moves the byte arrays' levels
+    if (int st = own_home(c)) return st;  // the wandering kernel moves the byte arrays' levels
     const int p = c->pend_wander;
     c->pend_wander = -1;
     return launch_wander(c, p);
+}
+
+// ------------------------------------------------------------- cell sweeps
+// The launch plan (cells.hpp) of a lattice: the tile and the sweeps per
+// launch with the least estimated time per sweep.  The estimate, in cycles
+// of 2.4 GHz: a half sweep of a work-group costs its waves' issue slots (four
+// SIMDs; 4 cycles per VALU instruction, about 36 per cell and half) or the
+// latency of one wave's chain, whichever is longer, and work-groups of one
+// unit share its SIMDs; a launch costs kCellLaunch beside that, and its
+// operands (72 B per cell computed on) at kCellBytes per cycle.  A whole
+// lattice in one work-group pays those once per call.  Measured against it
+// on one MI355X, us per sweep: 64^3 x 2, tiles of 8 x 8 rows and 6 sweeps
+// per launch 1.32 (estimate 1.41), 16 x 16 and 4 1.68 (1.45), one work-group
+// per lattice 1.73 (2.0); 128^3, 16 x 16 and 4 2.92 (2.7); 256^3, 16 x 16 and
+// 2 9.4 (6.2).
+constexpr double kCellIssue = 4.0 * 36, kCellChain = 340, kCellLaunch = 9000, kCellBytes = 2900;
+constexpr int kCellCap = kCellMaxNR * kCellLanes;
+
+bool cells_shape_ok(const micsa_ctx* c)
+{
+    const CellGeom cg = cell_geom(c);
+    return c->gamma == 1 && cg.plane < ((int64_t)1 << 30) && cg.W <= kCellCap / 25 && c->p.Ly < (1 << 22) && c->p.Lz < (1 << 22);
+}
+
+CellPlan cell_plan(const micsa_ctx* c)
+{
+    CellPlan best;
+    if (!cells_shape_ok(c)) return best;
+    const int W = (c->g.Kx + 31) / 32, Ly = c->p.Ly, Lz = c->p.Lz;
+    const int cus = c->cus > 0 ? c->cus : 256;
+    const int xm = W == 1 ? 0 : (c->g.Kx % 32 == 0 ? 1 : 2);
+    auto consider = [&](int TY, int TZ, int T) {
+        CellTile f{};
+        const int G = 2 * T;
+        f.TY = TY;
+        f.TZ = TZ;
+        f.GY = TY < Ly ? G : 0;
+        f.GZ = TZ < Lz ? G : 0;
+        f.EY = TY + 2 * f.GY;
+        f.EZ = TZ + 2 * f.GZ;
+        f.nty = (Ly + TY - 1) / TY;
+        f.ntz = (Lz + TZ - 1) / TZ;
+        f.inv_EYW = 1.0f / (float)(f.EY * W);
+        f.inv_W = 1.0f / (float)W;
+        f.inv_Ly = 1.0f / (float)Ly;
+        f.inv_Lz = 1.0f / (float)Lz;
+        const int64_t cells = (int64_t)f.EY * f.EZ * W;
+        const int nr = (int)((cells + kCellLanes - 1) / kCellLanes);
+        // (four cells of rows with a short last word do not fit the registers)
+        if (nr > (xm == 2 ? 3 : kCellMaxNR) || f.ntz > 65535) return;
+        const bool whole = f.nty * f.ntz == 1;
+        const int block = (int)(((cells + nr - 1) / nr + 63) / 64 * 64), waves = block / 64;
+        const double issue = kCellIssue * (xm == 0 ? 1.0 : (xm == 1 ? 1.15 : 1.2)) * nr;  // of one wave and half
+        // work-groups a unit holds at once: waves per SIMD by registers
+        const int fit = std::max(1, (nr == 1 ? 32 : (nr == 2 ? 20 : 16)) / waves);
+        const double wgs = (double)f.nty * f.ntz * c->L;
+        const double per_cu = std::ceil(wgs / cus);
+        const double m = std::min<double>(per_cu, fit), rounds = per_cu / m;
+        const double half = std::max(kCellChain + issue, std::ceil(m * waves / 4.0) * issue + 100.0);
+        const double load = kCellLaunch * rounds + (double)cells * wgs * 72.0 / kCellBytes;
+        const double t = rounds * half * 2.0 + (whole ? 0.0 : load / T);
+        if (!best.ok || t < best.cost) {
+            best.ok = true;
+            best.f = f;
+            best.nr = nr;
+            best.xm = xm;
+            best.block = (unsigned)block;
+            best.sweeps = whole ? 0 : T;
+            best.cost = t;
+        }
+    };
+    if ((int64_t)Ly * Lz * W <= kCellCap) consider(Ly, Lz, 1);
+    // tiles that divide a side about evenly, a few per factor of two
+    auto sides = [](int L) {
+        std::vector<int> v;
+        int last = 0;
+        for (double n = 1; n <= L; n = std::max(n + 1, n * 1.15)) {
+            const int t = (int)((L + (int)n - 1) / (int)n);
+            if (t != last) v.push_back(t);
+            last = t;
+        }
+        if (last != 1) v.push_back(1);
+        return v;
+    };
+    const std::vector<int> ys = sides(Ly), zs = sides(Lz);
+    for (int T : {1, 2, 3, 4, 5, 6, 8, 10})
+        for (int ty : ys)
+            for (int tz : zs) {
+                if (ty == Ly && tz == Lz) continue;
+                if ((int64_t)(ty + (ty < Ly ? 4 * T : 0)) * (tz + (tz < Lz ? 4 * T : 0)) * W <= kCellCap)
+                    consider(ty, tz, T);
+            }
+    return best;
+}
+
+// Estimated cycles per sweep of the two-sweep multispin pass: its steps along
+// z, each at least the latency of one wave's step (2800 cycles; 128^3, which
+// fills an eighth of the device, takes 12.8 us per sweep) or the issue of the
+// waves a SIMD holds (about 1700 each).
+double msc_cost(const micsa_ctx* c)
+{
+    const MscTile f = msc2_tile(c);
+    const int cus = c->cus > 0 ? c->cus : 256;
+    const double waves = (double)f.nty * f.ntz * c->L * (msc2_block(f, c->p.Lx / 128) / 64);
+    const double per_simd = std::ceil(waves / (4.0 * cus));
+    return 0.5 * (f.TZ + 6) * std::max(2800.0, 1700.0 * per_simd);
+}
+
+// MicSA takes the cell sweep: on request for the resident and slab forms,
+// and by default unless the multispin pass is estimated faster (us per sweep,
+// cells against the pass: 128^3 2.9 and 12.8, 256^3 9.4 and 13.5, 128^3 x 32
+// 20.2 and 17.6, 512^3 73.5 and 17).
+bool use_cells(const micsa_ctx* c)
+{
+    if (!c->plan.ok || c->bit) return false;
+    if (c->kernel_opt == MICSA_KERNEL_RESIDENT || c->kernel_opt == MICSA_KERNEL_SLAB) return true;
+    if (c->kernel_opt != MICSA_KERNEL_AUTO) return false;
+    return !msc_eligible(c) || resident_eligible(c) || c->plan.cost < msc_cost(c);
+}
+
+void* dev_alloc(size_t bytes)
+{
+    // also while the thread's stream is being captured: an allocation is no
+    // part of the graph
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    (void)hipThreadExchangeStreamCaptureMode(&mode);
+    void* p = nullptr;
+    const hipError_t e = hipMalloc(&p, bytes);
+    (void)hipThreadExchangeStreamCaptureMode(&mode);
+    if (e != hipSuccess) {
+        (void)hipGetLastError();
+        return nullptr;
+    }
+    return p;
+}
+
+// Planes (with their alternates where tiles read what others write) and room
+// for drawn levels.  Drawn levels: as many refreshes as fit 8 MiB or the
+// lattices' spins in bytes, whichever is more, at least one.
+int cells_alloc(micsa_ctx* c)
+{
+    const CellGeom cg = cell_geom(c);
+    const size_t words = (size_t)c->L * 2 * (size_t)cg.plane;
+    if (!c->ms || (c->plan.sweeps > 0 && !c->ms_alt)) {
+        if (msc_eligible(c)) {
+            if (int st = msc_alloc(c, true, false)) return st;
+        } else {
+            const size_t sets = (size_t)(c->L / c->g.R);
+            const size_t bond = sets * 6 * (size_t)cg.plane;
+            const size_t total = words * (c->plan.sweeps > 0 ? 6 : 3) + bond;
+            uint32_t* a = static_cast<uint32_t*>(dev_alloc(total * 4));
+            if (!a) return fail(c, MICSA_ENOMEM, "cell planes");
+            c->parena = a;
+            uint64_t** const at[] = {&c->ms, &c->md0, &c->md1, &c->ms_alt, &c->md0_alt, &c->md1_alt};
+            for (int i = 0; i < (c->plan.sweeps > 0 ? 6 : 3); ++i, a += words) *at[i] = reinterpret_cast<uint64_t*>(a);
+            c->mb = reinterpret_cast<uint64_t*>(a);
+        }
+    }
+    if (!c->cdr0) {
+        const size_t one = words * 4 * 2, room = std::max<size_t>((size_t)8 << 20, (size_t)c->L * 2 * (size_t)c->g.Nh);
+        const int64_t cap = std::max<int64_t>(1, std::min<int64_t>((int64_t)(room / one), 1024));
+        uint32_t* a = static_cast<uint32_t*>(dev_alloc(one * (size_t)cap));
+        if (!a) return fail(c, MICSA_ENOMEM, "drawn levels");
+        c->cdr0 = a;
+        c->cdr1 = a + words * (size_t)cap;
+        c->cdr_cap = cap;
+        c->cdr_n = 0;
+    }
+    return MICSA_OK;
+}
+
+// Draw the levels of the refreshes from sweep kr on that a call ending before
+// k_end needs, as many as there is room for; of a small lattice also later
+// ones, until the launch fills a good part of the device (they are kept for
+// the calls that follow, until the schedule changes).
+int cells_draw(micsa_ctx* c, int64_t kr, int64_t k_end)
+{
+    const CellGeom cg = cell_geom(c);
+    const int32_t P = c->sched.period;
+    const int64_t rho = refresh_index(kr, P);
+    const int64_t in_call = refresh_index(k_end - 1, P) - rho + 1;
+    const int64_t fill = 32768 / std::max<int64_t>(1, cg.plane * c->L);
+    const int64_t n = std::max<int64_t>(
+        1, std::min<int64_t>({std::max(in_call, fill), c->cdr_cap, refresh_count(c->sched) - rho}));
+    CellDraw D{};
+    D.cg = cg;
+    D.dr0 = c->cdr0;
+    D.dr1 = c->cdr1;
+    D.dth = c->d_dth;
+    D.rho0 = rho;
+    D.stride = (int64_t)c->L * 2 * cg.plane;
+    D.n = (int32_t)n;
+    D.L = c->L;
+    const int64_t blocks = std::min<int64_t>((n * cg.plane + 63) / 64, 16384);
+    {
+        TimedLaunch t(c, kTimeRefresh);
+        k_cells_draw<<<dim3((unsigned)blocks, (unsigned)c->L), 64, 0, c->stream>>>(D);
+    }
+    const int st = check_launch(c, "k_cells_draw");
+    if (st) return st;
+    c->cdr_rho0 = rho;
+    c->cdr_n = n;
+    return MICSA_OK;
+}
+
+using CellKernel = void (*)(CellSweep);
+CellKernel cell_kernel(int nr, int xm)
+{
+    static const CellKernel k[kCellMaxNR][3] = {
+        {k_cells_sweep<1, 0>, k_cells_sweep<1, 1>, k_cells_sweep<1, 2>},
+        {k_cells_sweep<2, 0>, k_cells_sweep<2, 1>, k_cells_sweep<2, 2>},
+        {k_cells_sweep<3, 0>, k_cells_sweep<3, 1>, k_cells_sweep<3, 2>},
+        {k_cells_sweep<4, 0>, k_cells_sweep<4, 1>, k_cells_sweep<4, 2>}};
+    return k[nr - 1][xm];
+}
+
+// MicSA sweeps k .. k + n - 1 on the cell kernel.  dlog (whole-lattice plans
+// only): every `stride` sweeps (U, sum m) of each lattice to
+// dlog[row][lattice][2].
+int sweep_cells(micsa_ctx* c, int64_t n, long long* dlog, int64_t stride)
+{
+    int st;
+    if ((st = cells_alloc(c)) || (st = need_planes(c))) return st;
+    const CellGeom cg = cell_geom(c);
+    const CellPlan& pl = c->plan;
+    const int32_t P = c->sched.period;
+    const int64_t k_first = c->k, k_end = c->k + n, stride_w = (int64_t)c->L * 2 * cg.plane;
+    c->home_ok = false;
+    while (c->k < k_end) {
+        const int64_t k = c->k;
+        int64_t len = std::min<int64_t>(k_end - k, pl.sweeps > 0 ? pl.sweeps : kResidentChunk);
+        // the refreshes of the launch: drawn, and in one slice
+        const int64_t kr = next_refresh(c, k, k + len);
+        int64_t slot = 0;
+        if (kr >= 0) {
+            const int64_t rho = refresh_index(kr, P);
+            if (rho < c->cdr_rho0 || rho >= c->cdr_rho0 + c->cdr_n)
+                if ((st = cells_draw(c, kr, k_end))) return st;
+            slot = rho - c->cdr_rho0;
+            const int64_t beyond = c->cdr_rho0 + c->cdr_n;  // first refresh not drawn
+            if (refresh_index(k + len - 1, P) >= beyond) len = refresh_sweep(beyond, P) - k;
+        }
+        CellSweep J{};
+        J.cg = cg;
+        J.f = pl.f;
+        J.s_in = w32(c->ms);
+        J.d0_in = w32(c->md0);
+        J.d1_in = w32(c->md1);
+        J.bond = w32(c->mb);
+        const bool whole = pl.sweeps == 0;
+        J.s_out = w32(whole ? c->ms : c->ms_alt);
+        J.d0_out = w32(whole ? c->md0 : c->md0_alt);
+        J.d1_out = w32(whole ? c->md1 : c->md1_alt);
+        J.dr0 = c->cdr0 + slot * stride_w;
+        J.dr1 = c->cdr1 + slot * stride_w;
+        J.dr_stride = stride_w;
+        J.tally = c->tally;
+        J.log = dlog;
+        J.log_row0 = dlog ? (k - k_first) / stride : 0;
+        J.log_stride = dlog ? (int32_t)std::min<int64_t>(stride, INT32_MAX) : 0;
+        J.log_first = dlog ? (int32_t)std::min<int64_t>(stride - (k - k_first) % stride, INT32_MAX) : 0;
+        J.k0 = k;
+        J.n = (int32_t)len;
+        J.ref0 = kr >= 0 && kr < k + len ? (int32_t)(kr - k) : (int32_t)len;
+        J.period = P;
+        J.lattices = c->L;
+        J.inv_bdiv = 1.0f / (float)cg.bdiv;
+        {
+            TimedLaunch t(c, kTimeSweep);
+            cell_kernel(pl.nr, pl.xm)<<<dim3((unsigned)pl.f.nty, (unsigned)pl.f.ntz, (unsigned)c->L), pl.block, 0,
+                                        c->stream>>>(J);
+        }
+        if ((st = check_launch(c, "k_cells_sweep"))) return st;
+        if (!whole) {
+            std::swap(c->ms, c->ms_alt);
+            std::swap(c->md0, c->md0_alt);
+            std::swap(c->md1, c->md1_alt);
+        }
+        c->k = k + len;
+    }
+    return MICSA_OK;
+}
+
+// A sweep call of this algorithm logs inside its launches (one work-group
+// per lattice).
+bool logs_in_kernel(const micsa_ctx* c, int32_t algo)
+{
+    if (algo == MICSA_ALGO_WALKERS) return false;
+    if (algo == MICSA_ALGO_MICSA && use_cells(c)) return c->plan.sweeps == 0;
+    return use_resident(c);
+}
+
+int sweep_logging(micsa_ctx* c, int32_t algo, int64_t n, long long* dlog, int64_t stride)
+{
+    if (algo == MICSA_ALGO_MICSA && use_cells(c)) return n > 0 ? sweep_cells(c, n, dlog, stride) : MICSA_OK;
+    if (int st = own_home(c)) return st;
+    return launch_resident(c, algo, n, dlog, stride);
 }
 
 int sweep_impl(micsa_ctx* c, int32_t algo, int64_t n)
@@ -1528,19 +1769,19 @@ int sweep_impl(micsa_ctx* c, int32_t algo, int64_t n)
     const bool walk_fused = algo == MICSA_ALGO_WALKERS && !c->bit && c->gamma == 1 && use_fused(c);
     // the one-launch multispin sweep takes an owed wandering on its loads
     // (and leaves one), as the fused byte sweep does
-    if (!walk_fused && !walk_msc && !(algo == MICSA_ALGO_MICSA && use_msc(c, n) && msc_one_launch(c)) &&
+    if (!walk_fused && !walk_msc && !(algo == MICSA_ALGO_MICSA && !use_cells(c) && use_msc(c, n) && msc_one_launch(c)) &&
         (st0 = settle_wander(c)))
         return st0;
     if (walk_msc) return n > 0 ? sweep_msc(c, n, true) : MICSA_OK;
+    if (algo == MICSA_ALGO_MICSA && use_cells(c)) return n > 0 ? sweep_cells(c, n, nullptr, 0) : MICSA_OK;
     if (algo == MICSA_ALGO_MICSA && use_msc(c, n)) return n > 0 ? sweep_msc(c, n) : MICSA_OK;
-    // every other path sweeps the byte arrays
-    if ((st0 = settle_msc(c))) return st0;
+    // every other path sweeps the layout's own arrays
+    if ((st0 = own_home(c))) return st0;
     if (algo != MICSA_ALGO_WALKERS) {
         if (use_resident(c)) return launch_resident(c, algo, n, nullptr, 0);
         if (use_graph(c) && n >= kGraphSweeps) return sweep_graph(c, algo, n);
     }
     if (algo == MICSA_ALGO_MICSA && bp_one_launch(c)) return sweep_bitplane(c, n);
-    if (algo == MICSA_ALGO_MICSA && use_slab(c)) return sweep_slab(c, n);
     for (int64_t i = 0; i < n; ++i) {
         // sweep k is sweep fam of timestep t (Sec. 2.8)
         const int64_t k = c->k;
@@ -1605,11 +1846,14 @@ void free_all(micsa_ctx* c)
     if (c->spin) (void)hipFree(c->spin);
     if (c->dem) (void)hipFree(c->dem);
     if (c->spin_alt) (void)hipFree(c->spin_alt);
-    for (uint8_t* q : c->sdr)
-        if (q) (void)hipFree(q);
     if (c->dem_alt) (void)hipFree(c->dem_alt);
     if (c->bspin) (void)hipFree(c->bspin);
     if (c->draw_stream) (void)hipStreamSynchronize(c->draw_stream);
+    if (c->parena) {  // the cell planes are one allocation
+        (void)hipFree(c->parena);
+        c->ms = c->md0 = c->md1 = c->mb = c->ms_alt = c->md0_alt = c->md1_alt = nullptr;
+    }
+    if (c->cdr0) (void)hipFree(c->cdr0);
     for (uint64_t* q : {c->ms, c->md0, c->md1, c->mb, c->ms_alt, c->md0_alt, c->md1_alt, c->mdr0, c->mdr1})
         if (q) (void)hipFree(q);
     if (c->draw_free) (void)hipEventDestroy(c->draw_free);
@@ -1717,6 +1961,8 @@ int micsa_create(const micsa_params* p, void* hip_stream, micsa_ctx** out)
     g.key1 = (uint32_t)(p->seed >> 32);
     g.gamma = gamma;
 
+    c->plan = cell_plan(c);
+
     const size_t nred = (size_t)std::max(c->L, p->n_samples);
     bool ok = hipMalloc(&c->tally, (size_t)c->L * kSlots * 8) == hipSuccess &&
               hipMalloc(&c->red, nred * kSlots * 8) == hipSuccess;
@@ -1724,8 +1970,9 @@ int micsa_create(const micsa_params* p, void* hip_stream, micsa_ctx** out)
     const size_t dstate = state * (size_t)gamma;  // every daemon family
     const size_t words = (size_t)word_lattices(c) * 2 * (size_t)g.Nh;
     if (ok && !c->bit) {
-        ok = hipMalloc(&c->spin, state) == hipSuccess && hipMalloc(&c->dem, dstate) == hipSuccess &&
-             hipMalloc(&c->spin_alt, state) == hipSuccess && hipMalloc(&c->dem_alt, dstate) == hipSuccess;
+        ok = hipMalloc(&c->spin, state) == hipSuccess && hipMalloc(&c->dem, dstate) == hipSuccess;
+        // the fused sweeps, and the wandering of several families, go from one copy to the other
+        if (ok && ((fused_eligible(c) && p->Lx >= 128) || gamma > 1)) ok = need_alt(c) == MICSA_OK;
     } else if (ok) {
         ok = hipMalloc(&c->bspin, words * 8) == hipSuccess && hipMalloc(&c->bdm0, words * 8) == hipSuccess &&
              hipMalloc(&c->bdm1, words * 8) == hipSuccess &&
@@ -1776,10 +2023,10 @@ int micsa_create(const micsa_params* p, void* hip_stream, micsa_ctx** out)
     // the working buffers of the sweep path the lattice takes by default
     // (counted in the pool footprint), so that the first sweep call does not
     // allocate; if they do not fit now, that call tries again
-    if (!c->bit && c->gamma == 1 && msc_eligible(c) && !resident_eligible(c)) {
+    if (use_cells(c)) {
+        if (cells_alloc(c) != MICSA_OK) c->err.clear();
+    } else if (!c->bit && c->gamma == 1 && msc_eligible(c)) {
         if (msc_alloc(c, true, true) != MICSA_OK) c->err.clear();
-    } else if (use_slab(c) && slab_pairs(c)) {
-        if (slab_alloc(c) != MICSA_OK) c->err.clear();
     }
     *out = c;
     return MICSA_OK;
@@ -1863,7 +2110,7 @@ int micsa_set_schedule(micsa_ctx* ctx, const micsa_schedule* s)
     ctx->d_hth = d2;
     ctx->d_mth = d3;
     ctx->sched = std::move(n);
-    ctx->sdr_k[0] = ctx->sdr_k[1] = -1;  // levels drawn ahead under the old temperatures
+    ctx->cdr_n = 0;  // levels drawn ahead under the old temperatures
     ctx->msc_drawn = -1;
     return MICSA_OK;
 }
@@ -1883,7 +2130,7 @@ int micsa_sweep_logged_d(micsa_ctx* ctx, int32_t algo, int64_t n, int64_t stride
     int st = check_sweep(ctx, algo, n);
     if (st) return st;
     if (rows == 0 || (!E_log && !D_log)) return sweep_impl(ctx, algo, n);
-    if (use_resident(ctx) && algo != MICSA_ALGO_WALKERS) {
+    if (logs_in_kernel(ctx, algo)) {
         const size_t need = (size_t)rows * L * 2;
         if (need > ctx->rlog_cap) {
             // the old buffer may still be in use by enqueued work
@@ -1900,7 +2147,7 @@ int micsa_sweep_logged_d(micsa_ctx* ctx, int32_t algo, int64_t n, int64_t stride
             }
             ctx->rlog_cap = need;
         }
-        if ((st = launch_resident(ctx, algo, n, ctx->rlog, stride))) return st;
+        if ((st = settle_wander(ctx)) || (st = sweep_logging(ctx, algo, n, ctx->rlog, stride))) return st;
         const int64_t e = rows * L;
         k_log_from_pairs<<<(unsigned)((e + 255) / 256), 256, 0, ctx->stream>>>(
             ctx->rlog, e, N, reinterpret_cast<long long*>(E_log), reinterpret_cast<long long*>(D_log));
@@ -1935,13 +2182,14 @@ int micsa_sweep_logged(micsa_ctx* ctx, int32_t algo, int64_t n, int64_t stride, 
     const int L = ctx->L;
     int st0 = check_sweep(ctx, algo, n);
     if (st0) return st0;
-    if (use_resident(ctx) && algo != MICSA_ALGO_WALKERS) {
+    if (logs_in_kernel(ctx, algo)) {
+        if ((st0 = settle_wander(ctx))) return st0;
         long long* rlog = nullptr;
         if (rows > 0 && hipMalloc(&rlog, (size_t)rows * L * 2 * 8) != hipSuccess) {
             (void)hipGetLastError();
             return fail(ctx, MICSA_ENOMEM, "log buffer");
         }
-        int st = launch_resident(ctx, algo, n, rows > 0 ? rlog : nullptr, stride);
+        int st = sweep_logging(ctx, algo, n, rows > 0 ? rlog : nullptr, stride);
         std::vector<int64_t> h((size_t)rows * L * 2);
         if (!st && rows > 0 &&
             hipMemcpyAsync(h.data(), rlog, h.size() * 8, hipMemcpyDeviceToHost, ctx->stream) != hipSuccess)
@@ -2086,7 +2334,7 @@ static C4Geom c4_geom(const micsa_ctx* c)
 int micsa_read_c4(micsa_ctx* ctx, int64_t* G)
 {
     if (!ctx || !G) return MICSA_EINVAL;
-    if (int st_ = settle_msc(ctx)) return st_;  // the byte arrays are read or written
+    if (int st_ = need_home(ctx)) return st_;
     if (ctx->p.n_replicas < 2) return fail(ctx, MICSA_EINVAL, "C4 needs at least two replicas");
     const C4Geom cg = c4_geom(ctx);
     std::vector<int64_t> D;
@@ -2144,7 +2392,7 @@ size_t align256(size_t n) { return (n + 255) & ~(size_t)255; }
 int micsa_read_c4_static(micsa_ctx* ctx, int64_t* G)
 {
     if (!ctx || !G) return MICSA_EINVAL;
-    if (int st_ = settle_msc(ctx)) return st_;  // the byte arrays are read or written
+    if (int st_ = need_home(ctx)) return st_;
     if (ctx->p.n_replicas < 2) return fail(ctx, MICSA_EINVAL, "C4 needs at least two replicas");
     const C4Geom cg = c4_geom(ctx);
     const int64_t ent = (int64_t)ctx->p.n_samples * 3 * (cg.rmax + 1);
@@ -2197,7 +2445,7 @@ int micsa_read_c4_static(micsa_ctx* ctx, int64_t* G)
 int micsa_read_xi(micsa_ctx* ctx, double* xi12, double* xi23)
 {
     if (!ctx || !xi12 || !xi23) return MICSA_EINVAL;
-    if (int st_ = settle_msc(ctx)) return st_;  // the byte arrays are read or written
+    if (int st_ = need_home(ctx)) return st_;
     if (ctx->p.n_replicas < 2) return fail(ctx, MICSA_EINVAL, "xi needs at least two replicas");
     const C4Geom cg = c4_geom(ctx);
     std::vector<int64_t> G((size_t)ctx->p.n_samples * 3 * (cg.rmax + 1));
@@ -2232,12 +2480,13 @@ int micsa_read_xi(micsa_ctx* ctx, double* xi12, double* xi23)
 int micsa_read_overlap(micsa_ctx* ctx, int32_t a, int32_t b, int64_t* Q)
 {
     if (!ctx || !Q) return MICSA_EINVAL;
-    if (int st_ = settle_msc(ctx)) return st_;  // the byte arrays are read or written
     if (a < 0 || b < 0 || a >= ctx->p.n_replicas || b >= ctx->p.n_replicas || a == b)
         return fail(ctx, MICSA_EINVAL, "replica indices out of range or equal");
     const int S = ctx->p.n_samples;
     int st;
-    if (ctx->bit) {
+    if (ctx->planes_ok) {
+        if ((st = zero_slots(ctx, ctx->red, S)) || (st = enqueue_cells_count<2>(ctx, S, a, b, ctx->red))) return st;
+    } else if (ctx->bit) {
         if ((st = enqueue_lane_count<2>(ctx, ctx->red, a, b))) return st;
     } else {
         if ((st = zero_slots(ctx, ctx->red, S))) return st;
@@ -2304,7 +2553,7 @@ static int read_words(micsa_ctx* ctx, const uint64_t* w0, const uint64_t* w1, ui
 int micsa_read_spins(micsa_ctx* ctx, uint8_t* sigma)
 {
     if (!ctx || !sigma) return MICSA_EINVAL;
-    if (int st_ = settle_msc(ctx)) return st_;  // the byte arrays are read or written
+    if (int st_ = need_home(ctx)) return st_;
     if (ctx->bit) return read_words(ctx, ctx->bspin, nullptr, sigma);
     return read_state(ctx, ctx->spin, sigma, ctx->L, 1);  // bit 0: even bytes also hold their bonds
 }
@@ -2312,7 +2561,7 @@ int micsa_read_spins(micsa_ctx* ctx, uint8_t* sigma)
 int micsa_read_demons(micsa_ctx* ctx, uint8_t* m)
 {
     if (!ctx || !m) return MICSA_EINVAL;
-    if (int st_ = settle_msc(ctx)) return st_;  // the byte arrays are read or written
+    if (int st_ = need_home(ctx)) return st_;
     if (ctx->bit) return read_words(ctx, ctx->bdm0, ctx->bdm1, m);
     const int st = settle_wander(ctx);
     if (st) return st;
@@ -2322,7 +2571,7 @@ int micsa_read_demons(micsa_ctx* ctx, uint8_t* m)
 int micsa_read_couplings(micsa_ctx* ctx, uint8_t* j)
 {
     if (!ctx || !j) return MICSA_EINVAL;
-    if (int st_ = settle_msc(ctx)) return st_;  // the byte arrays are read or written
+    if (int st_ = need_home(ctx)) return st_;
     const Geom& g = ctx->g;
     const int S = ctx->p.n_samples;
     std::vector<uint8_t> jbytes;
@@ -2416,7 +2665,7 @@ static int write_words(micsa_ctx* ctx, uint64_t* w0, uint64_t* w1, const uint8_t
 int micsa_write_spins(micsa_ctx* ctx, const uint8_t* sigma)
 {
     if (!ctx || !sigma) return MICSA_EINVAL;
-    if (int st_ = settle_msc(ctx)) return st_;  // the byte arrays are read or written
+    if (int st_ = own_home(ctx)) return st_;
     int st = ctx->bit ? write_words(ctx, ctx->bspin, nullptr, sigma, 1) : write_state(ctx, ctx->spin, sigma, 1, ctx->L);
     if (!st && !ctx->bit) st = enqueue_bonds(ctx);  // the written bytes hold spins only: restore the bond bits
     if (st) return st;
@@ -2430,7 +2679,7 @@ int micsa_write_spins(micsa_ctx* ctx, const uint8_t* sigma)
 int micsa_write_demons(micsa_ctx* ctx, const uint8_t* m)
 {
     if (!ctx || !m) return MICSA_EINVAL;
-    if (int st_ = settle_msc(ctx)) return st_;  // the byte arrays are read or written
+    if (int st_ = own_home(ctx)) return st_;
     if (ctx->bit) return write_words(ctx, ctx->bdm0, ctx->bdm1, m, 3);
     const int st = write_state(ctx, ctx->dem, m, 3, (int64_t)ctx->L * ctx->gamma);
     if (!st) ctx->pend_wander = -1;  // the written daemons are where they are
@@ -2485,7 +2734,7 @@ bool same_params(const micsa_params& a, const micsa_params& b)
 int micsa_save(micsa_ctx* ctx, void* buf, size_t* len)
 {
     if (!ctx || !len) return MICSA_EINVAL;
-    if (int st_ = settle_msc(ctx)) return st_;  // the byte arrays are read or written
+    if (int st_ = need_home(ctx)) return st_;
     const int64_t T_len = ctx->sched.set ? (int64_t)ctx->sched.table.size() : 0;
     const size_t total = ck_bytes(ctx, T_len);
     if (!buf) {
@@ -2540,7 +2789,7 @@ int micsa_save(micsa_ctx* ctx, void* buf, size_t* len)
 int micsa_load(micsa_ctx* ctx, const void* buf, size_t len)
 {
     if (!ctx) return MICSA_EINVAL;
-    if (int st_ = settle_msc(ctx)) return st_;  // the byte arrays are read or written
+    if (int st_ = need_home(ctx)) return st_;
     if (!buf) return fail(ctx, MICSA_EINVAL, "null checkpoint");
     const uint8_t* in = static_cast<const uint8_t*>(buf);
     CkHeader h;
@@ -2586,7 +2835,7 @@ int micsa_load(micsa_ctx* ctx, const void* buf, size_t len)
         if ((st = micsa_set_schedule(ctx, &s))) return st;
     } else {
         ctx->sched = Schedule{};
-        ctx->sdr_k[0] = ctx->sdr_k[1] = -1;
+        ctx->cdr_n = 0;
         ctx->msc_drawn = -1;
     }
     if ((st = micsa_write_spins(ctx, spins))) return st;
@@ -3011,6 +3260,7 @@ int micsa_pool_step(micsa_pool* pool, int64_t sweeps, int32_t* running, int32_t*
             micsa_ctx* c = j.ctx;
             const int64_t n = std::min<int64_t>(sweeps, c->sched.n_sweeps - c->k);
             if (n <= 0) continue;
+            if (const int st = own_home(c)) return st;
             ResidentSched rs{c->k, n, 0, c->sched.period, 0, 0};
             for (int l = 0; l < c->L; ++l)
                 items.push_back(ResidentItem{c->g, c->spin, c->dem, c->tally, c->d_dth, rs, l});

@@ -12,8 +12,8 @@
 //                   direction d (+x, -x, +y, -y, +z, -z): every bond has one
 //                   even end, so these six planes hold every coupling once
 // The planes are a working form of the byte layout: the library packs them
-// from the byte arrays at the start of a sweep call and unpacks them at its
-// end, so every other entry point reads the byte layout as before.
+// (cells.hpp) when a sweep call finds them stale and unpacks them when an
+// entry point next needs the byte arrays.
 //
 // Neighbours of parity-p site k of a row, in the other parity's planes: y
 // and z neighbours at the same k of the adjacent rows; x + 1 at k + q and
@@ -522,78 +522,6 @@ __global__ __launch_bounds__(64) void k_msc_draw(Geom g, MscGeom m, int32_t L, u
         d1[he] = e1;
         d0[ho] = o0;
         d1[ho] = o1;
-    }
-}
-
-// Byte layout -> planes (and back): one thread per (lattice, parity, row,
-// word), 64 consecutive bytes of the parity array.  An even spin byte holds
-// the spin in bit 0 and the coupling of direction d in bit 1 + d.
-__global__ __launch_bounds__(256) void k_msc_pack(Geom g, MscGeom m, const uint8_t* __restrict__ spin_b,
-                                                  const uint8_t* __restrict__ dem_b, uint64_t* __restrict__ spin,
-                                                  uint64_t* __restrict__ dem0, uint64_t* __restrict__ dem1,
-                                                  uint64_t* __restrict__ bond)
-{
-    const int64_t gw = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int l = blockIdx.y;
-    if (gw >= 2 * m.plane) return;
-    const int p = (int)(gw / m.plane);
-    const int64_t pw = gw - p * m.plane;  // row * W + w: its 64 bytes start at byte 64 pw of the parity array
-    const uint8_t* sb = spin_b + ((int64_t)l * 2 + p) * g.Nh + 64 * pw;
-    const uint8_t* db = dem_b + ((int64_t)l * 2 + p) * g.Nh + 64 * pw;
-    uint64_t s = 0, m0 = 0, m1 = 0, j[6] = {0, 0, 0, 0, 0, 0};
-    for (int v = 0; v < 4; ++v) {
-        const uint4 S4 = reinterpret_cast<const uint4*>(sb)[v];
-        const uint4 D4 = reinterpret_cast<const uint4*>(db)[v];
-        const uint32_t sw[4] = {S4.x, S4.y, S4.z, S4.w}, dw[4] = {D4.x, D4.y, D4.z, D4.w};
-        for (int t = 0; t < 16; ++t) {
-            const int b = 16 * v + t;
-            const uint32_t sbyte = (sw[t >> 2] >> (8 * (t & 3))) & 0xFFu;
-            const uint32_t dbyte = (dw[t >> 2] >> (8 * (t & 3))) & 0xFFu;
-            s |= (uint64_t)(sbyte & 1u) << b;
-            m0 |= (uint64_t)(dbyte & 1u) << b;
-            m1 |= (uint64_t)((dbyte >> 1) & 1u) << b;
-            if (p == 0)
-                for (int d = 0; d < 6; ++d) j[d] |= (uint64_t)((sbyte >> (1 + d)) & 1u) << b;
-        }
-    }
-    spin[((int64_t)l * 2 + p) * m.plane + pw] = s;
-    dem0[((int64_t)l * 2 + p) * m.plane + pw] = m0;
-    dem1[((int64_t)l * 2 + p) * m.plane + pw] = m1;
-    if (p == 0)
-        for (int d = 0; d < 6; ++d) bond[((int64_t)l * 6 + d) * m.plane + pw] = j[d];
-}
-
-__global__ __launch_bounds__(256) void k_msc_unpack(Geom g, MscGeom m, const uint64_t* __restrict__ spin,
-                                                    const uint64_t* __restrict__ dem0,
-                                                    const uint64_t* __restrict__ dem1,
-                                                    const uint64_t* __restrict__ bond, uint8_t* __restrict__ spin_b,
-                                                    uint8_t* __restrict__ dem_b)
-{
-    const int64_t gw = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int l = blockIdx.y;
-    if (gw >= 2 * m.plane) return;
-    const int p = (int)(gw / m.plane);
-    const int64_t pw = gw - p * m.plane;
-    const uint64_t s = spin[((int64_t)l * 2 + p) * m.plane + pw];
-    const uint64_t m0 = dem0[((int64_t)l * 2 + p) * m.plane + pw];
-    const uint64_t m1 = dem1[((int64_t)l * 2 + p) * m.plane + pw];
-    uint64_t j[6] = {0, 0, 0, 0, 0, 0};
-    if (p == 0)
-        for (int d = 0; d < 6; ++d) j[d] = bond[((int64_t)l * 6 + d) * m.plane + pw];
-    uint8_t* sb = spin_b + ((int64_t)l * 2 + p) * g.Nh + 64 * pw;
-    uint8_t* db = dem_b + ((int64_t)l * 2 + p) * g.Nh + 64 * pw;
-    for (int v = 0; v < 4; ++v) {
-        uint32_t sw[4] = {0, 0, 0, 0}, dw[4] = {0, 0, 0, 0};
-        for (int t = 0; t < 16; ++t) {
-            const int b = 16 * v + t;
-            uint32_t sbyte = (uint32_t)((s >> b) & 1u);
-            for (int d = 0; d < 6; ++d) sbyte |= (uint32_t)((j[d] >> b) & 1u) << (1 + d);
-            const uint32_t dbyte = (uint32_t)((m0 >> b) & 1u) | ((uint32_t)((m1 >> b) & 1u) << 1);
-            sw[t >> 2] |= sbyte << (8 * (t & 3));
-            dw[t >> 2] |= dbyte << (8 * (t & 3));
-        }
-        reinterpret_cast<uint4*>(sb)[v] = make_uint4(sw[0], sw[1], sw[2], sw[3]);
-        reinterpret_cast<uint4*>(db)[v] = make_uint4(dw[0], dw[1], dw[2], dw[3]);
     }
 }
 

@@ -1,0 +1,84 @@
+"""The cell sweep (rows in registers, several sweeps per launch) against the
+oracle, at the shapes where its tiles, word forms and launch lengths change."""
+import numpy as np
+import pytest
+
+from oracle import oracle as O
+from paper_2506_16240_amd import micsa as M
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = [
+    (8, 8, 8, 1, 1),        # one wave
+    (64, 2, 2, 1, 3),       # a full word per row, sides of 2
+    (32, 34, 32, 2, 1),     # one cell more than a work-group has lanes: two per lane
+    (48, 64, 40, 1, 2),     # three per lane
+    (64, 64, 64, 1, 20),    # a whole 64^3 per work-group: four per lane
+    (64, 64, 64, 1, 2),     # tiles with rings on all sides
+    (128, 26, 30, 1, 1),    # two full words per row, whole lattice
+    (72, 34, 34, 1, 2),     # a last word of 4 sites, whole lattice
+    (104, 46, 38, 2, 2),    # the same in tiles that divide neither side
+    (200, 50, 36, 1, 1),    # four words, the last of 4 sites
+    (8, 200, 60, 1, 1),     # rows of 4 sites, tiles
+    (24, 4, 600, 1, 1),     # one side whole, the other in tiles
+    (128, 64, 64, 1, 1),    # the multispin planes read as 32-bit words
+]
+
+
+def state(g, o):
+    assert np.array_equal(g.spins(), o.sigma), "spins differ"
+    assert np.array_equal(g.daemons(), o.m), "daemons differ"
+    E = o.energy()
+    assert np.array_equal(g.energy(), E) and np.array_equal(g.energy_tally(), E)
+    assert np.array_equal(g.daemon_energy(), o.daemon_energy())
+
+
+@pytest.mark.parametrize("shape", SHAPES)
+def test_cell_sweep_matches_oracle(shape):
+    """Calls of one sweep, of several launches and of a part of one, refreshes
+    on every sweep, every third, every tenth and at powers of two; energies
+    read with the planes live, states after unpacking; a logged call with a
+    ragged tail; the baselines in between."""
+    g, o = M.Lattice(*shape, 0xCE11), O.Lattice(*shape, 0xCE11)
+    for P, calls in ((10, (1, 23)), (3, (7,)), (1, (3,)), (M.REFRESH_LOG2, (9,))):
+        g.set_schedule(M.Schedule(M.SCHED_LINEAR, 2.5, 0.5, 200, P))
+        os_ = O.Schedule(O.SCHED_LINEAR, 2.5, 0.5, 200, P)
+        for n in calls:
+            g.sweep(M.ALGO_MICSA, n)
+            o.run(O.ALGO_MICSA, os_, n, 0)
+            assert np.array_equal(g.energy(), o.energy()) and np.array_equal(g.daemon_energy(), o.daemon_energy())
+            if shape[4] > 1:
+                assert np.array_equal(g.overlap(0, 1), o.overlap(0, 1))
+        state(g, o)
+    E, D = g.sweep_logged(M.ALGO_MICSA, 8, 3)
+    Eo, Do = o.run(O.ALGO_MICSA, os_, 8, 3)
+    assert np.array_equal(E, Eo) and np.array_equal(D, Do)
+    g.sweep(M.ALGO_METROPOLIS, 1)
+    o.run(O.ALGO_METROPOLIS, os_, 1, 0)
+    g.sweep(M.ALGO_MICSA, 2)
+    o.run(O.ALGO_MICSA, os_, 2, 0)
+    state(g, o)
+    g.close()
+
+
+def test_drawn_levels_across_calls_and_slices():
+    """Refresh levels drawn ahead in slices: a run longer than one slice (1024
+    refreshes of a small lattice), calls that start between, at and after the
+    refreshes a slice holds, a schedule changed in between."""
+    shape = (8, 4, 6, 1, 2)
+    g, o = M.Lattice(*shape, 7), O.Lattice(*shape, 7)
+    for T, P, calls in ((1.5, 2, (2500, 1, 1)), (0.8, 5, (4, 1, 17))):
+        g.set_schedule(M.Schedule(M.SCHED_CONST, T, T, 5000, P))
+        os_ = O.Schedule(O.SCHED_CONST, T, T, 5000, P)
+        for n in calls:
+            g.sweep(M.ALGO_MICSA, n)
+            o.run(O.ALGO_MICSA, os_, n, 0)
+            state(g, o)
+    image = g.save()
+    h = M.Lattice(*shape, 7)
+    h.load(image)
+    for x in (g, h):
+        x.sweep(M.ALGO_MICSA, 6)
+    o.run(O.ALGO_MICSA, os_, 6, 0)
+    state(g, o)
+    state(h, o)
