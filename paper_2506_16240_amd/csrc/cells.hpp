@@ -558,6 +558,85 @@ __global__ void __launch_bounds__(256) k_cells_unpack(CellGeom cg, const uint32_
     }
 }
 
+// Bit-plane layout (a word holds one site of 64 lattices) -> planes.  A wave
+// per (word lattice, parity, cell), a lane per lattice: the site's word is
+// uniform, so it is a lane mask, and one add-with-carry shifts each lane's
+// bit in.  Lattice (s, r) is plane set s R + r; the coupling planes of a
+// sample (cg.bdiv = R) are written by its replica 0.
+__device__ __forceinline__ uint32_t cell_bits(const uint64_t* __restrict__ w, int nv)
+{
+    uint32_t v = 0;
+#pragma unroll 4
+    for (int k = nv - 1; k >= 0; --k) v = v + v + (__builtin_amdgcn_inverse_ballot_w64(w[k]) ? 1u : 0u);
+    return v;
+}
+
+__global__ void __launch_bounds__(256) k_cells_pack_bits(GeomB gb, CellGeom cg, const uint64_t* __restrict__ bspin,
+                                                         const uint64_t* __restrict__ bm0,
+                                                         const uint64_t* __restrict__ bm1,
+                                                         const uint64_t* __restrict__ Jw, uint32_t* __restrict__ spin,
+                                                         uint32_t* __restrict__ d0, uint32_t* __restrict__ d1,
+                                                         uint32_t* __restrict__ bond)
+{
+    const Geom& g = cg.g;
+    const int wl = blockIdx.y;
+    const int64_t i = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * 4 + (threadIdx.x >> 6)));
+    if (i >= 2 * cg.plane) return;
+    const int p = i >= cg.plane ? 1 : 0;
+    const int64_t cell = i - p * cg.plane, row = cell / cg.W;
+    const int w = (int)(cell - row * cg.W), nv = min(32, g.Kx - 32 * w);
+    const int64_t h = row * g.Kx + 32 * w, at = ((int64_t)wl * 2 + p) * g.Nh + h;
+    const uint32_t vs = cell_bits(bspin + at, nv), v0 = cell_bits(bm0 + at, nv), v1 = cell_bits(bm1 + at, nv);
+    int s, r;
+    const bool live = bp_lattice(gb, wl, lane_id(), s, r);
+    const int64_t l = (int64_t)s * g.R + r, to = (l * 2 + p) * cg.plane + cell;
+    if (live) {
+        spin[to] = vs;
+        d0[to] = v0;
+        d1[to] = v1;
+    }
+    if (p == 0)
+#pragma unroll
+        for (int d = 0; d < 6; ++d) {
+            const uint32_t b = cell_bits(Jw + ((int64_t)bp_cset(gb, wl) * 6 + d) * g.Nh + h, nv);
+            if (live && r == 0) bond[((int64_t)s * 6 + d) * cg.plane + cell] = b;
+        }
+}
+
+// Planes -> bit-plane layout: a ballot per site, kept by the lane that
+// stores the site's word (lanes of no lattice hold 0).
+__global__ void __launch_bounds__(256) k_cells_unpack_bits(GeomB gb, CellGeom cg, const uint32_t* __restrict__ spin,
+                                                           const uint32_t* __restrict__ d0,
+                                                           const uint32_t* __restrict__ d1,
+                                                           uint64_t* __restrict__ bspin, uint64_t* __restrict__ bm0,
+                                                           uint64_t* __restrict__ bm1)
+{
+    const Geom& g = cg.g;
+    const int wl = blockIdx.y, lane = lane_id();
+    const int64_t i = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * 4 + (threadIdx.x >> 6)));
+    if (i >= 2 * cg.plane) return;
+    const int p = i >= cg.plane ? 1 : 0;
+    const int64_t cell = i - p * cg.plane, row = cell / cg.W;
+    const int w = (int)(cell - row * cg.W), nv = min(32, g.Kx - 32 * w);
+    int s, r;
+    const bool live = bp_lattice(gb, wl, lane, s, r);
+    const int64_t from = live ? (((int64_t)s * g.R + r) * 2 + p) * cg.plane + cell : 0;
+    const uint32_t vs = live ? spin[from] : 0u, v0 = live ? d0[from] : 0u, v1 = live ? d1[from] : 0u;
+    uint64_t os = 0, o0 = 0, o1 = 0;
+    for (int k = 0; k < nv; ++k) {
+        const uint64_t bs = __ballot((vs >> k) & 1u), b0 = __ballot((v0 >> k) & 1u), b1 = __ballot((v1 >> k) & 1u);
+        os = lane == k ? bs : os;
+        o0 = lane == k ? b0 : o0;
+        o1 = lane == k ? b1 : o1;
+    }
+    if (lane < nv) {
+        const int64_t at = ((int64_t)wl * 2 + p) * g.Nh + row * g.Kx + 32 * w + lane;
+        bspin[at] = os;
+        bm0[at] = o0;
+        bm1[at] = o1;
+    }
+}
+
 // -------------------------------------------------------------- reductions
 // KIND 0: unsatisfied bonds of lattice l (each at its even end); 1: level
 // sum; 2: sites where replicas a and b of sample blockIdx.y differ.  Grid

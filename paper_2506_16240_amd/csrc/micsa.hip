@@ -1187,8 +1187,13 @@ int need_home(micsa_ctx* c)
     const CellGeom cg = cell_geom(c);
     {
         TimedLaunch t(c, kTimeReduce);
-        k_cells_unpack<<<dim3((unsigned)((cg.plane + 255) / 256), (unsigned)c->L), 256, 0, c->stream>>>(
-            cg, w32(c->ms), w32(c->md0), w32(c->md1), w32(c->mb), c->spin, c->dem);
+        if (c->bit)
+            k_cells_unpack_bits<<<dim3((unsigned)((2 * cg.plane + 3) / 4), (unsigned)word_lattices(c)), 256, 0,
+                                  c->stream>>>(geomb(c), cg, w32(c->ms), w32(c->md0), w32(c->md1), c->bspin, c->bdm0,
+                                               c->bdm1);
+        else
+            k_cells_unpack<<<dim3((unsigned)((cg.plane + 255) / 256), (unsigned)c->L), 256, 0, c->stream>>>(
+                cg, w32(c->ms), w32(c->md0), w32(c->md1), w32(c->mb), c->spin, c->dem);
     }
     const int st = check_launch(c, "k_cells_unpack");
     if (!st) c->home_ok = true;
@@ -1211,8 +1216,13 @@ int need_planes(micsa_ctx* c)
     const CellGeom cg = cell_geom(c);
     {
         TimedLaunch t(c, kTimeReduce);
-        k_cells_pack<<<dim3((unsigned)((cg.plane + 255) / 256), (unsigned)c->L), 256, 0, c->stream>>>(
-            cg, c->spin, c->dem, w32(c->ms), w32(c->md0), w32(c->md1), w32(c->mb));
+        if (c->bit)
+            k_cells_pack_bits<<<dim3((unsigned)((2 * cg.plane + 3) / 4), (unsigned)word_lattices(c)), 256, 0,
+                                c->stream>>>(geomb(c), cg, c->bspin, c->bdm0, c->bdm1, c->bJ, w32(c->ms), w32(c->md0),
+                                             w32(c->md1), w32(c->mb));
+        else
+            k_cells_pack<<<dim3((unsigned)((cg.plane + 255) / 256), (unsigned)c->L), 256, 0, c->stream>>>(
+                cg, c->spin, c->dem, w32(c->ms), w32(c->md0), w32(c->md1), w32(c->mb));
     }
     const int st = check_launch(c, "k_cells_pack");
     if (!st) c->planes_ok = true;
@@ -1571,9 +1581,16 @@ double msc_cost(const micsa_ctx* c)
 // and by default unless the multispin pass is estimated faster (us per sweep,
 // cells against the pass: 128^3 2.9 and 12.8, 256^3 9.4 and 13.5, 128^3 x 32
 // 20.2 and 17.6, 512^3 73.5 and 17).
-bool use_cells(const micsa_ctx* c)
+// The bit-plane layout takes it for calls of at least kMscMinSweeps sweeps
+// (a call packs the planes if they are stale) unless a launch shape of its
+// own sweep is asked for: 256 x 2 lattices of 32^3 take 0.8 us per sweep, the
+// word-wise sweep 8.7.
+bool use_cells(const micsa_ctx* c, int64_t n = kMscMinSweeps)
 {
-    if (!c->plan.ok || c->bit) return false;
+    if (!c->plan.ok) return false;
+    if (c->bit)
+        return c->kernel_opt == MICSA_KERNEL_AUTO && !c->tile_y && !c->tile_z && !c->use_graphs && !c->draw_ahead &&
+               (n >= kMscMinSweeps || c->planes_ok);
     if (c->kernel_opt == MICSA_KERNEL_RESIDENT || c->kernel_opt == MICSA_KERNEL_SLAB) return true;
     if (c->kernel_opt != MICSA_KERNEL_AUTO) return false;
     return !msc_eligible(c) || resident_eligible(c) || c->plan.cost < msc_cost(c);
@@ -1744,16 +1761,16 @@ int sweep_cells(micsa_ctx* c, int64_t n, long long* dlog, int64_t stride)
 
 // A sweep call of this algorithm logs inside its launches (one work-group
 // per lattice).
-bool logs_in_kernel(const micsa_ctx* c, int32_t algo)
+bool logs_in_kernel(const micsa_ctx* c, int32_t algo, int64_t n)
 {
     if (algo == MICSA_ALGO_WALKERS) return false;
-    if (algo == MICSA_ALGO_MICSA && use_cells(c)) return c->plan.sweeps == 0;
+    if (algo == MICSA_ALGO_MICSA && use_cells(c, n)) return c->plan.sweeps == 0;
     return use_resident(c);
 }
 
 int sweep_logging(micsa_ctx* c, int32_t algo, int64_t n, long long* dlog, int64_t stride)
 {
-    if (algo == MICSA_ALGO_MICSA && use_cells(c)) return n > 0 ? sweep_cells(c, n, dlog, stride) : MICSA_OK;
+    if (algo == MICSA_ALGO_MICSA && use_cells(c, n)) return n > 0 ? sweep_cells(c, n, dlog, stride) : MICSA_OK;
     if (int st = own_home(c)) return st;
     return launch_resident(c, algo, n, dlog, stride);
 }
@@ -1769,11 +1786,11 @@ int sweep_impl(micsa_ctx* c, int32_t algo, int64_t n)
     const bool walk_fused = algo == MICSA_ALGO_WALKERS && !c->bit && c->gamma == 1 && use_fused(c);
     // the one-launch multispin sweep takes an owed wandering on its loads
     // (and leaves one), as the fused byte sweep does
-    if (!walk_fused && !walk_msc && !(algo == MICSA_ALGO_MICSA && !use_cells(c) && use_msc(c, n) && msc_one_launch(c)) &&
+    if (!walk_fused && !walk_msc && !(algo == MICSA_ALGO_MICSA && !use_cells(c, n) && use_msc(c, n) && msc_one_launch(c)) &&
         (st0 = settle_wander(c)))
         return st0;
     if (walk_msc) return n > 0 ? sweep_msc(c, n, true) : MICSA_OK;
-    if (algo == MICSA_ALGO_MICSA && use_cells(c)) return n > 0 ? sweep_cells(c, n, nullptr, 0) : MICSA_OK;
+    if (algo == MICSA_ALGO_MICSA && use_cells(c, n)) return n > 0 ? sweep_cells(c, n, nullptr, 0) : MICSA_OK;
     if (algo == MICSA_ALGO_MICSA && use_msc(c, n)) return n > 0 ? sweep_msc(c, n) : MICSA_OK;
     // every other path sweeps the layout's own arrays
     if ((st0 = own_home(c))) return st0;
@@ -2130,7 +2147,7 @@ int micsa_sweep_logged_d(micsa_ctx* ctx, int32_t algo, int64_t n, int64_t stride
     int st = check_sweep(ctx, algo, n);
     if (st) return st;
     if (rows == 0 || (!E_log && !D_log)) return sweep_impl(ctx, algo, n);
-    if (logs_in_kernel(ctx, algo)) {
+    if (logs_in_kernel(ctx, algo, n)) {
         const size_t need = (size_t)rows * L * 2;
         if (need > ctx->rlog_cap) {
             // the old buffer may still be in use by enqueued work
@@ -2182,7 +2199,7 @@ int micsa_sweep_logged(micsa_ctx* ctx, int32_t algo, int64_t n, int64_t stride, 
     const int L = ctx->L;
     int st0 = check_sweep(ctx, algo, n);
     if (st0) return st0;
-    if (logs_in_kernel(ctx, algo)) {
+    if (logs_in_kernel(ctx, algo, n)) {
         if ((st0 = settle_wander(ctx))) return st0;
         long long* rlog = nullptr;
         if (rows > 0 && hipMalloc(&rlog, (size_t)rows * L * 2 * 8) != hipSuccess) {

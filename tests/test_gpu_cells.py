@@ -82,3 +82,31 @@ def test_drawn_levels_across_calls_and_slices():
     o.run(O.ALGO_MICSA, os_, 6, 0)
     state(g, o)
     state(h, o)
+
+
+@pytest.mark.parametrize("shape,lanes", [((16, 6, 10, 65, 2), M.LANES_SAMPLES), ((72, 8, 6, 3, 2), M.LANES_SAMPLES),
+                                         ((8, 2, 2, 2, 70), M.LANES_REPLICAS), ((64, 40, 48, 1, 17), M.LANES_REPLICAS)])
+def test_bit_plane_layout_on_cells(shape, lanes):
+    """The bit-plane layout's long calls run on the cell planes: ragged lane
+    groups in both lane modes, short rows and words, a lattice larger than one
+    work-group; short calls (the word-wise sweep) and logged ones in between,
+    a written state, C4 from the unpacked words."""
+    g = M.Lattice(*shape, 0xB17, layout=M.LAYOUT_BITPLANE, lane_mode=lanes)
+    o = O.Lattice(*shape, 0xB17)
+    g.set_schedule(M.Schedule(M.SCHED_LINEAR, 2.5, 0.5, 200, 4))
+    os_ = O.Schedule(O.SCHED_LINEAR, 2.5, 0.5, 200, 4)
+    short = (3,) if shape[0] * shape[1] <= 2048 else ()  # larger planes: per half, without a tally
+    for n in short + (11, 2, 9):
+        g.sweep(M.ALGO_MICSA, n)
+        o.run(O.ALGO_MICSA, os_, n, 0)
+        assert np.array_equal(g.energy(), o.energy()) and np.array_equal(g.overlap(0, 1), o.overlap(0, 1))
+    state(g, o)
+    E, D = g.sweep_logged(M.ALGO_MICSA, 10, 4)
+    Eo, Do = o.run(O.ALGO_MICSA, os_, 10, 4)
+    assert np.array_equal(E, Eo) and np.array_equal(D, Do)
+    assert np.array_equal(g.c4_sums(), o.c4_sums())
+    g.write_daemons(np.zeros_like(o.m))
+    o.m[...] = 0
+    g.sweep(M.ALGO_MICSA, 8)
+    o.run(O.ALGO_MICSA, os_, 8, 0)
+    state(g, o)
