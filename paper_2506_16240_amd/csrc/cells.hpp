@@ -84,6 +84,14 @@ __device__ __forceinline__ uint32_t cell_move(const uint32_t (&u)[6], uint32_t& 
 }
 
 // ------------------------------------------------------------------- draws
+// v shifted up by one with the lane's bit of a lane mask coming in: one
+// add-with-carry.
+__device__ __forceinline__ void cell_push(uint32_t& v, uint64_t mask)
+{
+    uint64_t carry;
+    asm("v_addc_co_u32_e64 %0, %1, %2, %2, %3" : "=v"(v), "=s"(carry) : "v"(v), "s"(mask));
+}
+
 // Both parities' levels of word w of a row: 32 sites of each, 16 Philox
 // calls (nv / 2 for a shorter word).  The bits enter from the top word's end,
 // one add-with-carry each.
@@ -94,9 +102,9 @@ __device__ __forceinline__ void cell_draw(const Geom& g, int row, int w, int nv,
     const uint32_t base = (uint32_t)(((int64_t)g.Lx * row) >> 2) + fam_off + 16u * (uint32_t)w;
     uint32_t a0 = 0, a1 = 0, b0 = 0, b1 = 0;  // even-x and odd-x sites
     auto push = [&](uint32_t& l0, uint32_t& l1, uint32_t u) {
-        const bool p0 = u > t0, p1 = u > t1, p2 = u > t2;
-        l1 = l1 + l1 + (p1 ? 1u : 0u);
-        l0 = l0 + l0 + ((p0 ^ p1 ^ p2) ? 1u : 0u);
+        const uint64_t p0 = __ballot(u > t0), p1 = __ballot(u > t1), p2 = __ballot(u > t2);
+        cell_push(l1, p1);
+        cell_push(l0, p0 ^ p1 ^ p2);
     };
     for (int c = (nv >> 1) - 1; c >= 0; --c) {
         const u32x4 o = philox10(base + (uint32_t)c, rho, r, sw, g.key0, g.key1);
@@ -149,6 +157,85 @@ __device__ __forceinline__ void cells_draw_body(const CellDraw& D, int l, int64_
 __global__ void __launch_bounds__(256) k_cells_draw(CellDraw D)
 {
     cells_draw_body(D, blockIdx.y, (int64_t)blockIdx.x * blockDim.x + threadIdx.x, (int64_t)gridDim.x * blockDim.x);
+}
+
+// The canonical baselines draw a uniform u per site and half sweep (Philox
+// (h >> 2, 2k + p, r, stream | s), word h & 3, h the parity-split index) and
+// compare it with a table that falls with its index, so that the whole
+// comparison is one small number per site, drawn here for many sweeps at once:
+//   ALG 1, heat bath: c = #{v : u < tau[v]}, 0..7; the spin becomes 1 iff its
+//     count v of neighbours with J s = -1 is at least c.  Three bits.
+//   ALG 2, Metropolis: theta[0..3] take every move, c = #{q in 4..6 : u <
+//     theta[q]}; a spin with u unsatisfied bonds (q = 6 - u) flips iff
+//     u + c >= 3.  Two bits.
+// Planes: dr + ((it * 2 + p) * K + i) * L * plane + l * plane + cell, K bits.
+struct CellCanon {
+    CellGeom cg;
+    uint32_t* dr;
+    const HeatBathThresholds* tab;  // the schedule's table, an entry per refresh
+    int64_t k0;                     // first sweep
+    int32_t n, period, L, gamma;
+};
+
+__device__ __forceinline__ int64_t cell_refresh_index(int64_t k, int32_t P)
+{
+    return P >= 1 ? k / P : 63 - __clzll((unsigned long long)(k + 1));
+}
+
+// Thread per cell of lattice blockIdx.y and half sweep blockIdx.z (uniform, so
+// that its table is too), grid-stride.
+template <int ALG>
+__global__ void __launch_bounds__(64) k_cells_draw_canonical(CellCanon D)
+{
+    constexpr int K = ALG == 1 ? 3 : 2;
+    const CellGeom& cg = D.cg;
+    const int l = blockIdx.y;
+    const uint32_t rep = (uint32_t)(l % cg.g.R);
+    const uint32_t sw = stream_word(ALG == 1 ? kStreamHeatBath : kStreamMetropolis, (uint32_t)(l / cg.g.R));
+    const int64_t k = D.k0 + (blockIdx.z >> 1);
+    const uint32_t time = (uint32_t)(2 * k + (blockIdx.z & 1));
+    const HeatBathThresholds& th = D.tab[cell_refresh_index(k / D.gamma, D.period)];
+    // u < t as u <= t - 1, or never for t = 0 (t may be 2^32)
+    uint32_t t[7];
+    uint64_t on[7];
+#pragma unroll
+    for (int v = 0; v < 7; ++v) {
+        t[v] = (uint32_t)(th.tau[v] - (th.tau[v] ? 1u : 0u));
+        on[v] = th.tau[v] ? ~0ull : 0ull;
+    }
+    const bool some_never = th.tau[6] == 0;  // the smallest (the scalar unit is near its rate: no masks without it)
+    for (int64_t cell = (int64_t)blockIdx.x * 64 + threadIdx.x; cell < cg.plane; cell += (int64_t)gridDim.x * 64) {
+        const int64_t row = cell / cg.W;
+        const int w = (int)(cell - row * cg.W), n4 = min(32, cg.g.Kx - 32 * w) >> 2;
+        const uint32_t base = (uint32_t)((row * cg.g.Kx + 32 * w) >> 2);
+        uint32_t b[K] = {};
+        auto push = [&](uint32_t u) {
+            uint64_t M[7];
+#pragma unroll
+            for (int v = ALG == 1 ? 0 : 4; v < 7; ++v) M[v] = __ballot(u <= t[v]);
+            if (some_never)
+#pragma unroll
+                for (int v = ALG == 1 ? 0 : 4; v < 7; ++v) M[v] &= on[v];
+            if (ALG == 1) {
+                cell_push(b[0], M[0] ^ M[1] ^ M[2] ^ M[3] ^ M[4] ^ M[5] ^ M[6]);
+                cell_push(b[1], (M[1] & ~M[3]) | M[5]);
+                cell_push(b[K - 1], M[3]);
+            } else {
+                cell_push(b[0], M[4] ^ M[5] ^ M[6]);
+                cell_push(b[1], M[5]);
+            }
+        };
+        for (int c = n4 - 1; c >= 0; --c) {
+            const u32x4 o = philox10(base + (uint32_t)c, time, rep, sw, cg.g.key0, cg.g.key1);
+            push(o.v3);
+            push(o.v2);
+            push(o.v1);
+            push(o.v0);
+        }
+#pragma unroll
+        for (int i = 0; i < K; ++i)
+            D.dr[((int64_t)blockIdx.z * K + i) * D.L * cg.plane + (int64_t)l * cg.plane + cell] = b[i];
+    }
 }
 
 // ------------------------------------------------------------------ sweeps
@@ -218,7 +305,8 @@ __device__ __forceinline__ uint32_t wave_sum_dpp(uint32_t v)
 // XM: how a row's x neighbours are found.  0: the row is one word (rotate
 // within its Kx bits); 1: several full words (funnel shift with the next or
 // previous one); 2: several words, the last one short.
-template <int NR, int XM>
+// ALG 0: MicSA; 1, 2: the heat bath and Metropolis on drawn planes.
+template <int NR, int XM, int ALG>
 __device__ __forceinline__ void cells_body(const CellSweep& J, int l, int ty, int tz, uint32_t* lds, uint32_t* red)
 {
     constexpr int CAP = NR * kCellLanes;  // LDS words of one parity's plane
@@ -284,8 +372,8 @@ __device__ __forceinline__ void cells_body(const CellSweep& J, int l, int ty, in
 #pragma unroll
         for (int p = 0; p < 2; ++p) {
             s[p][i] = at(J.s_in + lp + p * cg.plane, gi[i]);
-            m0[p][i] = at(J.d0_in + lp + p * cg.plane, gi[i]);
-            m1[p][i] = at(J.d1_in + lp + p * cg.plane, gi[i]);
+            m0[p][i] = ALG == 0 ? at(J.d0_in + lp + p * cg.plane, gi[i]) : 0u;
+            m1[p][i] = ALG == 0 ? at(J.d1_in + lp + p * cg.plane, gi[i]) : 0u;
         }
         auto bd = [&](int d, int cell) { return at(bl + (int64_t)d * cg.plane, (uint32_t)cell << 2); };
         const uint32_t jpx = bd(kPx, me), jmx = bd(kMx, me);
@@ -332,7 +420,7 @@ __device__ __forceinline__ void cells_body(const CellSweep& J, int l, int ty, in
     auto msk = [&](int i) { return XM == 2 ? cell_mask((int)nvs[i]) : mask01; };
     // the levels of the next refresh, loaded ahead of it (with three or four
     // cells per thread the registers are needed elsewhere: loaded at it)
-    constexpr bool AHEAD = NR <= 2;
+    constexpr bool AHEAD = ALG == 0 && NR <= 2;
     uint32_t r0[2][NR], r1[2][NR];
     int64_t dr = 0;
     auto fetch = [&]() {
@@ -346,7 +434,24 @@ __device__ __forceinline__ void cells_body(const CellSweep& J, int l, int ty, in
     };
     int64_t ref = J.ref0;
     if (AHEAD) fetch();  // (with no refresh in the launch the addresses are still good)
-    int taken = levels();  // levels in, minus levels out, of the owned sites
+    // MicSA: levels in, minus levels out, of the owned sites; else a quarter of
+    // their energy change
+    int taken = ALG == 0 ? levels() : 0;
+    // the baselines' drawn bits of the next half sweep, loaded during this one
+    constexpr int K = ALG == 1 ? 3 : 2;
+    uint32_t nx[NR][K];
+    const int64_t lplane = (int64_t)J.lattices * cg.plane;
+    const uint32_t* cd = ALG ? J.dr0 + (int64_t)l * cg.plane : nullptr;
+    int halves = 2 * J.n;
+    auto fetch_half = [&]() {
+#pragma unroll
+        for (int i = 0; i < NR; ++i)
+#pragma unroll
+            for (int b = 0; b < K; ++b) nx[i][b] = at(cd + b * lplane, gi[i]);
+        --halves;
+        cd += halves > 0 ? K * lplane : 0;  // (past the last half: the same addresses again)
+    };
+    if (ALG != 0) fetch_half();
     lds_barrier();
 
     // the x neighbour word of parity p's sites other than the one at the same k
@@ -374,11 +479,47 @@ __device__ __forceinline__ void cells_body(const CellSweep& J, int l, int ty, in
     };
     auto half = [&](auto pc) {
         constexpr int p = decltype(pc)::value;
+        uint32_t cur[NR][K];
+        if (ALG != 0) {
+#pragma unroll
+            for (int i = 0; i < NR; ++i)
+#pragma unroll
+                for (int b = 0; b < K; ++b) cur[i][b] = nx[i][b];
+            fetch_half();
+        }
 #pragma unroll
         for (int i = 0; i < NR; ++i) {
             uint32_t u[6];
             unsat(i, p, u);
-            s[p][i] ^= cell_move(u, m0[p][i], m1[p][i]);
+            if (ALG == 0) {
+                s[p][i] ^= cell_move(u, m0[p][i], m1[p][i]);
+            } else {
+                const uint32_t s1 = xor3(u[0], u[1], u[2]), c1 = maj32(u[0], u[1], u[2]);
+                const uint32_t s2 = xor3(u[3], u[4], u[5]), c2 = maj32(u[3], u[4], u[5]);
+                const uint32_t u0 = s1 ^ s2, k0 = s1 & s2;
+                const uint32_t u1 = xor3(c1, c2, k0), u2 = maj32(c1, c2, k0);  // unsatisfied bonds
+                uint32_t f;
+                if (ALG == 2) {
+                    // u + c >= 3: u2, or u1 u0 + c1 c0 carries past 2
+                    const uint32_t a = cur[i][1], b = cur[i][0];
+                    f = u2 | (u1 & a) | ((u1 | a) & (u0 | b));
+                } else {
+                    // v = u for a spin 0, 6 - u for a spin 1; 6 - u has the bits
+                    // ~(u2 | (u1 & u0)), ~(u1 ^ u0), u0
+                    const uint32_t S = s[p][i];
+                    const uint32_t d1 = ~(u1 ^ u0), d2 = ~(u2 | (u1 & u0));
+                    const uint32_t v0 = u0, v1 = (S & d1) | (~S & u1), v2 = (S & d2) | (~S & u2);
+                    const uint32_t b0 = ~v0 & cur[i][0];
+                    const uint32_t b1 = maj32(~v1, cur[i][1], b0);
+                    const uint32_t b2 = maj32(~v2, cur[i][K - 1], b1);  // v < c
+                    f = S ^ ~b2;                                        // the spin becomes ~(v < c)
+                }
+                if (XM == 0 || XM == 2) f &= msk(i);
+                // dH = 12 - 4 u per flip
+                const int e = 3 * __popc(f) - __popc(f & u0) - 2 * __popc(f & u1) - 4 * __popc(f & u2);
+                taken += (own >> i) & 1u ? e : 0;
+                s[p][i] ^= f;
+            }
             lds[p * CAP + t + i * B] = s[p][i];
         }
         lds_barrier();
@@ -396,7 +537,7 @@ __device__ __forceinline__ void cells_body(const CellSweep& J, int l, int ty, in
     };
     int to_log = J.log_first, buf = 0;
     for (int it = 0; it < J.n; ++it) {
-        if (it == ref) {
+        if (ALG == 0 && it == ref) {
             taken -= levels();
             if (!AHEAD) fetch();
 #pragma unroll
@@ -444,15 +585,15 @@ __device__ __forceinline__ void cells_body(const CellSweep& J, int l, int ty, in
         lds_barrier();
         flush();
     }
-    taken -= levels();
+    if (ALG == 0) taken -= levels();
 #pragma unroll
     for (int i = 0; i < NR; ++i) {
         if (!((own >> i) & 1u)) continue;
 #pragma unroll
         for (int p = 0; p < 2; ++p) {
             put(J.s_out + lp + p * cg.plane, gi[i], s[p][i]);
-            put(J.d0_out + lp + p * cg.plane, gi[i], m0[p][i]);
-            put(J.d1_out + lp + p * cg.plane, gi[i], m1[p][i]);
+            if (ALG == 0) put(J.d0_out + lp + p * cg.plane, gi[i], m0[p][i]);
+            if (ALG == 0) put(J.d1_out + lp + p * cg.plane, gi[i], m1[p][i]);
         }
     }
     // a wave's sum fits 32 bits (at most 64 lanes x 4 cells x 64 sites x 3, per refresh met)
@@ -463,12 +604,12 @@ __device__ __forceinline__ void cells_body(const CellSweep& J, int l, int ty, in
 }
 
 // Grid (tiles along y, tiles along z, lattices).
-template <int NR, int XM>
+template <int NR, int XM, int ALG>
 __global__ void __launch_bounds__(kCellLanes) k_cells_sweep(CellSweep J)
 {
     __shared__ uint32_t lds[2 * NR * kCellLanes];
     __shared__ uint32_t red[4];
-    cells_body<NR, XM>(J, blockIdx.z, blockIdx.x, blockIdx.y, lds, red);
+    cells_body<NR, XM, ALG>(J, blockIdx.z, blockIdx.x, blockIdx.y, lds, red);
 }
 
 // ------------------------------------------------- planes <-> other layouts

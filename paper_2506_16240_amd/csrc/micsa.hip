@@ -886,57 +886,6 @@ inline void split_index(const micsa_ctx* c, int64_t i, int& par, int64_t& h)
     h = i >> 1;
 }
 
-// n sweeps from c->k in resident launches of up to kResidentChunk sweeps;
-// with dlog != nullptr every `stride` sweeps (U, D) per lattice are written
-// to dlog[row][L][2], rows counted from the first sweep of the call.
-int launch_resident(micsa_ctx* c, int32_t algo, int64_t n, long long* dlog, int64_t stride)
-{
-    const size_t lds = (size_t)c->g.Nh * 3;
-    // kernel instance: 0 MicSA, 1 heat bath, 2 Metropolis
-    const int inst = algo == MICSA_ALGO_MICSA ? 0 : (algo == MICSA_ALGO_HEATBATH ? 1 : 2);
-    static const void* const kernels[3] = {(const void*)k_resident<0>, (const void*)k_resident<1>,
-                                           (const void*)k_resident<2>};
-    static bool attr_set[3] = {false, false, false};
-    if (!attr_set[inst]) {
-        const hipError_t e =
-            hipFuncSetAttribute(kernels[inst], hipFuncAttributeMaxDynamicSharedMemorySize, (int)kResidentLdsMax);
-        if (e != hipSuccess) return fail(c, MICSA_EHIP, std::string("hipFuncSetAttribute: ") + hipGetErrorString(e));
-        attr_set[inst] = true;
-    }
-    const HeatBathThresholds* tab = canonical_table(c, algo);
-    const int tkind = inst == 0 ? kTimeSweep : canonical_timing(algo);
-    int64_t done = 0;
-    while (done < n) {
-        int64_t chunk = std::min<int64_t>(kResidentChunk, n - done);
-        if (dlog && chunk % stride) chunk = std::max<int64_t>(stride, chunk / stride * stride);
-        chunk = std::min(chunk, n - done);
-        ResidentSched rs;
-        rs.k0 = c->k + done;
-        rs.n = chunk;
-        rs.rho0 = 0;
-        rs.period = c->sched.period;
-        rs.log_stride = dlog ? (int32_t)stride : 0;
-        rs.log_row0 = dlog ? done / stride : 0;
-        {
-            TimedLaunch t(c, tkind);
-            if (inst == 0)
-                k_resident<0><<<c->L, kResidentBlock, lds, c->stream>>>(c->g, c->spin, c->dem, c->tally, rs,
-                                                                        c->d_dth, tab, dlog);
-            else if (inst == 1)
-                k_resident<1><<<c->L, kResidentBlock, lds, c->stream>>>(c->g, c->spin, c->dem, c->tally, rs,
-                                                                        c->d_dth, tab, dlog);
-            else
-                k_resident<2><<<c->L, kResidentBlock, lds, c->stream>>>(c->g, c->spin, c->dem, c->tally, rs,
-                                                                        c->d_dth, tab, dlog);
-        }
-        const int st = check_launch(c, "k_resident");
-        if (st) return st;
-        done += chunk;
-    }
-    c->k += n;
-    return MICSA_OK;
-}
-
 // ------------------------------------------------------- replayable graphs
 // The per-half paths (byte layout without the resident/fused kernels, and
 // the bit-plane layout) launch 3 kernels per sweep, so small and mid-size
@@ -1541,11 +1490,12 @@ CellPlan cell_plan(const micsa_ctx* c)
         }
     };
     if ((int64_t)Ly * Lz * W <= kCellCap) consider(Ly, Lz, 1);
+    if (best.ok && best.nr <= 2) return best;  // no tile makes up for its launches here
     // tiles that divide a side about evenly, a few per factor of two
     auto sides = [](int L) {
         std::vector<int> v;
         int last = 0;
-        for (double n = 1; n <= L; n = std::max(n + 1, n * 1.15)) {
+        for (double n = 1; n <= L; n = std::max(n + 1, n * 1.2)) {
             const int t = (int)((L + (int)n - 1) / (int)n);
             if (t != last) v.push_back(t);
             last = t;
@@ -1554,7 +1504,7 @@ CellPlan cell_plan(const micsa_ctx* c)
         return v;
     };
     const std::vector<int> ys = sides(Ly), zs = sides(Lz);
-    for (int T : {1, 2, 3, 4, 5, 6, 8, 10})
+    for (int T : {1, 2, 3, 4, 6, 8})
         for (int ty : ys)
             for (int tz : zs) {
                 if (ty == Ly && tz == Lz) continue;
@@ -1592,7 +1542,7 @@ bool use_cells(const micsa_ctx* c, int64_t n = kMscMinSweeps)
         return c->kernel_opt == MICSA_KERNEL_AUTO && !c->tile_y && !c->tile_z && !c->use_graphs && !c->draw_ahead &&
                (n >= kMscMinSweeps || c->planes_ok);
     if (c->kernel_opt == MICSA_KERNEL_RESIDENT || c->kernel_opt == MICSA_KERNEL_SLAB) return true;
-    if (c->kernel_opt != MICSA_KERNEL_AUTO) return false;
+    if (c->kernel_opt != MICSA_KERNEL_AUTO || use_graph(c)) return false;
     return !msc_eligible(c) || resident_eligible(c) || c->plan.cost < msc_cost(c);
 }
 
@@ -1614,7 +1564,8 @@ void* dev_alloc(size_t bytes)
 
 // Planes (with their alternates where tiles read what others write) and room
 // for drawn levels.  Drawn levels: as many refreshes as fit 8 MiB or the
-// lattices' spins in bytes, whichever is more, at least one.
+// lattices' spins in bytes, whichever is more, at least two (a sweep of a
+// baseline draws the words of one and a half).
 int cells_alloc(micsa_ctx* c)
 {
     const CellGeom cg = cell_geom(c);
@@ -1636,7 +1587,7 @@ int cells_alloc(micsa_ctx* c)
     }
     if (!c->cdr0) {
         const size_t one = words * 4 * 2, room = std::max<size_t>((size_t)8 << 20, (size_t)c->L * 2 * (size_t)c->g.Nh);
-        const int64_t cap = std::max<int64_t>(1, std::min<int64_t>((int64_t)(room / one), 1024));
+        const int64_t cap = std::max<int64_t>(2, std::min<int64_t>((int64_t)(room / one), 1024));
         uint32_t* a = static_cast<uint32_t*>(dev_alloc(one * (size_t)cap));
         if (!a) return fail(c, MICSA_ENOMEM, "drawn levels");
         c->cdr0 = a;
@@ -1682,14 +1633,62 @@ int cells_draw(micsa_ctx* c, int64_t kr, int64_t k_end)
 }
 
 using CellKernel = void (*)(CellSweep);
+template <int ALG>
 CellKernel cell_kernel(int nr, int xm)
 {
     static const CellKernel k[kCellMaxNR][3] = {
-        {k_cells_sweep<1, 0>, k_cells_sweep<1, 1>, k_cells_sweep<1, 2>},
-        {k_cells_sweep<2, 0>, k_cells_sweep<2, 1>, k_cells_sweep<2, 2>},
-        {k_cells_sweep<3, 0>, k_cells_sweep<3, 1>, k_cells_sweep<3, 2>},
-        {k_cells_sweep<4, 0>, k_cells_sweep<4, 1>, k_cells_sweep<4, 2>}};
+        {k_cells_sweep<1, 0, ALG>, k_cells_sweep<1, 1, ALG>, k_cells_sweep<1, 2, ALG>},
+        {k_cells_sweep<2, 0, ALG>, k_cells_sweep<2, 1, ALG>, k_cells_sweep<2, 2, ALG>},
+        {k_cells_sweep<3, 0, ALG>, k_cells_sweep<3, 1, ALG>, k_cells_sweep<3, 2, ALG>},
+        {k_cells_sweep<4, 0, ALG>, k_cells_sweep<4, 1, ALG>, nullptr}};
     return k[nr - 1][xm];
+}
+
+// One launch of the cell kernel on the planes (filled in: J's sweeps, draws
+// and logging); tiles go from one copy to the other.
+int launch_cells(micsa_ctx* c, int alg, CellSweep& J)
+{
+    const CellPlan& pl = c->plan;
+    J.cg = cell_geom(c);
+    J.f = pl.f;
+    J.s_in = w32(c->ms);
+    J.d0_in = w32(c->md0);
+    J.d1_in = w32(c->md1);
+    J.bond = w32(c->mb);
+    const bool whole = pl.sweeps == 0;
+    J.s_out = w32(whole ? c->ms : c->ms_alt);
+    J.d0_out = w32(whole ? c->md0 : c->md0_alt);
+    J.d1_out = w32(whole ? c->md1 : c->md1_alt);
+    J.tally = c->tally;
+    J.period = c->sched.period;
+    J.lattices = c->L;
+    J.inv_bdiv = 1.0f / (float)J.cg.bdiv;
+    {
+        TimedLaunch t(c, alg == 0 ? kTimeSweep : (alg == 1 ? kTimeHeatBath : kTimeMetropolis));
+        const CellKernel k = alg == 0 ? cell_kernel<0>(pl.nr, pl.xm)
+                                      : (alg == 1 ? cell_kernel<1>(pl.nr, pl.xm) : cell_kernel<2>(pl.nr, pl.xm));
+        k<<<dim3((unsigned)pl.f.nty, (unsigned)pl.f.ntz, (unsigned)c->L), pl.block, 0, c->stream>>>(J);
+    }
+    if (int st = check_launch(c, "k_cells_sweep")) return st;
+    if (!whole) {
+        std::swap(c->ms, c->ms_alt);
+        if (alg == 0) {  // the baselines leave the levels where they are
+            std::swap(c->md0, c->md0_alt);
+            std::swap(c->md1, c->md1_alt);
+        }
+    }
+    return MICSA_OK;
+}
+
+// Logging fields of a launch of the sweeps from done on, in a call that logs
+// every stride sweeps to dlog.
+void cell_log(CellSweep& J, long long* dlog, int64_t done, int64_t stride)
+{
+    J.log = dlog;
+    if (!dlog) return;
+    J.log_row0 = done / stride;
+    J.log_stride = (int32_t)std::min<int64_t>(stride, INT32_MAX);
+    J.log_first = (int32_t)std::min<int64_t>(stride - done % stride, INT32_MAX);
 }
 
 // MicSA sweeps k .. k + n - 1 on the cell kernel.  dlog (whole-lattice plans
@@ -1700,13 +1699,12 @@ int sweep_cells(micsa_ctx* c, int64_t n, long long* dlog, int64_t stride)
     int st;
     if ((st = cells_alloc(c)) || (st = need_planes(c))) return st;
     const CellGeom cg = cell_geom(c);
-    const CellPlan& pl = c->plan;
     const int32_t P = c->sched.period;
     const int64_t k_first = c->k, k_end = c->k + n, stride_w = (int64_t)c->L * 2 * cg.plane;
     c->home_ok = false;
     while (c->k < k_end) {
         const int64_t k = c->k;
-        int64_t len = std::min<int64_t>(k_end - k, pl.sweeps > 0 ? pl.sweeps : kResidentChunk);
+        int64_t len = std::min<int64_t>(k_end - k, c->plan.sweeps > 0 ? c->plan.sweeps : kResidentChunk);
         // the refreshes of the launch: drawn, and in one slice
         const int64_t kr = next_refresh(c, k, k + len);
         int64_t slot = 0;
@@ -1719,42 +1717,76 @@ int sweep_cells(micsa_ctx* c, int64_t n, long long* dlog, int64_t stride)
             if (refresh_index(k + len - 1, P) >= beyond) len = refresh_sweep(beyond, P) - k;
         }
         CellSweep J{};
-        J.cg = cg;
-        J.f = pl.f;
-        J.s_in = w32(c->ms);
-        J.d0_in = w32(c->md0);
-        J.d1_in = w32(c->md1);
-        J.bond = w32(c->mb);
-        const bool whole = pl.sweeps == 0;
-        J.s_out = w32(whole ? c->ms : c->ms_alt);
-        J.d0_out = w32(whole ? c->md0 : c->md0_alt);
-        J.d1_out = w32(whole ? c->md1 : c->md1_alt);
         J.dr0 = c->cdr0 + slot * stride_w;
         J.dr1 = c->cdr1 + slot * stride_w;
         J.dr_stride = stride_w;
-        J.tally = c->tally;
-        J.log = dlog;
-        J.log_row0 = dlog ? (k - k_first) / stride : 0;
-        J.log_stride = dlog ? (int32_t)std::min<int64_t>(stride, INT32_MAX) : 0;
-        J.log_first = dlog ? (int32_t)std::min<int64_t>(stride - (k - k_first) % stride, INT32_MAX) : 0;
+        cell_log(J, dlog, k - k_first, stride);
         J.k0 = k;
         J.n = (int32_t)len;
         J.ref0 = kr >= 0 && kr < k + len ? (int32_t)(kr - k) : (int32_t)len;
-        J.period = P;
-        J.lattices = c->L;
-        J.inv_bdiv = 1.0f / (float)cg.bdiv;
-        {
-            TimedLaunch t(c, kTimeSweep);
-            cell_kernel(pl.nr, pl.xm)<<<dim3((unsigned)pl.f.nty, (unsigned)pl.f.ntz, (unsigned)c->L), pl.block, 0,
-                                        c->stream>>>(J);
-        }
-        if ((st = check_launch(c, "k_cells_sweep"))) return st;
-        if (!whole) {
-            std::swap(c->ms, c->ms_alt);
-            std::swap(c->md0, c->md0_alt);
-            std::swap(c->md1, c->md1_alt);
-        }
+        if ((st = launch_cells(c, 0, J))) return st;
         c->k = k + len;
+    }
+    return MICSA_OK;
+}
+
+// The heat bath and Metropolis on the cell kernel: their comparisons drawn
+// for as many sweeps as there is room for by one launch on the whole device,
+// then the sweeps.  Against the byte-wise kernels, which pay one Philox call
+// per four updates and about as much again for the comparisons, in the sweep
+// itself: at most 700 updates/ns on a full device, where the draws alone run
+// at about 1550 and the sweep adds its plan's estimate.  Lattices too narrow
+// for the fused kernel pay two launches per sweep there.
+bool use_cells_canonical(const micsa_ctx* c)
+{
+    if (!c->plan.ok || c->bit) return false;
+    if (c->kernel_opt == MICSA_KERNEL_RESIDENT) return true;
+    if (c->kernel_opt != MICSA_KERNEL_AUTO || use_graph(c)) return false;
+    if (!use_fused(c)) return true;
+    const double sites = (double)c->L * 2.0 * (double)c->g.Nh;
+    return c->plan.cost / 2.4e3 + sites / 1.5e6 < sites / 0.68e6;
+}
+
+int sweep_cells_canonical(micsa_ctx* c, int32_t algo, int64_t n, long long* dlog, int64_t stride)
+{
+    int st;
+    if ((st = cells_alloc(c)) || (st = need_planes(c))) return st;
+    const CellGeom cg = cell_geom(c);
+    const int alg = algo == MICSA_ALGO_METROPOLIS ? 2 : 1, K = alg == 1 ? 3 : 2;
+    const int64_t k_first = c->k, k_end = c->k + n, plane = (int64_t)c->L * cg.plane;
+    c->home_ok = false;
+    c->cdr_n = 0;  // the buffer holds the baselines' draws from here on
+    const int64_t room = std::min<int64_t>(4 * plane * c->cdr_cap / (2 * K * plane), 4096);  // sweeps drawn at once
+    while (c->k < k_end) {
+        const int64_t len = std::min<int64_t>(k_end - c->k, room), k_draw = c->k;
+        CellCanon D{};
+        D.cg = cg;
+        D.dr = c->cdr0;
+        D.tab = canonical_table(c, algo);
+        D.k0 = k_draw;
+        D.n = (int32_t)len;
+        D.period = c->sched.period;
+        D.L = c->L;
+        D.gamma = c->gamma;
+        const dim3 grid((unsigned)std::min<int64_t>((cg.plane + 63) / 64, 16384), (unsigned)c->L, (unsigned)(2 * len));
+        {
+            TimedLaunch t(c, canonical_timing(algo));
+            if (alg == 1)
+                k_cells_draw_canonical<1><<<grid, 64, 0, c->stream>>>(D);
+            else
+                k_cells_draw_canonical<2><<<grid, 64, 0, c->stream>>>(D);
+        }
+        if ((st = check_launch(c, "k_cells_draw_canonical"))) return st;
+        while (c->k < k_draw + len) {
+            const int64_t m = std::min<int64_t>(k_draw + len - c->k, c->plan.sweeps > 0 ? c->plan.sweeps : len);
+            CellSweep J{};
+            J.dr0 = c->cdr0 + (c->k - k_draw) * 2 * K * plane;
+            cell_log(J, dlog, c->k - k_first, stride);
+            J.k0 = c->k;
+            J.n = (int32_t)m;
+            if ((st = launch_cells(c, alg, J))) return st;
+            c->k += m;
+        }
     }
     return MICSA_OK;
 }
@@ -1764,15 +1796,14 @@ int sweep_cells(micsa_ctx* c, int64_t n, long long* dlog, int64_t stride)
 bool logs_in_kernel(const micsa_ctx* c, int32_t algo, int64_t n)
 {
     if (algo == MICSA_ALGO_WALKERS) return false;
-    if (algo == MICSA_ALGO_MICSA && use_cells(c, n)) return c->plan.sweeps == 0;
-    return use_resident(c);
+    if (algo == MICSA_ALGO_MICSA) return use_cells(c, n) && c->plan.sweeps == 0;
+    return use_cells_canonical(c) && c->plan.sweeps == 0;
 }
 
 int sweep_logging(micsa_ctx* c, int32_t algo, int64_t n, long long* dlog, int64_t stride)
 {
-    if (algo == MICSA_ALGO_MICSA && use_cells(c, n)) return n > 0 ? sweep_cells(c, n, dlog, stride) : MICSA_OK;
-    if (int st = own_home(c)) return st;
-    return launch_resident(c, algo, n, dlog, stride);
+    if (n <= 0) return MICSA_OK;
+    return algo == MICSA_ALGO_MICSA ? sweep_cells(c, n, dlog, stride) : sweep_cells_canonical(c, algo, n, dlog, stride);
 }
 
 int sweep_impl(micsa_ctx* c, int32_t algo, int64_t n)
@@ -1792,10 +1823,11 @@ int sweep_impl(micsa_ctx* c, int32_t algo, int64_t n)
     if (walk_msc) return n > 0 ? sweep_msc(c, n, true) : MICSA_OK;
     if (algo == MICSA_ALGO_MICSA && use_cells(c, n)) return n > 0 ? sweep_cells(c, n, nullptr, 0) : MICSA_OK;
     if (algo == MICSA_ALGO_MICSA && use_msc(c, n)) return n > 0 ? sweep_msc(c, n) : MICSA_OK;
+    if ((algo == MICSA_ALGO_HEATBATH || algo == MICSA_ALGO_METROPOLIS) && use_cells_canonical(c))
+        return n > 0 ? sweep_cells_canonical(c, algo, n, nullptr, 0) : MICSA_OK;
     // every other path sweeps the layout's own arrays
     if ((st0 = own_home(c))) return st0;
     if (algo != MICSA_ALGO_WALKERS) {
-        if (use_resident(c)) return launch_resident(c, algo, n, nullptr, 0);
         if (use_graph(c) && n >= kGraphSweeps) return sweep_graph(c, algo, n);
     }
     if (algo == MICSA_ALGO_MICSA && bp_one_launch(c)) return sweep_bitplane(c, n);

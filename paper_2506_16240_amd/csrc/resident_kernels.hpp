@@ -228,19 +228,6 @@ __device__ __forceinline__ void resident_body(const Geom& g, uint8_t* __restrict
     block_add(tally + (int64_t)l * kSlots, dE);
 }
 
-template <int ALGO>
-__global__ void __launch_bounds__(512) k_resident(Geom g, uint8_t* __restrict__ spin, uint8_t* __restrict__ dem,
-                                                  unsigned long long* __restrict__ tally,
-                                                  ResidentSched rs, const DaemonThresholds* __restrict__ dth,
-                                                  const HeatBathThresholds* __restrict__ hth,
-                                                  long long* __restrict__ log)
-{
-    extern __shared__ uint32_t lds32[];
-    __shared__ long long red[16];
-    __shared__ uint64_t tau[8];
-    resident_body<ALGO>(g, spin, dem, tally, rs, dth, hth, log, blockIdx.x, gridDim.x, lds32, red, tau);
-}
-
 // One lattice of some context per work-group: the batched launch of the
 // serving pool, where lattices of different sizes, schedules and sweep
 // indices advance together (each keeps its own counters and thresholds).

@@ -110,3 +110,29 @@ def test_bit_plane_layout_on_cells(shape, lanes):
     g.sweep(M.ALGO_MICSA, 8)
     o.run(O.ALGO_MICSA, os_, 8, 0)
     state(g, o)
+
+
+@pytest.mark.parametrize("algo", [M.ALGO_HEATBATH, M.ALGO_METROPOLIS])
+@pytest.mark.parametrize("shape", SHAPES)
+def test_canonical_sweeps_on_cells(shape, algo):
+    """The baselines on planes of drawn comparisons, at the cell sweep's shapes:
+    tables with certain and impossible moves (low T), calls of one sweep, of
+    several launches and of more sweeps than one draw holds, a logged call,
+    MicSA (whose drawn levels share the buffer) in between; the tally counts
+    every flip."""
+    g, o = M.Lattice(*shape, 0xCA40), O.Lattice(*shape, 0xCA40)
+    for T0, T1, P, calls in ((3.0, 0.02, 2, (1, 13)), (0.9, 0.9, M.REFRESH_LOG2, (6,))):
+        g.set_schedule(M.Schedule(M.SCHED_LINEAR, T0, T1, 40, P))
+        os_ = O.Schedule(O.SCHED_LINEAR, T0, T1, 40, P)
+        for n in calls:
+            g.sweep(algo, n)
+            o.run(algo, os_, n, 0)
+            assert np.array_equal(g.energy(), o.energy()) and np.array_equal(g.energy_tally(), o.energy())
+        g.sweep(M.ALGO_MICSA, 3)
+        o.run(O.ALGO_MICSA, os_, 3, 0)
+        state(g, o)
+    E, D = g.sweep_logged(algo, 5, 2)
+    Eo, Do = o.run(algo, os_, 5, 2)
+    assert np.array_equal(E, Eo)
+    state(g, o)
+    g.close()
