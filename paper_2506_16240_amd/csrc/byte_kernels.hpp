@@ -347,13 +347,25 @@ __global__ void __launch_bounds__(256) k_heatbath_half(Geom g, uint8_t* __restri
 // backward X, Y, Z).
 __constant__ const int kWalkerDir[6] = {kPx, kPy, kPz, kMx, kMy, kMz};
 
+// Parity of each family's wandering; a family with -1 stays (is copied).
+struct WanderParity {
+    int32_t p[6];
+};
+
 __global__ void __launch_bounds__(256) k_wander(Geom g, const uint8_t* __restrict__ dem_in,
-                                                uint8_t* __restrict__ dem_out, int p)
+                                                uint8_t* __restrict__ dem_out, WanderParity wp)
 {
     const int l = blockIdx.y;  // (lattice, family) pair
     const int dir = kWalkerDir[l % g.gamma];
+    const int p = wp.p[l % g.gamma];
     const uint32_t w = blockIdx.x * blockDim.x + threadIdx.x;
     if (w >= (uint32_t)g.rows * (uint32_t)g.Wr) return;
+    if (p < 0) {
+        for (int par = 0; par < 2; ++par)
+            reinterpret_cast<uint32_t*>(dem_out + ((int64_t)l * 2 + par) * g.Nh)[w] =
+                reinterpret_cast<const uint32_t*>(dem_in + ((int64_t)l * 2 + par) * g.Nh)[w];
+        return;
+    }
     const int row = (int)(w / (uint32_t)g.Wr), c = (int)(w - (uint32_t)row * (uint32_t)g.Wr);
     const int z = row / g.Ly, y = row - z * g.Ly;
     const int sgn = (dir & 1) ? -1 : 1;  // even dir index: forward

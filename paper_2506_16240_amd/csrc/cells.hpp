@@ -28,6 +28,14 @@
 // planes at the edge read themselves in place of a neighbour they do not
 // have; nobody uses what that gives.
 //
+// Walkers (Sec. 2.6).  With one per site the wandering is along x: a row's
+// levels move by 0 or 1 site into the other parity's words, in registers,
+// the bits that cross from word to word exchanged through LDS.  With several
+// families (Sec. 2.8; also several daemons per site) a launch covers at most
+// one sweep of each: a family's levels are loaded for its sweep, displaced by
+// the wandering it owes since its last one, and stored after it, so that no
+// wandering is a pass of its own.
+//
 // Refresh levels (Sec. 2.7) depend on the refresh index and temperature
 // only: k_cells_draw draws those of many refreshes in one launch on the
 // whole device, and the sweep reads them (loaded a refresh ahead).
@@ -126,6 +134,8 @@ __device__ __forceinline__ void cell_draw(const Geom& g, int row, int w, int nv,
 struct CellDraw {
     CellGeom cg;
     uint32_t *dr0, *dr1;
+    uint32_t *fam0[6], *fam1[6];  // several families: the planes of each (n = 1), in place of dr0 / dr1
+    int32_t families;             // grid.y runs over lattice * families + family
     const DaemonThresholds* dth;  // the schedule's table
     int64_t rho0, stride;
     int32_t n, L;
@@ -133,9 +143,12 @@ struct CellDraw {
 
 // Thread per (refresh, cell) of lattice l, grid-stride.  Bound: the Philox
 // multiplications (quarter rate).
-__device__ __forceinline__ void cells_draw_body(const CellDraw& D, int l, int64_t first, int64_t step)
+__device__ __forceinline__ void cells_draw_body(const CellDraw& D, int lf, int64_t first, int64_t step)
 {
     const CellGeom& cg = D.cg;
+    const int l = lf / D.families, fam = lf - l * D.families;
+    uint32_t* const o0 = D.families > 1 ? D.fam0[fam] : D.dr0;
+    uint32_t* const o1 = D.families > 1 ? D.fam1[fam] : D.dr1;
     const int64_t total = (int64_t)D.n * cg.plane;
     for (int64_t i = first; i < total; i += step) {
         const int j = (int)(i / cg.plane);
@@ -143,14 +156,14 @@ __device__ __forceinline__ void cells_draw_body(const CellDraw& D, int l, int64_
         const int row = (int)(cell / cg.W), w = (int)(cell - (int64_t)row * cg.W);
         const DaemonThresholds th = D.dth[D.rho0 + j];
         uint32_t d0[2], d1[2];
-        cell_draw(cg.g, row, w, min(32, cg.g.Kx - 32 * w), 0u, (uint32_t)(D.rho0 + j), (uint32_t)(l % cg.g.R),
+        cell_draw(cg.g, row, w, min(32, cg.g.Kx - 32 * w), (uint32_t)fam * (uint32_t)(cg.g.Nh / 2), (uint32_t)(D.rho0 + j), (uint32_t)(l % cg.g.R),
                   stream_word(kStreamDaemon, (uint32_t)(l / cg.g.R)), (uint32_t)(th.t0 - 1u), (uint32_t)(th.t1 - 1u),
                   (uint32_t)(th.t2 - 1u), d0, d1);
         const int64_t at = (int64_t)j * D.stride + (int64_t)l * 2 * cg.plane + cell;
-        D.dr0[at] = d0[0];
-        D.dr1[at] = d1[0];
-        D.dr0[at + cg.plane] = d0[1];
-        D.dr1[at + cg.plane] = d1[1];
+        o0[at] = d0[0];
+        o1[at] = d1[0];
+        o0[at + cg.plane] = d0[1];
+        o1[at + cg.plane] = d1[1];
     }
 }
 
@@ -284,6 +297,15 @@ struct CellSweep {
     int32_t log_first;   // sweeps until the launch's first one
     int32_t lattices;
     float inv_bdiv;      // 1 / cg.bdiv
+    int32_t wander0;     // walkers, one per site: parity of the wandering owed at the start, or -1
+};
+
+// Several families: the levels of each sweep of the launch (in and out), the
+// direction of its family and the parity of the wandering it owes (-1: none).
+struct CellFamilies {
+    const uint32_t *in0[6], *in1[6];
+    uint32_t *out0[6], *out1[6];
+    int32_t dir[6], owed[6];
 };
 
 // Sweeps from one refresh (at k) to the next.
@@ -305,11 +327,15 @@ __device__ __forceinline__ uint32_t wave_sum_dpp(uint32_t v)
 // XM: how a row's x neighbours are found.  0: the row is one word (rotate
 // within its Kx bits); 1: several full words (funnel shift with the next or
 // previous one); 2: several words, the last one short.
-// ALG 0: MicSA; 1, 2: the heat bath and Metropolis on drawn planes.
+// ALG 0: MicSA; 1, 2: the heat bath and Metropolis on drawn planes; 3: walkers,
+// one per site; 4: daemons or walkers in several families (F).
 template <int NR, int XM, int ALG>
-__device__ __forceinline__ void cells_body(const CellSweep& J, int l, int ty, int tz, uint32_t* lds, uint32_t* red)
+__device__ __forceinline__ void cells_body(const CellSweep& J, const CellFamilies* F, int l, int ty, int tz,
+                                           uint32_t* lds, uint32_t* red)
 {
     constexpr int CAP = NR * kCellLanes;  // LDS words of one parity's plane
+    constexpr bool LEVELS = ALG == 0 || ALG == 3;  // one family, in registers for the whole launch
+    constexpr bool CANON = ALG == 1 || ALG == 2;
     const CellGeom& cg = J.cg;
     const Geom& g = cg.g;
     const CellTile& f = J.f;
@@ -323,7 +349,8 @@ __device__ __forceinline__ void cells_body(const CellSweep& J, int l, int ty, in
     uint32_t j[2][NR][6];                     // couplings: x same k, x shifted, y + 1, y - 1, z + 1, z - 1
     int iyp[NR], iym[NR], izp[NR], izm[NR];   // LDS words of the neighbours
     int adj[2][NR];                           // XM > 0: the other x word of each parity's sites
-    uint32_t sa[NR], sb[NR], sc[2][NR], sd[2][NR], nvs[NR];
+    uint32_t sa[NR], sb[NR], sc[2][NR], sd[2][NR], nvs[NR], nvps[NR];
+    uint32_t gyp[NR], gym[NR], gzp[NR], gzm[NR], gxn[NR], gxp[NR];  // families: byte steps to the neighbour cells
     bool qq[NR];
     uint32_t gi[NR];                          // byte offset of the cell in a plane (fewer than 2^30 cells)
     uint32_t own = 0, valid = 0;              // bit i: cell i is owned / exists
@@ -353,6 +380,7 @@ __device__ __forceinline__ void cells_body(const CellSweep& J, int l, int ty, in
         qq[i] = q;
         const int nv = min(32, g.Kx - 32 * w), nvp = min(32, g.Kx - 32 * wp);
         nvs[i] = (uint32_t)nv;
+        nvps[i] = (uint32_t)nvp;
         // the shifted x neighbour of a parity-p site is at k + 1 (q ^ p = 1) or k - 1
         if (XM == 0) {
             sa[i] = q ? 1u : (uint32_t)(g.Kx - 1);
@@ -372,8 +400,8 @@ __device__ __forceinline__ void cells_body(const CellSweep& J, int l, int ty, in
 #pragma unroll
         for (int p = 0; p < 2; ++p) {
             s[p][i] = at(J.s_in + lp + p * cg.plane, gi[i]);
-            m0[p][i] = ALG == 0 ? at(J.d0_in + lp + p * cg.plane, gi[i]) : 0u;
-            m1[p][i] = ALG == 0 ? at(J.d1_in + lp + p * cg.plane, gi[i]) : 0u;
+            m0[p][i] = LEVELS ? at(J.d0_in + lp + p * cg.plane, gi[i]) : 0u;
+            m1[p][i] = LEVELS ? at(J.d1_in + lp + p * cg.plane, gi[i]) : 0u;
         }
         auto bd = [&](int d, int cell) { return at(bl + (int64_t)d * cg.plane, (uint32_t)cell << 2); };
         const uint32_t jpx = bd(kPx, me), jmx = bd(kMx, me);
@@ -394,10 +422,18 @@ __device__ __forceinline__ void cells_body(const CellSweep& J, int l, int ty, in
             }
             j[1][i][1] = (q ? (jB << 1) | (N >> (nvp - 1)) : (jB >> 1) | (N << (nv - 1))) & cell_mask(nv);
         }
-        j[1][i][2] = bd(kMy, me + (y + 1 == g.Ly ? W - ZS : W));
-        j[1][i][3] = bd(kPy, me + (y == 0 ? ZS - W : -W));
-        j[1][i][4] = bd(kMz, me + (z + 1 == g.Lz ? ZS - (int)cg.plane : ZS));
-        j[1][i][5] = bd(kPz, me + (z == 0 ? (int)cg.plane - ZS : -ZS));
+        const int syp = y + 1 == g.Ly ? W - ZS : W, sym = y == 0 ? ZS - W : -W;
+        const int szp = z + 1 == g.Lz ? ZS - (int)cg.plane : ZS, szm = z == 0 ? (int)cg.plane - ZS : -ZS;
+        j[1][i][2] = bd(kMy, me + syp);
+        j[1][i][3] = bd(kPy, me + sym);
+        j[1][i][4] = bd(kMz, me + szp);
+        j[1][i][5] = bd(kPz, me + szm);
+        gyp[i] = (uint32_t)syp << 2;
+        gym[i] = (uint32_t)sym << 2;
+        gzp[i] = (uint32_t)szp << 2;
+        gzm[i] = (uint32_t)szm << 2;
+        gxn[i] = (uint32_t)(wn - w) << 2;
+        gxp[i] = (uint32_t)(wp - w) << 2;
         const bool o = ok && (unsigned)(ey - f.GY) < (unsigned)ownY && (unsigned)(ez - f.GZ) < (unsigned)ownZ;
         own |= (o ? 1u : 0u) << i;
         valid |= (ok ? 1u : 0u) << i;
@@ -420,7 +456,7 @@ __device__ __forceinline__ void cells_body(const CellSweep& J, int l, int ty, in
     auto msk = [&](int i) { return XM == 2 ? cell_mask((int)nvs[i]) : mask01; };
     // the levels of the next refresh, loaded ahead of it (with three or four
     // cells per thread the registers are needed elsewhere: loaded at it)
-    constexpr bool AHEAD = ALG == 0 && NR <= 2;
+    constexpr bool AHEAD = LEVELS && NR <= 2;
     uint32_t r0[2][NR], r1[2][NR];
     int64_t dr = 0;
     auto fetch = [&]() {
@@ -436,12 +472,12 @@ __device__ __forceinline__ void cells_body(const CellSweep& J, int l, int ty, in
     if (AHEAD) fetch();  // (with no refresh in the launch the addresses are still good)
     // MicSA: levels in, minus levels out, of the owned sites; else a quarter of
     // their energy change
-    int taken = ALG == 0 ? levels() : 0;
+    int taken = LEVELS ? levels() : 0;
     // the baselines' drawn bits of the next half sweep, loaded during this one
     constexpr int K = ALG == 1 ? 3 : 2;
     uint32_t nx[NR][K];
     const int64_t lplane = (int64_t)J.lattices * cg.plane;
-    const uint32_t* cd = ALG ? J.dr0 + (int64_t)l * cg.plane : nullptr;
+    const uint32_t* cd = CANON ? J.dr0 + (int64_t)l * cg.plane : nullptr;
     int halves = 2 * J.n;
     auto fetch_half = [&]() {
 #pragma unroll
@@ -451,7 +487,108 @@ __device__ __forceinline__ void cells_body(const CellSweep& J, int l, int ty, in
         --halves;
         cd += halves > 0 ? K * lplane : 0;  // (past the last half: the same addresses again)
     };
-    if (ALG != 0) fetch_half();
+    if (CANON) fetch_half();
+    // families: the next sweep's levels at the places they come from (and the
+    // adjacent words of the same row, for a move along x), loaded a sweep ahead
+    uint32_t n0[2][NR], n1[2][NR], a0[2][NR], a1[2][NR];
+    auto fetch_family = [&](int it) {
+        const int dir = F->dir[it], owed = F->owed[it];
+        const int axis = dir >> 1, sgn = (dir & 1) ? -1 : 1;
+        const uint32_t *b0 = F->in0[it] + lp, *b1 = F->in1[it] + lp;
+#pragma unroll
+        for (int i = 0; i < NR; ++i)
+#pragma unroll
+            for (int p = 0; p < 2; ++p) {
+                // a site of the wandering's parity takes the level one step along the
+                // direction, a site of the other parity one step against it, both from
+                // the other parity's plane
+                const int toward = p == owed ? sgn : -sgn;
+                uint32_t off = gi[i];
+                if (owed >= 0 && axis == 1) off += toward > 0 ? gyp[i] : gym[i];
+                if (owed >= 0 && axis == 2) off += toward > 0 ? gzp[i] : gzm[i];
+                const int64_t pl = (owed >= 0 ? 1 - p : p) * cg.plane;
+                n0[p][i] = at(b0 + pl, off);
+                n1[p][i] = at(b1 + pl, off);
+                if (XM > 0) {
+                    const uint32_t side = gi[i] + (toward > 0 ? gxn[i] : gxp[i]);
+                    a0[p][i] = at(b0 + pl, side);
+                    a1[p][i] = at(b1 + pl, side);
+                }
+            }
+    };
+    auto take_family = [&](int it) {
+        const int dir = F->dir[it], owed = F->owed[it];
+        const bool alongx = owed >= 0 && (dir >> 1) == 0;
+        const int sgn = (dir & 1) ? -1 : 1;
+#pragma unroll
+        for (int i = 0; i < NR; ++i)
+#pragma unroll
+            for (int p = 0; p < 2; ++p) {
+                uint32_t v0 = n0[p][i], v1 = n1[p][i];
+                if (alongx) {
+                    // x +- 1 of a site at x = 2k + q is index k + q (forwards) or k + q - 1
+                    const int q = (qq[i] ? 1 : 0) ^ p;
+                    const int toward = p == owed ? sgn : -sgn;
+                    const int shift = toward > 0 ? q : q - 1;
+                    const uint32_t c0 = XM == 0 ? v0 : a0[p][i], c1 = XM == 0 ? v1 : a1[p][i];
+                    const uint32_t nv = nvs[i], nvp = XM == 0 ? nv : nvps[i];
+                    const uint32_t s0 = toward > 0 ? (v0 >> 1) | (c0 << (nv - 1)) : (v0 << 1) | (c0 >> (nvp - 1));
+                    const uint32_t s1 = toward > 0 ? (v1 >> 1) | (c1 << (nv - 1)) : (v1 << 1) | (c1 >> (nvp - 1));
+                    v0 = shift ? s0 & cell_mask((int)nv) : v0;
+                    v1 = shift ? s1 & cell_mask((int)nv) : v1;
+                }
+                m0[p][i] = v0;
+                m1[p][i] = v1;
+            }
+    };
+    if (ALG == 4) fetch_family(0);
+    // walkers, one per site: the wandering of parity w, within each row
+    auto wander = [&](auto wc) {
+        constexpr int w = decltype(wc)::value;
+        uint32_t* edge = lds + 2 * CAP;
+        if (XM > 0) {
+#pragma unroll
+            for (int i = 0; i < NR; ++i) {
+                const uint32_t top = nvs[i] - 1;
+                edge[t + i * B] = (m0[1 - w][i] & 1u) | ((m1[1 - w][i] & 1u) << 1) |
+                                  (((m0[w][i] >> top) & 1u) << 2) | (((m1[w][i] >> top) & 1u) << 3);
+            }
+            lds_barrier();
+        }
+#pragma unroll
+        for (int i = 0; i < NR; ++i) {
+            const uint32_t f0 = m0[1 - w][i], f1 = m1[1 - w][i], g0 = m0[w][i], g1 = m1[w][i];
+            uint32_t fd0, fd1, gu0, gu1;  // f a site down, g a site up
+            if (XM == 0) {
+                const uint32_t top = (uint32_t)g.Kx - 1u;
+                fd0 = (f0 >> 1) | (f0 << top);
+                fd1 = (f1 >> 1) | (f1 << top);
+                gu0 = (g0 << 1) | (g0 >> top);
+                gu1 = (g1 << 1) | (g1 >> top);
+            } else {
+                // the row's next and previous words (adj holds both, by the row's offset)
+                const uint32_t en = edge[qq[i] ? adj[0][i] : adj[1][i]], ep = edge[qq[i] ? adj[1][i] : adj[0][i]];
+                const uint32_t top = nvs[i] - 1;
+                fd0 = (f0 >> 1) | ((en & 1u) << top);
+                fd1 = (f1 >> 1) | (((en >> 1) & 1u) << top);
+                gu0 = (g0 << 1) | ((ep >> 2) & 1u);
+                gu1 = (g1 << 1) | ((ep >> 3) & 1u);
+            }
+            const bool moved = w ? !qq[i] : qq[i];  // the sites of parity w sit at odd x
+            const uint32_t mk = msk(i);
+            m0[w][i] = moved ? fd0 & mk : f0;
+            m1[w][i] = moved ? fd1 & mk : f1;
+            m0[1 - w][i] = moved ? gu0 & mk : g0;
+            m1[1 - w][i] = moved ? gu1 & mk : g1;
+        }
+    };
+    auto wander_parity = [&](int w) {
+        if (w)
+            wander(std::integral_constant<int, 1>{});
+        else
+            wander(std::integral_constant<int, 0>{});
+    };
+    if (ALG == 3 && J.wander0 >= 0) wander_parity(J.wander0);
     lds_barrier();
 
     // the x neighbour word of parity p's sites other than the one at the same k
@@ -480,7 +617,7 @@ __device__ __forceinline__ void cells_body(const CellSweep& J, int l, int ty, in
     auto half = [&](auto pc) {
         constexpr int p = decltype(pc)::value;
         uint32_t cur[NR][K];
-        if (ALG != 0) {
+        if (CANON) {
 #pragma unroll
             for (int i = 0; i < NR; ++i)
 #pragma unroll
@@ -491,7 +628,7 @@ __device__ __forceinline__ void cells_body(const CellSweep& J, int l, int ty, in
         for (int i = 0; i < NR; ++i) {
             uint32_t u[6];
             unsat(i, p, u);
-            if (ALG == 0) {
+            if (!CANON) {
                 s[p][i] ^= cell_move(u, m0[p][i], m1[p][i]);
             } else {
                 const uint32_t s1 = xor3(u[0], u[1], u[2]), c1 = maj32(u[0], u[1], u[2]);
@@ -537,7 +674,13 @@ __device__ __forceinline__ void cells_body(const CellSweep& J, int l, int ty, in
     };
     int to_log = J.log_first, buf = 0;
     for (int it = 0; it < J.n; ++it) {
-        if (ALG == 0 && it == ref) {
+        if (ALG == 3 && it > 0 && it != ref) wander_parity((int)((J.k0 + it - 1) & 1));
+        if (ALG == 4) {
+            take_family(it);
+            fetch_family(it + 1 < J.n ? it + 1 : it);
+            taken += levels();
+        }
+        if (LEVELS && it == ref) {
             taken -= levels();
             if (!AHEAD) fetch();
 #pragma unroll
@@ -556,6 +699,18 @@ __device__ __forceinline__ void cells_body(const CellSweep& J, int l, int ty, in
         half(std::integral_constant<int, 0>{});
         flush();
         half(std::integral_constant<int, 1>{});
+        if (ALG == 4) {
+            taken -= levels();
+#pragma unroll
+            for (int i = 0; i < NR; ++i) {
+                if (!((own >> i) & 1u)) continue;
+#pragma unroll
+                for (int p = 0; p < 2; ++p) {
+                    put(F->out0[it] + lp + p * cg.plane, gi[i], m0[p][i]);
+                    put(F->out1[it] + lp + p * cg.plane, gi[i], m1[p][i]);
+                }
+            }
+        }
         if (J.log && --to_log == 0) {
             to_log = J.log_stride;
             // from-scratch energy (every bond once, at its even end) and the
@@ -585,15 +740,15 @@ __device__ __forceinline__ void cells_body(const CellSweep& J, int l, int ty, in
         lds_barrier();
         flush();
     }
-    if (ALG == 0) taken -= levels();
+    if (LEVELS) taken -= levels();
 #pragma unroll
     for (int i = 0; i < NR; ++i) {
         if (!((own >> i) & 1u)) continue;
 #pragma unroll
         for (int p = 0; p < 2; ++p) {
             put(J.s_out + lp + p * cg.plane, gi[i], s[p][i]);
-            if (ALG == 0) put(J.d0_out + lp + p * cg.plane, gi[i], m0[p][i]);
-            if (ALG == 0) put(J.d1_out + lp + p * cg.plane, gi[i], m1[p][i]);
+            if (LEVELS) put(J.d0_out + lp + p * cg.plane, gi[i], m0[p][i]);
+            if (LEVELS) put(J.d1_out + lp + p * cg.plane, gi[i], m1[p][i]);
         }
     }
     // a wave's sum fits 32 bits (at most 64 lanes x 4 cells x 64 sites x 3, per refresh met)
@@ -607,9 +762,17 @@ __device__ __forceinline__ void cells_body(const CellSweep& J, int l, int ty, in
 template <int NR, int XM, int ALG>
 __global__ void __launch_bounds__(kCellLanes) k_cells_sweep(CellSweep J)
 {
+    __shared__ uint32_t lds[(ALG == 3 && XM > 0 ? 3 : 2) * NR * kCellLanes];
+    __shared__ uint32_t red[4];
+    cells_body<NR, XM, ALG>(J, nullptr, blockIdx.z, blockIdx.x, blockIdx.y, lds, red);
+}
+
+template <int NR, int XM>
+__global__ void __launch_bounds__(kCellLanes) k_cells_sweep_families(CellSweep J, CellFamilies F)
+{
     __shared__ uint32_t lds[2 * NR * kCellLanes];
     __shared__ uint32_t red[4];
-    cells_body<NR, XM, ALG>(J, blockIdx.z, blockIdx.x, blockIdx.y, lds, red);
+    cells_body<NR, XM, 4>(J, &F, blockIdx.z, blockIdx.x, blockIdx.y, lds, red);
 }
 
 // ------------------------------------------------- planes <-> other layouts
@@ -619,10 +782,14 @@ __device__ __forceinline__ uint32_t spread4(uint32_t n) { return ((n & 0xFu) * 0
 
 // Byte layout -> planes, thread per (lattice, cell): 32 bytes of each parity.
 // Coupling planes are written by the first lattice of each set.
+struct CellLevels {
+    uint32_t *d0[6], *d1[6];  // level planes of each family
+    int32_t families;
+};
+
 __global__ void __launch_bounds__(256) k_cells_pack(CellGeom cg, const uint8_t* __restrict__ spin_b,
                                                     const uint8_t* __restrict__ dem_b, uint32_t* __restrict__ spin,
-                                                    uint32_t* __restrict__ d0, uint32_t* __restrict__ d1,
-                                                    uint32_t* __restrict__ bond)
+                                                    CellLevels lv, uint32_t* __restrict__ bond)
 {
     const Geom& g = cg.g;
     const int64_t cell = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -632,40 +799,44 @@ __global__ void __launch_bounds__(256) k_cells_pack(CellGeom cg, const uint8_t* 
     const int w = (int)(cell - row * cg.W);
     const int n4 = min(32, g.Kx - 32 * w) >> 2;
     const int64_t h = row * g.Kx + 32 * w;
+    const int64_t at = (int64_t)l * 2 * cg.plane + cell;
     const uint32_t *ev = reinterpret_cast<const uint32_t*>(spin_b + (int64_t)l * 2 * g.Nh + h),
-                   *od = reinterpret_cast<const uint32_t*>(spin_b + ((int64_t)l * 2 + 1) * g.Nh + h),
-                   *me = reinterpret_cast<const uint32_t*>(dem_b + (int64_t)l * 2 * g.Nh + h),
-                   *mo = reinterpret_cast<const uint32_t*>(dem_b + ((int64_t)l * 2 + 1) * g.Nh + h);
-    uint32_t se = 0, so = 0, e0 = 0, e1 = 0, o0 = 0, o1 = 0, jb[6] = {0, 0, 0, 0, 0, 0};
+                   *od = reinterpret_cast<const uint32_t*>(spin_b + ((int64_t)l * 2 + 1) * g.Nh + h);
+    uint32_t se = 0, so = 0, jb[6] = {0, 0, 0, 0, 0, 0};
 #pragma unroll
     for (int v = 0; v < 8; ++v) {
         if (v >= n4) break;
-        const uint32_t a = ev[v], b = od[v], c = me[v], d = mo[v];
+        const uint32_t a = ev[v], b = od[v];
         se |= gather4(a) << (4 * v);
         so |= gather4(b) << (4 * v);
-        e0 |= gather4(c) << (4 * v);
-        e1 |= gather4(c >> 1) << (4 * v);
-        o0 |= gather4(d) << (4 * v);
-        o1 |= gather4(d >> 1) << (4 * v);
 #pragma unroll
         for (int k = 0; k < 6; ++k) jb[k] |= gather4(a >> (1 + k)) << (4 * v);
     }
-    const int64_t at = (int64_t)l * 2 * cg.plane + cell;
     spin[at] = se;
     spin[at + cg.plane] = so;
-    d0[at] = e0;
-    d0[at + cg.plane] = o0;
-    d1[at] = e1;
-    d1[at + cg.plane] = o1;
     if (l % cg.bdiv == 0)
 #pragma unroll
         for (int k = 0; k < 6; ++k) bond[((int64_t)(l / cg.bdiv) * 6 + k) * cg.plane + cell] = jb[k];
+    for (int f = 0; f < lv.families; ++f)
+        for (int p = 0; p < 2; ++p) {
+            const uint32_t* m = reinterpret_cast<const uint32_t*>(
+                dem_b + (((int64_t)l * lv.families + f) * 2 + p) * g.Nh + h);
+            uint32_t e0 = 0, e1 = 0;
+#pragma unroll
+            for (int v = 0; v < 8; ++v) {
+                if (v >= n4) break;
+                const uint32_t c = m[v];
+                e0 |= gather4(c) << (4 * v);
+                e1 |= gather4(c >> 1) << (4 * v);
+            }
+            lv.d0[f][at + p * cg.plane] = e0;
+            lv.d1[f][at + p * cg.plane] = e1;
+        }
 }
 
-__global__ void __launch_bounds__(256) k_cells_unpack(CellGeom cg, const uint32_t* __restrict__ spin,
-                                                      const uint32_t* __restrict__ d0, const uint32_t* __restrict__ d1,
-                                                      const uint32_t* __restrict__ bond, uint8_t* __restrict__ spin_b,
-                                                      uint8_t* __restrict__ dem_b)
+__global__ void __launch_bounds__(256) k_cells_unpack(CellGeom cg, const uint32_t* __restrict__ spin, CellLevels lv,
+                                                      const uint32_t* __restrict__ bond,
+                                                      uint8_t* __restrict__ spin_b, uint8_t* __restrict__ dem_b)
 {
     const Geom& g = cg.g;
     const int64_t cell = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -675,14 +846,10 @@ __global__ void __launch_bounds__(256) k_cells_unpack(CellGeom cg, const uint32_
     const int w = (int)(cell - row * cg.W);
     const int n4 = min(32, g.Kx - 32 * w) >> 2;
     const int64_t h = row * g.Kx + 32 * w;
-    uint32_t *ev = reinterpret_cast<uint32_t*>(spin_b + (int64_t)l * 2 * g.Nh + h),
-             *od = reinterpret_cast<uint32_t*>(spin_b + ((int64_t)l * 2 + 1) * g.Nh + h),
-             *me = reinterpret_cast<uint32_t*>(dem_b + (int64_t)l * 2 * g.Nh + h),
-             *mo = reinterpret_cast<uint32_t*>(dem_b + ((int64_t)l * 2 + 1) * g.Nh + h);
     const int64_t at = (int64_t)l * 2 * cg.plane + cell;
+    uint32_t *ev = reinterpret_cast<uint32_t*>(spin_b + (int64_t)l * 2 * g.Nh + h),
+             *od = reinterpret_cast<uint32_t*>(spin_b + ((int64_t)l * 2 + 1) * g.Nh + h);
     const uint32_t se = spin[at], so = spin[at + cg.plane];
-    const uint32_t e0 = d0[at], o0 = d0[at + cg.plane];
-    const uint32_t e1 = d1[at], o1 = d1[at + cg.plane];
     uint32_t jb[6];
 #pragma unroll
     for (int k = 0; k < 6; ++k) jb[k] = bond[((int64_t)(l / cg.bdiv) * 6 + k) * cg.plane + cell];
@@ -694,9 +861,17 @@ __global__ void __launch_bounds__(256) k_cells_unpack(CellGeom cg, const uint32_
         for (int k = 0; k < 6; ++k) a |= spread4(jb[k] >> (4 * v)) << (1 + k);
         ev[v] = a;
         od[v] = spread4(so >> (4 * v));
-        me[v] = spread4(e0 >> (4 * v)) | (spread4(e1 >> (4 * v)) << 1);
-        mo[v] = spread4(o0 >> (4 * v)) | (spread4(o1 >> (4 * v)) << 1);
     }
+    for (int f = 0; f < lv.families; ++f)
+        for (int p = 0; p < 2; ++p) {
+            uint32_t* m = reinterpret_cast<uint32_t*>(dem_b + (((int64_t)l * lv.families + f) * 2 + p) * g.Nh + h);
+            const uint32_t e0 = lv.d0[f][at + p * cg.plane], e1 = lv.d1[f][at + p * cg.plane];
+#pragma unroll
+            for (int v = 0; v < 8; ++v) {
+                if (v >= n4) break;
+                m[v] = spread4(e0 >> (4 * v)) | (spread4(e1 >> (4 * v)) << 1);
+            }
+        }
 }
 
 // Bit-plane layout (a word holds one site of 64 lattices) -> planes.  A wave
@@ -783,8 +958,7 @@ __global__ void __launch_bounds__(256) k_cells_unpack_bits(GeomB gb, CellGeom cg
 // sum; 2: sites where replicas a and b of sample blockIdx.y differ.  Grid
 // (blocks, lattices or samples), grid-stride over the cells.
 template <int KIND>
-__global__ void __launch_bounds__(256) k_cells_count(CellGeom cg, const uint32_t* __restrict__ spin,
-                                                     const uint32_t* __restrict__ d0, const uint32_t* __restrict__ d1,
+__global__ void __launch_bounds__(256) k_cells_count(CellGeom cg, const uint32_t* __restrict__ spin, CellLevels lv,
                                                      const uint32_t* __restrict__ bond, int a, int b,
                                                      unsigned long long* __restrict__ out)
 {
@@ -795,8 +969,9 @@ __global__ void __launch_bounds__(256) k_cells_count(CellGeom cg, const uint32_t
     int v = 0;
     for (int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; c < cg.plane; c += step) {
         if (KIND == 1) {
-            v += __popc(d0[lp + c]) + __popc(d0[lp + cg.plane + c]) +
-                 2 * (__popc(d1[lp + c]) + __popc(d1[lp + cg.plane + c]));
+            for (int f = 0; f < lv.families; ++f)
+                v += __popc(lv.d0[f][lp + c]) + __popc(lv.d0[f][lp + cg.plane + c]) +
+                     2 * (__popc(lv.d1[f][lp + c]) + __popc(lv.d1[f][lp + cg.plane + c]));
         } else if (KIND == 2) {
             const int64_t pa = ((int64_t)l * g.R + a) * 2 * cg.plane + c, pb = ((int64_t)l * g.R + b) * 2 * cg.plane + c;
             v += __popc(spin[pa] ^ spin[pb]) +

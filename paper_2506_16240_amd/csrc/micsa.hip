@@ -122,6 +122,12 @@ struct micsa_ctx {
     void* parena = nullptr;
     uint32_t *cdr0 = nullptr, *cdr1 = nullptr;
     int64_t cdr_rho0 = 0, cdr_n = 0, cdr_cap = 0;
+    // several daemon (walker) families: level planes of each in two copies,
+    // the copy that is current, and the parity of the wandering the planes of
+    // a family owe (-1: none; the home arrays never owe one then)
+    uint32_t* fl[2][6] = {};
+    uint8_t fcur[6] = {};
+    int32_t fowed[6] = {-1, -1, -1, -1, -1, -1};
     // refresh sweep whose levels the multispin draw planes hold, drawn during
     // an earlier call (-1: none)
     int64_t msc_drawn = -1;
@@ -833,6 +839,7 @@ int enqueue_bonds(micsa_ctx* c)
 
 // Count over the planes (k_cells_count) into the zeroed slots of n entities.
 CellGeom cell_geom(const micsa_ctx* c);
+CellLevels cell_levels(const micsa_ctx* c);
 template <int KIND>
 int enqueue_cells_count(micsa_ctx* c, int n, int a, int b, unsigned long long* dst)
 {
@@ -842,8 +849,8 @@ int enqueue_cells_count(micsa_ctx* c, int n, int a, int b, unsigned long long* d
     {
         TimedLaunch t(c, kTimeReduce);
         k_cells_count<KIND><<<dim3((unsigned)blocks, (unsigned)n), 256, 0, c->stream>>>(
-            cg, reinterpret_cast<const uint32_t*>(c->ms), reinterpret_cast<const uint32_t*>(c->md0),
-            reinterpret_cast<const uint32_t*>(c->md1), reinterpret_cast<const uint32_t*>(c->mb), a, b, dst);
+            cg, reinterpret_cast<const uint32_t*>(c->ms), cell_levels(c), reinterpret_cast<const uint32_t*>(c->mb), a,
+            b, dst);
     }
     return check_launch(c, "k_cells_count");
 }
@@ -983,18 +990,24 @@ int check_sweep(micsa_ctx* c, int32_t algo, int64_t n)
 
 // Wandering step of every walker family at the end of timestep t (each
 // family along its own direction, the half of the cycle given by t's parity).
-int launch_wander(micsa_ctx* c, int64_t t)
+int launch_wander_families(micsa_ctx* c, const WanderParity& wp)
 {
     if (int st = need_alt(c)) return st;
     const int64_t words = (int64_t)c->g.rows * c->g.Wr;
     {
         TimedLaunch tl(c, kTimeSweep);
-        k_wander<<<grid_for(words, c->L * c->gamma), kBlock, 0, c->stream>>>(c->g, c->dem, c->dem_alt, (int)(t & 1));
+        k_wander<<<grid_for(words, c->L * c->gamma), kBlock, 0, c->stream>>>(c->g, c->dem, c->dem_alt, wp);
     }
     const int st = check_launch(c, "k_wander");
     if (st) return st;
     std::swap(c->dem, c->dem_alt);
     return MICSA_OK;
+}
+
+int launch_wander(micsa_ctx* c, int64_t t)
+{
+    const int32_t p = (int32_t)(t & 1);
+    return launch_wander_families(c, WanderParity{{p, p, p, p, p, p}});
 }
 
 // Tile of the one-launch multispin sweep: TY rows x TZ planes per work-group
@@ -1128,6 +1141,24 @@ CellGeom cell_geom(const micsa_ctx* c)
 
 uint32_t* w32(uint64_t* p) { return reinterpret_cast<uint32_t*>(p); }
 
+// Current level planes of every family.
+CellLevels cell_levels(const micsa_ctx* c)
+{
+    CellLevels lv{};
+    lv.families = c->gamma;
+    if (c->gamma == 1) {
+        lv.d0[0] = w32(c->md0);
+        lv.d1[0] = w32(c->md1);
+        return lv;
+    }
+    const int64_t words = (int64_t)c->L * 2 * cell_geom(c).plane;
+    for (int a = 0; a < c->gamma; ++a) {
+        lv.d0[a] = c->fl[c->fcur[a]][a];
+        lv.d1[a] = lv.d0[a] + words;
+    }
+    return lv;
+}
+
 // Unpack the planes into the layout's own arrays if those are stale (before
 // anything reads them).
 int need_home(micsa_ctx* c)
@@ -1142,9 +1173,16 @@ int need_home(micsa_ctx* c)
                                                c->bdm1);
         else
             k_cells_unpack<<<dim3((unsigned)((cg.plane + 255) / 256), (unsigned)c->L), 256, 0, c->stream>>>(
-                cg, w32(c->ms), w32(c->md0), w32(c->md1), w32(c->mb), c->spin, c->dem);
+                cg, w32(c->ms), cell_levels(c), w32(c->mb), c->spin, c->dem);
     }
-    const int st = check_launch(c, "k_cells_unpack");
+    int st = check_launch(c, "k_cells_unpack");
+    bool owes = false;
+    for (int a = 0; a < c->gamma && c->gamma > 1; ++a) owes = owes || c->fowed[a] >= 0;
+    if (!st && owes) {
+        WanderParity wp{{-1, -1, -1, -1, -1, -1}};
+        for (int a = 0; a < c->gamma; ++a) wp.p[a] = c->fowed[a];
+        st = launch_wander_families(c, wp);
+    }
     if (!st) c->home_ok = true;
     return st;
 }
@@ -1171,9 +1209,10 @@ int need_planes(micsa_ctx* c)
                                              w32(c->md1), w32(c->mb));
         else
             k_cells_pack<<<dim3((unsigned)((cg.plane + 255) / 256), (unsigned)c->L), 256, 0, c->stream>>>(
-                cg, c->spin, c->dem, w32(c->ms), w32(c->md0), w32(c->md1), w32(c->mb));
+                cg, c->spin, c->dem, w32(c->ms), cell_levels(c), w32(c->mb));
     }
     const int st = check_launch(c, "k_cells_pack");
+    for (int32_t& o : c->fowed) o = -1;
     if (!st) c->planes_ok = true;
     return st;
 }
@@ -1439,7 +1478,7 @@ constexpr int kCellCap = kCellMaxNR * kCellLanes;
 bool cells_shape_ok(const micsa_ctx* c)
 {
     const CellGeom cg = cell_geom(c);
-    return c->gamma == 1 && cg.plane < ((int64_t)1 << 30) && cg.W <= kCellCap / 25 && c->p.Ly < (1 << 22) && c->p.Lz < (1 << 22);
+    return cg.plane < ((int64_t)1 << 30) && cg.W <= kCellCap / 25 && c->p.Ly < (1 << 22) && c->p.Lz < (1 << 22);
 }
 
 CellPlan cell_plan(const micsa_ctx* c)
@@ -1466,8 +1505,9 @@ CellPlan cell_plan(const micsa_ctx* c)
         f.inv_Lz = 1.0f / (float)Lz;
         const int64_t cells = (int64_t)f.EY * f.EZ * W;
         const int nr = (int)((cells + kCellLanes - 1) / kCellLanes);
-        // (four cells of rows with a short last word do not fit the registers)
-        if (nr > (xm == 2 ? 3 : kCellMaxNR) || f.ntz > 65535) return;
+        // (four cells of rows with a short last word, or of several families, do
+        // not fit the registers)
+        if (nr > (xm == 2 || c->gamma > 1 ? 3 : kCellMaxNR) || f.ntz > 65535) return;
         const bool whole = f.nty * f.ntz == 1;
         const int block = (int)(((cells + nr - 1) / nr + 63) / 64 * 64), waves = block / 64;
         const double issue = kCellIssue * (xm == 0 ? 1.0 : (xm == 1 ? 1.15 : 1.2)) * nr;  // of one wave and half
@@ -1478,7 +1518,8 @@ CellPlan cell_plan(const micsa_ctx* c)
         const double m = std::min<double>(per_cu, fit), rounds = per_cu / m;
         const double half = std::max(kCellChain + issue, std::ceil(m * waves / 4.0) * issue + 100.0);
         const double load = kCellLaunch * rounds + (double)cells * wgs * 72.0 / kCellBytes;
-        const double t = rounds * half * 2.0 + (whole ? 0.0 : load / T);
+        // (several families: at most one sweep of each per launch)
+        const double t = rounds * half * 2.0 + (whole ? (c->gamma > 1 ? load / c->gamma : 0.0) : load / T);
         if (!best.ok || t < best.cost) {
             best.ok = true;
             best.f = f;
@@ -1504,13 +1545,15 @@ CellPlan cell_plan(const micsa_ctx* c)
         return v;
     };
     const std::vector<int> ys = sides(Ly), zs = sides(Lz);
-    for (int T : {1, 2, 3, 4, 6, 8})
+    for (int T : {1, 2, 3, 4, 6, 8}) {
+        if (c->gamma > 1 && T > c->gamma) break;
         for (int ty : ys)
             for (int tz : zs) {
                 if (ty == Ly && tz == Lz) continue;
                 if ((int64_t)(ty + (ty < Ly ? 4 * T : 0)) * (tz + (tz < Lz ? 4 * T : 0)) * W <= kCellCap)
                     consider(ty, tz, T);
             }
+    }
     return best;
 }
 
@@ -1576,12 +1619,27 @@ int cells_alloc(micsa_ctx* c)
         } else {
             const size_t sets = (size_t)(c->L / c->g.R);
             const size_t bond = sets * 6 * (size_t)cg.plane;
-            const size_t total = words * (c->plan.sweeps > 0 ? 6 : 3) + bond;
+            const bool alt = c->plan.sweeps > 0;
+            const size_t fams = c->gamma > 1 ? (size_t)4 * c->gamma : 0;  // two bits, two copies each
+            const size_t total = words * ((alt ? 2 : 1) + (c->gamma > 1 ? fams : (alt ? 4 : 2))) + bond;
             uint32_t* a = static_cast<uint32_t*>(dev_alloc(total * 4));
             if (!a) return fail(c, MICSA_ENOMEM, "cell planes");
             c->parena = a;
-            uint64_t** const at[] = {&c->ms, &c->md0, &c->md1, &c->ms_alt, &c->md0_alt, &c->md1_alt};
-            for (int i = 0; i < (c->plan.sweeps > 0 ? 6 : 3); ++i, a += words) *at[i] = reinterpret_cast<uint64_t*>(a);
+            auto take = [&](uint64_t*& q) {
+                q = reinterpret_cast<uint64_t*>(a);
+                a += words;
+            };
+            take(c->ms);
+            if (alt) take(c->ms_alt);
+            if (c->gamma > 1) {
+                for (int copy = 0; copy < 2; ++copy)
+                    for (int f = 0; f < c->gamma; ++f, a += 2 * words) c->fl[copy][f] = a;
+            } else {
+                take(c->md0);
+                take(c->md1);
+                if (alt) take(c->md0_alt);
+                if (alt) take(c->md1_alt);
+            }
             c->mb = reinterpret_cast<uint64_t*>(a);
         }
     }
@@ -1620,6 +1678,7 @@ int cells_draw(micsa_ctx* c, int64_t kr, int64_t k_end)
     D.stride = (int64_t)c->L * 2 * cg.plane;
     D.n = (int32_t)n;
     D.L = c->L;
+    D.families = 1;
     const int64_t blocks = std::min<int64_t>((n * cg.plane + 63) / 64, 16384);
     {
         TimedLaunch t(c, kTimeRefresh);
@@ -1646,7 +1705,7 @@ CellKernel cell_kernel(int nr, int xm)
 
 // One launch of the cell kernel on the planes (filled in: J's sweeps, draws
 // and logging); tiles go from one copy to the other.
-int launch_cells(micsa_ctx* c, int alg, CellSweep& J)
+int launch_cells(micsa_ctx* c, int alg, CellSweep& J, const CellFamilies* F = nullptr)
 {
     const CellPlan& pl = c->plan;
     J.cg = cell_geom(c);
@@ -1664,15 +1723,27 @@ int launch_cells(micsa_ctx* c, int alg, CellSweep& J)
     J.lattices = c->L;
     J.inv_bdiv = 1.0f / (float)J.cg.bdiv;
     {
-        TimedLaunch t(c, alg == 0 ? kTimeSweep : (alg == 1 ? kTimeHeatBath : kTimeMetropolis));
-        const CellKernel k = alg == 0 ? cell_kernel<0>(pl.nr, pl.xm)
-                                      : (alg == 1 ? cell_kernel<1>(pl.nr, pl.xm) : cell_kernel<2>(pl.nr, pl.xm));
-        k<<<dim3((unsigned)pl.f.nty, (unsigned)pl.f.ntz, (unsigned)c->L), pl.block, 0, c->stream>>>(J);
+        TimedLaunch t(c, alg == 1 ? kTimeHeatBath : (alg == 2 ? kTimeMetropolis : kTimeSweep));
+        const dim3 grid((unsigned)pl.f.nty, (unsigned)pl.f.ntz, (unsigned)c->L);
+        if (alg == 4) {
+            using Kern = void (*)(CellSweep, CellFamilies);
+            static const Kern k[3][3] = {
+                {k_cells_sweep_families<1, 0>, k_cells_sweep_families<1, 1>, k_cells_sweep_families<1, 2>},
+                {k_cells_sweep_families<2, 0>, k_cells_sweep_families<2, 1>, k_cells_sweep_families<2, 2>},
+                {k_cells_sweep_families<3, 0>, k_cells_sweep_families<3, 1>, k_cells_sweep_families<3, 2>}};
+            k[pl.nr - 1][pl.xm]<<<grid, pl.block, 0, c->stream>>>(J, *F);
+        } else {
+            const CellKernel k = alg == 0   ? cell_kernel<0>(pl.nr, pl.xm)
+                                 : alg == 1 ? cell_kernel<1>(pl.nr, pl.xm)
+                                 : alg == 2 ? cell_kernel<2>(pl.nr, pl.xm)
+                                            : cell_kernel<3>(pl.nr, pl.xm);
+            k<<<grid, pl.block, 0, c->stream>>>(J);
+        }
     }
     if (int st = check_launch(c, "k_cells_sweep")) return st;
     if (!whole) {
         std::swap(c->ms, c->ms_alt);
-        if (alg == 0) {  // the baselines leave the levels where they are
+        if (alg == 0 || alg == 3) {  // the baselines leave the levels where they are
             std::swap(c->md0, c->md0_alt);
             std::swap(c->md1, c->md1_alt);
         }
@@ -1694,7 +1765,7 @@ void cell_log(CellSweep& J, long long* dlog, int64_t done, int64_t stride)
 // MicSA sweeps k .. k + n - 1 on the cell kernel.  dlog (whole-lattice plans
 // only): every `stride` sweeps (U, sum m) of each lattice to
 // dlog[row][lattice][2].
-int sweep_cells(micsa_ctx* c, int64_t n, long long* dlog, int64_t stride)
+int sweep_cells(micsa_ctx* c, int64_t n, long long* dlog, int64_t stride, bool walkers = false)
 {
     int st;
     if ((st = cells_alloc(c)) || (st = need_planes(c))) return st;
@@ -1724,10 +1795,101 @@ int sweep_cells(micsa_ctx* c, int64_t n, long long* dlog, int64_t stride)
         J.k0 = k;
         J.n = (int32_t)len;
         J.ref0 = kr >= 0 && kr < k + len ? (int32_t)(kr - k) : (int32_t)len;
-        if ((st = launch_cells(c, 0, J))) return st;
+        J.wander0 = walkers && kr != k ? c->pend_wander : -1;
+        if ((st = launch_cells(c, walkers ? 3 : 0, J))) return st;
+        c->pend_wander = walkers ? (int32_t)((k + len - 1) & 1) : -1;
         c->k = k + len;
     }
     return MICSA_OK;
+}
+
+// Several daemons or walkers per site: at most one sweep of each family per
+// launch, each with its own level planes; a refresh (before a timestep's
+// first sweep) redraws all of them in place.
+int sweep_cells_families(micsa_ctx* c, int64_t n, bool walkers)
+{
+    int st;
+    if ((st = cells_alloc(c)) || (st = need_planes(c))) return st;
+    const CellGeom cg = cell_geom(c);
+    const int gamma = c->gamma;
+    const int64_t words = (int64_t)c->L * 2 * cg.plane, k_end = c->k + n;
+    const int32_t P = c->sched.period;
+    while (c->k < k_end) {
+        if ((st = need_planes(c))) return st;
+        c->home_ok = false;
+        if (c->k % gamma == 0 && is_refresh(c->k / gamma, P)) {
+            CellDraw D{};
+            const CellLevels lv = cell_levels(c);
+            D.cg = cg;
+            for (int a = 0; a < gamma; ++a) {
+                D.fam0[a] = lv.d0[a];
+                D.fam1[a] = lv.d1[a];
+                c->fowed[a] = -1;
+            }
+            D.dth = c->d_dth;
+            D.rho0 = refresh_index(c->k / gamma, P);
+            D.n = 1;
+            D.L = c->L;
+            D.families = gamma;
+            {
+                TimedLaunch t(c, kTimeRefresh);
+                k_cells_draw<<<dim3((unsigned)std::min<int64_t>((cg.plane + 63) / 64, 16384), (unsigned)(c->L * gamma)),
+                               64, 0, c->stream>>>(D);
+            }
+            if ((st = check_launch(c, "k_cells_draw"))) return st;
+        }
+        CellSweep J{};
+        CellFamilies F{};
+        const int64_t most = std::min<int64_t>(k_end - c->k, c->plan.sweeps > 0 ? std::min(c->plan.sweeps, gamma) : gamma);
+        J.k0 = c->k;
+        int64_t len = 0;
+        bool settle = false;  // a family would owe a second wandering
+        while (len < most && !settle) {
+            const int64_t k = c->k + len, t = k / gamma;
+            const int a = (int)(k - t * gamma);
+            if (len > 0 && a == 0 && is_refresh(t, P)) break;
+            const int in = c->fcur[a];
+            F.in0[len] = c->fl[in][a];
+            F.in1[len] = c->fl[in][a] + words;
+            F.out0[len] = c->fl[1 - in][a];
+            F.out1[len] = c->fl[1 - in][a] + words;
+            F.dir[len] = a < 3 ? 2 * a : 2 * (a - 3) + 1;  // +x, +y, +z, -x, -y, -z
+            F.owed[len] = c->fowed[a];
+            c->fowed[a] = -1;
+            c->fcur[a] = (uint8_t)(1 - in);
+            ++len;
+            if (walkers && a == gamma - 1) {
+                for (int f = 0; f < gamma; ++f) settle = settle || c->fowed[f] >= 0;
+                if (!settle)
+                    for (int f = 0; f < gamma; ++f) c->fowed[f] = (int32_t)(t & 1);
+            }
+        }
+        J.n = (int32_t)len;
+        J.ref0 = J.n;
+        if ((st = launch_cells(c, 4, J, &F))) return st;
+        c->k += len;
+        if (settle) {  // (other algorithms ran the sweeps that would have used the family's levels)
+            if ((st = own_home(c)) || (st = need_planes(c))) return st;
+            c->home_ok = false;
+            for (int f = 0; f < gamma; ++f) c->fowed[f] = (int32_t)((c->k / gamma - 1) & 1);
+        }
+    }
+    return MICSA_OK;
+}
+
+// Walkers on the cell kernel: against the per-half kernels and their wandering
+// pass always; against the multispin and fused byte sweeps (one walker per
+// site) where those leave the device idle (us per sweep, cells against them).
+bool use_cells_walkers(const micsa_ctx* c, int64_t n)
+{
+    if (!c->plan.ok || c->bit) return false;
+    if (c->kernel_opt != MICSA_KERNEL_AUTO && c->kernel_opt != MICSA_KERNEL_RESIDENT &&
+        c->kernel_opt != MICSA_KERNEL_SLAB)
+        return false;
+    if (c->gamma > 1 || c->kernel_opt != MICSA_KERNEL_AUTO) return true;
+    if (use_msc(c, n, MICSA_ALGO_WALKERS)) return c->plan.cost < msc_cost(c);
+    const double sites = (double)c->L * 2.0 * (double)c->g.Nh;
+    return !use_fused(c) || c->plan.cost * 1.2 / 2.4e3 < std::max(8.0, sites / 1.4e6);
 }
 
 // The heat bath and Metropolis on the cell kernel: their comparisons drawn
@@ -1795,15 +1957,18 @@ int sweep_cells_canonical(micsa_ctx* c, int32_t algo, int64_t n, long long* dlog
 // per lattice).
 bool logs_in_kernel(const micsa_ctx* c, int32_t algo, int64_t n)
 {
-    if (algo == MICSA_ALGO_WALKERS) return false;
-    if (algo == MICSA_ALGO_MICSA) return use_cells(c, n) && c->plan.sweeps == 0;
-    return use_cells_canonical(c) && c->plan.sweeps == 0;
+    if (c->plan.sweeps > 0) return false;
+    if (algo == MICSA_ALGO_WALKERS) return c->gamma == 1 && use_cells_walkers(c, n);
+    if (algo == MICSA_ALGO_MICSA) return c->gamma == 1 && use_cells(c, n);
+    return c->gamma == 1 && use_cells_canonical(c);
 }
 
 int sweep_logging(micsa_ctx* c, int32_t algo, int64_t n, long long* dlog, int64_t stride)
 {
     if (n <= 0) return MICSA_OK;
-    return algo == MICSA_ALGO_MICSA ? sweep_cells(c, n, dlog, stride) : sweep_cells_canonical(c, algo, n, dlog, stride);
+    if (algo == MICSA_ALGO_MICSA || algo == MICSA_ALGO_WALKERS)
+        return sweep_cells(c, n, dlog, stride, algo == MICSA_ALGO_WALKERS);
+    return sweep_cells_canonical(c, algo, n, dlog, stride);
 }
 
 int sweep_impl(micsa_ctx* c, int32_t algo, int64_t n)
@@ -1813,15 +1978,19 @@ int sweep_impl(micsa_ctx* c, int32_t algo, int64_t n)
     if (st0) return st0;
     // walkers (gamma = 1) on the fused sweep carry their wandering into the
     // next sweep's loads; every other path needs the daemons in place
-    const bool walk_msc = algo == MICSA_ALGO_WALKERS && use_msc(c, n, algo);
-    const bool walk_fused = algo == MICSA_ALGO_WALKERS && !c->bit && c->gamma == 1 && use_fused(c);
+    const bool walk_cells = algo == MICSA_ALGO_WALKERS && use_cells_walkers(c, n);
+    const bool walk_msc = algo == MICSA_ALGO_WALKERS && !walk_cells && use_msc(c, n, algo);
+    const bool walk_fused = algo == MICSA_ALGO_WALKERS && !walk_cells && !c->bit && c->gamma == 1 && use_fused(c);
     // the one-launch multispin sweep takes an owed wandering on its loads
     // (and leaves one), as the fused byte sweep does
-    if (!walk_fused && !walk_msc && !(algo == MICSA_ALGO_MICSA && !use_cells(c, n) && use_msc(c, n) && msc_one_launch(c)) &&
+    if (!walk_cells && !walk_fused && !walk_msc && !(algo == MICSA_ALGO_MICSA && !use_cells(c, n) && use_msc(c, n) && msc_one_launch(c)) &&
         (st0 = settle_wander(c)))
         return st0;
+    if (walk_cells || (algo == MICSA_ALGO_MICSA && use_cells(c, n))) {
+        if (n <= 0) return MICSA_OK;
+        return c->gamma > 1 ? sweep_cells_families(c, n, walk_cells) : sweep_cells(c, n, nullptr, 0, walk_cells);
+    }
     if (walk_msc) return n > 0 ? sweep_msc(c, n, true) : MICSA_OK;
-    if (algo == MICSA_ALGO_MICSA && use_cells(c, n)) return n > 0 ? sweep_cells(c, n, nullptr, 0) : MICSA_OK;
     if (algo == MICSA_ALGO_MICSA && use_msc(c, n)) return n > 0 ? sweep_msc(c, n) : MICSA_OK;
     if ((algo == MICSA_ALGO_HEATBATH || algo == MICSA_ALGO_METROPOLIS) && use_cells_canonical(c))
         return n > 0 ? sweep_cells_canonical(c, algo, n, nullptr, 0) : MICSA_OK;
@@ -2020,8 +2189,8 @@ int micsa_create(const micsa_params* p, void* hip_stream, micsa_ctx** out)
     const size_t words = (size_t)word_lattices(c) * 2 * (size_t)g.Nh;
     if (ok && !c->bit) {
         ok = hipMalloc(&c->spin, state) == hipSuccess && hipMalloc(&c->dem, dstate) == hipSuccess;
-        // the fused sweeps, and the wandering of several families, go from one copy to the other
-        if (ok && ((fused_eligible(c) && p->Lx >= 128) || gamma > 1)) ok = need_alt(c) == MICSA_OK;
+        // the fused sweeps go from one copy to the other
+        if (ok && fused_eligible(c) && p->Lx >= 128) ok = need_alt(c) == MICSA_OK;
     } else if (ok) {
         ok = hipMalloc(&c->bspin, words * 8) == hipSuccess && hipMalloc(&c->bdm0, words * 8) == hipSuccess &&
              hipMalloc(&c->bdm1, words * 8) == hipSuccess &&
@@ -2196,7 +2365,9 @@ int micsa_sweep_logged_d(micsa_ctx* ctx, int32_t algo, int64_t n, int64_t stride
             }
             ctx->rlog_cap = need;
         }
-        if ((st = settle_wander(ctx)) || (st = sweep_logging(ctx, algo, n, ctx->rlog, stride))) return st;
+        if ((algo != MICSA_ALGO_WALKERS && (st = settle_wander(ctx))) ||
+            (st = sweep_logging(ctx, algo, n, ctx->rlog, stride)))
+            return st;
         const int64_t e = rows * L;
         k_log_from_pairs<<<(unsigned)((e + 255) / 256), 256, 0, ctx->stream>>>(
             ctx->rlog, e, N, reinterpret_cast<long long*>(E_log), reinterpret_cast<long long*>(D_log));
@@ -2232,7 +2403,7 @@ int micsa_sweep_logged(micsa_ctx* ctx, int32_t algo, int64_t n, int64_t stride, 
     int st0 = check_sweep(ctx, algo, n);
     if (st0) return st0;
     if (logs_in_kernel(ctx, algo, n)) {
-        if ((st0 = settle_wander(ctx))) return st0;
+        if (algo != MICSA_ALGO_WALKERS && (st0 = settle_wander(ctx))) return st0;
         long long* rlog = nullptr;
         if (rows > 0 && hipMalloc(&rlog, (size_t)rows * L * 2 * 8) != hipSuccess) {
             (void)hipGetLastError();

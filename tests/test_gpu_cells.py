@@ -136,3 +136,39 @@ def test_canonical_sweeps_on_cells(shape, algo):
     assert np.array_equal(E, Eo)
     state(g, o)
     g.close()
+
+
+@pytest.mark.parametrize("algo", [M.ALGO_MICSA, M.ALGO_WALKERS])
+@pytest.mark.parametrize("gamma", [1, 2, 6])
+@pytest.mark.parametrize("shape", [s for s in SHAPES if s[0] * s[1] * s[2] * s[4] < 600_000])
+def test_walkers_and_families_on_cells(shape, gamma, algo):
+    """Walkers and several daemons per site: calls that end inside a timestep,
+    refreshes on every, every second and no timestep of a call, reads of the
+    levels between calls (the owed wandering applied), daemon calls after
+    walker calls, a baseline that skips sweeps of a timestep."""
+    if gamma == 1 and algo == M.ALGO_MICSA:
+        pytest.skip("covered by test_cell_sweep_matches_oracle")
+    g, o = M.Lattice(*shape, 0x3A1C, gamma=gamma), O.Lattice(*shape, 0x3A1C, gamma=gamma)
+    for P, calls in ((2, (3 * gamma + 1, 1, 2 * gamma)), (1, (gamma + 2,)), (M.REFRESH_LOG2, (5, 7))):
+        g.set_schedule(M.Schedule(M.SCHED_LINEAR, 2.5, 0.5, 400, P))
+        os_ = O.Schedule(O.SCHED_LINEAR, 2.5, 0.5, 400, P)
+        for n in calls:
+            g.sweep(algo, n)
+            o.run(algo, os_, n, 0)
+            assert np.array_equal(g.energy(), o.energy()) and np.array_equal(g.energy_tally(), o.energy())
+            assert np.array_equal(g.daemon_energy(), o.daemon_energy())
+        assert np.array_equal(g.daemons(), o.m) and np.array_equal(g.spins(), o.sigma)
+    g.sweep(algo, 2)
+    o.run(algo, os_, 2, 0)
+    g.sweep(M.ALGO_HEATBATH, gamma + 1)
+    o.run(O.ALGO_HEATBATH, os_, gamma + 1, 0)
+    g.sweep(algo, 3 * gamma)
+    o.run(algo, os_, 3 * gamma, 0)
+    g.sweep(M.ALGO_MICSA, 2)
+    o.run(O.ALGO_MICSA, os_, 2, 0)
+    E, D = g.sweep_logged(algo, 2 * gamma + 3, 2)
+    Eo, Do = o.run(algo, os_, 2 * gamma + 3, 2)
+    assert np.array_equal(E, Eo) and np.array_equal(D, Do)
+    assert np.array_equal(g.daemons(), o.m) and np.array_equal(g.spins(), o.sigma)
+    assert np.array_equal(g.energy_tally(), o.energy())
+    g.close()
