@@ -83,7 +83,8 @@ __device__ __forceinline__ uint32_t cell_move(const uint32_t (&u)[6], uint32_t& 
     const uint32_t x0 = __builtin_amdgcn_bitop3_b32(s1, m0, s2, 0x69);   // ~(m0 ^ s1 ^ s2) = ~w0
     const uint32_t cw0 = __builtin_amdgcn_bitop3_b32(s1, m0, s2, 0x48);  // m0 & (s1 ^ s2)
     const uint32_t w1 = xor3(m1, u1, cw0), cw1 = maj32(m1, u1, cw0);
-    const uint32_t p = w1 & ~x0, r = w1 | ~x0;                               // w1 & w0, w1 | w0
+    const uint32_t p = __builtin_amdgcn_bitop3_b32(w1, x0, w1, 0x30);    // w1 & w0
+    const uint32_t r = __builtin_amdgcn_bitop3_b32(w1, x0, w1, 0xF3);    // w1 | w0
     const uint32_t acc = __builtin_amdgcn_bitop3_b32(u2, p, cw1, 0x16);  // ~(u2 & cw1) & (u2 ^ cw1 ^ p)
     const uint32_t v = __builtin_amdgcn_bitop3_b32(u2, r, cw1, 0x48);    // (u2 ^ cw1) & r
     m0 = (acc & x0) | (~acc & m0);

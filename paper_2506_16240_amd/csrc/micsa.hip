@@ -119,6 +119,7 @@ struct micsa_ctx {
     // where the multispin sweep owns them), and the levels of cdr_n refreshes
     // from index cdr_rho0 on, drawn ahead (room for cdr_cap of them)
     CellPlan plan;
+    MscTile tile2{};  // tile of the two-sweep multispin pass (follows the tile options)
     void* parena = nullptr;
     uint32_t *cdr0 = nullptr, *cdr1 = nullptr;
     int64_t cdr_rho0 = 0, cdr_n = 0, cdr_cap = 0;
@@ -655,6 +656,9 @@ FusedTile choose_tile(const micsa_ctx* c)
 
 void* dev_alloc(size_t bytes);
 
+CellGeom cell_geom(const micsa_ctx* c);
+uint32_t* w32(uint64_t* p);
+
 // The alternate byte arrays (allocated with the context where a path that
 // needs them is the default, else by the first call that takes one).
 int need_alt(micsa_ctx* c)
@@ -838,7 +842,6 @@ int enqueue_bonds(micsa_ctx* c)
 }
 
 // Count over the planes (k_cells_count) into the zeroed slots of n entities.
-CellGeom cell_geom(const micsa_ctx* c);
 CellLevels cell_levels(const micsa_ctx* c);
 template <int KIND>
 int enqueue_cells_count(micsa_ctx* c, int n, int a, int b, unsigned long long* dst)
@@ -1034,42 +1037,70 @@ MscTile msc_tile(const micsa_ctx* c)
     return f;
 }
 
-// Tile of the two-sweep multispin pass (msc2_kernels.hpp): (TY + 8) W lanes,
-// whole waves up to two (Lx = 512: 24 rows, 128 lanes), and up to 16 planes,
-// so that the march's ramp of six steps is a small share of it (at 512^3:
-// 18.2 us per sweep, against 22.4 with 40 rows and 8 planes).
+// Tile of the two-sweep multispin pass (msc2_kernels.hpp): lanes of 32 sites,
+// (TY + 8) rows of Lx / 64 words, or every row of the lattice without a ring
+// where they fit, by TZ planes; neither need divide its side.  The automatic
+// tile is the one with the least estimated time: TZ + 6 steps of a chain's
+// latency and the issue and LDS time of the waves a unit holds (2.4 GHz
+// cycles).  Measured, us per pass of 512^3 by rows x planes, with the waves per
+// unit: 32 x 16 30.3 (10), 24 x 16 32.0 (12), 32 x 32 34.2 (5), 56 x 32 38 (8),
+// 24 x 8 37 (two rounds of 12); of 32 lattices of 128^3: 128 x 8 18.8 (8), 128 x
+// 16 21.1 (4); of 256^3: 24 x 4 11.0 (6), 24 x 16 17.0 (4).
 constexpr int kMscPassSweeps = 2;
+constexpr double kMsc2Chain = 1500, kMsc2Wave = 150, kMsc2Launch = 3600;
 
-MscTile msc2_tile(const micsa_ctx* c)
+int msc2_block(const MscTile& f, int W) { return ((f.TY + (f.nty > 1 ? 4 * kMscPassSweeps : 0)) * W + 63) / 64 * 64; }
+
+size_t msc2_lds(const MscTile& f, int W) { return (size_t)4 * kMsc2Words * (size_t)(msc2_block(f, W) + W); }
+
+// Estimated cycles per launch (two sweeps of every lattice).
+double msc2_cost(const micsa_ctx* c, const MscTile& f)
 {
-    const int W = c->p.Lx / 128, ring = 4 * kMscPassSweeps;
-    MscTile f{};
-    if (c->tile_y) {
-        f.TY = c->tile_y;
-    } else {
-        int rows = 0;
-        for (int r = ring + 1; r * W <= 128; ++r)
-            if ((r * W) % 64 == 0) rows = r;
-        f.TY = rows ? std::min(rows - ring, c->p.Ly) : std::max(1, std::min(c->p.Ly, kMsc2Lanes / W - ring));
-    }
-    f.TZ = c->tile_z ? c->tile_z : divisor_at_most(c->p.Lz, 16);
-    f.nty = (c->p.Ly + f.TY - 1) / f.TY;
-    f.ntz = c->p.Lz / f.TZ;
-    f.xcd = c->xcd_map == 2 && f.ntz % 8 == 0 ? 2 : (c->xcd_map && (f.nty * f.ntz) % 8 == 0 ? 1 : 0);
-    return f;
+    const int W = c->p.Lx / 64, waves = msc2_block(f, W) / 64, cus = c->cus > 0 ? c->cus : 256;
+    const int fit = (int)std::max<size_t>(1, std::min<size_t>((size_t)160 * 1024 / msc2_lds(f, W), (size_t)(16 / waves)));
+    const double per_cu = std::ceil((double)f.nty * f.ntz * c->L / cus);
+    const double m = std::min<double>(per_cu, fit), rounds = std::ceil(per_cu / fit);
+    return rounds * (f.TZ + 6) * (kMsc2Chain + kMsc2Wave * m * waves) + kMsc2Launch;
 }
 
-int msc2_block(const MscTile& f, int W) { return ((f.TY + 4 * kMscPassSweeps) * W + 63) / 64 * 64; }
+MscTile msc2_plan(const micsa_ctx* c)
+{
+    if (!msc_eligible(c)) return MscTile{};
+    const int W = c->p.Lx / 64, ring = 4 * kMscPassSweeps, Ly = c->p.Ly, Lz = c->p.Lz;
+    MscTile best{};
+    double cost = 0;
+    auto consider = [&](int TY, int TZ) {
+        MscTile f{};
+        f.TY = TY;
+        f.TZ = TZ;
+        f.nty = (Ly + TY - 1) / TY;
+        f.ntz = (Lz + TZ - 1) / TZ;
+        f.xcd = c->xcd_map && f.nty * f.ntz >= 8;
+        if (msc2_block(f, W) > kMsc2Lanes && !c->tile_y) return;
+        const double t = msc2_cost(c, f);
+        if (!best.TY || t < cost) {
+            best = f;
+            cost = t;
+        }
+    };
+    for (int ny = 1; ny <= Ly && (ny == 1 || Ly / ny >= 6); ++ny) {
+        const int TY = c->tile_y ? c->tile_y : (Ly + ny - 1) / ny;
+        if (c->tile_y || ny == 1 || (TY + ring) * W <= kMsc2Lanes)
+            for (int nz = 1; nz <= Lz; nz = nz < 16 ? nz + 1 : nz + nz / 8) {
+                consider(TY, c->tile_z ? c->tile_z : (Lz + nz - 1) / nz);
+                if (c->tile_z) break;
+            }
+        if (c->tile_y || ((TY + ring) * W <= 64 && best.TY)) break;  // narrower than a wave: no use
+    }
+    return best;
+}
 
-size_t msc2_lds(const MscTile& f, int W) { return (size_t)8 * kMsc2Words * (size_t)(msc2_block(f, W) + W); }
-
-// The pass fits a work-group: lanes and LDS (at most 96 KiB: one or two
-// work-groups per CU).
+// The pass fits a work-group: lanes and LDS (at most 96 KiB).
 bool msc2_fits(const micsa_ctx* c)
 {
-    const MscTile f = msc2_tile(c);
-    const int W = c->p.Lx / 128;
-    return c->msc_pass == 2 && msc2_block(f, W) <= kMsc2Lanes && msc2_lds(f, W) <= 96 * 1024;
+    const MscTile& f = c->tile2;
+    const int W = c->p.Lx / 64;
+    return c->msc_pass == 2 && f.TY > 0 && msc2_block(f, W) <= kMsc2Lanes && msc2_lds(f, W) <= 96 * 1024;
 }
 
 bool msc_one_launch(const micsa_ctx* c)
@@ -1077,7 +1108,12 @@ bool msc_one_launch(const micsa_ctx* c)
     return c->msc_fused && ((msc_tile(c).TY + 4) * (c->p.Lx / 128) + 63) / 64 * 64 <= kMscSweepLanes;
 }
 
-constexpr int64_t kDrawBlocks = 1024;  // draw-ahead grid: one wave per SIMD, beside the sweeps
+// Draw-ahead grid, beside the sweeps: up to four waves per SIMD, which fill the
+// slots that the sweep's waves (of a higher issue priority) leave.  512^3 with a
+// refresh every 20 sweeps takes 18.3 us per sweep with 1024 blocks, 17.7 with
+// 4096, 19.0 with a thread per word (15.5 without refreshes); 32 lattices of
+// 128^3 with one every 10: 13.3, 11.2, 12.3 (9.5).
+constexpr int64_t kDrawBlocks = 4096;
 
 
 // Launch the draw of refresh sweep kr's levels on the side stream, after
@@ -1085,18 +1121,27 @@ constexpr int64_t kDrawBlocks = 1024;  // draw-ahead grid: one wave per SIMD, be
 // reads the same planes); the refresh sweep waits for draw_done.
 // alone: nothing of the call runs beside the draw (a refresh at the call's
 // first sweep), so it takes a full grid, a thread per word
-int draw_levels(micsa_ctx* c, const MscGeom& m, int64_t kr, bool alone = false)
+int draw_levels(micsa_ctx* c, int64_t kr, bool alone = false)
 {
     const int64_t rho = refresh_index(kr, c->sched.period);
     const double T = temperature(c->sched, rho);
     if (!(T > 0.0) || !std::isfinite(T)) return fail(c, MICSA_ERANGE, "no temperature for this refresh");
-    const int64_t total = (int64_t)c->L * m.plane;
-    const unsigned blocks = (unsigned)(alone ? (total + 63) / 64 : std::min<int64_t>((total + 63) / 64, kDrawBlocks));
+    CellDraw D{};
+    D.cg = cell_geom(c);
+    D.dr0 = w32(c->mdr0);
+    D.dr1 = w32(c->mdr1);
+    D.dth = c->d_dth;
+    D.rho0 = rho;
+    D.n = 1;
+    D.L = c->L;
+    D.families = 1;
+    const int64_t full = (D.cg.plane + 63) / 64;
+    const int64_t blocks = alone ? std::min<int64_t>(full, 65535)
+                                 : std::max<int64_t>(1, std::min<int64_t>(full, kDrawBlocks / c->L));
     HIP_TRY(c, hipEventRecord(c->draw_free, c->stream));
     HIP_TRY(c, hipStreamWaitEvent(c->draw_stream, c->draw_free, 0));
-    k_msc_draw<<<blocks, 64, 0, c->draw_stream>>>(c->g, m, c->L, c->mdr0, c->mdr1, (uint32_t)rho,
-                                                   daemon_thresholds(T));
-    const int st = check_launch(c, "k_msc_draw");
+    k_cells_draw<<<dim3((unsigned)blocks, (unsigned)c->L), 64, 0, c->draw_stream>>>(D);
+    const int st = check_launch(c, "k_cells_draw");
     if (st) return st;
     HIP_TRY(c, hipEventRecord(c->draw_done, c->draw_stream));
     return MICSA_OK;
@@ -1266,6 +1311,8 @@ int sweep_msc(micsa_ctx* c, int64_t n, bool walkers = false)
     const int lanes = (f.TY + 4) * m.W;
     const bool one = msc_one_launch(c);
     const bool ahead = one && c->draw_ahead;
+    const bool fits2 = msc2_fits(c);
+    const MscTile f2 = c->tile2;
     (void)words;
     if (int st = msc_alloc(c, one, ahead)) return st;
     int st = MICSA_OK;
@@ -1277,7 +1324,7 @@ int sweep_msc(micsa_ctx* c, int64_t n, bool walkers = false)
     // drawn by a full grid, enqueued before the pack so that the two run side
     // by side, and the call's first sweeps read them like any other.
     if (ahead && (drawn = next_refresh(c, c->k, k_end)) >= 0 && drawn != c->msc_drawn &&
-        (st = draw_levels(c, m, drawn, drawn == c->k)))
+        (st = draw_levels(c, drawn, drawn == c->k)))
         return st;
     c->msc_drawn = -1;
     if ((st = need_planes(c))) return st;
@@ -1295,7 +1342,7 @@ int sweep_msc(micsa_ctx* c, int64_t n, bool walkers = false)
         const DaemonThresholds th = refresh ? daemon_thresholds(T) : DaemonThresholds{0, 0, 0};
         // walkers pass their levels' carry words between the lanes of a row,
         // which share a wave when Lx / 128 divides 64
-        if (one && (walkers ? 64 % m.W == 0 : c->pend_wander < 0) && i + 1 < n && msc2_fits(c)) {
+        if (one && (walkers ? 64 % (2 * m.W) == 0 : c->pend_wander < 0) && i + 1 < n && fits2) {
             // sweeps k and k + 1 in one pass; a refresh among them reads its
             // drawn levels (at most one refresh per pass, drawn ahead)
             const bool refresh2 = is_refresh(k + 1, c->sched.period);
@@ -1303,10 +1350,10 @@ int sweep_msc(micsa_ctx* c, int64_t n, bool walkers = false)
                              !(refresh && refresh2);
             if (ok2) {
                 if (refresh || refresh2) HIP_TRY(c, hipStreamWaitEvent(c->stream, c->draw_done, 0));
-                const MscTile f2 = msc2_tile(c);
-                const dim3 grid2((unsigned)(f2.nty * f2.ntz), (unsigned)c->L);
-                const unsigned block2 = (unsigned)msc2_block(f2, m.W);
-                const size_t lds2 = msc2_lds(f2, m.W);
+                const int n2 = f2.nty * f2.ntz;
+                const dim3 grid2((unsigned)(f2.xcd ? (n2 + 7) / 8 * 8 : n2), (unsigned)c->L);
+                const unsigned block2 = (unsigned)msc2_block(f2, 2 * m.W);
+                const size_t lds2 = msc2_lds(f2, 2 * m.W);
                 const auto kern = walkers ? (refresh2 ? k_msc_sweep_multi<kMscPassSweeps, 1, true>
                                                       : k_msc_sweep_multi<kMscPassSweeps, -1, true>)
                                           : (refresh2 ? k_msc_sweep_multi<kMscPassSweeps, 1, false>
@@ -1315,19 +1362,19 @@ int sweep_msc(micsa_ctx* c, int64_t n, bool walkers = false)
                     hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds2) !=
                         hipSuccess)
                     return fail(c, MICSA_EHIP, "k_msc_sweep_multi LDS attribute");
-                Geom a_g = c->g;
-                MscGeom a_m = m;
+                CellGeom a_g = cell_geom(c);
                 MscTile a_f = f2;
-                const uint64_t *a_s = c->ms, *a_d0 = refresh ? c->mdr0 : c->md0, *a_d1 = refresh ? c->mdr1 : c->md1,
-                               *a_b = c->mb, *a_r0 = c->mdr0, *a_r1 = c->mdr1;
-                uint64_t *o_s = c->ms_alt, *o_d0 = c->md0_alt, *o_d1 = c->md1_alt;
+                const uint32_t *a_s = w32(c->ms), *a_d0 = w32(refresh ? c->mdr0 : c->md0),
+                               *a_d1 = w32(refresh ? c->mdr1 : c->md1), *a_b = w32(c->mb), *a_r0 = w32(c->mdr0),
+                               *a_r1 = w32(c->mdr1);
+                uint32_t *o_s = w32(c->ms_alt), *o_d0 = w32(c->md0_alt), *o_d1 = w32(c->md1_alt);
                 unsigned long long* a_t = c->tally;
                 // walkers: the wandering owed to sweep k's levels (none after a
                 // refresh), and sweep k's own, applied before sweep k + 1 (none
                 // when that one refreshes)
                 int a_w = walkers && !refresh ? c->pend_wander : -1;
                 int a_wA = walkers && !refresh2 ? (int)(k & 1) : -1;
-                void* args[] = {&a_g, &a_m, &a_f, &a_s, &a_d0, &a_d1, &a_b, &a_r0, &a_r1, &o_s, &o_d0, &o_d1,
+                void* args[] = {&a_g, &a_f, &a_s, &a_d0, &a_d1, &a_b, &a_r0, &a_r1, &o_s, &o_d0, &o_d1,
                                 &a_t, &a_w, &a_wA};
                 hipEvent_t e0 = nullptr, e1 = nullptr;
                 if (c->timing && (hipEventCreate(&e0) != hipSuccess || hipEventCreate(&e1) != hipSuccess)) {
@@ -1347,8 +1394,10 @@ int sweep_msc(micsa_ctx* c, int64_t n, bool walkers = false)
                 if (le != hipSuccess)
                     return fail(c, MICSA_EHIP, std::string("k_msc_sweep_multi: ") + hipGetErrorString(le));
                 if ((st = check_launch(c, "k_msc_sweep_multi"))) return st;
-                if ((refresh || refresh2) && (drawn = next_refresh(c, k + 2, k_end)) >= 0 &&
-                    (st = draw_levels(c, m, drawn)))
+                // the next refresh, in this call or (within the window) a later one
+                if ((refresh || refresh2) && ahead &&
+                    (drawn = next_refresh(c, k + 2, std::min(c->sched.n_sweeps, k_end + kMscDrawWindow))) >= 0 &&
+                    (st = draw_levels(c, drawn)))
                     return st;
                 std::swap(c->ms, c->ms_alt);
                 std::swap(c->md0, c->md0_alt);
@@ -1407,7 +1456,7 @@ int sweep_msc(micsa_ctx* c, int64_t n, bool walkers = false)
             // window) a later one
             if (refresh && ahead &&
                 (drawn = next_refresh(c, k + 1, std::min(c->sched.n_sweeps, k_end + kMscDrawWindow))) >= 0 &&
-                (st = draw_levels(c, m, drawn)))
+                (st = draw_levels(c, drawn)))
                 return st;
             std::swap(c->ms, c->ms_alt);
             std::swap(c->md0, c->md0_alt);
@@ -1557,18 +1606,8 @@ CellPlan cell_plan(const micsa_ctx* c)
     return best;
 }
 
-// Estimated cycles per sweep of the two-sweep multispin pass: its steps along
-// z, each at least the latency of one wave's step (2800 cycles; 128^3, which
-// fills an eighth of the device, takes 12.8 us per sweep) or the issue of the
-// waves a SIMD holds (about 1700 each).
-double msc_cost(const micsa_ctx* c)
-{
-    const MscTile f = msc2_tile(c);
-    const int cus = c->cus > 0 ? c->cus : 256;
-    const double waves = (double)f.nty * f.ntz * c->L * (msc2_block(f, c->p.Lx / 128) / 64);
-    const double per_simd = std::ceil(waves / (4.0 * cus));
-    return 0.5 * (f.TZ + 6) * std::max(2800.0, 1700.0 * per_simd);
-}
+// Estimated cycles per sweep of the two-sweep multispin pass.
+double msc_cost(const micsa_ctx* c) { return c->tile2.TY > 0 ? msc2_cost(c, c->tile2) / kMscPassSweeps : 1e30; }
 
 // MicSA takes the cell sweep: on request for the resident and slab forms,
 // and by default unless the multispin pass is estimated faster (us per sweep,
@@ -2180,6 +2219,7 @@ int micsa_create(const micsa_params* p, void* hip_stream, micsa_ctx** out)
     g.gamma = gamma;
 
     c->plan = cell_plan(c);
+    c->tile2 = msc2_plan(c);
 
     const size_t nred = (size_t)std::max(c->L, p->n_samples);
     bool ok = hipMalloc(&c->tally, (size_t)c->L * kSlots * 8) == hipSuccess &&
@@ -3151,7 +3191,7 @@ const char* micsa_kernel_name(const micsa_ctx* ctx, int32_t algo)
         return msc_one_launch(ctx) ? (msc2_fits(ctx) ? "k_msc_sweep_multi" : "k_msc_sweep") : "k_msc_half";
     // walkers on the fused sweeps wander on the next sweep's loads
     if (ctx && algo == MICSA_ALGO_WALKERS && use_msc(ctx, kMscMinSweeps, algo))
-        return msc_one_launch(ctx) && msc2_fits(ctx) && 64 % (ctx->p.Lx / 128) == 0 ? "k_msc_sweep_multi"
+        return msc_one_launch(ctx) && msc2_fits(ctx) && 64 % (ctx->p.Lx / 64) == 0 ? "k_msc_sweep_multi"
                                                                                     : "k_msc_sweep";
     if (algo == MICSA_ALGO_WALKERS)
         return ctx && use_fused(ctx) && ctx->gamma == 1
@@ -3194,6 +3234,7 @@ int micsa_set_option(micsa_ctx* ctx, int32_t option, int64_t value)
         if (value < 0 || value > ctx->p.Ly || (value > 0 && (value + 4) * (ctx->p.Lx / 32) > 1024))
             return fail(ctx, MICSA_EINVAL, "tile_y must be at most Ly and fit a work-group");
         ctx->tile_y = (int32_t)value;
+        ctx->tile2 = msc2_plan(ctx);
         return MICSA_OK;
     case MICSA_OPT_GRAPHS:
         if (value != 0 && value != 1) return fail(ctx, MICSA_EINVAL, "graphs is 0 or 1");
@@ -3222,11 +3263,13 @@ int micsa_set_option(micsa_ctx* ctx, int32_t option, int64_t value)
     case MICSA_OPT_XCD_MAP:
         if (value < 0 || value > 2) return fail(ctx, MICSA_EINVAL, "xcd_map is 0, 1 or 2");
         ctx->xcd_map = (int32_t)value;
+        ctx->tile2 = msc2_plan(ctx);
         return MICSA_OK;
     case MICSA_OPT_TILE_Z:
         if (value < 0 || (value > 0 && ctx->p.Lz % value != 0))
             return fail(ctx, MICSA_EINVAL, "tile_z must divide Lz");
         ctx->tile_z = (int32_t)value;
+        ctx->tile2 = msc2_plan(ctx);
         return MICSA_OK;
     default: return fail(ctx, MICSA_EINVAL, "unknown option");
     }

@@ -10,7 +10,7 @@
 // and planes on each side (recomputed from the same old state as the
 // neighbouring tile, so no work-group waits for another), and loads the old
 // odd spins on a ring of 2T rows and planes.  Lanes: (TY + 4T) rows x W
-// words.
+// words of 32 sites.
 //
 // March along z (as the one-sweep kernel): at step st, with z = zstart + dz
 // st, half h works on plane z - dz h.  Half h's inputs are then at hand:
@@ -32,7 +32,7 @@
 // the pass refreshes (RJ < 0: none does).
 //
 // Walkers (WALK; Sec. 2.6, forward-X wandering; a row's lanes share a wave,
-// Lx / 128 dividing 64): the levels move by 0 or +-1 site across the two
+// Lx / 64 dividing 64): the levels move by 0 or +-1 site across the two
 // parities' planes at the end of each timestep.  The wandering owed from
 // before the pass (parity `wander`, -1 none) is applied as halves 0 and 1
 // load their levels, from the other parity's planes, as the one-sweep kernel
@@ -66,31 +66,42 @@
 // its word of each plane -- the 4T result planes (two step buffers) and six
 // coupling planes for each of six ring slots, slot st mod 6 written at step
 // st (six slots, one more than the ring needs, so that the slot is the
-// step's phase in the unrolled march) -- an odd number of 64-bit words, so
-// that a wave's 64-bit reads at consecutive lanes fall in distinct banks.
+// step's phase in the unrolled march) -- an odd number of words, so that a
+// wave's reads at consecutive lanes fall in distinct banks.
 // Every LDS address is then one of five per-lane registers (the lane's word
 // and its x and y neighbours') plus a constant.
 //
-// Grid (nty * ntz, L); block B = 64 ceil((TY + 4T) W / 64) <= kMsc2Lanes;
-// LDS 8 kMsc2Words (B + W) bytes (the slack W keeps the neighbour reads of
+// Grid (nty * ntz, L); block B = 64 ceil((TY + 4T) W / 64) <= kMsc2Lanes, W = Lx / 64;
+// LDS 4 kMsc2Words (B + W) bytes (the slack W keeps the neighbour reads of
 // the last lanes inside).
+//
+// Lanes of 32 sites.  With 64 a wave's step was about 375 instructions and
+// 191 registers, so that a SIMD held one or two waves, unevenly (704
+// work-groups of two waves at 512^3: half the SIMDs two, half one, 17.2 us
+// per sweep).  With 32 it is about 230 and 103 registers; ten to twelve waves
+// per unit spread evenly: 15.2 us per sweep at 512^3 (rows of eight words, 32 x
+// 16 tiles), of which 10.3 us with neither loads nor stores.  Where every row
+// of the lattice fits the lanes there is no ring along y (Lx = 128: 9.4 against
+// 15.5 us per sweep of 32 lattices of 128^3).
+
 #pragma once
 #include <type_traits>
+#include "cells.hpp"
 #include "msc_kernels.hpp"
 
 namespace micsa {
 
-constexpr int kMsc2Lanes = 256;
+constexpr int kMsc2Lanes = 512;
 constexpr int kMsc2Words = 45;  // LDS words per lane: 8 result planes + 6 x 6 coupling planes, made odd
 
 template <bool DRAWN>
 struct Msc2Stage {
-    uint64_t O, Es, J[6], me0, me1, mo0, mo1;
+    uint32_t O, Es, J[6], me0, me1, mo0, mo1;
 };
 template <>
 struct Msc2Stage<true> {
-    uint64_t O, Es, J[6], me0, me1, mo0, mo1;
-    uint64_t re0, re1, ro0, ro1;  // drawn levels for the halves of the refresh sweep RJ
+    uint32_t O, Es, J[6], me0, me1, mo0, mo1;
+    uint32_t re0, re1, ro0, ro1;  // drawn levels for the halves of the refresh sweep RJ
 };
 
 // A wrapped index moved by dz = +-1 along an axis of length L.
@@ -100,56 +111,15 @@ __device__ __forceinline__ int step_wrap(int v, int dz, int L)
     return v == L ? 0 : (v < 0 ? L - 1 : v);
 }
 
-// The Creutz move of msc_move with the gates of a 32-bit half fused into
-// three-input v_bitop3 operations (24 per half instead of about 30), every
-// truth table symmetric in its first and third operands.  With x0 = ~w0
-// (w0 = m0 ^ s1 ^ s2, the sum bit of m + u): cw0 = m0 & (s1 ^ s2), the
-// carry into bit 1; acc = !w3 & (w2 ^ (w1 & w0)) with w2 = u2 ^ cw1 and
-// w3 = u2 & cw1; m' = acc ? (w2 & (w1 | w0), ~w0) : (m1, m0).
-template <int TT>
-__device__ __forceinline__ uint64_t b3(uint64_t a, uint64_t b, uint64_t c)
+// v shifted right by q in {0, 1} with bit 0 of nxt moving in at the top.
+__device__ __forceinline__ uint32_t shr_q(uint32_t v, uint32_t nxt, uint32_t q)
 {
-    const uint32_t lo = __builtin_amdgcn_bitop3_b32((uint32_t)a, (uint32_t)b, (uint32_t)c, TT);
-    const uint32_t hi = __builtin_amdgcn_bitop3_b32((uint32_t)(a >> 32), (uint32_t)(b >> 32), (uint32_t)(c >> 32), TT);
-    return (uint64_t)lo | ((uint64_t)hi << 32);
+    return __builtin_amdgcn_alignbit(nxt, v, q);
 }
-__device__ __forceinline__ uint64_t msc_move_fused(uint64_t s, const uint64_t (&n)[6], const uint64_t (&j)[6],
-                                                   uint64_t& m0, uint64_t& m1)
+// v shifted left by one with the top bit of prv moving in at the bottom, or v.
+__device__ __forceinline__ uint32_t shl_t(uint32_t v, uint32_t prv, bool t)
 {
-    const uint64_t a = xor3(s, n[0], j[0]), b = xor3(s, n[1], j[1]), c = xor3(s, n[2], j[2]);
-    const uint64_t d = xor3(s, n[3], j[3]), e = xor3(s, n[4], j[4]), f = xor3(s, n[5], j[5]);
-    const uint64_t s1 = xor3(a, b, c), c1 = maj3w(a, b, c);
-    const uint64_t s2 = xor3(d, e, f), c2 = maj3w(d, e, f);
-    const uint64_t k0 = s1 & s2;
-    const uint64_t u1 = xor3(c1, c2, k0), u2 = maj3w(c1, c2, k0);
-    const uint64_t x0 = b3<0x69>(s1, m0, s2);   // ~(m0 ^ s1 ^ s2) = ~w0
-    const uint64_t cw0 = b3<0x48>(s1, m0, s2);  // m0 & (s1 ^ s2)
-    const uint64_t w1 = xor3(m1, u1, cw0), cw1 = maj3w(m1, u1, cw0);
-    const uint64_t p = b3<0x30>(w1, x0, w1);    // w1 & w0 (first and third operand the same)
-    const uint64_t r = b3<0xF3>(w1, x0, w1);    // w1 | w0
-    const uint64_t acc = b3<0x16>(u2, p, cw1);  // ~(u2 & cw1) & (u2 ^ cw1 ^ p)
-    const uint64_t v = b3<0x48>(u2, r, cw1);    // (u2 ^ cw1) & r
-    const uint64_t n0 = (acc & x0) | (~acc & m0);
-    const uint64_t n1 = (acc & v) | (~acc & m1);
-    m0 = n0;
-    m1 = n1;
-    return s ^ acc;
-}
-
-// v shifted right by q in {0, 1} with bit 0 of nxt moving in at bit 63
-// (shift_next for q = 1): two funnel shifts.
-__device__ __forceinline__ uint64_t shr_q(uint64_t v, uint64_t nxt, uint32_t q)
-{
-    const uint32_t vl = (uint32_t)v, vh = (uint32_t)(v >> 32), nl = (uint32_t)nxt;
-    const uint32_t lo = __builtin_amdgcn_alignbit(vh, vl, q);
-    const uint32_t hi = __builtin_amdgcn_alignbit(nl, vh, q);
-    return (uint64_t)lo | ((uint64_t)hi << 32);
-}
-// v shifted left by t in {0, 1} with bit 63 of prv moving in at bit 0
-// (shift_prev for t = 1).
-__device__ __forceinline__ uint64_t shl_t(uint64_t v, uint64_t prv, uint32_t t)
-{
-    return (v << t) | (uint64_t)((uint32_t)(prv >> 63) & t);
+    return t ? __builtin_amdgcn_alignbit(v, prv, 31) : v;
 }
 
 // The levels of a row moved by amt in {0, 1} sites (the wandering) towards
@@ -157,31 +127,23 @@ __device__ __forceinline__ uint64_t shl_t(uint64_t v, uint64_t prv, uint32_t t)
 // next lane ln of the wave) or higher ones (site k takes site k - amt, the
 // carry from the previous lane lp).  The direction is uniform in a step,
 // the amount the row's parity offset.
-__device__ __forceinline__ uint64_t shfl64(uint64_t v, int src)
+__device__ __forceinline__ uint32_t wander_shift(uint32_t v, bool fwd, uint32_t amt, int ln, int lp)
 {
-    const uint32_t lo = (uint32_t)__shfl((int)(uint32_t)v, src, 64);
-    const uint32_t hi = (uint32_t)__shfl((int)(uint32_t)(v >> 32), src, 64);
-    return (uint64_t)lo | ((uint64_t)hi << 32);
-}
-__device__ __forceinline__ uint64_t wander_shift(uint64_t v, bool fwd, uint32_t amt, int ln, int lp)
-{
-    return fwd ? shr_q(v, shfl64(v, ln), amt) : shl_t(v, shfl64(v, lp), amt);
+    const uint32_t o = (uint32_t)__shfl((int)v, fwd ? ln : lp, 64);
+    return fwd ? shr_q(v, o, amt) : shl_t(v, o, amt != 0);
 }
 
-__device__ __forceinline__ int level_count(uint64_t m0, uint64_t m1)
-{
-    return __popcll(m0) + 2 * __popcll(m1);
-}
+__device__ __forceinline__ int level_count(uint32_t m0, uint32_t m1) { return __popc(m0) + 2 * __popc(m1); }
 
 template <int T, int RJ, bool WALK>
-__global__ __launch_bounds__(kMsc2Lanes, 2) void k_msc_sweep_multi(
-    Geom g, MscGeom m, MscTile f, const uint64_t* __restrict__ spin_in, const uint64_t* __restrict__ d0_in,
-    const uint64_t* __restrict__ d1_in, const uint64_t* __restrict__ bond, const uint64_t* __restrict__ dr0,
-    const uint64_t* __restrict__ dr1, uint64_t* __restrict__ spin_out, uint64_t* __restrict__ d0_out,
-    uint64_t* __restrict__ d1_out, unsigned long long* __restrict__ tally, int wander, int wanderA)
+__global__ __launch_bounds__(kMsc2Lanes, 4) void k_msc_sweep_multi(
+    CellGeom cg, MscTile f, const uint32_t* __restrict__ spin_in, const uint32_t* __restrict__ d0_in,
+    const uint32_t* __restrict__ d1_in, const uint32_t* __restrict__ bond, const uint32_t* __restrict__ dr0,
+    const uint32_t* __restrict__ dr1, uint32_t* __restrict__ spin_out, uint32_t* __restrict__ d0_out,
+    uint32_t* __restrict__ d1_out, unsigned long long* __restrict__ tally, int wander, int wanderA)
 {
     constexpr int H = 2 * T;      // halves per pass
-    static_assert(!WALK || T == 2, "walkers: two sweeps per pass");
+    static_assert(T == 2, "four halves");
     constexpr int D = 2 * T + 1;  // planes in the coupling ring
     constexpr bool DRAWN = RJ >= 1;
     static_assert(RJ < T, "the refresh sweep is one of the pass");
@@ -192,69 +154,81 @@ __global__ __launch_bounds__(kMsc2Lanes, 2) void k_msc_sweep_multi(
     constexpr int kRe0 = DRAWN ? 2 * RJ : 0, kRo0 = DRAWN ? 2 * RJ + 1 : 0;
     __builtin_amdgcn_s_setprio(1);
     static_assert(D <= 6 && 2 * H + 36 <= kMsc2Words, "six ring slots, one per step phase");
-    extern __shared__ uint64_t lds_m2[];
-    const int W = m.W;
+    extern __shared__ uint32_t lds_m2[];
+    const Geom& g = cg.g;
+    const int W = cg.W;
+    const int64_t plane = cg.plane;
     // word k of a lane: SB(buf, 0) old odd spins of plane z, SB(buf, h) half
     // h - 1's result plane; CB(slot, d) coupling d of the even sites
     constexpr auto SB = [](int buf, int k) { return buf * H + k; };
     constexpr auto CB = [](int slot, int d) { return 2 * H + slot * 6 + d; };
 
     const int l = blockIdx.y;
-    int t = blockIdx.x, ty, tz;
-    if (f.xcd == 2) {  // XCD x takes a band of z tiles of every y tile (msc_kernels.hpp)
-        const int band = f.ntz >> 3, i = t >> 3;
-        ty = i / band;
-        tz = (t & 7) * band + (i - ty * band);
-    } else {
-        if (f.xcd) t = (t & 7) * (f.nty * f.ntz / 8) + (t >> 3);
-        ty = t / f.ntz;
-        tz = t - ty * f.ntz;
+    int t = blockIdx.x;
+    if (f.xcd) {
+        // XCD x (block b runs on XCD b mod 8) takes tiles [x n / 8, (x + 1) n / 8),
+        // y fastest, so that most y neighbours share its L2; the grid is padded
+        // to a multiple of 8 and the blocks past an XCD's share have no tile
+        const int n = f.nty * f.ntz, x = t & 7, first = x * n / 8;
+        t = first + (t >> 3);
+        if (t >= (x + 1) * n / 8) return;
     }
+    const int tz = t / f.nty, ty = t - tz * f.nty;
     const int y0 = ty * f.TY, z0 = tz * f.TZ;
+    const int TZ = min(f.TZ, g.Lz - z0);  // the last tile along z may be shorter
     const int dz = (tz & 1) ? -1 : 1;
-    const int zstart = dz > 0 ? z0 - (H - 1) : z0 + f.TZ - 1 + (H - 1);
-    const int steps = f.TZ + 2 * H - 2;
+    const int zstart = dz > 0 ? z0 - (H - 1) : z0 + TZ - 1 + (H - 1);
+    const int steps = TZ + 2 * H - 2;
     const int ry = threadIdx.x / W, w = threadIdx.x - (threadIdx.x / W) * W;
+    // rows of this tile with their rings of RG rows, or the whole side, periodic
+    const bool whole = f.nty == 1;
+    const int RG = whole ? 0 : H;
     const int own = min(f.TY, g.Ly - y0);
-    const int nrows = own + 2 * H;  // rows of this tile with their rings
+    const int nrows = own + 2 * RG;
     auto wrap = [](int v, int L) { v %= L; return v < 0 ? v + L : v; };
-    auto clampr = [&](int lo, int hi) { return wrap(y0 - H + min(max(ry, lo), hi), g.Ly); };
-    const int y = wrap(y0 - H + ry, g.Ly);
-    const bool own_row = ry >= H && ry < own + H;
+    // ring rows that a value is not needed on read a row of the tile instead,
+    // whose line the work-group fetches anyway
+    auto clampr = [&](int lo, int hi) {
+        return whole ? min(ry, g.Ly - 1) : wrap(y0 - H + min(max(ry, lo), hi), g.Ly);
+    };
+    const int y = whole ? min(ry, g.Ly - 1) : wrap(y0 - H + ry, g.Ly);
+    const bool own_row = ry >= RG && ry < own + RG;
     const int yO = clampr(0, nrows - 1), yE = clampr(1, nrows - 2), yD = clampr(2, nrows - 3);
     const int yRe = clampr(2 * RJ + 1, nrows - 2 - 2 * RJ), yRo = clampr(2 * RJ + 2, nrows - 3 - 2 * RJ);
     const int me = threadIdx.x;  // = ry W + w
     const int rowW = ry * W;
     const int mxn = rowW + (w + 1 == W ? 0 : w + 1), mxp = rowW + (w == 0 ? W - 1 : w - 1);
-    const int myn = me + W, myp = ry > 0 ? me - W : me;  // rows y +- 1 (row 0 reads itself: never used)
-    uint64_t* const Lme = lds_m2 + me * kMsc2Words;
-    const uint64_t* const Lxn = lds_m2 + mxn * kMsc2Words;
-    const uint64_t* const Lxp = lds_m2 + mxp * kMsc2Words;
-    const uint64_t* const Lyn = lds_m2 + myn * kMsc2Words;
-    const uint64_t* const Lyp = lds_m2 + myp * kMsc2Words;
+    // rows y +- 1 (without the whole side, row 0 reads itself: never used)
+    const int myn = whole && ry + 1 >= g.Ly ? w : me + W;
+    const int myp = ry > 0 ? me - W : (whole ? (g.Ly - 1) * W + w : me);
+    uint32_t* const Lme = lds_m2 + me * kMsc2Words;
+    const uint32_t* const Lxn = lds_m2 + mxn * kMsc2Words;
+    const uint32_t* const Lxp = lds_m2 + mxp * kMsc2Words;
+    const uint32_t* const Lyn = lds_m2 + myn * kMsc2Words;
+    const uint32_t* const Lyp = lds_m2 + myp * kMsc2Words;
     const int ybit = y & 1;
     // walkers: the wave lanes holding this row's next and previous words
     const int lane_n = mxn & 63, lane_p = mxp & 63;
     const bool owedA = WALK && wander >= 0;  // A's input levels come from the other parity's planes
 
-    const int64_t lp = (int64_t)l * 2 * m.plane;
-    const uint64_t* ev_in = spin_in + lp;
-    const uint64_t* od_in = spin_in + lp + m.plane;
-    const uint64_t* bl = bond + (int64_t)l * 6 * m.plane;
+    const int64_t lp = (int64_t)l * 2 * plane;
+    const uint32_t* ev_in = spin_in + lp;
+    const uint32_t* od_in = spin_in + lp + plane;
+    const uint32_t* bl = bond + (int64_t)l * 6 * plane;
     const uint32_t zstride = (uint32_t)(g.Ly * W);
     // z couplings in march orientation: word 4 of a stage (and of the LDS
     // coupling ring) is the bond towards z + dz, word 5 the bond towards z - dz
     const int kFw = dz > 0 ? kPz : kMz, kBw = dz > 0 ? kMz : kPz;
-    const uint64_t* const bfw = bl + (int64_t)kFw * m.plane;
-    const uint64_t* const bbw = bl + (int64_t)kBw * m.plane;
+    const uint32_t* const bfw = bl + (int64_t)kFw * plane;
+    const uint32_t* const bbw = bl + (int64_t)kBw * plane;
     const uint32_t rO = (uint32_t)(yO * W + w), rE = (uint32_t)(yE * W + w), rD = (uint32_t)(yD * W + w),
                    rY = (uint32_t)(y * W + w), rRe = (uint32_t)(yRe * W + w), rRo = (uint32_t)(yRo * W + w);
     auto zoff = [&](int z) { return (uint32_t)z * zstride; };
-    auto ld = [](const uint64_t* base, uint32_t i) {
-        return *reinterpret_cast<const uint64_t*>(reinterpret_cast<const char*>(base) + (i << 3));
+    auto ld = [](const uint32_t* base, uint32_t i) {
+        return *reinterpret_cast<const uint32_t*>(reinterpret_cast<const char*>(base) + (i << 2));
     };
-    auto st8 = [](uint64_t* base, uint32_t i, uint64_t v) {
-        *reinterpret_cast<uint64_t*>(reinterpret_cast<char*>(base) + (i << 3)) = v;
+    auto put = [](uint32_t* base, uint32_t i, uint32_t v) {
+        *reinterpret_cast<uint32_t*>(reinterpret_cast<char*>(base) + (i << 2)) = v;
     };
 
     // zc[k] = the wrapped plane zz - k dz of the current step (uniform)
@@ -271,10 +245,10 @@ __global__ __launch_bounds__(kMsc2Lanes, 2) void k_msc_sweep_multi(
         const uint32_t h = zoff(zE) + rE;
         S.Es = ld(ev_in, h);
 #pragma unroll
-        for (int d = 0; d < 4; ++d) S.J[d] = ld(bl + (int64_t)d * m.plane, h);
+        for (int d = 0; d < 4; ++d) S.J[d] = ld(bl + (int64_t)d * plane, h);
         S.J[4] = ld(bfw, h);
         S.J[5] = ld(bbw, h);
-        const int64_t pe = lp + (owedA ? m.plane : 0), po = lp + (owedA ? 0 : m.plane);
+        const int64_t pe = lp + (owedA ? plane : 0), po = lp + (owedA ? 0 : plane);
         S.me0 = ld(d0_in + pe, h);
         S.me1 = ld(d1_in + pe, h);
         const uint32_t ho = zoff(zDn) + rD;
@@ -284,16 +258,32 @@ __global__ __launch_bounds__(kMsc2Lanes, 2) void k_msc_sweep_multi(
             const uint32_t he = zoff(zRe) + rRe, hr = zoff(zRo) + rRo;
             S.re0 = ld(dr0 + lp, he);
             S.re1 = ld(dr1 + lp, he);
-            S.ro0 = ld(dr0 + lp + m.plane, hr);
-            S.ro1 = ld(dr1 + lp + m.plane, hr);
+            S.ro0 = ld(dr0 + lp + plane, hr);
+            S.ro1 = ld(dr1 + lp + plane, hr);
+        }
+    };
+
+    uint32_t out[2][3] = {};  // the step's results of the last two halves: spins and level bits by parity
+    // store those of the step before st: half h worked on the plane that is zc[h + 1] now
+    auto store = [&](int st) {
+#pragma unroll
+        for (int par = 0; par < 2; ++par) {
+            const int h = H - 2 + par;
+            if (own_row && (uint32_t)(st - 1 - h - (H - 1)) < (uint32_t)TZ) {
+                const uint32_t ho = zoff(zc[h + 1]) + rY;
+                const int64_t pp = lp + (par ? plane : 0);
+                put(spin_out + pp, ho, out[par][0]);
+                put(d0_out + pp, ho, out[par][1]);
+                put(d1_out + pp, ho, out[par][2]);
+            }
         }
     };
 
     Stage STG[2] = {};
-    uint64_t Oq[3];                          // old odd spins loaded at steps st, st - 1, st - 2 (by st mod 3)
-    uint64_t RES[H - 1][3] = {};             // half h's result at its site, by st mod 3
-    uint64_t LV0[H > 2 ? H - 2 : 1][3] = {}, LV1[H > 2 ? H - 2 : 1][3] = {};  // its levels (read by half h + 2)
-    uint64_t L3a = 0, L3b = 0;               // walkers: half 0's levels three steps back
+    uint32_t Oq[3];                          // old odd spins loaded at steps st, st - 1, st - 2 (by st mod 3)
+    uint32_t RES[H - 1][3] = {};             // half h's result at its site, by st mod 3
+    uint32_t LV0[H > 2 ? H - 2 : 1][3] = {}, LV1[H > 2 ? H - 2 : 1][3] = {};  // its levels (read by half h + 2)
+    uint32_t L3a = 0, L3b = 0;               // walkers: half 0's levels three steps back
     int cin = 0, cout = 0;                   // telescoped level sums of the owned sites
     {
         // before step 0: odd spins of zstart - dz and zstart (ring positions of steps -2 and -1)
@@ -318,6 +308,10 @@ __global__ __launch_bounds__(kMsc2Lanes, 2) void k_msc_sweep_multi(
         const int zp1 = step_wrap(zc[0], dz, g.Lz), zp2 = step_wrap(zp1, dz, g.Lz);
         if (st + 1 < steps)
             load(STG[pb], zp2, zp1, zc[0], zc[kRe], zc[kRo]);
+        // the last step's results are stored behind this step's loads: the wait
+        // at the next step's start covers stores too, and finds these a whole
+        // step old
+        if constexpr (!FIRST || ph > 0) store(st);
         Oq[c0] = C.O;
         Lme[SB(buf, 0)] = Oq[c1];
         // the slot of this step (st mod 6) was last read at step st - 2
@@ -328,53 +322,81 @@ __global__ __launch_bounds__(kMsc2Lanes, 2) void k_msc_sweep_multi(
         // x offset of the row's sites of the half's parity: (par + y + zh) & 1
         // = (y + zz) & 1 for every half of the step (zh = zz - dz h, even sides)
         const uint32_t q = (uint32_t)((ybit + zc[0]) & 1), qn = q ^ 1u;
+        // A half's LDS words (its source plane, and the couplings of its sites)
+        // are read a half ahead of their use, so that the latency of the reads
+        // passes behind the move before: they depend on the step's barrier only,
+        // but the compiler cannot move them over the result words that the halves
+        // write.
+        struct In {
+            uint32_t C, Cn, Cp, nyp, nym, j[8];
+        };
+        In in[2];
+        auto gather = [&](auto hc) {
+            constexpr int h = decltype(hc)::value;
+            if constexpr (h < H && live(h)) {
+                In& I = in[h & 1];
+                constexpr int src = SB(h == 0 ? buf : pb, h);
+                I.C = Lme[src];
+                I.Cn = Lxn[src];
+                I.Cp = Lxp[src];
+                I.nyp = Lyn[src];
+                I.nym = Lyp[src];
+                constexpr int sl = slot(h);
+                if constexpr (h & 1) {
+                    // an odd site's coupling in direction d is its even neighbour's in
+                    // direction -d; along z the even site at plane zh + dz (ring slot of
+                    // step st - h + 1) bonds to this site with its bond towards z - dz,
+                    // the one at zh - dz (step st - h - 1) with its bond towards z + dz
+                    I.j[0] = Lme[CB(sl, kMx)];
+                    I.j[1] = Lxn[CB(sl, kMx)];
+                    I.j[2] = Lme[CB(sl, kPx)];
+                    I.j[3] = Lxp[CB(sl, kPx)];
+                    I.j[4] = Lyn[CB(sl, kMy)];
+                    I.j[5] = Lyp[CB(sl, kPy)];
+                    I.j[6] = Lme[CB(slot(h - 1), 5)];
+                    I.j[7] = Lme[CB(slot(h + 1), 4)];
+                } else if constexpr (h > 0) {
 #pragma unroll
-        for (int h = 0; h < H; ++h) {
-            if (!live(h)) continue;  // not started yet
-            const int zh = zc[h];
-            const int par = h & 1;
-            const int src = SB(h == 0 ? buf : pb, h);
-            // every read unconditional (a select, not a branch, picks the shifted word)
-            const uint64_t Cc = Lme[src], Cn = Lxn[src], Cp = Lxp[src];
-            const uint64_t nyp = Lyn[src], nym = Lyp[src];
-            const uint64_t nxp = shr_q(Cc, Cn, q);   // q ? shift_next(Cc, Cn) : Cc
-            const uint64_t nxm = shl_t(Cc, Cp, qn);  // q ? Cc : shift_prev(Cc, Cp)
-            uint64_t up, dn;  // source results at planes zh + dz and zh - dz
-            if (h == 0) {
+                    for (int d = 0; d < 6; ++d) I.j[d] = Lme[CB(sl, d)];
+                }
+            }
+        };
+        auto half = [&](auto hc) {
+            constexpr int h = decltype(hc)::value;
+            if constexpr (!live(h)) return;  // not started yet
+            gather(std::integral_constant<int, h + 1>{});
+            const In& I = in[h & 1];
+            constexpr int par = h & 1;
+            const uint32_t Cc = I.C, nyp = I.nyp, nym = I.nym;
+            const uint32_t nxp = shr_q(Cc, I.Cn, q);  // q ? shift_next(Cc, Cn) : Cc
+            const uint32_t nxm = shl_t(Cc, I.Cp, !q);  // q ? Cc : shift_prev(Cc, Cp)
+            uint32_t up, dn;  // source results at planes zh + dz and zh - dz
+            if constexpr (h == 0) {
                 up = Oq[c0];
                 dn = Oq[c2];
             } else {
                 up = RES[h - 1][c0];
                 dn = RES[h - 1][c2];
             }
-            uint64_t jb[6];
-            if (par == 0) {
-                if (h == 0) {
+            uint32_t jb[6];
+            if constexpr (h == 0) {
 #pragma unroll
-                    for (int d = 0; d < 6; ++d) jb[d] = C.J[d];
-                } else {
-                    const int sl = slot(h);
+                for (int d = 0; d < 6; ++d) jb[d] = C.J[d];
+            } else if constexpr (par == 0) {
 #pragma unroll
-                    for (int d = 0; d < 6; ++d) jb[d] = Lme[CB(sl, d)];
-                }
-            } else {  // an odd site's coupling in direction d is its even neighbour's in direction -d
-                const int sl = slot(h);
-                jb[0] = shr_q(Lme[CB(sl, kMx)], Lxn[CB(sl, kMx)], q);
-                jb[1] = shl_t(Lme[CB(sl, kPx)], Lxp[CB(sl, kPx)], qn);
-                jb[2] = Lyn[CB(sl, kMy)];
-                jb[3] = Lyp[CB(sl, kPy)];
-                // the even site at plane zh + dz (ring slot of step st - h + 1)
-                // bonds to this site with its bond towards z - dz, the one at
-                // zh - dz (step st - h - 1) with its bond towards z + dz
-                jb[4] = Lme[CB(slot(h - 1), 5)];
-                jb[5] = Lme[CB(slot(h + 1), 4)];
+                for (int d = 0; d < 6; ++d) jb[d] = I.j[d];
+            } else {
+                jb[0] = shr_q(I.j[0], I.j[1], q);
+                jb[1] = shl_t(I.j[2], I.j[3], !q);
+#pragma unroll
+                for (int d = 2; d < 6; ++d) jb[d] = I.j[d + 2];
             }
             // the half's plane is owned iff 0 <= st - h - (H - 1) < TZ, in
             // either march direction
-            const bool owned = own_row && (uint32_t)(st - h - (H - 1)) < (uint32_t)f.TZ;
+            const bool owned = own_row && (uint32_t)(st - h - (H - 1)) < (uint32_t)TZ;
             // own spin and levels
-            uint64_t s0, m0, m1;
-            if (h == 0) {
+            uint32_t s0, m0, m1;
+            if constexpr (h == 0) {
                 s0 = C.Es;
                 m0 = C.me0;
                 m1 = C.me1;
@@ -383,7 +405,7 @@ __global__ __launch_bounds__(kMsc2Lanes, 2) void k_msc_sweep_multi(
                     m0 = wander_shift(m0, fwd, fwd ? q : qn, lane_n, lane_p);
                     m1 = wander_shift(m1, fwd, fwd ? q : qn, lane_n, lane_p);
                 }
-            } else if (h == 1) {
+            } else if constexpr (h == 1) {
                 s0 = Oq[c2];
                 m0 = C.mo0;
                 m1 = C.mo1;
@@ -398,8 +420,8 @@ __global__ __launch_bounds__(kMsc2Lanes, 2) void k_msc_sweep_multi(
                 m1 = LV1[h - 2][c2];
                 bool drawn_here = false;
                 if constexpr (DRAWN) {
-                    if ((h >> 1) == RJ) {  // the refresh: drawn levels replace those half h - 2 left
-                        const uint64_t r0 = par ? C.ro0 : C.re0, r1 = par ? C.ro1 : C.re1;
+                    if constexpr ((h >> 1) == RJ) {  // the refresh: drawn levels replace those half h - 2 left
+                        const uint32_t r0 = par ? C.ro0 : C.re0, r1 = par ? C.ro1 : C.re1;
                         const int dc = level_count(r0, r1) - level_count(m0, m1);
                         cin += owned ? dc : 0;
                         m0 = r0;
@@ -413,33 +435,35 @@ __global__ __launch_bounds__(kMsc2Lanes, 2) void k_msc_sweep_multi(
                         // levels of the step before (same plane), odd sites of
                         // half 3 half 0's of three steps before, each moved by
                         // she / sho of the parity wanderA
-                        const uint64_t a0 = par ? L3a : LV0[1][c1], a1 = par ? L3b : LV1[1][c1];
+                        const uint32_t a0 = par ? L3a : LV0[1][c1], a1 = par ? L3b : LV1[1][c1];
                         const bool fwd = (par == 0) == (wanderA == 0);
                         m0 = wander_shift(a0, fwd, fwd ? q : qn, lane_n, lane_p);
                         m1 = wander_shift(a1, fwd, fwd ? q : qn, lane_n, lane_p);
                     }
                 }
             }
-            if (h < 2) cin += owned ? level_count(m0, m1) : 0;
-            const uint64_t nb[6] = {nxp, nxm, nyp, nym, up, dn};
-            const uint64_t Sn = msc_move_fused(s0, nb, jb, m0, m1);
-            if (h < H - 1) RES[h][c0] = Sn;
-            if (h < H - 2) {
+            if constexpr (h < 2) cin += owned ? level_count(m0, m1) : 0;
+            const uint32_t u[6] = {xor3(s0, nxp, jb[0]), xor3(s0, nxm, jb[1]), xor3(s0, nyp, jb[2]),
+                                   xor3(s0, nym, jb[3]), xor3(s0, up, jb[4]),  xor3(s0, dn, jb[5])};
+            const uint32_t Sn = s0 ^ cell_move(u, m0, m1);
+            if constexpr (h < H - 1) RES[h][c0] = Sn;
+            if constexpr (h < H - 2) {
                 LV0[h][c0] = m0;
                 LV1[h][c0] = m1;
             }
-            if (h + 1 < H) Lme[SB(buf, h + 1)] = Sn;
-            if (h >= H - 2) {
+            if constexpr (h + 1 < H) Lme[SB(buf, h + 1)] = Sn;
+            if constexpr (h >= H - 2) {
                 cout += owned ? level_count(m0, m1) : 0;
-                if (owned) {
-                    const uint32_t ho = zoff(zh) + rY;
-                    const int64_t pp = lp + (par ? m.plane : 0);
-                    st8(spin_out + pp, ho, Sn);
-                    st8(d0_out + pp, ho, m0);
-                    st8(d1_out + pp, ho, m1);
-                }
+                out[par][0] = Sn;
+                out[par][1] = m0;
+                out[par][2] = m1;
             }
-        }
+        };
+        gather(std::integral_constant<int, 0>{});
+        half(std::integral_constant<int, 0>{});
+        half(std::integral_constant<int, 1>{});
+        half(std::integral_constant<int, 2>{});
+        half(std::integral_constant<int, 3>{});
         // advance the wrapped planes by one step
 #pragma unroll
         for (int k = ZH - 1; k > 0; --k) zc[k] = zc[k - 1];
@@ -472,6 +496,7 @@ __global__ __launch_bounds__(kMsc2Lanes, 2) void k_msc_sweep_multi(
         if (st + 5 >= steps) break;
         step(std::integral_constant<int, 5>{}, No{}, st + 5);
     }
+    store(steps);
     block_add(tally + (int64_t)l * kSlots, 4ll * (long long)(cin - cout));
 }
 

@@ -499,30 +499,4 @@ __global__ __launch_bounds__(kMscSweepLanes, 3) void k_msc_sweep(
     block_add(tally + (int64_t)l * kSlots, 4 * (so - sn));
 }
 
-// Daemon levels of a refresh sweep drawn ahead into planes of the working
-// layout: both parities of every word, with the same Philox counters as the
-// sweep's own draw.  The levels of a refresh depend on its index and
-// temperature only, not on the state, so they can be drawn while the sweeps
-// before that refresh run; the refresh sweep then reads them in place of the
-// stored levels.  Grid-stride over every (lattice, row, word); block 64.
-__global__ __launch_bounds__(64) void k_msc_draw(Geom g, MscGeom m, int32_t L, uint64_t* __restrict__ d0,
-                                                 uint64_t* __restrict__ d1, uint32_t rho, DaemonThresholds th)
-{
-    const int64_t total = (int64_t)L * m.plane;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < total; i += (int64_t)gridDim.x * blockDim.x) {
-        const int l = (int)(i / m.plane);
-        const int64_t pw = i - (int64_t)l * m.plane;
-        const int row = (int)(pw / m.W), w = (int)(pw - (int64_t)row * m.W);
-        const int y = row % g.Ly, z = row / g.Ly;
-        uint64_t e0, e1, o0, o1;
-        msc_draw2(g, row, w, (y + z) & 1, rho, (uint32_t)(l % g.R), stream_word(kStreamDaemon, (uint32_t)(l / g.R)),
-                  th, e0, e1, o0, o1);
-        const int64_t he = (int64_t)l * 2 * m.plane + pw, ho = he + m.plane;
-        d0[he] = e0;
-        d1[he] = e1;
-        d0[ho] = o0;
-        d1[ho] = o1;
-    }
-}
-
 }  // namespace micsa
