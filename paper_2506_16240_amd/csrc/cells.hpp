@@ -776,6 +776,32 @@ __global__ void __launch_bounds__(kCellLanes) k_cells_sweep_families(CellSweep J
     cells_body<NR, XM, 4>(J, &F, blockIdx.z, blockIdx.x, blockIdx.y, lds, red);
 }
 
+// The batched launches of the serving pool: whole lattices of different jobs,
+// each with its own shape, schedule and sweep index, a work-group per item.
+// Table entries are uniform per work-group.
+struct CellItem {
+    int32_t job, lattice;
+};
+
+template <int NR, int XM>
+__global__ void __launch_bounds__(kCellLanes) k_cells_sweep_batch(const CellSweep* __restrict__ jobs,
+                                                                  const CellItem* __restrict__ items)
+{
+    __shared__ uint32_t lds[2 * NR * kCellLanes];
+    __shared__ uint32_t red[4];
+    const CellItem it = items[blockIdx.x];
+    const CellSweep J = jobs[it.job];
+    cells_body<NR, XM, 0>(J, nullptr, it.lattice, 0, 0, lds, red);
+}
+
+__global__ void __launch_bounds__(256) k_cells_draw_batch(const CellDraw* __restrict__ jobs,
+                                                          const CellItem* __restrict__ items)
+{
+    const CellItem it = items[blockIdx.y];
+    const CellDraw D = jobs[it.job];
+    cells_draw_body(D, it.lattice, (int64_t)blockIdx.x * blockDim.x + threadIdx.x, (int64_t)gridDim.x * blockDim.x);
+}
+
 // ------------------------------------------------- planes <-> other layouts
 // Bit 0 of each byte of a word as four bits, and back.
 __device__ __forceinline__ uint32_t gather4(uint32_t w) { return ((w & 0x01010101u) * 0x01020408u) >> 24; }

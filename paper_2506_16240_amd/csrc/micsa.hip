@@ -24,7 +24,6 @@
 #include "msc_kernels.hpp"
 #include "msc2_kernels.hpp"
 #include "observables.hpp"
-#include "resident_kernels.hpp"
 #include "micsa.h"
 
 using namespace micsa;
@@ -123,6 +122,7 @@ struct micsa_ctx {
     void* parena = nullptr;
     uint32_t *cdr0 = nullptr, *cdr1 = nullptr;
     int64_t cdr_rho0 = 0, cdr_n = 0, cdr_cap = 0;
+    size_t draw_room = 0;  // bytes for them (0: chosen by size)
     // several daemon (walker) families: level planes of each in two copies,
     // the copy that is current, and the parity of the wandering the planes of
     // a family owe (-1: none; the home arrays never owe one then)
@@ -539,12 +539,10 @@ int launch_refresh(micsa_ctx* c, int64_t rho, double T)
     return check_launch(c, "k_refresh");
 }
 
-// The fused sweep needs whole 16-site chunks per row and a work-group that
-// holds at least a one-row tile with its four ring rows.
-// Resident sweeps keep a state byte per site and a coupling byte per even
-// site (1.5 B per site) in the LDS of one work-group.
+// The resident variant (a small lattice in one or a few work-groups for many
+// sweeps per launch: the cell sweep) is asked for, and taken by default before
+// every other path, up to this size.
 constexpr size_t kResidentLdsMax = 150 * 1024;
-constexpr int kResidentBlock = 512;
 constexpr int64_t kResidentChunk = 2048;  // sweeps per resident launch
 
 bool resident_eligible(const micsa_ctx* c)
@@ -1646,8 +1644,9 @@ void* dev_alloc(size_t bytes)
 
 // Planes (with their alternates where tiles read what others write) and room
 // for drawn levels.  Drawn levels: as many refreshes as fit 8 MiB or the
-// lattices' spins in bytes, whichever is more, at least two (a sweep of a
-// baseline draws the words of one and a half).
+// lattices' spins in bytes, whichever is more (a pool's job: 1 MiB, or what its
+// footprint leaves), at least two (a sweep of a baseline draws the words of one
+// and a half).
 int cells_alloc(micsa_ctx* c)
 {
     const CellGeom cg = cell_geom(c);
@@ -1683,7 +1682,9 @@ int cells_alloc(micsa_ctx* c)
         }
     }
     if (!c->cdr0) {
-        const size_t one = words * 4 * 2, room = std::max<size_t>((size_t)8 << 20, (size_t)c->L * 2 * (size_t)c->g.Nh);
+        const size_t one = words * 4 * 2;
+        const size_t room = c->draw_room ? c->draw_room
+                                         : std::max<size_t>((size_t)8 << 20, (size_t)c->L * 2 * (size_t)c->g.Nh);
         const int64_t cap = std::max<int64_t>(2, std::min<int64_t>((int64_t)(room / one), 1024));
         uint32_t* a = static_cast<uint32_t*>(dev_alloc(one * (size_t)cap));
         if (!a) return fail(c, MICSA_ENOMEM, "drawn levels");
@@ -1699,7 +1700,7 @@ int cells_alloc(micsa_ctx* c)
 // k_end needs, as many as there is room for; of a small lattice also later
 // ones, until the launch fills a good part of the device (they are kept for
 // the calls that follow, until the schedule changes).
-int cells_draw(micsa_ctx* c, int64_t kr, int64_t k_end)
+CellDraw cells_draw_slice(micsa_ctx* c, int64_t kr, int64_t k_end)
 {
     const CellGeom cg = cell_geom(c);
     const int32_t P = c->sched.period;
@@ -1718,17 +1719,12 @@ int cells_draw(micsa_ctx* c, int64_t kr, int64_t k_end)
     D.n = (int32_t)n;
     D.L = c->L;
     D.families = 1;
-    const int64_t blocks = std::min<int64_t>((n * cg.plane + 63) / 64, 16384);
-    {
-        TimedLaunch t(c, kTimeRefresh);
-        k_cells_draw<<<dim3((unsigned)blocks, (unsigned)c->L), 64, 0, c->stream>>>(D);
-    }
-    const int st = check_launch(c, "k_cells_draw");
-    if (st) return st;
     c->cdr_rho0 = rho;
     c->cdr_n = n;
-    return MICSA_OK;
+    return D;
 }
+
+int64_t cells_draw_blocks(const CellDraw& D) { return std::min<int64_t>((D.n * D.cg.plane + 63) / 64, 16384); }
 
 using CellKernel = void (*)(CellSweep);
 template <int ALG>
@@ -1742,9 +1738,8 @@ CellKernel cell_kernel(int nr, int xm)
     return k[nr - 1][xm];
 }
 
-// One launch of the cell kernel on the planes (filled in: J's sweeps, draws
-// and logging); tiles go from one copy to the other.
-int launch_cells(micsa_ctx* c, int alg, CellSweep& J, const CellFamilies* F = nullptr)
+// The launch's planes and shape (J holds its sweeps, draws and logging).
+void fill_cells(const micsa_ctx* c, CellSweep& J)
 {
     const CellPlan& pl = c->plan;
     J.cg = cell_geom(c);
@@ -1761,6 +1756,14 @@ int launch_cells(micsa_ctx* c, int alg, CellSweep& J, const CellFamilies* F = nu
     J.period = c->sched.period;
     J.lattices = c->L;
     J.inv_bdiv = 1.0f / (float)J.cg.bdiv;
+}
+
+// One launch of the cell kernel on the planes; tiles go from one copy to the
+// other.
+int launch_cells(micsa_ctx* c, int alg, CellSweep& J, const CellFamilies* F = nullptr)
+{
+    const CellPlan& pl = c->plan;
+    fill_cells(c, J);
     {
         TimedLaunch t(c, alg == 1 ? kTimeHeatBath : (alg == 2 ? kTimeMetropolis : kTimeSweep));
         const dim3 grid((unsigned)pl.f.nty, (unsigned)pl.f.ntz, (unsigned)c->L);
@@ -1780,7 +1783,7 @@ int launch_cells(micsa_ctx* c, int alg, CellSweep& J, const CellFamilies* F = nu
         }
     }
     if (int st = check_launch(c, "k_cells_sweep")) return st;
-    if (!whole) {
+    if (pl.sweeps > 0) {
         std::swap(c->ms, c->ms_alt);
         if (alg == 0 || alg == 3) {  // the baselines leave the levels where they are
             std::swap(c->md0, c->md0_alt);
@@ -1801,43 +1804,63 @@ void cell_log(CellSweep& J, long long* dlog, int64_t done, int64_t stride)
     J.log_first = (int32_t)std::min<int64_t>(stride - done % stride, INT32_MAX);
 }
 
-// MicSA sweeps k .. k + n - 1 on the cell kernel.  dlog (whole-lattice plans
-// only): every `stride` sweeps (U, sum m) of each lattice to
-// dlog[row][lattice][2].
+// The next launch of MicSA sweeps from sweep k on, in a run to k_end: its
+// sweeps (at most `most`; up to the first refresh beyond the drawn ones) and
+// its refreshes.  *draw is set, with the slice in *D, if their levels have to
+// be drawn first.
+CellSweep cells_next(micsa_ctx* c, int64_t k, int64_t k_end, int64_t most, bool* draw, CellDraw* D)
+{
+    const int32_t P = c->sched.period;
+    const int64_t stride_w = (int64_t)c->L * 2 * cell_geom(c).plane;
+    int64_t len = std::min(k_end - k, most), slot = 0;
+    const int64_t kr = next_refresh(c, k, k + len);
+    *draw = false;
+    if (kr >= 0) {
+        const int64_t rho = refresh_index(kr, P);
+        if (rho < c->cdr_rho0 || rho >= c->cdr_rho0 + c->cdr_n) {
+            *D = cells_draw_slice(c, kr, k_end);
+            *draw = true;
+        }
+        slot = rho - c->cdr_rho0;
+        const int64_t beyond = c->cdr_rho0 + c->cdr_n;  // first refresh not drawn
+        if (refresh_index(k + len - 1, P) >= beyond) len = refresh_sweep(beyond, P) - k;
+    }
+    CellSweep J{};
+    J.dr0 = c->cdr0 + slot * stride_w;
+    J.dr1 = c->cdr1 + slot * stride_w;
+    J.dr_stride = stride_w;
+    J.k0 = k;
+    J.n = (int32_t)len;
+    J.ref0 = kr >= 0 && kr < k + len ? (int32_t)(kr - k) : (int32_t)len;
+    return J;
+}
+
+// MicSA (or one walker per site) sweeps k .. k + n - 1 on the cell kernel.
+// dlog (whole-lattice plans only): every `stride` sweeps (U, sum m) of each
+// lattice to dlog[row][lattice][2].
 int sweep_cells(micsa_ctx* c, int64_t n, long long* dlog, int64_t stride, bool walkers = false)
 {
     int st;
     if ((st = cells_alloc(c)) || (st = need_planes(c))) return st;
-    const CellGeom cg = cell_geom(c);
-    const int32_t P = c->sched.period;
-    const int64_t k_first = c->k, k_end = c->k + n, stride_w = (int64_t)c->L * 2 * cg.plane;
+    const int64_t k_first = c->k, k_end = c->k + n;
     c->home_ok = false;
     while (c->k < k_end) {
         const int64_t k = c->k;
-        int64_t len = std::min<int64_t>(k_end - k, c->plan.sweeps > 0 ? c->plan.sweeps : kResidentChunk);
-        // the refreshes of the launch: drawn, and in one slice
-        const int64_t kr = next_refresh(c, k, k + len);
-        int64_t slot = 0;
-        if (kr >= 0) {
-            const int64_t rho = refresh_index(kr, P);
-            if (rho < c->cdr_rho0 || rho >= c->cdr_rho0 + c->cdr_n)
-                if ((st = cells_draw(c, kr, k_end))) return st;
-            slot = rho - c->cdr_rho0;
-            const int64_t beyond = c->cdr_rho0 + c->cdr_n;  // first refresh not drawn
-            if (refresh_index(k + len - 1, P) >= beyond) len = refresh_sweep(beyond, P) - k;
+        bool draw;
+        CellDraw D;
+        CellSweep J = cells_next(c, k, k_end, c->plan.sweeps > 0 ? c->plan.sweeps : kResidentChunk, &draw, &D);
+        if (draw) {
+            {
+                TimedLaunch t(c, kTimeRefresh);
+                k_cells_draw<<<dim3((unsigned)cells_draw_blocks(D), (unsigned)c->L), 64, 0, c->stream>>>(D);
+            }
+            if ((st = check_launch(c, "k_cells_draw"))) return st;
         }
-        CellSweep J{};
-        J.dr0 = c->cdr0 + slot * stride_w;
-        J.dr1 = c->cdr1 + slot * stride_w;
-        J.dr_stride = stride_w;
         cell_log(J, dlog, k - k_first, stride);
-        J.k0 = k;
-        J.n = (int32_t)len;
-        J.ref0 = kr >= 0 && kr < k + len ? (int32_t)(kr - k) : (int32_t)len;
-        J.wander0 = walkers && kr != k ? c->pend_wander : -1;
+        J.wander0 = walkers && J.ref0 > 0 ? c->pend_wander : -1;
         if ((st = launch_cells(c, walkers ? 3 : 0, J))) return st;
-        c->pend_wander = walkers ? (int32_t)((k + len - 1) & 1) : -1;
-        c->k = k + len;
+        c->k = k + J.n;
+        c->pend_wander = walkers ? (int32_t)((c->k - 1) & 1) : -1;
     }
     return MICSA_OK;
 }
@@ -2174,20 +2197,13 @@ const char* micsa_status_string(int status)
 
 const char* micsa_last_error(const micsa_ctx* ctx) { return ctx ? ctx->err.c_str() : "null context"; }
 
-int micsa_create(const micsa_params* p, void* hip_stream, micsa_ctx** out)
+// Parameters, geometry and launch plans (no device memory).
+static int setup_ctx(micsa_ctx* c, const micsa_params* p, hipStream_t stream)
 {
-    if (!out) return MICSA_EINVAL;
-    *out = nullptr;
-    if (!p) return MICSA_EINVAL;
-    if (!params_ok(p)) return MICSA_EINVAL;
     const int64_t N = (int64_t)p->Lx * p->Ly * p->Lz;
     const int gamma = p->gamma == 0 ? 1 : p->gamma;
-
-    micsa_ctx* c = new (std::nothrow) micsa_ctx();
-    if (!c) return MICSA_ENOMEM;
     if (hipGetDevice(&c->device) != hipSuccess) {
         (void)hipGetLastError();
-        delete c;
         return MICSA_EHIP;
     }
     if (hipDeviceGetAttribute(&c->cus, hipDeviceAttributeMultiprocessorCount, c->device) != hipSuccess) {
@@ -2197,7 +2213,7 @@ int micsa_create(const micsa_params* p, void* hip_stream, micsa_ctx** out)
     c->p = *p;
     c->p.gamma = gamma;
     c->gamma = gamma;
-    c->stream = (hipStream_t)hip_stream;
+    c->stream = stream;
     c->L = p->n_samples * p->n_replicas;
     c->bit = p->layout == MICSA_LAYOUT_BITPLANE;
     // the bit-plane sweep is latency-bound: a draw beside it slows it more
@@ -2220,6 +2236,26 @@ int micsa_create(const micsa_params* p, void* hip_stream, micsa_ctx** out)
 
     c->plan = cell_plan(c);
     c->tile2 = msc2_plan(c);
+    return MICSA_OK;
+}
+
+static int create_ctx(const micsa_params* p, void* hip_stream, size_t draw_room, micsa_ctx** out)
+{
+    if (!out) return MICSA_EINVAL;
+    *out = nullptr;
+    if (!p) return MICSA_EINVAL;
+    if (!params_ok(p)) return MICSA_EINVAL;
+    const int64_t N = (int64_t)p->Lx * p->Ly * p->Lz;
+    const int gamma = p->gamma == 0 ? 1 : p->gamma;
+
+    micsa_ctx* c = new (std::nothrow) micsa_ctx();
+    if (!c) return MICSA_ENOMEM;
+    if (const int st = setup_ctx(c, p, (hipStream_t)hip_stream)) {
+        delete c;
+        return st;
+    }
+    c->draw_room = draw_room;
+    const Geom& g = c->g;
 
     const size_t nred = (size_t)std::max(c->L, p->n_samples);
     bool ok = hipMalloc(&c->tally, (size_t)c->L * kSlots * 8) == hipSuccess &&
@@ -2289,6 +2325,8 @@ int micsa_create(const micsa_params* p, void* hip_stream, micsa_ctx** out)
     *out = c;
     return MICSA_OK;
 }
+
+int micsa_create(const micsa_params* p, void* hip_stream, micsa_ctx** out) { return create_ctx(p, hip_stream, 0, out); }
 
 int micsa_destroy(micsa_ctx* ctx)
 {
@@ -3287,8 +3325,8 @@ struct PoolJob {
     int32_t state = MICSA_JOB_QUEUED;
     size_t bytes = 0;
     micsa_ctx* ctx = nullptr;
-    // Jobs the resident kernel holds run in the pool's batched launch on the
-    // pool stream; every other job gets a stream of its own (default
+    // Small lattices (batches()) run in the pool's batched launches on the pool
+    // stream; every other job gets a stream of its own (default
     // priority), so large jobs overlap with each other and with the batch.
     bool batched = false;
     hipStream_t stream = nullptr;
@@ -3334,11 +3372,11 @@ struct micsa_pool {
     hipStream_t stream = nullptr;
     int64_t next_id = 1;
     std::vector<PoolJob> jobs;  // every job not yet released, in arrival order
-    // batched launches: two launches in flight at most, each with its item
-    // table (the host may refill one while the other is read)
-    ResidentItem* d_items[2] = {nullptr, nullptr};
-    size_t d_items_cap[2] = {0, 0};
-    std::vector<ResidentItem> h_items[2];  // host copy of each table, kept until its launch has finished
+    // batches: two in flight at most, each with its tables (the host may refill
+    // one while the other is read)
+    uint8_t* d_tab[2] = {nullptr, nullptr};
+    size_t d_tab_cap[2] = {0, 0};
+    std::vector<uint8_t> h_tab[2];  // host copy of each, kept until its launches have finished
     hipEvent_t bev[2] = {nullptr, nullptr};
     int64_t batches = 0;
 };
@@ -3403,7 +3441,7 @@ int micsa_pool_destroy(micsa_pool* pool)
         free_job_stream(j);
     }
     for (int b = 0; b < 2; ++b) {
-        if (pool->d_items[b]) (void)hipFree(pool->d_items[b]);
+        if (pool->d_tab[b]) (void)hipFree(pool->d_tab[b]);
         if (pool->bev[b]) (void)hipEventDestroy(pool->bev[b]);
     }
     delete pool;
@@ -3457,6 +3495,138 @@ static PoolJob* find_job(micsa_pool* pool, int64_t id)
     return nullptr;
 }
 
+// Jobs that share batched launches: lattices of at most two cells per lane of
+// one work-group, in the byte layout.
+static bool batches(const micsa_ctx* c)
+{
+    return use_cells(c) && !c->bit && c->gamma == 1 && c->plan.sweeps == 0 && c->plan.nr <= 2;
+}
+
+// Enqueue the next chunk of the batched jobs, if one of the two batches is free:
+// in rounds of one draw launch (the refresh levels that run out) and one sweep
+// launch per kernel form, each over the lattices of every job.
+static int enqueue_batch(micsa_pool* pool, int64_t sweeps)
+{
+    const int slot = (int)(pool->batches & 1);
+    if (!slot_free(pool->bev[slot])) return MICSA_OK;
+    struct Part {
+        PoolJob* j;
+        int64_t k, end;  // next sweep, end of the chunk
+    };
+    std::vector<Part> parts;
+    for (auto& j : pool->jobs) {
+        if (j.state != MICSA_JOB_RUNNING || !j.batched) continue;
+        micsa_ctx* c = j.ctx;
+        const int64_t n = std::min<int64_t>(sweeps, c->sched.n_sweeps - c->k);
+        if (n <= 0) continue;
+        int st;
+        if ((st = cells_alloc(c)) || (st = need_planes(c))) return st;
+        c->home_ok = false;
+        parts.push_back(Part{&j, c->k, c->k + n});
+    }
+    if (parts.empty()) return MICSA_OK;
+    struct Launch {
+        int nr, xm;  // nr = 0: a draw
+        unsigned block, items, blocks;
+        size_t first;  // of its items
+    };
+    std::vector<CellSweep> jobs;
+    std::vector<CellDraw> draws;
+    std::vector<CellItem> items;
+    std::vector<Launch> seq;
+    for (bool more = true; more;) {
+        more = false;
+        const size_t d0 = items.size();
+        int64_t dblocks = 1;
+        std::vector<std::pair<micsa_ctx*, size_t>> round;  // jobs of the round and their entries
+        for (auto& p : parts) {
+            if (p.k >= p.end) continue;
+            micsa_ctx* c = p.j->ctx;
+            bool draw;
+            CellDraw D;
+            CellSweep J = cells_next(c, p.k, p.end, kResidentChunk, &draw, &D);
+            fill_cells(c, J);
+            if (draw) {
+                for (int l = 0; l < c->L; ++l) items.push_back(CellItem{(int32_t)draws.size(), l});
+                draws.push_back(D);
+                dblocks = std::max(dblocks, cells_draw_blocks(D));
+            }
+            round.emplace_back(c, jobs.size());
+            jobs.push_back(J);
+            p.k += J.n;
+            more = more || p.k < p.end;
+        }
+        if (items.size() > d0)
+            seq.push_back(Launch{0, 0, 64, (unsigned)(items.size() - d0), (unsigned)std::min<int64_t>(dblocks, 1024), d0});
+        for (int nr = 1; nr <= 2; ++nr)
+            for (int xm = 0; xm < 3; ++xm) {
+                const size_t s0 = items.size();
+                unsigned block = 0;
+                for (auto& r : round) {
+                    if (r.first->plan.nr != nr || r.first->plan.xm != xm) continue;
+                    for (int l = 0; l < r.first->L; ++l) items.push_back(CellItem{(int32_t)r.second, l});
+                    block = std::max(block, r.first->plan.block);
+                }
+                if (block) seq.push_back(Launch{nr, xm, block, (unsigned)(items.size() - s0), 1, s0});
+            }
+    }
+    // one table: jobs, draws, items
+    const size_t o_d = (jobs.size() * sizeof(CellSweep) + 63) / 64 * 64;
+    const size_t o_i = o_d + (draws.size() * sizeof(CellDraw) + 63) / 64 * 64;
+    std::vector<uint8_t>& h = pool->h_tab[slot];
+    h.resize(o_i + items.size() * sizeof(CellItem));
+    std::memcpy(h.data(), jobs.data(), jobs.size() * sizeof(CellSweep));
+    if (!draws.empty()) std::memcpy(h.data() + o_d, draws.data(), draws.size() * sizeof(CellDraw));
+    std::memcpy(h.data() + o_i, items.data(), items.size() * sizeof(CellItem));
+    if (h.size() > pool->d_tab_cap[slot]) {
+        if (pool->d_tab[slot]) (void)hipFree(pool->d_tab[slot]);
+        pool->d_tab[slot] = nullptr;
+        pool->d_tab_cap[slot] = 0;
+        if (hipMalloc(&pool->d_tab[slot], 2 * h.size()) != hipSuccess) {
+            (void)hipGetLastError();
+            return MICSA_ENOMEM;
+        }
+        pool->d_tab_cap[slot] = 2 * h.size();
+    }
+    if (!pool->bev[slot] && hipEventCreateWithFlags(&pool->bev[slot], hipEventDisableTiming) != hipSuccess)
+        return MICSA_EHIP;
+    // the table is copied from pageable memory: the copy returns once the
+    // host buffer may be reused, and the stream orders it before the launches
+    if (hipMemcpyAsync(pool->d_tab[slot], h.data(), h.size(), hipMemcpyHostToDevice, pool->stream) != hipSuccess)
+        return MICSA_EHIP;
+    const auto* dj = reinterpret_cast<const CellSweep*>(pool->d_tab[slot]);
+    const auto* dd = reinterpret_cast<const CellDraw*>(pool->d_tab[slot] + o_d);
+    const auto* di = reinterpret_cast<const CellItem*>(pool->d_tab[slot] + o_i);
+    using Kern = void (*)(const CellSweep*, const CellItem*);
+    static const Kern kern[2][3] = {{k_cells_sweep_batch<1, 0>, k_cells_sweep_batch<1, 1>, k_cells_sweep_batch<1, 2>},
+                                    {k_cells_sweep_batch<2, 0>, k_cells_sweep_batch<2, 1>, k_cells_sweep_batch<2, 2>}};
+    for (const Launch& q : seq) {
+        if (q.nr == 0)
+            for (unsigned y = 0; y < q.items; y += 65535)
+                k_cells_draw_batch<<<dim3(q.blocks, std::min(65535u, q.items - y)), q.block, 0, pool->stream>>>(
+                    dd, di + q.first + y);
+        else
+            kern[q.nr - 1][q.xm]<<<q.items, q.block, 0, pool->stream>>>(dj, di + q.first);
+        if (hipGetLastError() != hipSuccess) return MICSA_EHIP;
+    }
+    if (hipEventRecord(pool->bev[slot], pool->stream) != hipSuccess) return MICSA_EHIP;
+    for (auto& p : parts) {
+        p.j->ctx->k = p.end;
+        p.j->last_batch = pool->batches;
+    }
+    ++pool->batches;
+    return MICSA_OK;
+}
+
+static int pool_batch(micsa_pool* pool, int64_t sweeps)
+{
+    const int st = enqueue_batch(pool, sweeps);
+    if (st)  // slices of drawn levels may have been planned and not launched
+        for (auto& j : pool->jobs)
+            if (j.batched && j.ctx) j.ctx->cdr_n = 0;
+    return st;
+}
+
 int micsa_pool_step(micsa_pool* pool, int64_t sweeps, int32_t* running, int32_t* queued)
 {
     if (!pool || sweeps < 0) return MICSA_EINVAL;
@@ -3477,9 +3647,14 @@ int micsa_pool_step(micsa_pool* pool, int64_t sweeps, int32_t* running, int32_t*
         if (nrun >= pool->max_running || pool->used + j.bytes > pool->budget) break;
         micsa_params pr = j.p;
         micsa_ctx* probe = nullptr;
-        // the resident kernel's jobs share the pool stream; the others get their own
-        const bool batched = pr.layout == MICSA_LAYOUT_BYTE && (pr.gamma == 0 || pr.gamma == 1) &&
-                             (size_t)((int64_t)pr.Lx * pr.Ly * pr.Lz / 2) * 3 <= kResidentLdsMax;
+        micsa_ctx shape;
+        if (const int st = setup_ctx(&shape, &pr, nullptr)) return st;
+        const bool batched = batches(&shape);
+        // what the footprint leaves beside the home arrays and the planes, or 1 MiB
+        const size_t sites = (size_t)shape.L * 2 * (size_t)shape.g.Nh;
+        const size_t words = (size_t)shape.L * 2 * (size_t)cell_geom(&shape).plane * 4;
+        const size_t taken = (shape.bit ? j.bytes : 2 * sites) + words * (shape.plan.sweeps > 0 ? 6 : 3) + words * 3;
+        const size_t room = std::max<size_t>(j.bytes > taken ? j.bytes - taken : 0, (size_t)1 << 20);
         hipStream_t st_job = pool->stream;
         if (!batched) {
             if (hipStreamCreateWithFlags(&j.stream, hipStreamNonBlocking) != hipSuccess ||
@@ -3491,7 +3666,7 @@ int micsa_pool_step(micsa_pool* pool, int64_t sweeps, int32_t* running, int32_t*
             }
             st_job = j.stream;
         }
-        int st = micsa_create(&pr, st_job, &probe);
+        int st = create_ctx(&pr, st_job, room, &probe);
         if (st == MICSA_ENOMEM) {  // the device is fuller than the budget says: retry next step
             free_job_stream(j);
             break;
@@ -3512,60 +3687,7 @@ int micsa_pool_step(micsa_pool* pool, int64_t sweeps, int32_t* running, int32_t*
     // 3. enqueue the next chunk of sweeps of every running job with a free
     // chunk slot (at most two chunks in flight per job, and per batch).
     // Nothing waits for the device: the call returns once the work is queued.
-    const int bslot = (int)(pool->batches & 1);
-    std::vector<ResidentItem>& items = pool->h_items[bslot];
-    std::vector<std::pair<PoolJob*, int64_t>> batched;
-    size_t lds = 0;
-    if (slot_free(pool->bev[bslot])) {
-        items.clear();
-        for (auto& j : pool->jobs) {
-            if (j.state != MICSA_JOB_RUNNING || !j.batched) continue;
-            micsa_ctx* c = j.ctx;
-            const int64_t n = std::min<int64_t>(sweeps, c->sched.n_sweeps - c->k);
-            if (n <= 0) continue;
-            if (const int st = own_home(c)) return st;
-            ResidentSched rs{c->k, n, 0, c->sched.period, 0, 0};
-            for (int l = 0; l < c->L; ++l)
-                items.push_back(ResidentItem{c->g, c->spin, c->dem, c->tally, c->d_dth, rs, l});
-            lds = std::max(lds, (size_t)c->g.Nh * 3);
-            batched.emplace_back(&j, n);
-        }
-    }
-    if (!batched.empty()) {
-        // a resident job's counter moves only once its batch is launched
-        if (items.size() > pool->d_items_cap[bslot]) {
-            if (pool->d_items[bslot]) (void)hipFree(pool->d_items[bslot]);
-            pool->d_items[bslot] = nullptr;
-            pool->d_items_cap[bslot] = 0;
-            if (hipMalloc(&pool->d_items[bslot], items.size() * sizeof(ResidentItem)) != hipSuccess) {
-                (void)hipGetLastError();
-                return MICSA_ENOMEM;
-            }
-            pool->d_items_cap[bslot] = items.size();
-        }
-        if (!pool->bev[bslot] && hipEventCreateWithFlags(&pool->bev[bslot], hipEventDisableTiming) != hipSuccess)
-            return MICSA_EHIP;
-        // the table is copied from pageable memory: the copy returns once the
-        // host buffer may be reused, and the stream orders it before the launch
-        if (hipMemcpyAsync(pool->d_items[bslot], items.data(), items.size() * sizeof(ResidentItem),
-                           hipMemcpyHostToDevice, pool->stream) != hipSuccess)
-            return MICSA_EHIP;
-        static bool attr = false;
-        if (!attr) {
-            if (hipFuncSetAttribute((const void*)k_resident_batch, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                    (int)kResidentLdsMax) != hipSuccess)
-                return MICSA_EHIP;
-            attr = true;
-        }
-        k_resident_batch<<<(unsigned)items.size(), kResidentBlock, lds, pool->stream>>>(pool->d_items[bslot]);
-        if (hipGetLastError() != hipSuccess) return MICSA_EHIP;
-        if (hipEventRecord(pool->bev[bslot], pool->stream) != hipSuccess) return MICSA_EHIP;
-        for (auto& b : batched) {
-            b.first->ctx->k += b.second;
-            b.first->last_batch = pool->batches;
-        }
-        ++pool->batches;
-    }
+    if (const int st = pool_batch(pool, sweeps)) return st;
     for (auto& j : pool->jobs) {
         if (j.state != MICSA_JOB_RUNNING || j.batched) continue;
         micsa_ctx* c = j.ctx;
