@@ -909,7 +909,6 @@ __global__ void __launch_bounds__(256) k_cells_unpack(CellGeom cg, const uint32_
 __device__ __forceinline__ uint32_t cell_bits(const uint64_t* __restrict__ w, int nv)
 {
     uint32_t v = 0;
-#pragma unroll 4
     for (int k = nv - 1; k >= 0; --k) v = v + v + (__builtin_amdgcn_inverse_ballot_w64(w[k]) ? 1u : 0u);
     return v;
 }
@@ -983,7 +982,9 @@ __global__ void __launch_bounds__(256) k_cells_unpack_bits(GeomB gb, CellGeom cg
 // -------------------------------------------------------------- reductions
 // KIND 0: unsatisfied bonds of lattice l (each at its even end); 1: level
 // sum; 2: sites where replicas a and b of sample blockIdx.y differ.  Grid
-// (blocks, lattices or samples), grid-stride over the cells.
+// (blocks, lattices or samples), grid-stride over the cells.  Up to kSlots
+// blocks store their slot each, and the first one zeros the others: a read of
+// a small lattice is this launch and a copy.
 template <int KIND>
 __global__ void __launch_bounds__(256) k_cells_count(CellGeom cg, const uint32_t* __restrict__ spin, CellLevels lv,
                                                      const uint32_t* __restrict__ bond, int a, int b,
@@ -1023,7 +1024,19 @@ __global__ void __launch_bounds__(256) k_cells_count(CellGeom cg, const uint32_t
                  __popc((S ^ od(y, z == 0 ? g.Lz - 1 : z - 1, w) ^ bd(kMz)) & m);
         }
     }
-    block_add(out + (int64_t)l * kSlots, v);
+    unsigned long long* const to = out + (int64_t)l * kSlots;
+    if (gridDim.x > (unsigned)kSlots) {  // slots set to zero beforehand
+        block_add(to, v);
+        return;
+    }
+    __shared__ long long part[4];
+    const long long s = wave_sum64(v);
+    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = s;
+    __syncthreads();
+    if (threadIdx.x == 0)
+        to[blockIdx.x] = (unsigned long long)(part[0] + part[1] + part[2] + part[3]);
+    else if (blockIdx.x == 0 && threadIdx.x >= gridDim.x && threadIdx.x < (unsigned)kSlots)
+        to[threadIdx.x] = 0;
 }
 
 }  // namespace micsa

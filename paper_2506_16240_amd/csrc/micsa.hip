@@ -55,11 +55,57 @@ struct CellPlan {
     double cost = 0;  // estimated cycles per sweep of every lattice
 };
 
+// Device blocks and streams that a serving pool hands from one job to the next.
+// Allocating and freeing them per job cost a pool of 16 jobs 33 of its 76 ms:
+// a free waits for everything the device has in flight, of other jobs too, and
+// the device then idles until the host has fed it again.  A block is given
+// back once its job's streams have finished, so the next job may write it at
+// once.  What lies idle is bounded by limit (the budget less the footprints of
+// the running jobs) and freed with the pool.  Contexts of one pool may be used
+// from several threads: every access holds the lock.
+struct JobStore {
+    struct Block {
+        int device;
+        size_t bytes;
+        void* p;
+    };
+    std::mutex lock;
+    std::vector<Block> idle;  // oldest first
+    std::vector<std::pair<int, hipStream_t>> streams;
+    size_t held = 0, limit = 0;  // bytes of idle, and their bound
+
+    static constexpr size_t kStreams = 32;  // idle streams kept at most
+
+    void trim(size_t to)
+    {
+        size_t n = 0;
+        while (n < idle.size() && held > to) {
+            held -= idle[n].bytes;
+            (void)hipFree(idle[n++].p);
+        }
+        idle.erase(idle.begin(), idle.begin() + (long)n);
+    }
+    ~JobStore()
+    {
+        trim(0);
+        for (auto& s : streams) (void)hipStreamDestroy(s.second);
+    }
+};
+
 }  // namespace
 
 struct micsa_ctx {
     micsa_params p{};
     hipStream_t stream = nullptr;
+    // a pool's small jobs sweep on this stream, the pool's; `stream` is another
+    // one while such a job is set up and after it has finished (see micsa_pool)
+    hipStream_t sweep_stream = nullptr;
+    // device memory: blocks of this context, from the pool's store if it has
+    // one; what is known at creation lies in the first, filled from its start
+    JobStore* store = nullptr;
+    std::vector<JobStore::Block> owned;
+    uint8_t* arena = nullptr;
+    size_t arena_left = 0;
     int device = 0;  // the device current at creation, which holds the state
     int cus = 0;     // its compute units
     Geom g{};
@@ -114,12 +160,10 @@ struct micsa_ctx {
     // Whatever reads the home arrays unpacks the planes first, whatever
     // writes them makes the planes stale.
     bool home_ok = true, planes_ok = false;
-    // cell sweeps (cells.hpp): launch plan, planes in one allocation (null
-    // where the multispin sweep owns them), and the levels of cdr_n refreshes
+    // cell sweeps (cells.hpp): launch plan, and the levels of cdr_n refreshes
     // from index cdr_rho0 on, drawn ahead (room for cdr_cap of them)
     CellPlan plan;
     MscTile tile2{};  // tile of the two-sweep multispin pass (follows the tile options)
-    void* parena = nullptr;
     uint32_t *cdr0 = nullptr, *cdr1 = nullptr;
     int64_t cdr_rho0 = 0, cdr_n = 0, cdr_cap = 0;
     size_t draw_room = 0;  // bytes for them (0: chosen by size)
@@ -139,6 +183,7 @@ struct micsa_ctx {
     const void* gkey[kAlgos] = {};  // state buffer the graph was captured with
     unsigned long long* tally = nullptr;  // [L][kSlots]
     unsigned long long* red = nullptr;    // [max(L, S)][kSlots] reduction scratch
+    long long* sums = nullptr;            // [max(L, S)] slots summed for a read
     // device-pointer logging: one row of slots [2][L][kSlots] (energy, then
     // level sums), and the resident kernel's (U, sum m) pairs, grown on demand
     unsigned long long* logslots = nullptr;
@@ -149,6 +194,7 @@ struct micsa_ctx {
     DaemonThresholds* d_dth = nullptr;
     HeatBathThresholds* d_hth = nullptr;
     MetropolisThresholds* d_mth = nullptr;
+    std::vector<uint8_t> h_tables;  // what they were copied from (the copy may be under way)
     int64_t k = 0;
     std::string err;
     // timing
@@ -175,6 +221,131 @@ int own_home(micsa_ctx* c);
         if (e_ != hipSuccess)                                                                    \
             return fail((ctx), MICSA_EHIP, std::string(#call) + ": " + hipGetErrorString(e_)); \
     } while (0)
+
+// ---------------------------------------------------------- device memory
+void* dev_alloc(size_t bytes)
+{
+    // also while the thread's stream is being captured: an allocation is no
+    // part of the graph
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    (void)hipThreadExchangeStreamCaptureMode(&mode);
+    void* p = nullptr;
+    const hipError_t e = hipMalloc(&p, bytes);
+    (void)hipThreadExchangeStreamCaptureMode(&mode);
+    if (e != hipSuccess) {
+        (void)hipGetLastError();
+        return nullptr;
+    }
+    return p;
+}
+
+constexpr size_t arena_size(size_t bytes) { return (bytes + 255) / 256 * 256; }
+
+// A block of the context's own.  From a store: the smallest idle one that is
+// at most a quarter larger, else a new one, for which idle ones make room.
+void* own_block(micsa_ctx* c, size_t bytes)
+{
+    JobStore::Block b{c->device, arena_size(std::max<size_t>(bytes, 1)), nullptr};
+    if (JobStore* s = c->store) {
+        std::lock_guard<std::mutex> hold(s->lock);
+        size_t best = s->idle.size();
+        for (size_t i = 0; i < s->idle.size(); ++i) {
+            const JobStore::Block& q = s->idle[i];
+            if (q.device == b.device && q.bytes >= b.bytes && q.bytes - b.bytes <= b.bytes / 4 &&
+                (best == s->idle.size() || q.bytes < s->idle[best].bytes))
+                best = i;
+        }
+        if (best < s->idle.size()) {
+            b = s->idle[best];
+            s->held -= b.bytes;
+            s->idle.erase(s->idle.begin() + (long)best);
+        } else {
+            s->trim(s->limit);
+            b.p = dev_alloc(b.bytes);
+            if (!b.p && s->held) {
+                s->trim(0);
+                b.p = dev_alloc(b.bytes);
+            }
+        }
+    } else {
+        b.p = dev_alloc(b.bytes);
+    }
+    if (b.p) c->owned.push_back(b);
+    return b.p;
+}
+
+void* ctx_alloc(micsa_ctx* c, size_t bytes)
+{
+    const size_t n = arena_size(bytes);
+    if (n <= c->arena_left) {
+        uint8_t* p = c->arena;
+        c->arena += n;
+        c->arena_left -= n;
+        return p;
+    }
+    return own_block(c, bytes);
+}
+
+template <class T>
+bool ctx_alloc(micsa_ctx* c, T*& p, size_t bytes)
+{
+    return (p = static_cast<T*>(ctx_alloc(c, bytes))) != nullptr;
+}
+
+void drop_block(micsa_ctx* c, const JobStore::Block& b)
+{
+    if (JobStore* s = c->store) {
+        std::lock_guard<std::mutex> hold(s->lock);
+        s->idle.push_back(b);
+        s->held += b.bytes;
+        s->trim(s->limit);
+    } else {
+        (void)hipFree(b.p);
+    }
+}
+
+// Free a block before its context (work on it may be queued; a part of the
+// arena stays until the context goes).
+void ctx_free(micsa_ctx* c, void* p)
+{
+    for (size_t i = 0; p && i < c->owned.size(); ++i)
+        if (c->owned[i].p == p) {
+            if (c->store) {  // the next owner does not wait for this one's streams
+                (void)hipStreamSynchronize(c->stream);
+                if (c->draw_stream) (void)hipStreamSynchronize(c->draw_stream);
+            }
+            drop_block(c, c->owned[i]);
+            c->owned.erase(c->owned.begin() + (long)i);
+            return;
+        }
+}
+
+// A stream of default priority, and its end (its work has finished).
+hipError_t take_stream(JobStore* s, int device, hipStream_t* out)
+{
+    if (s) {
+        std::lock_guard<std::mutex> hold(s->lock);
+        for (size_t i = 0; i < s->streams.size(); ++i)
+            if (s->streams[i].first == device) {
+                *out = s->streams[i].second;
+                s->streams.erase(s->streams.begin() + (long)i);
+                return hipSuccess;
+            }
+    }
+    return hipStreamCreateWithFlags(out, hipStreamNonBlocking);
+}
+
+void drop_stream(JobStore* s, int device, hipStream_t q)
+{
+    if (s) {
+        std::lock_guard<std::mutex> hold(s->lock);
+        if (s->streams.size() < JobStore::kStreams) {
+            s->streams.emplace_back(device, q);
+            return;
+        }
+    }
+    (void)hipStreamDestroy(q);
+}
 
 // ----------------------------------------------------------- schedule maths
 // Refresh points and temperatures (Sec. 2.7-2.8).  Host double arithmetic,
@@ -294,9 +465,19 @@ int zero_slots(micsa_ctx* c, unsigned long long* p, int64_t n)
     return check_launch(c, "k_fill_i64");
 }
 
-// Copy the slots of n entities to the host and sum them per entity.
+// Copy the slots of n entities to the host and sum them per entity (on the
+// device first where they are many: 512 lattices' slots are 256 KiB, copied
+// through pageable memory).
 int read_slots(micsa_ctx* c, const unsigned long long* dev, int64_t n, std::vector<int64_t>& out)
 {
+    if (n > 16 && n <= std::max(c->L, c->p.n_samples)) {
+        k_sum_slots<<<(unsigned)((n + 3) / 4), 256, 0, c->stream>>>(dev, n, c->sums);
+        if (int st = check_launch(c, "k_sum_slots")) return st;
+        out.resize((size_t)n);
+        HIP_TRY(c, hipMemcpyAsync(out.data(), c->sums, (size_t)n * 8, hipMemcpyDeviceToHost, c->stream));
+        HIP_TRY(c, hipStreamSynchronize(c->stream));
+        return MICSA_OK;
+    }
     std::vector<int64_t> raw((size_t)(n * kSlots));
     HIP_TRY(c, hipMemcpyAsync(raw.data(), dev, raw.size() * 8, hipMemcpyDeviceToHost, c->stream));
     HIP_TRY(c, hipStreamSynchronize(c->stream));
@@ -395,11 +576,10 @@ int launch_bp_sweep(micsa_ctx* c, bool drawn)
         const size_t words = (size_t)word_lattices(c) * 2 * (size_t)c->g.Nh;
         bool ok = true;
         for (uint64_t** q : {&c->bspin_alt, &c->bdm0_alt, &c->bdm1_alt})
-            ok = ok && hipMalloc(q, words * 8) == hipSuccess;
+            ok = ok && ctx_alloc(c, *q, words * 8);
         if (!ok) {
-            (void)hipGetLastError();
             for (uint64_t** q : {&c->bspin_alt, &c->bdm0_alt, &c->bdm1_alt}) {
-                if (*q) (void)hipFree(*q);
+                ctx_free(c, *q);
                 *q = nullptr;
             }
             return fail(c, MICSA_ENOMEM, "bit-plane sweep buffers");
@@ -436,15 +616,14 @@ int draw_bp_levels(micsa_ctx* c, int64_t kr)
     if (!(T > 0.0) || !std::isfinite(T)) return fail(c, MICSA_ERANGE, "no temperature for this refresh");
     if (!c->bdr0) {
         const size_t words = (size_t)word_lattices(c) * 2 * (size_t)c->g.Nh;
-        if (hipMalloc(&c->bdr0, words * 8) != hipSuccess || hipMalloc(&c->bdr1, words * 8) != hipSuccess) {
-            (void)hipGetLastError();
-            if (c->bdr0) (void)hipFree(c->bdr0);
+        if (!ctx_alloc(c, c->bdr0, words * 8) || !ctx_alloc(c, c->bdr1, words * 8)) {
+            ctx_free(c, c->bdr0);
             c->bdr0 = c->bdr1 = nullptr;
             return fail(c, MICSA_ENOMEM, "bit-plane drawn levels");
         }
     }
     if (!c->draw_stream) {
-        HIP_TRY(c, hipStreamCreateWithFlags(&c->draw_stream, hipStreamNonBlocking));
+        HIP_TRY(c, take_stream(c->store, c->device, &c->draw_stream));
         HIP_TRY(c, hipEventCreateWithFlags(&c->draw_free, hipEventDisableTiming));
         HIP_TRY(c, hipEventCreateWithFlags(&c->draw_done, hipEventDisableTiming));
     }
@@ -652,8 +831,6 @@ FusedTile choose_tile(const micsa_ctx* c)
     return f;
 }
 
-void* dev_alloc(size_t bytes);
-
 CellGeom cell_geom(const micsa_ctx* c);
 uint32_t* w32(uint64_t* p);
 
@@ -662,8 +839,8 @@ uint32_t* w32(uint64_t* p);
 int need_alt(micsa_ctx* c)
 {
     const size_t state = (size_t)c->L * 2 * (size_t)c->g.Nh;
-    if (!c->spin_alt) c->spin_alt = static_cast<uint8_t*>(dev_alloc(state));
-    if (!c->dem_alt) c->dem_alt = static_cast<uint8_t*>(dev_alloc(state * (size_t)c->gamma));
+    if (!c->spin_alt) ctx_alloc(c, c->spin_alt, state);
+    if (!c->dem_alt) ctx_alloc(c, c->dem_alt, state * (size_t)c->gamma);
     return c->spin_alt && c->dem_alt ? MICSA_OK : fail(c, MICSA_ENOMEM, "alternate state buffers");
 }
 
@@ -839,7 +1016,7 @@ int enqueue_bonds(micsa_ctx* c)
     return check_launch(c, "k_init_couplings");
 }
 
-// Count over the planes (k_cells_count) into the zeroed slots of n entities.
+// Count over the planes (k_cells_count) into the slots of n entities.
 CellLevels cell_levels(const micsa_ctx* c);
 template <int KIND>
 int enqueue_cells_count(micsa_ctx* c, int n, int a, int b, unsigned long long* dst)
@@ -847,6 +1024,8 @@ int enqueue_cells_count(micsa_ctx* c, int n, int a, int b, unsigned long long* d
     const CellGeom cg = cell_geom(c);
     // a few words per thread, enough work-groups to fill the device
     const int64_t blocks = std::max<int64_t>(1, std::min<int64_t>((cg.plane + 255) / 256, 4096 / std::max(1, n) + 1));
+    if (blocks > kSlots)  // fewer store their slots themselves
+        if (int st = zero_slots(c, dst, n)) return st;
     {
         TimedLaunch t(c, kTimeReduce);
         k_cells_count<KIND><<<dim3((unsigned)blocks, (unsigned)n), 256, 0, c->stream>>>(
@@ -860,9 +1039,9 @@ int enqueue_cells_count(micsa_ctx* c, int n, int a, int b, unsigned long long* d
 int enqueue_energy(micsa_ctx* c, unsigned long long* dst)
 {
     if (c->bit && !c->planes_ok) return enqueue_lane_count<0>(c, dst, 0, 0);
+    if (c->planes_ok) return enqueue_cells_count<0>(c, c->L, 0, 0, dst);
     int st = zero_slots(c, dst, c->L);
     if (st) return st;
-    if (c->planes_ok) return enqueue_cells_count<0>(c, c->L, 0, 0, dst);
     TimedLaunch t(c, kTimeReduce);
     k_unsat_bonds<<<grid_for((int64_t)c->g.rows * c->g.Wr, c->L), kBlock, 0, c->stream>>>(c->g, c->spin,
                                                                                            dst);
@@ -872,9 +1051,9 @@ int enqueue_energy(micsa_ctx* c, unsigned long long* dst)
 int enqueue_level_sum(micsa_ctx* c, unsigned long long* dst)
 {
     if (c->bit && !c->planes_ok) return enqueue_lane_count<1>(c, dst, 0, 0);
+    if (c->planes_ok) return enqueue_cells_count<1>(c, c->L, 0, 0, dst);
     int st = zero_slots(c, dst, c->L);
     if (st) return st;
-    if (c->planes_ok) return enqueue_cells_count<1>(c, c->L, 0, 0, dst);
     TimedLaunch t(c, kTimeReduce);
     const int64_t wpl = (int64_t)c->gamma * 2 * c->g.Nh / 4;  // every family of the lattice
     k_level_sum<<<grid_for(wpl, c->L), kBlock, 0, c->stream>>>(wpl, reinterpret_cast<const uint32_t*>(c->dem),
@@ -944,7 +1123,7 @@ int sweep_graph(micsa_ctx* c, int32_t algo, int64_t n)
         (void)hipGraphExecDestroy(ex);
         ex = nullptr;
     }
-    if (!c->d_k) HIP_TRY(c, hipMalloc(&c->d_k, 8));
+    if (!c->d_k && !ctx_alloc(c, c->d_k, 8)) return fail(c, MICSA_EHIP, "sweep counter");
     if (!ex && n >= kGraphSweeps) {
         if (!c->cap_stream) HIP_TRY(c, hipStreamCreateWithFlags(&c->cap_stream, hipStreamNonBlocking));
         HIP_TRY(c, hipStreamBeginCapture(c->cap_stream, hipStreamCaptureModeThreadLocal));
@@ -1271,10 +1450,7 @@ int msc_alloc(micsa_ctx* c, bool one, bool ahead)
     std::vector<uint64_t**> fresh;
     auto get = [&](uint64_t** q, size_t n) {
         if (*q) return true;
-        if (hipMalloc(q, n * 8) != hipSuccess) {
-            *q = nullptr;
-            return false;
-        }
+        if (!ctx_alloc(c, *q, n * 8)) return false;
         fresh.push_back(q);
         return true;
     };
@@ -1282,15 +1458,14 @@ int msc_alloc(micsa_ctx* c, bool one, bool ahead)
     if (ok && one) ok = get(&c->ms_alt, words) && get(&c->md0_alt, words) && get(&c->md1_alt, words);
     if (ok && ahead) ok = get(&c->mdr0, words) && get(&c->mdr1, words);
     if (!ok) {
-        (void)hipGetLastError();
         for (uint64_t** q : fresh) {
-            (void)hipFree(*q);
+            ctx_free(c, *q);
             *q = nullptr;
         }
         return fail(c, MICSA_ENOMEM, "multispin planes");
     }
     if (ahead && !c->draw_stream) {
-        HIP_TRY(c, hipStreamCreateWithFlags(&c->draw_stream, hipStreamNonBlocking));
+        HIP_TRY(c, take_stream(c->store, c->device, &c->draw_stream));
         HIP_TRY(c, hipEventCreateWithFlags(&c->draw_free, hipEventDisableTiming));
         HIP_TRY(c, hipEventCreateWithFlags(&c->draw_done, hipEventDisableTiming));
     }
@@ -1626,27 +1801,30 @@ bool use_cells(const micsa_ctx* c, int64_t n = kMscMinSweeps)
     return !msc_eligible(c) || resident_eligible(c) || c->plan.cost < msc_cost(c);
 }
 
-void* dev_alloc(size_t bytes)
-{
-    // also while the thread's stream is being captured: an allocation is no
-    // part of the graph
-    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
-    (void)hipThreadExchangeStreamCaptureMode(&mode);
-    void* p = nullptr;
-    const hipError_t e = hipMalloc(&p, bytes);
-    (void)hipThreadExchangeStreamCaptureMode(&mode);
-    if (e != hipSuccess) {
-        (void)hipGetLastError();
-        return nullptr;
-    }
-    return p;
-}
-
 // Planes (with their alternates where tiles read what others write) and room
 // for drawn levels.  Drawn levels: as many refreshes as fit 8 MiB or the
 // lattices' spins in bytes, whichever is more (a pool's job: 1 MiB, or what its
 // footprint leaves), at least two (a sweep of a baseline draws the words of one
 // and a half).
+int64_t cells_draw_cap(const micsa_ctx* c)
+{
+    const size_t one = (size_t)c->L * 2 * (size_t)cell_geom(c).plane * 4 * 2;
+    const size_t room =
+        c->draw_room ? c->draw_room : std::max<size_t>((size_t)8 << 20, (size_t)c->L * 2 * (size_t)c->g.Nh);
+    return std::max<int64_t>(2, std::min<int64_t>((int64_t)(room / one), 1024));
+}
+
+// Words of the planes (own planes: not those of the multispin sweep).
+size_t cells_plane_words(const micsa_ctx* c)
+{
+    const CellGeom cg = cell_geom(c);
+    const size_t words = (size_t)c->L * 2 * (size_t)cg.plane;
+    const bool alt = c->plan.sweeps > 0;
+    const size_t levels = c->gamma > 1 ? (size_t)4 * c->gamma  // two bits, two copies each
+                                       : (alt ? 4 : 2);
+    return words * ((alt ? 2 : 1) + levels) + (size_t)(c->L / c->g.R) * 6 * (size_t)cg.plane;
+}
+
 int cells_alloc(micsa_ctx* c)
 {
     const CellGeom cg = cell_geom(c);
@@ -1655,14 +1833,9 @@ int cells_alloc(micsa_ctx* c)
         if (msc_eligible(c)) {
             if (int st = msc_alloc(c, true, false)) return st;
         } else {
-            const size_t sets = (size_t)(c->L / c->g.R);
-            const size_t bond = sets * 6 * (size_t)cg.plane;
             const bool alt = c->plan.sweeps > 0;
-            const size_t fams = c->gamma > 1 ? (size_t)4 * c->gamma : 0;  // two bits, two copies each
-            const size_t total = words * ((alt ? 2 : 1) + (c->gamma > 1 ? fams : (alt ? 4 : 2))) + bond;
-            uint32_t* a = static_cast<uint32_t*>(dev_alloc(total * 4));
-            if (!a) return fail(c, MICSA_ENOMEM, "cell planes");
-            c->parena = a;
+            uint32_t* a = nullptr;
+            if (!ctx_alloc(c, a, cells_plane_words(c) * 4)) return fail(c, MICSA_ENOMEM, "cell planes");
             auto take = [&](uint64_t*& q) {
                 q = reinterpret_cast<uint64_t*>(a);
                 a += words;
@@ -1682,12 +1855,9 @@ int cells_alloc(micsa_ctx* c)
         }
     }
     if (!c->cdr0) {
-        const size_t one = words * 4 * 2;
-        const size_t room = c->draw_room ? c->draw_room
-                                         : std::max<size_t>((size_t)8 << 20, (size_t)c->L * 2 * (size_t)c->g.Nh);
-        const int64_t cap = std::max<int64_t>(2, std::min<int64_t>((int64_t)(room / one), 1024));
-        uint32_t* a = static_cast<uint32_t*>(dev_alloc(one * (size_t)cap));
-        if (!a) return fail(c, MICSA_ENOMEM, "drawn levels");
+        const int64_t cap = cells_draw_cap(c);
+        uint32_t* a = nullptr;
+        if (!ctx_alloc(c, a, words * 8 * (size_t)cap)) return fail(c, MICSA_ENOMEM, "drawn levels");
         c->cdr0 = a;
         c->cdr1 = a + words * (size_t)cap;
         c->cdr_cap = cap;
@@ -2033,8 +2203,17 @@ int sweep_logging(micsa_ctx* c, int32_t algo, int64_t n, long long* dlog, int64_
     return sweep_cells_canonical(c, algo, n, dlog, stride);
 }
 
+// A finished job of a pool that sweeps again does so on the pool's stream.
+void run_stream(micsa_ctx* c)
+{
+    if (!c || !c->sweep_stream || c->stream == c->sweep_stream) return;
+    (void)hipStreamSynchronize(c->stream);
+    c->stream = c->sweep_stream;
+}
+
 int sweep_impl(micsa_ctx* c, int32_t algo, int64_t n)
 {
+    run_stream(c);
     if (!c) return MICSA_EINVAL;
     int st0 = check_sweep(c, algo, n);
     if (st0) return st0;
@@ -2123,43 +2302,27 @@ int sweep_impl(micsa_ctx* c, int32_t algo, int64_t n)
 void free_all(micsa_ctx* c)
 {
     if (!c) return;
-    if (c->spin) (void)hipFree(c->spin);
-    if (c->dem) (void)hipFree(c->dem);
-    if (c->spin_alt) (void)hipFree(c->spin_alt);
-    if (c->dem_alt) (void)hipFree(c->dem_alt);
-    if (c->bspin) (void)hipFree(c->bspin);
     if (c->draw_stream) (void)hipStreamSynchronize(c->draw_stream);
-    if (c->parena) {  // the cell planes are one allocation
-        (void)hipFree(c->parena);
-        c->ms = c->md0 = c->md1 = c->mb = c->ms_alt = c->md0_alt = c->md1_alt = nullptr;
-    }
-    if (c->cdr0) (void)hipFree(c->cdr0);
-    for (uint64_t* q : {c->ms, c->md0, c->md1, c->mb, c->ms_alt, c->md0_alt, c->md1_alt, c->mdr0, c->mdr1})
-        if (q) (void)hipFree(q);
     if (c->draw_free) (void)hipEventDestroy(c->draw_free);
     if (c->draw_done) (void)hipEventDestroy(c->draw_done);
-    if (c->draw_stream) (void)hipStreamDestroy(c->draw_stream);
-    if (c->bdm0) (void)hipFree(c->bdm0);
-    for (uint64_t* q : {c->bspin_alt, c->bdm0_alt, c->bdm1_alt, c->bdr0, c->bdr1})
-        if (q) (void)hipFree(q);
-    if (c->bdm1) (void)hipFree(c->bdm1);
-    if (c->bJ) (void)hipFree(c->bJ);
-    if (c->d_dth) (void)hipFree(c->d_dth);
-    if (c->d_hth) (void)hipFree(c->d_hth);
-    if (c->d_mth) (void)hipFree(c->d_mth);
+    if (c->draw_stream) drop_stream(c->store, c->device, c->draw_stream);
     for (auto& e : c->gexec)
         if (e) (void)hipGraphExecDestroy(e);
-    if (c->d_k) (void)hipFree(c->d_k);
     if (c->cap_stream) (void)hipStreamDestroy(c->cap_stream);
-    if (c->tally) (void)hipFree(c->tally);
-    if (c->red) (void)hipFree(c->red);
-    if (c->logslots) (void)hipFree(c->logslots);
-    if (c->rlog) (void)hipFree(c->rlog);
     for (auto& v : c->events)
         for (auto& e : v) {
             (void)hipEventDestroy(e.first);
             (void)hipEventDestroy(e.second);
         }
+    for (const JobStore::Block& b : c->owned) drop_block(c, b);
+}
+
+// tally <- energies recomputed from the state, on the device.
+int tally_from_state(micsa_ctx* c)
+{
+    if (int st = enqueue_energy(c, c->red)) return st;
+    k_tally_from_bonds<<<(unsigned)c->L, kSlots, 0, c->stream>>>(c->red, n_sites(c), c->tally);
+    return check_launch(c, "k_tally_from_bonds");
 }
 
 // Parameters a context accepts (include/micsa.h, micsa_create).
@@ -2239,38 +2402,62 @@ static int setup_ctx(micsa_ctx* c, const micsa_params* p, hipStream_t stream)
     return MICSA_OK;
 }
 
-static int create_ctx(const micsa_params* p, void* hip_stream, size_t draw_room, micsa_ctx** out)
+static int create_ctx(const micsa_params* p, hipStream_t stream, size_t draw_room, JobStore* store, micsa_ctx** out)
 {
     if (!out) return MICSA_EINVAL;
     *out = nullptr;
     if (!p) return MICSA_EINVAL;
     if (!params_ok(p)) return MICSA_EINVAL;
-    const int64_t N = (int64_t)p->Lx * p->Ly * p->Lz;
     const int gamma = p->gamma == 0 ? 1 : p->gamma;
 
     micsa_ctx* c = new (std::nothrow) micsa_ctx();
     if (!c) return MICSA_ENOMEM;
-    if (const int st = setup_ctx(c, p, (hipStream_t)hip_stream)) {
+    if (const int st = setup_ctx(c, p, stream)) {
         delete c;
         return st;
     }
     c->draw_room = draw_room;
     const Geom& g = c->g;
 
+    c->store = store;
     const size_t nred = (size_t)std::max(c->L, p->n_samples);
-    bool ok = hipMalloc(&c->tally, (size_t)c->L * kSlots * 8) == hipSuccess &&
-              hipMalloc(&c->red, nred * kSlots * 8) == hipSuccess;
     const size_t state = (size_t)c->L * 2 * (size_t)g.Nh;
     const size_t dstate = state * (size_t)gamma;  // every daemon family
     const size_t words = (size_t)word_lattices(c) * 2 * (size_t)g.Nh;
+    const size_t bonds = c->bit ? (size_t)bp_coupling_sets(geomb(c)) * 6 * (size_t)g.Nh * 8 : 0;
+    // the fused sweeps go from one copy to the other
+    const bool alt = !c->bit && fused_eligible(c) && p->Lx >= 128;
+    // Working buffers of the sweep path the lattice takes by default (counted
+    // in the pool footprint), so that the first sweep call does not allocate;
+    // if they do not fit now, that call tries again.
+    const bool cells = use_cells(c), msc = !cells && !c->bit && c->gamma == 1 && msc_eligible(c);
+    // One allocation for all of it: nine took 90 us of the 230 us that a 16^3
+    // context took to set up.
+    const size_t home = arena_size((size_t)c->L * kSlots * 8) + arena_size(nred * kSlots * 8) + arena_size(nred * 8) +
+                        (c->bit ? 3 * arena_size(words * 8) + arena_size(bonds)
+                                : (alt ? 2 : 1) * (arena_size(state) + arena_size(dstate)));
+    size_t work = 0;
+    if (msc || (cells && msc_eligible(c))) {
+        const size_t mw = (size_t)c->L * 2 * (size_t)msc_geom(c).plane * 8;
+        work = (msc ? 8 : 6) * arena_size(mw) + arena_size(3 * mw);
+    } else if (cells) {
+        work = arena_size(cells_plane_words(c) * 4);
+    }
+    if (cells) work += arena_size((size_t)c->L * 2 * (size_t)cell_geom(c).plane * 8 * (size_t)cells_draw_cap(c));
+    c->arena = static_cast<uint8_t*>(own_block(c, home + work));
+    c->arena_left = home + work;
+    if (!c->arena) {
+        c->arena = static_cast<uint8_t*>(own_block(c, home));
+        c->arena_left = home;
+    }
+    bool ok = c->arena && ctx_alloc(c, c->tally, (size_t)c->L * kSlots * 8) &&
+              ctx_alloc(c, c->red, nred * kSlots * 8) && ctx_alloc(c, c->sums, nred * 8);
     if (ok && !c->bit) {
-        ok = hipMalloc(&c->spin, state) == hipSuccess && hipMalloc(&c->dem, dstate) == hipSuccess;
-        // the fused sweeps go from one copy to the other
-        if (ok && fused_eligible(c) && p->Lx >= 128) ok = need_alt(c) == MICSA_OK;
+        ok = ctx_alloc(c, c->spin, state) && ctx_alloc(c, c->dem, dstate);
+        if (ok && alt) ok = need_alt(c) == MICSA_OK;
     } else if (ok) {
-        ok = hipMalloc(&c->bspin, words * 8) == hipSuccess && hipMalloc(&c->bdm0, words * 8) == hipSuccess &&
-             hipMalloc(&c->bdm1, words * 8) == hipSuccess &&
-             hipMalloc(&c->bJ, (size_t)bp_coupling_sets(geomb(c)) * 6 * (size_t)g.Nh * 8) == hipSuccess;
+        ok = ctx_alloc(c, c->bspin, words * 8) && ctx_alloc(c, c->bdm0, words * 8) &&
+             ctx_alloc(c, c->bdm1, words * 8) && ctx_alloc(c, c->bJ, bonds);
     }
     if (!ok) {
         (void)hipGetLastError();
@@ -2299,34 +2486,26 @@ static int create_ctx(const micsa_params* p, void* hip_stream, size_t draw_room,
                     hipMemsetAsync(c->bdm1, 0, words * 8, c->stream) != hipSuccess))
             st = MICSA_EHIP;
     }
-    if (!st) {
-        // tally <- from-scratch energy (2U - 3N)
-        std::vector<int64_t> U;
-        st = enqueue_energy(c, c->red);
-        if (!st) st = read_slots(c, c->red, c->L, U);
-        if (!st) {
-            for (auto& u : U) u = 2 * u - 3 * N;
-            st = set_tally(c, U);
-        }
-    }
+    if (!st) st = tally_from_state(c);
     if (st) {
         free_all(c);
         delete c;
         return st;
     }
-    // the working buffers of the sweep path the lattice takes by default
-    // (counted in the pool footprint), so that the first sweep call does not
-    // allocate; if they do not fit now, that call tries again
-    if (use_cells(c)) {
+    if (cells) {
         if (cells_alloc(c) != MICSA_OK) c->err.clear();
-    } else if (!c->bit && c->gamma == 1 && msc_eligible(c)) {
+    } else if (msc) {
         if (msc_alloc(c, true, true) != MICSA_OK) c->err.clear();
     }
     *out = c;
     return MICSA_OK;
 }
 
-int micsa_create(const micsa_params* p, void* hip_stream, micsa_ctx** out) { return create_ctx(p, hip_stream, 0, out); }
+int micsa_create(const micsa_params* p, void* hip_stream, micsa_ctx** out) 
+{
+    return create_ctx(p, (hipStream_t)hip_stream, 0, nullptr, out);
+}
+
 
 int micsa_destroy(micsa_ctx* ctx)
 {
@@ -2367,44 +2546,35 @@ int micsa_set_schedule(micsa_ctx* ctx, const micsa_schedule* s)
     }
     // threshold tables for every refresh of the schedule (used by the resident sweeps)
     const int64_t nrho = std::max<int64_t>(refresh_count(n), 1);
-    std::vector<DaemonThresholds> dth((size_t)nrho);
-    std::vector<HeatBathThresholds> hth((size_t)nrho);
-    std::vector<MetropolisThresholds> mth((size_t)nrho);
+    const size_t o_h = (size_t)nrho * sizeof(DaemonThresholds), o_m = o_h + (size_t)nrho * sizeof(HeatBathThresholds);
+    std::vector<uint8_t> tab(o_m + (size_t)nrho * sizeof(MetropolisThresholds));
+    static_assert(sizeof(DaemonThresholds) % 8 == 0 && sizeof(HeatBathThresholds) % 8 == 0, "tables of 64-bit words");
+    auto* dth = reinterpret_cast<DaemonThresholds*>(tab.data());
+    auto* hth = reinterpret_cast<HeatBathThresholds*>(tab.data() + o_h);
+    auto* mth = reinterpret_cast<MetropolisThresholds*>(tab.data() + o_m);
     for (int64_t rho = 0; rho < nrho; ++rho) {
         const double T = temperature(n, rho);
-        dth[(size_t)rho] = daemon_thresholds(T);
-        hth[(size_t)rho] = heatbath_thresholds(T);
-        mth[(size_t)rho] = metropolis_thresholds(T);
+        dth[rho] = daemon_thresholds(T);
+        hth[rho] = heatbath_thresholds(T);
+        mth[rho] = metropolis_thresholds(T);
     }
-    DaemonThresholds* d1 = nullptr;
-    HeatBathThresholds* d2 = nullptr;
-    MetropolisThresholds* d3 = nullptr;
-    if (hipMalloc(&d1, dth.size() * sizeof(DaemonThresholds)) != hipSuccess ||
-        hipMalloc(&d2, hth.size() * sizeof(HeatBathThresholds)) != hipSuccess ||
-        hipMalloc(&d3, mth.size() * sizeof(MetropolisThresholds)) != hipSuccess) {
-        (void)hipGetLastError();
-        if (d1) (void)hipFree(d1);
-        if (d2) (void)hipFree(d2);
-        return fail(ctx, MICSA_ENOMEM, "schedule tables");
+    uint8_t* d = nullptr;
+    if (!ctx_alloc(ctx, d, tab.size())) return fail(ctx, MICSA_ENOMEM, "schedule tables");
+    if (ctx->d_dth) HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));  // the tables in use go
+    if (hipMemcpyAsync(d, tab.data(), tab.size(), hipMemcpyHostToDevice, ctx->stream) != hipSuccess) {
+        ctx_free(ctx, d);
+        return fail(ctx, MICSA_EHIP, "schedule tables");
     }
-    HIP_TRY(ctx, hipMemcpyAsync(d1, dth.data(), dth.size() * sizeof(DaemonThresholds), hipMemcpyHostToDevice,
-                                ctx->stream));
-    HIP_TRY(ctx, hipMemcpyAsync(d2, hth.data(), hth.size() * sizeof(HeatBathThresholds), hipMemcpyHostToDevice,
-                                ctx->stream));
-    HIP_TRY(ctx, hipMemcpyAsync(d3, mth.data(), mth.size() * sizeof(MetropolisThresholds), hipMemcpyHostToDevice,
-                                ctx->stream));
-    HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
-    if (ctx->d_dth) (void)hipFree(ctx->d_dth);
-    if (ctx->d_hth) (void)hipFree(ctx->d_hth);
-    if (ctx->d_mth) (void)hipFree(ctx->d_mth);
+    if (ctx->d_dth) ctx_free(ctx, ctx->d_dth);
+    ctx->h_tables = std::move(tab);
     for (auto& e : ctx->gexec)  // captured graphs point at the old tables
         if (e) {
             (void)hipGraphExecDestroy(e);
             e = nullptr;
         }
-    ctx->d_dth = d1;
-    ctx->d_hth = d2;
-    ctx->d_mth = d3;
+    ctx->d_dth = reinterpret_cast<DaemonThresholds*>(d);
+    ctx->d_hth = reinterpret_cast<HeatBathThresholds*>(d + o_h);
+    ctx->d_mth = reinterpret_cast<MetropolisThresholds*>(d + o_m);
     ctx->sched = std::move(n);
     ctx->cdr_n = 0;  // levels drawn ahead under the old temperatures
     ctx->msc_drawn = -1;
@@ -2420,6 +2590,7 @@ int micsa_sweep_logged_d(micsa_ctx* ctx, int32_t algo, int64_t n, int64_t stride
     if (stride < 1) return fail(ctx, MICSA_EINVAL, "stride must be >= 1");
     if (!ctx->sched.set) return fail(ctx, MICSA_ESTATE, "no schedule installed");
     if (n < 0 || ctx->k + n > ctx->sched.n_sweeps) return fail(ctx, MICSA_ERANGE, "sweeps beyond the schedule");
+    run_stream(ctx);
     const int64_t rows = n / stride;
     const int L = ctx->L;
     const int64_t N = n_sites(ctx);
@@ -2432,15 +2603,11 @@ int micsa_sweep_logged_d(micsa_ctx* ctx, int32_t algo, int64_t n, int64_t stride
             // the old buffer may still be in use by enqueued work
             if (ctx->rlog) {
                 HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
-                (void)hipFree(ctx->rlog);
+                ctx_free(ctx, ctx->rlog);
                 ctx->rlog = nullptr;
                 ctx->rlog_cap = 0;
             }
-            if (hipMalloc(&ctx->rlog, need * 8) != hipSuccess) {
-                (void)hipGetLastError();
-                ctx->rlog = nullptr;
-                return fail(ctx, MICSA_ENOMEM, "log buffer");
-            }
+            if (!ctx_alloc(ctx, ctx->rlog, need * 8)) return fail(ctx, MICSA_ENOMEM, "log buffer");
             ctx->rlog_cap = need;
         }
         if ((algo != MICSA_ALGO_WALKERS && (st = settle_wander(ctx))) ||
@@ -2451,11 +2618,8 @@ int micsa_sweep_logged_d(micsa_ctx* ctx, int32_t algo, int64_t n, int64_t stride
             ctx->rlog, e, N, reinterpret_cast<long long*>(E_log), reinterpret_cast<long long*>(D_log));
         return check_launch(ctx, "k_log_from_pairs");
     }
-    if (!ctx->logslots && hipMalloc(&ctx->logslots, (size_t)2 * L * kSlots * 8) != hipSuccess) {
-        (void)hipGetLastError();
-        ctx->logslots = nullptr;
+    if (!ctx->logslots && !ctx_alloc(ctx, ctx->logslots, (size_t)2 * L * kSlots * 8))
         return fail(ctx, MICSA_ENOMEM, "log slots");
-    }
     unsigned long long* U = ctx->logslots;
     unsigned long long* Ms = ctx->logslots + (size_t)L * kSlots;
     for (int64_t r = 0; r < rows; ++r) {
@@ -2476,6 +2640,7 @@ int micsa_sweep_logged(micsa_ctx* ctx, int32_t algo, int64_t n, int64_t stride, 
     if (stride < 1) return fail(ctx, MICSA_EINVAL, "stride must be >= 1");
     if (!ctx->sched.set) return fail(ctx, MICSA_ESTATE, "no schedule installed");
     if (n < 0 || ctx->k + n > ctx->sched.n_sweeps) return fail(ctx, MICSA_ERANGE, "sweeps beyond the schedule");
+    run_stream(ctx);
     const int64_t rows = n / stride;
     const int L = ctx->L;
     int st0 = check_sweep(ctx, algo, n);
@@ -2483,17 +2648,15 @@ int micsa_sweep_logged(micsa_ctx* ctx, int32_t algo, int64_t n, int64_t stride, 
     if (logs_in_kernel(ctx, algo, n)) {
         if (algo != MICSA_ALGO_WALKERS && (st0 = settle_wander(ctx))) return st0;
         long long* rlog = nullptr;
-        if (rows > 0 && hipMalloc(&rlog, (size_t)rows * L * 2 * 8) != hipSuccess) {
-            (void)hipGetLastError();
+        if (rows > 0 && !ctx_alloc(ctx, rlog, (size_t)rows * L * 2 * 8))
             return fail(ctx, MICSA_ENOMEM, "log buffer");
-        }
         int st = sweep_logging(ctx, algo, n, rows > 0 ? rlog : nullptr, stride);
         std::vector<int64_t> h((size_t)rows * L * 2);
         if (!st && rows > 0 &&
             hipMemcpyAsync(h.data(), rlog, h.size() * 8, hipMemcpyDeviceToHost, ctx->stream) != hipSuccess)
             st = fail(ctx, MICSA_EHIP, "log copy");
         if (!st && hipStreamSynchronize(ctx->stream) != hipSuccess) st = fail(ctx, MICSA_EHIP, "sync");
-        if (rlog) (void)hipFree(rlog);
+        ctx_free(ctx, rlog);
         if (st) return st;
         const int64_t N = n_sites(ctx);
         for (int64_t r = 0; r < rows; ++r)
@@ -2505,10 +2668,7 @@ int micsa_sweep_logged(micsa_ctx* ctx, int32_t algo, int64_t n, int64_t stride, 
     }
     unsigned long long* dlog = nullptr;
     const size_t row_len = (size_t)L * 2 * kSlots;
-    if (rows > 0 && hipMalloc(&dlog, (size_t)rows * row_len * 8) != hipSuccess) {
-        (void)hipGetLastError();
-        return fail(ctx, MICSA_ENOMEM, "log buffer");
-    }
+    if (rows > 0 && !ctx_alloc(ctx, dlog, (size_t)rows * row_len * 8)) return fail(ctx, MICSA_ENOMEM, "log buffer");
     int st = MICSA_OK;
     int64_t done = 0;
     for (int64_t r = 0; r < rows && !st; ++r) {
@@ -2521,7 +2681,7 @@ int micsa_sweep_logged(micsa_ctx* ctx, int32_t algo, int64_t n, int64_t stride, 
     std::vector<int64_t> h;
     if (!st && rows > 0) st = read_slots(ctx, dlog, rows * L * 2, h);
     if (!st && hipStreamSynchronize(ctx->stream) != hipSuccess) st = fail(ctx, MICSA_EHIP, "sync");
-    if (dlog) (void)hipFree(dlog);
+    ctx_free(ctx, dlog);
     if (st) return st;
     const int64_t N = n_sites(ctx);
     for (int64_t r = 0; r < rows; ++r)
@@ -2586,10 +2746,8 @@ static int c4_counts(micsa_ctx* c, const C4Geom& cg, std::vector<int64_t>& D)
     const int64_t chunk = std::max<int64_t>(1, std::min<int64_t>({total, budget_words / per_pair, 65535}));
     unsigned long long* dD = nullptr;
     uint32_t* Q = nullptr;
-    if (hipMalloc(&dD, (size_t)ent * kSlots * 8) != hipSuccess ||
-        hipMalloc(&Q, (size_t)(chunk * per_pair) * 4) != hipSuccess) {
-        (void)hipGetLastError();
-        if (dD) (void)hipFree(dD);
+    if (!ctx_alloc(c, dD, (size_t)ent * kSlots * 8) || !ctx_alloc(c, Q, (size_t)(chunk * per_pair) * 4)) {
+        ctx_free(c, dD);
         return fail(c, MICSA_ENOMEM, "correlation buffers");
     }
     int st = zero_slots(c, dD, ent);
@@ -2614,8 +2772,8 @@ static int c4_counts(micsa_ctx* c, const C4Geom& cg, std::vector<int64_t>& D)
         st = check_launch(c, "k_c4_count");
     }
     if (!st) st = read_slots(c, dD, ent, D);
-    (void)hipFree(Q);
-    (void)hipFree(dD);
+    ctx_free(c, Q);
+    ctx_free(c, dD);
     return st;
 }
 
@@ -2725,7 +2883,7 @@ int micsa_read_c4_static(micsa_ctx* ctx, int64_t* G)
                      ctx->stream>>>(ctx->g, cg, (int)sp0, Q, dD);
         if ((st = check_launch(ctx, "k_c4_count"))) return st;
     }
-    k_sum_slots<<<grid_for(ent, 1), kBlock, 0, ctx->stream>>>(dD, ent, sums);
+    k_sum_slots<<<(unsigned)((ent + 3) / 4), 256, 0, ctx->stream>>>(dD, ent, sums);
     if ((st = check_launch(ctx, "k_sum_slots"))) return st;
     HIP_TRY(ctx, hipMemcpyAsync(G, sums, (size_t)ent * 8, hipMemcpyDeviceToHost, ctx->stream));
     HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
@@ -2783,7 +2941,7 @@ int micsa_read_overlap(micsa_ctx* ctx, int32_t a, int32_t b, int64_t* Q)
     const int S = ctx->p.n_samples;
     int st;
     if (ctx->planes_ok) {
-        if ((st = zero_slots(ctx, ctx->red, S)) || (st = enqueue_cells_count<2>(ctx, S, a, b, ctx->red))) return st;
+        if ((st = enqueue_cells_count<2>(ctx, S, a, b, ctx->red))) return st;
     } else if (ctx->bit) {
         if ((st = enqueue_lane_count<2>(ctx, ctx->red, a, b))) return st;
     } else {
@@ -2967,9 +3125,7 @@ int micsa_write_spins(micsa_ctx* ctx, const uint8_t* sigma)
     int st = ctx->bit ? write_words(ctx, ctx->bspin, nullptr, sigma, 1) : write_state(ctx, ctx->spin, sigma, 1, ctx->L);
     if (!st && !ctx->bit) st = enqueue_bonds(ctx);  // the written bytes hold spins only: restore the bond bits
     if (st) return st;
-    std::vector<int64_t> E((size_t)ctx->L);
-    if ((st = micsa_read_energy(ctx, E.data()))) return st;
-    if ((st = set_tally(ctx, E))) return st;
+    if ((st = tally_from_state(ctx))) return st;
     ctx->tally_ok = true;
     return MICSA_OK;
 }
@@ -3375,10 +3531,16 @@ struct micsa_pool {
     // batches: two in flight at most, each with its tables (the host may refill
     // one while the other is read)
     uint8_t* d_tab[2] = {nullptr, nullptr};
-    size_t d_tab_cap[2] = {0, 0};
-    std::vector<uint8_t> h_tab[2];  // host copy of each, kept until its launches have finished
+    uint8_t* h_tab[2] = {nullptr, nullptr};  // pinned host copy of each, kept until its launches have finished
+    size_t tab_cap[2] = {0, 0};
     hipEvent_t bev[2] = {nullptr, nullptr};
     int64_t batches = 0;
+    // Small jobs are set up on a stream of their own and move to the pool's for
+    // their batches; finished ones are read on it, so that neither waits for
+    // the batches in flight.
+    hipStream_t side = nullptr;
+    int side_device = 0;
+    JobStore store;
 };
 
 namespace {
@@ -3394,7 +3556,8 @@ bool slot_free(hipEvent_t e)
     return true;
 }
 
-void free_job_stream(PoolJob& j)
+// (the stream's work has finished)
+void free_job_stream(micsa_pool* pool, PoolJob& j, int device)
 {
     for (auto& e : j.ev)
         if (e) {
@@ -3402,7 +3565,7 @@ void free_job_stream(PoolJob& j)
             e = nullptr;
         }
     if (j.stream) {
-        (void)hipStreamDestroy(j.stream);
+        drop_stream(&pool->store, device, j.stream);
         j.stream = nullptr;
     }
 }
@@ -3437,11 +3600,14 @@ int micsa_pool_destroy(micsa_pool* pool)
     if (!pool) return MICSA_OK;
     (void)hipStreamSynchronize(pool->stream);
     for (auto& j : pool->jobs) {
+        const int device = j.ctx ? j.ctx->device : 0;
         if (j.ctx) micsa_destroy(j.ctx);  // synchronises the job's stream
-        free_job_stream(j);
+        free_job_stream(pool, j, device);
     }
+    if (pool->side) drop_stream(&pool->store, pool->side_device, pool->side);
     for (int b = 0; b < 2; ++b) {
         if (pool->d_tab[b]) (void)hipFree(pool->d_tab[b]);
+        if (pool->h_tab[b]) (void)hipHostFree(pool->h_tab[b]);
         if (pool->bev[b]) (void)hipEventDestroy(pool->bev[b]);
     }
     delete pool;
@@ -3452,6 +3618,7 @@ int micsa_pool_sync(micsa_pool* pool)
 {
     if (!pool) return MICSA_EINVAL;
     if (hipStreamSynchronize(pool->stream) != hipSuccess) return MICSA_EHIP;
+    if (pool->side && hipStreamSynchronize(pool->side) != hipSuccess) return MICSA_EHIP;
     for (auto& j : pool->jobs)
         if (j.stream && hipStreamSynchronize(j.stream) != hipSuccess) return MICSA_EHIP;
     return MICSA_OK;
@@ -3573,26 +3740,26 @@ static int enqueue_batch(micsa_pool* pool, int64_t sweeps)
     // one table: jobs, draws, items
     const size_t o_d = (jobs.size() * sizeof(CellSweep) + 63) / 64 * 64;
     const size_t o_i = o_d + (draws.size() * sizeof(CellDraw) + 63) / 64 * 64;
-    std::vector<uint8_t>& h = pool->h_tab[slot];
-    h.resize(o_i + items.size() * sizeof(CellItem));
-    std::memcpy(h.data(), jobs.data(), jobs.size() * sizeof(CellSweep));
-    if (!draws.empty()) std::memcpy(h.data() + o_d, draws.data(), draws.size() * sizeof(CellDraw));
-    std::memcpy(h.data() + o_i, items.data(), items.size() * sizeof(CellItem));
-    if (h.size() > pool->d_tab_cap[slot]) {
+    const size_t bytes = o_i + items.size() * sizeof(CellItem);
+    if (bytes > pool->tab_cap[slot]) {
         if (pool->d_tab[slot]) (void)hipFree(pool->d_tab[slot]);
-        pool->d_tab[slot] = nullptr;
-        pool->d_tab_cap[slot] = 0;
-        if (hipMalloc(&pool->d_tab[slot], 2 * h.size()) != hipSuccess) {
+        if (pool->h_tab[slot]) (void)hipHostFree(pool->h_tab[slot]);
+        pool->d_tab[slot] = pool->h_tab[slot] = nullptr;
+        pool->tab_cap[slot] = 0;
+        const size_t cap = std::max<size_t>(2 * bytes, (size_t)1 << 20);
+        if (hipMalloc(&pool->d_tab[slot], cap) != hipSuccess || hipHostMalloc(&pool->h_tab[slot], cap) != hipSuccess) {
             (void)hipGetLastError();
             return MICSA_ENOMEM;
         }
-        pool->d_tab_cap[slot] = 2 * h.size();
+        pool->tab_cap[slot] = cap;
     }
+    uint8_t* const h = pool->h_tab[slot];
+    std::memcpy(h, jobs.data(), jobs.size() * sizeof(CellSweep));
+    if (!draws.empty()) std::memcpy(h + o_d, draws.data(), draws.size() * sizeof(CellDraw));
+    std::memcpy(h + o_i, items.data(), items.size() * sizeof(CellItem));
     if (!pool->bev[slot] && hipEventCreateWithFlags(&pool->bev[slot], hipEventDisableTiming) != hipSuccess)
         return MICSA_EHIP;
-    // the table is copied from pageable memory: the copy returns once the
-    // host buffer may be reused, and the stream orders it before the launches
-    if (hipMemcpyAsync(pool->d_tab[slot], h.data(), h.size(), hipMemcpyHostToDevice, pool->stream) != hipSuccess)
+    if (hipMemcpyAsync(pool->d_tab[slot], h, bytes, hipMemcpyHostToDevice, pool->stream) != hipSuccess)
         return MICSA_EHIP;
     const auto* dj = reinterpret_cast<const CellSweep*>(pool->d_tab[slot]);
     const auto* dd = reinterpret_cast<const CellDraw*>(pool->d_tab[slot] + o_d);
@@ -3618,6 +3785,14 @@ static int enqueue_batch(micsa_pool* pool, int64_t sweeps)
     return MICSA_OK;
 }
 
+// What lies idle, and the footprints of the jobs that hold memory, fit the budget.
+static void limit_store(micsa_pool* pool, size_t used)
+{
+    std::lock_guard<std::mutex> hold(pool->store.lock);
+    pool->store.limit = pool->budget > used ? pool->budget - used : 0;
+    pool->store.trim(pool->store.limit);
+}
+
 static int pool_batch(micsa_pool* pool, int64_t sweeps)
 {
     const int st = enqueue_batch(pool, sweeps);
@@ -3637,7 +3812,9 @@ int micsa_pool_step(micsa_pool* pool, int64_t sweeps, int32_t* running, int32_t*
         const bool fin = j.batched ? (j.last_batch < 0 || pool->batches > j.last_batch + 2 ||
                                       slot_free(pool->bev[j.last_batch & 1]))
                                    : (j.chunks == 0 || slot_free(j.ev[(j.chunks - 1) & 1]));
-        if (fin) j.state = MICSA_JOB_DONE;
+        if (!fin) continue;
+        j.state = MICSA_JOB_DONE;
+        if (j.batched) j.ctx->stream = pool->side;  // until it sweeps again (run_stream)
     }
     // 2. admit queued jobs in arrival order while they fit
     int32_t nrun = 0;
@@ -3655,24 +3832,34 @@ int micsa_pool_step(micsa_pool* pool, int64_t sweeps, int32_t* running, int32_t*
         const size_t words = (size_t)shape.L * 2 * (size_t)cell_geom(&shape).plane * 4;
         const size_t taken = (shape.bit ? j.bytes : 2 * sites) + words * (shape.plan.sweeps > 0 ? 6 : 3) + words * 3;
         const size_t room = std::max<size_t>(j.bytes > taken ? j.bytes - taken : 0, (size_t)1 << 20);
-        hipStream_t st_job = pool->stream;
-        if (!batched) {
-            if (hipStreamCreateWithFlags(&j.stream, hipStreamNonBlocking) != hipSuccess ||
-                hipEventCreateWithFlags(&j.ev[0], hipEventDisableTiming) != hipSuccess ||
-                hipEventCreateWithFlags(&j.ev[1], hipEventDisableTiming) != hipSuccess) {
+        const int device = shape.device;
+        if (batched && pool->side && pool->side_device != device) {
+            if (hipStreamSynchronize(pool->side) != hipSuccess) return MICSA_EHIP;
+            for (auto& o : pool->jobs)  // their reads go on where they swept
+                if (o.ctx && o.ctx->stream == pool->side) o.ctx->stream = pool->stream;
+            drop_stream(&pool->store, pool->side_device, pool->side);
+            pool->side = nullptr;
+        }
+        if (batched && !pool->side) {
+            if (take_stream(&pool->store, device, &pool->side) != hipSuccess) {
                 (void)hipGetLastError();
-                free_job_stream(j);
+                pool->side = nullptr;
                 return MICSA_EHIP;
             }
-            st_job = j.stream;
+            pool->side_device = device;
         }
-        int st = create_ctx(&pr, st_job, room, &probe);
-        if (st == MICSA_ENOMEM) {  // the device is fuller than the budget says: retry next step
-            free_job_stream(j);
-            break;
+        if (!batched && (take_stream(&pool->store, device, &j.stream) != hipSuccess ||
+                         hipEventCreateWithFlags(&j.ev[0], hipEventDisableTiming) != hipSuccess ||
+                         hipEventCreateWithFlags(&j.ev[1], hipEventDisableTiming) != hipSuccess)) {
+            (void)hipGetLastError();
+            free_job_stream(pool, j, device);
+            return MICSA_EHIP;
         }
+        limit_store(pool, pool->used + j.bytes);
+        int st = create_ctx(&pr, batched ? pool->side : j.stream, room, &pool->store, &probe);
         if (st) {
-            free_job_stream(j);
+            free_job_stream(pool, j, device);
+            if (st == MICSA_ENOMEM) break;  // the device is fuller than the budget says: retry next step
             return st;
         }
         j.ctx = probe;
@@ -3680,6 +3867,10 @@ int micsa_pool_step(micsa_pool* pool, int64_t sweeps, int32_t* running, int32_t*
         micsa_schedule cs{j.sched.kind, j.sched.period, j.sched.T0, j.sched.T1, j.sched.n_sweeps,
                           j.sched.table.empty() ? nullptr : j.sched.table.data(), (int64_t)j.sched.table.size()};
         if ((st = micsa_set_schedule(j.ctx, &cs))) return st;
+        if (batched) {
+            if (hipStreamSynchronize(pool->side) != hipSuccess) return MICSA_EHIP;
+            j.ctx->stream = j.ctx->sweep_stream = pool->stream;
+        }
         j.state = MICSA_JOB_RUNNING;
         pool->used += j.bytes;
         ++nrun;
@@ -3742,8 +3933,10 @@ int micsa_pool_release(micsa_pool* pool, int64_t job)
         PoolJob& j = pool->jobs[i];
         if (j.id != job) continue;
         if (j.state != MICSA_JOB_DONE) return MICSA_EINVAL;
+        const int device = j.ctx->device;
+        limit_store(pool, pool->used - j.bytes);
         micsa_destroy(j.ctx);  // synchronises the job's stream
-        free_job_stream(j);
+        free_job_stream(pool, j, device);
         pool->used -= j.bytes;
         pool->jobs.erase(pool->jobs.begin() + (long)i);
         return MICSA_OK;

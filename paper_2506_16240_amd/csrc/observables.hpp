@@ -115,15 +115,24 @@ __global__ void __launch_bounds__(256) k_c4_count(Geom g, C4Geom cg, int sp0, co
     block_add(D + ((int64_t)(s * 3 + mu) * (cg.rmax + 1) + r) * kSlots, cnt);
 }
 
-// out[e] = sum of the kSlots accumulator slots of entity e (thread per entity).
+// Slots of n entities summed, a wave per entity.
 __global__ void __launch_bounds__(256) k_sum_slots(const unsigned long long* __restrict__ slots, int64_t n,
                                                    long long* __restrict__ out)
 {
-    const int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+    const int64_t e = blockIdx.x * 4ll + (threadIdx.x >> 6);
     if (e >= n) return;
-    unsigned long long t = 0;
-    for (int k = 0; k < kSlots; ++k) t += slots[e * kSlots + k];
-    out[e] = (long long)t;
+    const long long v = wave_sum64((long long)slots[e * kSlots + (threadIdx.x & 63)]);
+    if ((threadIdx.x & 63) == 0) out[e] = v;
+}
+
+// Energy tally of lattice blockIdx.x from its unsatisfied bonds U (slots):
+// 2 U - 3 N in slot 0.  A wave per lattice.
+__global__ void __launch_bounds__(kSlots) k_tally_from_bonds(const unsigned long long* __restrict__ U, int64_t N,
+                                                             unsigned long long* __restrict__ tally)
+{
+    const int64_t at = (int64_t)blockIdx.x * kSlots + threadIdx.x;
+    const long long u = wave_sum64((long long)U[at]);
+    tally[at] = threadIdx.x == 0 ? (unsigned long long)(2 * u - 3 * N) : 0ull;
 }
 
 // Device-pointer logging: one row of the energy and daemon logs from the

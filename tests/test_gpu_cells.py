@@ -172,3 +172,35 @@ def test_walkers_and_families_on_cells(shape, gamma, algo):
     assert np.array_equal(g.daemons(), o.m) and np.array_equal(g.spins(), o.sigma)
     assert np.array_equal(g.energy_tally(), o.energy())
     g.close()
+
+
+@pytest.mark.parametrize("jobs_at_once", [1.2, 3.5])
+def test_jobs_one_after_another(jobs_at_once):
+    """Jobs of one pool that come and go, in memory that earlier ones held
+    (room for one, or for three of the largest): each equals the lattice run
+    alone, also where it sweeps on under a new schedule after it has finished."""
+    sizes = [(16, 2), (64, 1), (32, 3), (16, 2), (64, 1), (128, 1), (8, 40), (32, 3), (128, 1), (16, 1)]
+    pool = M.Pool(int(M.footprint(128, 128, 128, 1, 1) * jobs_at_once))
+    s1, s2 = M.Schedule(M.SCHED_LINEAR, 3.0, 0.3, 45, 10), M.Schedule(M.SCHED_CONST, 0.8, 0.8, 60, 5)
+    jobs = {pool.submit(L, L, L, 1, R, 50 + i, s1): (L, R, 50 + i) for i, (L, R) in enumerate(sizes)}
+    for _ in range(100_000):
+        if not jobs:
+            break
+        pool.step(20)
+        for j in [j for j in jobs if pool.state(j)[0] == M.JOB_DONE]:
+            L, R, seed = jobs.pop(j)
+            with M.Lattice(L, L, L, 1, R, seed) as alone:
+                alone.set_schedule(s1)
+                alone.sweep(M.ALGO_MICSA, 45)
+                lat = pool.lattice(j)
+                assert np.array_equal(lat.energy_tally(), alone.energy_tally())
+                assert np.array_equal(lat.energy(), alone.energy())
+                if seed % 2:
+                    for c in (alone, lat):
+                        c.set_schedule(s2)
+                        c.sweep(M.ALGO_MICSA, 13)
+                assert np.array_equal(lat.spins(), alone.spins())
+                assert np.array_equal(lat.daemons(), alone.daemons())
+            pool.release(j)
+    assert not jobs
+    pool.close()
