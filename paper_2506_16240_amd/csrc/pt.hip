@@ -28,11 +28,15 @@ struct micsa_pt {
     int32_t kernel = MICSA_PT_KERNEL_AUTO;
     int32_t G = 0;        // temperatures per work-group of the register kernel (0: not eligible)
     uint32_t reg_lds = 0;
+    int32_t Gt = 0;       // the same of the variant with field tables (0: they do not fit)
+    uint32_t tab_lds = 0;
+    uint32_t* ftab = nullptr;    // field tables
     int4* rec = nullptr;         // [N][2] records, x-major
     uint64_t* spins = nullptr;   // [runs][2][M][R0]
     int32_t* perm = nullptr;     // [runs][2][M]
     int64_t* E = nullptr;        // [runs][2][M] by slot
     int64_t* swaps = nullptr;    // [runs][2][M-1]
+    int64_t* out = nullptr;      // [kPtReadWords] results of a read
     uint32_t* wtab = nullptr;    // [M][kPtTable] device form (thresholds - 1, guides)
     uint32_t* ptab = nullptr;    // [M-1][kPtTable]
     std::vector<int32_t> Jq;     // [3][N]
@@ -47,7 +51,9 @@ struct micsa_pt {
 
 namespace {
 
+constexpr uint32_t kPtLds = 160u * 1024u;  // of a compute unit
 constexpr uint32_t kPtLdsMax = 150u * 1024u;
+constexpr int64_t kPtReadWords = 1 << 16;  // buffer of a read's results
 
 int pt_fail(micsa_pt* c, int st, const std::string& m)
 {
@@ -114,7 +120,7 @@ void free_pt(micsa_pt* c)
 {
     if (!c) return;
     for (void* ptr : {(void*)c->rec, (void*)c->spins, (void*)c->perm, (void*)c->E, (void*)c->swaps, (void*)c->wtab,
-                      (void*)c->ptab})
+                      (void*)c->ptab, (void*)c->out, (void*)c->ftab})
         if (ptr) (void)hipFree(ptr);
     for (auto& ev : c->events)
         for (hipEvent_t x : ev) (void)hipEventDestroy(x);
@@ -153,6 +159,65 @@ RegKernel reg_kernel(int Lx, int algo, bool houd)
     case 16: return reg_kernel_lx<16>(algo, houd);
     default: return nullptr;
     }
+}
+
+using TabKernel = void (*)(PtGeom, int, const uint32_t*, uint64_t*, const int32_t*, int64_t*, const uint32_t*,
+                          uint32_t);
+
+// The walkers' variant with field tables, of the same row lengths.
+TabKernel tab_kernel(int Lx, bool houd)
+{
+    switch (Lx) {
+    case 4: return houd ? k_pt_emcs_tab<4, true> : k_pt_emcs_tab<4, false>;
+    case 6: return houd ? k_pt_emcs_tab<6, true> : k_pt_emcs_tab<6, false>;
+    case 8: return houd ? k_pt_emcs_tab<8, true> : k_pt_emcs_tab<8, false>;
+    case 10: return houd ? k_pt_emcs_tab<10, true> : k_pt_emcs_tab<10, false>;
+    case 12: return houd ? k_pt_emcs_tab<12, true> : k_pt_emcs_tab<12, false>;
+    case 16: return houd ? k_pt_emcs_tab<16, true> : k_pt_emcs_tab<16, false>;
+    default: return nullptr;
+    }
+}
+
+// Temperatures per work-group of that variant, at most Gmax: the least time of
+// the rounds that the work-groups take on the device, where one's time goes as
+// what shares its compute unit and as its temperatures, with two more for the
+// staging.  (0: no work-group fits.)
+int tab_temperatures(const PtGeom& g, int Gmax, int cus)
+{
+    int best = 0;
+    double cost = 0;
+    for (int G = 1; G <= Gmax; ++G) {
+        const uint32_t lds = pt_tab_layout(g, G).total;
+        if (lds > kPtLdsMax) break;
+        const int waves = 2 * ((G * g.R0 + 63) / 64);
+        const int per = std::max(1, std::min({(int)(kPtLds / lds), 32 / waves, 16}));
+        const int64_t wgs = (int64_t)g.runs * ((g.M + G - 1) / G), rounds = (wgs + (int64_t)per * cus - 1) / ((int64_t)per * cus);
+        const double c = (double)rounds * (double)std::min<int64_t>(per, (wgs + cus - 1) / cus) * (G + 2);
+        if (!best || c <= cost) best = G, cost = c;
+    }
+    return best;
+}
+
+// Field tables (k_pt_emcs_tab) from the coupling records.
+std::vector<uint32_t> field_tables(const PtGeom& g, const std::vector<int32_t>& rec)
+{
+    const size_t stride = pt_tab_stride(g.Lx);
+    std::vector<uint32_t> T(2 * (size_t)g.R0 * stride, 0u);
+    for (int r = 0; r < g.R0; ++r) {
+        const int y = r % g.Ly, z = r / g.Ly, q = (y + z) & 1, h = z * (g.Ly / 2) + (y >> 1);
+        for (int x = 0; x < g.Lx; ++x) {
+            const int c = (x + q) & 1;
+            const int32_t* J = rec.data() + ((size_t)x * g.R0 + r) * 8;
+            uint32_t* o = T.data() + ((size_t)c * g.R0 + q * (g.R0 / 2) + h) * stride + (size_t)(x >> 1) * 16;
+            for (int side = 0; side < 2; ++side)
+                for (int k = 0; k < 8; ++k) {
+                    int32_t v = 0;
+                    for (int d = 0; d < 3; ++d) v += 2 * J[3 * side + d] * (2 * ((k >> d) & 1) - 1);
+                    o[8 * side + k] = (uint32_t)v;
+                }
+        }
+    }
+    return T;
 }
 
 bool use_reg(const micsa_pt* c)
@@ -278,6 +343,7 @@ int micsa_pt_create(const micsa_pt_params* p, const double* J, const double* T, 
               hipMalloc(&c->spins, nslot * g.R0 * 8) == hipSuccess && hipMalloc(&c->perm, nslot * 4) == hipSuccess &&
               hipMalloc(&c->E, nslot * 8) == hipSuccess &&
               hipMalloc(&c->swaps, (size_t)g.runs * 2 * (M - 1) * 8) == hipSuccess &&
+              hipMalloc(&c->out, (size_t)kPtReadWords * 8) == hipSuccess &&
               hipMalloc(&c->wtab, dw.size() * 4) == hipSuccess && hipMalloc(&c->ptab, std::max<size_t>(dp.size(), 1) * 4) == hipSuccess;
     if (!ok) {
         (void)hipGetLastError();
@@ -323,6 +389,30 @@ int micsa_pt_create(const micsa_pt_params* p, const double* J, const double* T, 
                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)c->reg_lds) != hipSuccess)
                 return fin(MICSA_EHIP);
         }
+        // with field tables (64 bytes per site in LDS, twice the records) where they fit
+        int cus = 0;
+        int device = 0;
+        if (hipGetDevice(&device) != hipSuccess ||
+            hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess)
+            return fin(MICSA_EHIP);
+        const int Gt = walkers ? tab_temperatures(g, G, std::max(cus, 1)) : 0;
+        if (Gt > 0) {
+            const std::vector<uint32_t> T = field_tables(g, rec);
+            const uint32_t lds = pt_tab_layout(g, Gt).total;
+            if (lds > 65536u && hipFuncSetAttribute((const void*)tab_kernel(g.Lx, p->houdayer != 0),
+                                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
+                return fin(MICSA_EHIP);
+            if (hipMalloc(&c->ftab, T.size() * 4) != hipSuccess) {
+                (void)hipGetLastError();
+                c->ftab = nullptr;
+                return fin(MICSA_ENOMEM);
+            }
+            if (hipMemcpyAsync(c->ftab, T.data(), T.size() * 4, hipMemcpyHostToDevice, c->stream) != hipSuccess ||
+                hipStreamSynchronize(c->stream) != hipSuccess)
+                return fin(MICSA_EHIP);
+            c->Gt = Gt;
+            c->tab_lds = lds;
+        }
     }
     *out = c;
     return MICSA_OK;
@@ -345,8 +435,10 @@ int micsa_pt_step(micsa_pt* pt, int64_t n)
     const dim3 grid((unsigned)pt->g.M, (unsigned)pt->g.runs);
     const bool reg = use_reg(pt);
     const RegKernel kr = reg ? reg_kernel(pt->g.Lx, pt->p.algo, pt->p.houdayer != 0) : nullptr;
-    const dim3 rgrid((unsigned)((pt->g.M + pt->G - 1) / std::max(pt->G, 1)), (unsigned)pt->g.runs);
-    const unsigned rblock = reg ? (unsigned)(64 * ((2 * pt->G * pt->g.R0 + 63) / 64)) : 0u;
+    const TabKernel kt = reg && pt->Gt > 0 ? tab_kernel(pt->g.Lx, pt->p.houdayer != 0) : nullptr;
+    const int G = kt ? pt->Gt : std::max(pt->G, 1);
+    const dim3 rgrid((unsigned)((pt->g.M + G - 1) / G), (unsigned)pt->g.runs);
+    const unsigned rblock = (unsigned)(kt ? 128 * ((G * pt->g.R0 + 63) / 64) : 64 * ((2 * G * pt->g.R0 + 63) / 64));
     const unsigned sgrid = (unsigned)((2 * pt->g.runs + 3) / 4);
     for (int64_t i = 0; i < n; ++i) {
         const uint32_t e = (uint32_t)pt->e;
@@ -356,7 +448,9 @@ int micsa_pt_step(micsa_pt* pt, int64_t n)
             pt->events.push_back(ev);  // owned by the context from here on
             PT_TRY(pt, hipEventRecord(ev[0], pt->stream));
         }
-        if (reg)
+        if (kt)
+            kt<<<rgrid, rblock, pt->tab_lds, pt->stream>>>(pt->g, G, pt->ftab, pt->spins, pt->perm, pt->E, pt->wtab, e);
+        else if (reg)
             kr<<<rgrid, rblock, pt->reg_lds, pt->stream>>>(pt->g, pt->G, pt->rec, pt->spins, pt->perm, pt->E,
                                                            pt->wtab, e);
         else
@@ -389,32 +483,23 @@ int micsa_pt_read(micsa_pt* pt, int64_t* E, int64_t* Q)
 {
     if (!pt) return MICSA_EINVAL;
     const PtGeom& g = pt->g;
-    const size_t nslot = (size_t)g.runs * 2 * g.M;
-    std::vector<int32_t> perm(nslot);
-    std::vector<int64_t> Es(nslot);
-    PT_TRY(pt, hipMemcpyAsync(perm.data(), pt->perm, nslot * 4, hipMemcpyDeviceToHost, pt->stream));
-    PT_TRY(pt, hipMemcpyAsync(Es.data(), pt->E, nslot * 8, hipMemcpyDeviceToHost, pt->stream));
-    std::vector<uint64_t> rows;
-    if (Q) {
-        rows.resize(nslot * g.R0);
-        PT_TRY(pt, hipMemcpyAsync(rows.data(), pt->spins, rows.size() * 8, hipMemcpyDeviceToHost, pt->stream));
+    if (!E && !Q) {
+        PT_TRY(pt, hipStreamSynchronize(pt->stream));
+        return MICSA_OK;
     }
-    PT_TRY(pt, hipStreamSynchronize(pt->stream));
-    for (int u = 0; u < g.runs; ++u)
-        for (int t = 0; t < g.M; ++t) {
-            const size_t b0 = ((size_t)u * 2 + 0) * g.M, b1 = ((size_t)u * 2 + 1) * g.M;
-            if (E) {
-                E[b0 + t] = Es[b0 + perm[b0 + t]];
-                E[b1 + t] = Es[b1 + perm[b1 + t]];
-            }
-            if (Q) {  // sum_x s^a s^b = N - 2 (number of differing sites)
-                const uint64_t* ra = rows.data() + (b0 + perm[b0 + t]) * g.R0;
-                const uint64_t* rb = rows.data() + (b1 + perm[b1 + t]) * g.R0;
-                int64_t d = 0;
-                for (int r = 0; r < g.R0; ++r) d += __builtin_popcountll((ra[r] ^ rb[r]) & g.xmask);
-                Q[(size_t)u * g.M + t] = g.N - 2 * d;
-            }
-        }
+    // as many runs at a time as the read buffer holds
+    const int64_t per = (int64_t)3 * g.M, chunk = std::min<int64_t>(kPtReadWords / per, 65535);
+    for (int64_t u = 0; u < g.runs; u += chunk) {
+        const int64_t n = std::min<int64_t>(chunk, g.runs - u);
+        int64_t *dE = E ? pt->out : nullptr, *dQ = Q ? pt->out + (size_t)chunk * 2 * g.M : nullptr;
+        k_pt_read<<<dim3((unsigned)g.M, (unsigned)n), 64, 0, pt->stream>>>(g, (int)u, pt->perm, pt->E, pt->spins, dE,
+                                                                          dQ);
+        PT_TRY(pt, hipGetLastError());
+        if (E)
+            PT_TRY(pt, hipMemcpyAsync(E + u * 2 * g.M, dE, (size_t)n * 2 * g.M * 8, hipMemcpyDeviceToHost, pt->stream));
+        if (Q) PT_TRY(pt, hipMemcpyAsync(Q + u * g.M, dQ, (size_t)n * g.M * 8, hipMemcpyDeviceToHost, pt->stream));
+        PT_TRY(pt, hipStreamSynchronize(pt->stream));
+    }
     return MICSA_OK;
 }
 

@@ -73,27 +73,37 @@ __device__ __forceinline__ uint64_t rot_down(uint64_t m, const PtGeom& g)  // bi
     return ((m >> 1) | (m << (g.Lx - 1))) & g.xmask;
 }
 
-// Digit d of a draw: the number of thresholds <= w, found between the
-// guide's bounds for the bucket of w by bisection.
-__device__ __forceinline__ int32_t digit_draw(const uint32_t* tab, int d, uint32_t w)
-{
-    const uint32_t gb = ((const uint16_t*)(tab + 1024))[d * 256 + (w >> 24)];
-    int32_t lo = (int32_t)(gb & 255u), hi = (int32_t)(gb >> 8);
-    const uint32_t* t = tab + d * 256;
-    while (lo < hi) {
-        const int32_t mid = (lo + hi) >> 1;
-        if (w > t[mid])
-            lo = mid + 1;
-        else
-            hi = mid;
-    }
-    return lo;
-}
-
+// The four digits of a draw: digit d is the number of thresholds below word d.
+// The guide's lower bound and one compare settle nearly every word (the buckets
+// of the low digits hold about one threshold each), so the four go side by
+// side without a branch; what is left lies in a steep digit's last bucket,
+// whose counts fall off geometrically, and goes on in growing steps.  (Digit after
+// digit by bisection, each waiting for its own LDS reads, the draws of 16 M
+// walkers took 67 us.)  Entry 255 of a digit is the largest word.
 __device__ __forceinline__ int32_t exp_draw4(const uint32_t* tab, const u32x4& w)
 {
-    return digit_draw(tab, 0, w.v0) + (digit_draw(tab, 1, w.v1) << 8) + (digit_draw(tab, 2, w.v2) << 16) +
-           (digit_draw(tab, 3, w.v3) << 24);
+    const uint32_t ws[4] = {w.v0, w.v1, w.v2, w.v3};
+    uint32_t gb[4], t[4];
+    int32_t n[4];
+#pragma unroll
+    for (int d = 0; d < 4; ++d) gb[d] = ((const uint16_t*)(tab + 1024))[d * 256 + (ws[d] >> 24)];
+#pragma unroll
+    for (int d = 0; d < 4; ++d) t[d] = tab[d * 256 + (gb[d] & 255u)];
+#pragma unroll
+    for (int d = 0; d < 4; ++d) n[d] = (int32_t)(gb[d] & 255u) + (ws[d] > t[d] ? 1 : 0);
+#pragma unroll
+    for (int d = 0; d < 4; ++d) {
+        int32_t hi = (int32_t)(gb[d] >> 8), step = 1;
+        if (ws[d] > t[d])
+            while (n[d] < hi) {
+                const int32_t m = min(n[d] + step, hi) - 1;
+                const bool above = ws[d] > tab[d * 256 + m];
+                n[d] = above ? m + 1 : n[d];
+                hi = above ? hi : m;
+                step = above ? 2 * step : 1;
+            }
+    }
+    return n[0] + (n[1] << 8) + (n[2] << 16) + (n[3] << 24);
 }
 
 // n >= k for the mesh exponential n drawn from words w.  Digit d of n
@@ -373,10 +383,15 @@ __global__ __launch_bounds__(kPtBlock) void k_pt_emcs(PtGeom g, const int4* __re
 // test uses a constant offset.  Forward-X wandering pairs site j of the
 // moving class with site j (or j + 1 when the class starts at x = 1) of the
 // other class, all within the row.
-// LDS: tables [G][1024] u64 | records [N][2] int4 | rows [G][2][R0] u32 |
-//      mark, diff [G][R0] u32 | energies [G][2] u64 | flag.
+// It runs the Metropolis sweeps, and the walkers of lattices whose field tables
+// (k_pt_emcs_tab) exceed LDS.  Metropolis stays within 64 registers, so that
+// two work-groups share a compute unit (10^3 with Houdayer moves: 605 us per
+// EMCS, 790 with one).
+// LDS: tables [G][kPtTable] u32 | records [N][2] int4 | rows [G][2][R0] u32 |
+//      mark, diff [G][R0] u32 | energies [G][2] u64; the Houdayer move
+//      keeps the neighbour rows [R0] 4 x u16 over the tables.
 struct PtRegLds {
-    uint32_t tab, rec, rows, mark, diff, esum, flag, total;
+    uint32_t tab, rec, rows, mark, diff, esum, total;
 };
 
 __host__ __device__ inline PtRegLds pt_reg_layout(const PtGeom& g, int G)
@@ -396,8 +411,6 @@ __host__ __device__ inline PtRegLds pt_reg_layout(const PtGeom& g, int G)
     o = (o + 7u) & ~7u;
     l.esum = o;
     o += (uint32_t)G * 16u;
-    l.flag = o;
-    o += 16u;
     l.total = o;
     return l;
 }
@@ -413,6 +426,99 @@ __device__ __forceinline__ uint32_t rot_up32(uint32_t m)  // bit x <- bit x - 1
 {
     constexpr uint32_t MASK = LX == 32 ? 0xFFFFFFFFu : ((1u << LX) - 1u);
     return ((m << 1) | (m >> (LX - 1))) & MASK;
+}
+
+// The cyclic runs of the row d that hold a bit of m (m within d): the carry of
+// d + m runs through a run's bits above its lowest mark, and those of the
+// reversed words through the bits below; two copies of the row side by side
+// make the runs that cross its end whole.
+template <int LX>
+__device__ __forceinline__ uint32_t row_fill(uint32_t d, uint32_t m)
+{
+    static_assert(2 * LX <= 32, "two copies of a row in a word");
+    constexpr uint32_t MASK = (1u << LX) - 1u;
+    const uint32_t dd = d | (d << LX), mm = m | (m << LX);
+    const uint32_t up = dd & (~(dd + mm) | mm);
+    const uint32_t rd = __brev(dd), rm = __brev(mm);
+    const uint32_t f = up | __brev(rd & (~(rd + rm) | rm));
+    return (f | (f >> LX)) & MASK;
+}
+
+// A row's marks grown by its neighbours' and closed along the row.
+template <int LX>
+__device__ __forceinline__ bool grow_row(uint32_t* mq, int r, uint32_t d, ushort4 n)
+{
+    const uint32_t m = mq[r];
+    const uint32_t m2 = row_fill<LX>(d, d & (m | mq[n.x] | mq[n.y] | mq[n.z] | mq[n.w]));
+    if (m2 == m) return false;
+    mq[r] = m2;
+    return true;
+}
+
+// Houdayer's move of temperatures t0 .. t0 + G of a run: a site drawn among
+// those where the replicas differ (diff: a word per row), and its connected
+// component in mark (zero on entry).  One wave per temperature: prefix over
+// the rows in site order, then growth with no barrier (the wave alone writes
+// the temperature's marks, and a wave's LDS accesses are in order).  All waves
+// growing together, with three barriers a round and the rows closed bit by
+// bit, took 100 of an EMCS's 363 us at 10^3.  nbr: rows along +y, -y, +z, -z.
+template <int LX>
+__device__ __forceinline__ void houdayer_grow(const PtGeom& g, int G, int t0, uint32_t run, uint32_t e,
+                                              const uint32_t* diff, uint32_t* mark, const ushort4* nbr)
+{
+    const int R0 = g.R0, wave = threadIdx.x >> 6, lane = threadIdx.x & 63, nwave = blockDim.x >> 6;
+    const int chunk = (R0 + 63) / 64;
+    for (int q = wave; q < G; q += nwave) {
+        if (t0 + q >= g.M) continue;
+        const uint32_t* dq = diff + q * R0;
+        uint32_t* mq = mark + q * R0;
+        int32_t mine = 0;
+        for (int rr = lane * chunk; rr < min(R0, (lane + 1) * chunk); ++rr) mine += __popc(dq[rr]);
+        int32_t incl = mine;
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            const int32_t v = __shfl_up(incl, off, 64);
+            if (lane >= off) incl += v;
+        }
+        const int32_t count = __shfl(incl, 63, 64);
+        if (count == 0) continue;
+        const uint32_t u = philox10((uint32_t)(t0 + q), e, 0u, stream_word(kStreamPtHoudayer, run), g.key0, g.key1).v0;
+        const int32_t k = (int32_t)(((uint64_t)u * (uint64_t)count) >> 32);
+        const int32_t before = incl - mine;
+        if (k >= before && k < incl) {
+            int32_t left = k - before;
+            for (int rr = lane * chunk; rr < min(R0, (lane + 1) * chunk); ++rr) {
+                uint32_t d = dq[rr];
+                const int32_t c = __popc(d);
+                if (left < c) {
+                    for (; left > 0; --left) d &= d - 1;
+                    mq[rr] = d & (~d + 1u);
+                    break;
+                }
+                left -= c;
+            }
+        }
+        // up to four rows per lane held, so that their reads overlap
+        ushort4 n[4];
+        uint32_t d[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int rr = min(lane + 64 * i, R0 - 1);
+            n[i] = nbr[rr];
+            d[i] = dq[rr];
+        }
+        bool grown;
+        do {
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            grown = false;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int rr = lane + 64 * i;
+                if (rr < R0) grown |= grow_row<LX>(mq, rr, d[i], n[i]);
+            }
+            for (int rr = lane + 256; rr < R0; rr += 64) grown |= grow_row<LX>(mq, rr, dq[rr], nbr[rr]);
+        } while (__any(grown));
+    }
 }
 
 __device__ __forceinline__ int32_t sbit(uint32_t w, int pos)  // 0 or -1
@@ -482,7 +588,7 @@ __device__ __forceinline__ void reg_wander(int32_t (&A)[K], int32_t (&B)[K], int
 // Grid (ceil(M / G), runs); block 64 * ceil(2 G R0 / 64) <= 1024 threads;
 // dynamic LDS pt_reg_layout(g, G).
 template <int LX, int ALGO, bool HOUD>
-__global__ __launch_bounds__(1024) void k_pt_emcs_reg(PtGeom g, int G, const int4* __restrict__ grec,
+__global__ __launch_bounds__(1024, ALGO == 1 ? 8 : 4) void k_pt_emcs_reg(PtGeom g, int G, const int4* __restrict__ grec,
                                                       uint64_t* __restrict__ spins, const int32_t* __restrict__ perm,
                                                       int64_t* __restrict__ E, const uint32_t* __restrict__ wtab,
                                                       uint32_t e)
@@ -497,7 +603,7 @@ __global__ __launch_bounds__(1024) void k_pt_emcs_reg(PtGeom g, int G, const int
     uint32_t* mark = (uint32_t*)(lds + L.mark);
     uint32_t* diff = (uint32_t*)(lds + L.diff);
     unsigned long long* esum = (unsigned long long*)(lds + L.esum);
-    int32_t* flag = (int32_t*)(lds + L.flag);
+    ushort4* nbr = (ushort4*)(lds + L.tab);
 
     const int R0 = g.R0, tid = threadIdx.x, nthr = blockDim.x;
     const int tl = tid / (2 * R0), rem = tid - tl * 2 * R0;
@@ -521,9 +627,9 @@ __global__ __launch_bounds__(1024) void k_pt_emcs_reg(PtGeom g, int G, const int
         rows[base + r] = (uint32_t)*grow;
     }
     if (tid < 2 * G) esum[tid] = 0ull;
+    const PtRowNb nb = pt_row_nb(g, live ? r : 0);
     __syncthreads();
 
-    const PtRowNb nb = pt_row_nb(g, live ? r : 0);
     const uint32_t* tab = tabs + (live ? tl : 0) * kPtTable;
     int32_t wk0[K], wk1[K];
 #pragma unroll
@@ -556,72 +662,15 @@ __global__ __launch_bounds__(1024) void k_pt_emcs_reg(PtGeom g, int G, const int
     }
 
     if (HOUD) {
-        // one wave per temperature: differing sites per row, prefix in site order, chosen site
-        const int wave = tid >> 6, lane = tid & 63, nwave = nthr >> 6;
-        const int chunk = (R0 + 63) / 64;
-        for (int q = wave; q < G; q += nwave) {
-            if (t0 + q >= g.M) continue;
-            const uint32_t* ra = rows + (q * 2 + 0) * R0;
-            const uint32_t* rb = rows + (q * 2 + 1) * R0;
-            int32_t mine = 0;
-            for (int rr = lane * chunk; rr < min(R0, (lane + 1) * chunk); ++rr) {
-                const uint32_t d = (ra[rr] ^ rb[rr]) & MASK;
-                diff[q * R0 + rr] = d;
-                mark[q * R0 + rr] = 0u;
-                mine += __popc(d);
-            }
-            int32_t incl = mine;
-#pragma unroll
-            for (int off = 1; off < 64; off <<= 1) {
-                const int32_t v = __shfl_up(incl, off, 64);
-                if (lane >= off) incl += v;
-            }
-            const int32_t count = __shfl(incl, 63, 64);
-            if (count > 0) {
-                const uint32_t u = philox10((uint32_t)(t0 + q), e, 0u, stream_word(kStreamPtHoudayer, sw), g.key0,
-                                            g.key1).v0;
-                const int32_t k = (int32_t)(((uint64_t)u * (uint64_t)count) >> 32);
-                const int32_t before = incl - mine;
-                if (k >= before && k < incl) {
-                    int32_t left = k - before;
-                    for (int rr = lane * chunk; rr < min(R0, (lane + 1) * chunk); ++rr) {
-                        uint32_t d = diff[q * R0 + rr];
-                        const int32_t c = __popc(d);
-                        if (left < c) {
-                            for (; left > 0; --left) d &= d - 1;
-                            mark[q * R0 + rr] = d & (~d + 1u);
-                            break;
-                        }
-                        left -= c;
-                    }
-                }
-            }
+        // (the tables are no longer read; the first R0 threads own the rows of a temperature)
+        if (tid < R0) nbr[tid] = make_ushort4((uint16_t)nb.yp, (uint16_t)nb.ym, (uint16_t)nb.zp, (uint16_t)nb.zm);
+        if (live && rep == 0) {
+            diff[tl * R0 + r] = (rows[base + r] ^ rows[base + R0 + r]) & MASK;
+            mark[tl * R0 + r] = 0u;
         }
-        // grow every temperature's cluster together until none changes
-        const int q = tid / R0, rr = tid - q * R0;
-        const bool grower = q < G && t0 + q < g.M;
-        const PtRowNb gb = pt_row_nb(g, grower ? rr : 0);
-        for (;;) {
-            __syncthreads();
-            if (tid == 0) flag[0] = 0;
-            __syncthreads();
-            if (grower) {
-                const uint32_t* mq = mark + q * R0;
-                const uint32_t d = diff[q * R0 + rr], m = mq[rr];
-                uint32_t m2 = d & (m | mq[gb.yp] | mq[gb.ym] | mq[gb.zp] | mq[gb.zm]);
-                for (;;) {
-                    const uint32_t m3 = d & (m2 | rot_up32<LX>(m2) | rot_down32<LX>(m2));
-                    if (m3 == m2) break;
-                    m2 = m3;
-                }
-                if (m2 != m) {
-                    mark[q * R0 + rr] = m2;
-                    flag[0] = 1;
-                }
-            }
-            __syncthreads();
-            if (flag[0] == 0) break;
-        }
+        __syncthreads();
+        houdayer_grow<LX>(g, G, t0, sw, e, diff, mark, nbr);
+        __syncthreads();
         if (live) rows[base + r] ^= mark[tl * R0 + r];
         __syncthreads();
     }
@@ -640,6 +689,271 @@ __global__ __launch_bounds__(1024) void k_pt_emcs_reg(PtGeom g, int G, const int
     }
     __syncthreads();
     if (live && r == 0) E[((int64_t)run * 2 + rep) * g.M + slot] = (int64_t)esum[tl * 2 + rep];
+}
+
+// ---------------------------------------------------------------------------
+// Table variant for rows of LX <= 16 sites: the field of a site from two reads.
+// A work-group holds G temperatures (both replicas each), a thread one row of
+// one replica, as two words: class c holds the row's sites x = 2j + ((c + q)
+// & 1), q = (y + z) & 1 (parity c), site j at bit 4j.  Then the neighbours of a
+// class are the other class's words, along y and z at the same j, along x at j
+// and j + 1 or j - 1, and three of them combine into an index per nibble:
+//   T[c][q * H + h][(2 j + side) * 8 + k] = 2 sum J_d (2 k_d - 1), d = x, y, z
+// forward (side 0) or backward (1), k_d = 1 where the bond's spins differ, so
+// that n - 2 s h = n + T + T', and a lattice's energy is half the sum of the
+// forward entries.  Rows of T are an odd number of words apart, so that lanes
+// of consecutive rows start in different banks.
+// A walker moves right (RM) or left (LM) by one site each sweep, so half sweep
+// 0 takes RM and LM in turn, and the arrays turn by one index every second
+// sweep: after even sweeps in rows of q = 1, after odd ones in those of q = 0.
+// Threads are ordered by q, so that a wave has one: no lane selects.
+// Bound: VALU issue and LDS reads about alike: per site 12 instructions and 2
+// reads, where one field from six masked couplings took 35 and two 16-byte
+// reads.  200 runs of 40 temperatures of 10^3, 10 sweeps and a Houdayer move:
+// 235 us per EMCS (k_pt_emcs_reg 368): 8.5 a sweep (17), 42 the Houdayer move
+// (81 to 106), the rest draws, staging and energies.
+// The draws' tables and T share LDS, so that two work-groups of 10^3 fit a
+// compute unit and one's Houdayer move and draws run under the other's sweeps.
+// (Metropolis sweeps need both at once and are bound by their Philox calls: at
+// 10^3 they took 695 us here, 562 on the records, k_pt_emcs_reg.)
+struct PtTabLds {
+    uint32_t tab, T, W, mark, diff, nbr, esum, total;
+};
+
+// Words per row of T.
+__host__ __device__ constexpr uint32_t pt_tab_stride(int Lx) { return 8u * (uint32_t)Lx + 1u; }
+
+__host__ __device__ inline PtTabLds pt_tab_layout(const PtGeom& g, int G)
+{
+    PtTabLds l;
+    const uint32_t tab = (uint32_t)G * kPtTable * 4u, T = 2u * (uint32_t)g.R0 * pt_tab_stride(g.Lx) * 4u;
+    l.tab = l.T = 0;
+    uint32_t o = tab > T ? tab : T;
+    l.W = o;
+    o += (uint32_t)G * 4u * g.R0 * 4u;
+    l.mark = o;
+    o += (uint32_t)G * g.R0 * 4u;
+    l.diff = o;
+    o += (uint32_t)G * g.R0 * 4u;
+    l.nbr = o;
+    o += (uint32_t)g.R0 * 8u;
+    l.esum = o;
+    o += (uint32_t)G * 16u;
+    l.total = o;
+    return l;
+}
+
+__device__ __forceinline__ uint32_t spread4(uint32_t v)  // bit 2j -> bit 4j, j < 8
+{
+    v &= 0x5555u;
+    v = (v | (v << 8)) & 0x00550055u;
+    v = (v | (v << 4)) & 0x05050505u;
+    return (v | (v << 2)) & 0x11111111u;
+}
+__device__ __forceinline__ uint32_t gather2(uint32_t v)  // bit 4j -> bit 2j
+{
+    v = (v | (v >> 2)) & 0x05050505u;
+    v = (v | (v >> 4)) & 0x00550055u;
+    return (v | (v >> 8)) & 0x5555u;
+}
+template <int K>
+__device__ __forceinline__ uint32_t nib_next(uint32_t w)  // site j <- site j + 1
+{
+    return (w >> 4) | ((w & 0xFu) << (4 * K - 4));
+}
+template <int K>
+__device__ __forceinline__ uint32_t nib_prev(uint32_t w)  // site j <- site j - 1
+{
+    constexpr uint32_t MASK = K == 8 ? 0xFFFFFFFFu : (1u << (4 * K)) - 1u;
+    return ((w << 4) & MASK) | (w >> (4 * K - 4));
+}
+
+// Indices into T of a row's sites of one class: own word, the other class's
+// word of the row, and the neighbour rows' words along +y, +z or -y, -z.
+template <int K>
+__device__ __forceinline__ uint32_t tab_index(uint32_t own, uint32_t x, uint32_t y, uint32_t z)
+{
+    return (x | (y << 1) | (z << 2)) ^ (own | (own << 1) | (own << 2));
+}
+
+struct PtTabRow {
+    unsigned char* lds;
+    // byte offsets of class 0 in it: the row's entries of T, its word, and its
+    // neighbours' words; and from class 0 to class 1 of T and of W
+    uint32_t T, W, yp, ym, zp, zm, cT, cW;
+    int q;
+
+    __device__ __forceinline__ uint32_t& at(uint32_t o) const { return *(uint32_t*)(lds + o); }
+    // entry idx_j of site j, the nibbles of idx holding one each
+    __device__ __forceinline__ int32_t entry(uint32_t row, uint32_t idx, int j, int side) const
+    {
+        return (int32_t)at(row + (__builtin_amdgcn_ubfe(idx, 4 * j, 3) << 2) + 64 * j + 32 * side);
+    }
+};
+
+template <int LX, int P>
+__device__ __forceinline__ void tab_half(const PtTabRow& a, uint32_t& own, uint32_t other, int32_t (&wk)[LX / 2])
+{
+    constexpr int K = LX / 2;
+    const uint32_t o = P ? 0 : a.cW;  // the other class
+    const uint32_t yp = a.at(a.yp + o), ym = a.at(a.ym + o), zp = a.at(a.zp + o), zm = a.at(a.zm + o);
+    const bool odd = P ? !a.q : a.q;  // the class starts at x = 1
+    const uint32_t xp = odd ? nib_next<K>(other) : other, xm = odd ? other : nib_prev<K>(other);
+    const uint32_t F = tab_index<K>(own, xp, yp, zp), B = tab_index<K>(own, xm, ym, zm);
+    const uint32_t T = a.T + (P ? a.cT : 0);
+    constexpr uint32_t ONES = K == 8 ? 0x11111111u : 0x11111111u & ((1u << (4 * K)) - 1u);
+    uint32_t refused = 0;  // bit 4j + 3
+    int32_t v[K];
+#pragma unroll
+    for (int j = 0; j < K; ++j) v[j] = a.entry(T, F, j, 0) + a.entry(T, B, j, 1);
+#pragma unroll
+    for (int j = K - 1; j >= 0; --j) {
+        const int32_t nn = wk[j] + v[j];
+        wk[j] = nn >= 0 ? nn : wk[j];
+        refused = __builtin_amdgcn_alignbit(refused, (uint32_t)nn, 28);
+    }
+    own ^= ~(refused >> 3) & ONES;
+    a.at(a.W + (P ? a.cW : 0)) = own;
+}
+
+// Grid (ceil(M / G), runs); block 128 * ceil(G R0 / 64) <= 1024 threads (whole
+// waves of each row parity); dynamic LDS pt_tab_layout(g, G).
+template <int LX, bool HOUD>
+__global__ __launch_bounds__(1024, LX <= 10 ? 8 : 4) void k_pt_emcs_tab(
+    PtGeom g, int G, const uint32_t* __restrict__ gT, uint64_t* __restrict__ spins, const int32_t* __restrict__ perm,
+    int64_t* __restrict__ E, const uint32_t* __restrict__ wtab, uint32_t e)
+{
+    constexpr int K = LX / 2;
+    extern __shared__ __align__(16) unsigned char lds[];
+    const PtTabLds L = pt_tab_layout(g, G);
+    uint32_t* tabs = (uint32_t*)(lds + L.tab);
+    uint4* T = (uint4*)(lds + L.T);
+    uint32_t* mark = (uint32_t*)(lds + L.mark);
+    uint32_t* diff = (uint32_t*)(lds + L.diff);
+    unsigned long long* esum = (unsigned long long*)(lds + L.esum);
+    ushort4* nbr = (ushort4*)(lds + L.nbr);
+
+    const int R0 = g.R0, H = R0 / 2, Y = g.Ly / 2, tid = threadIdx.x, nthr = blockDim.x;
+    const int q = __builtin_amdgcn_readfirstlane(tid >= nthr / 2);
+    const int k = tid - q * (nthr / 2);  // (temperature, replica, row of parity q)
+    const int tl = k / R0, rep = (k - tl * R0) / H, h = k - (2 * tl + rep) * H;
+    const int t0 = blockIdx.x * G, t = t0 + tl, run = blockIdx.y;
+    const bool live = tl < G && t < g.M;
+    const int z = h / Y, y = 2 * (h - z * Y) + ((q + z) & 1), r = y + g.Ly * z;
+    const int yp = y + 1 == g.Ly ? 0 : y + 1, ym = y == 0 ? g.Ly - 1 : y - 1;
+    const int zp = z + 1 == g.Lz ? 0 : z + 1, zm = z == 0 ? g.Lz - 1 : z - 1;
+
+    // the draws' tables, and T behind them; the rest of T after the draws
+    const int nt = min(G, g.M - t0) * kPtTable / 4, nG = G * kPtTable / 4;  // 16-byte words
+    const int nT = 2 * R0 * (int)pt_tab_stride(LX) / 4;                     // (R0 is a multiple of 4)
+    for (int i = tid; i < nt; i += nthr) T[i] = ((const uint4*)wtab)[(int64_t)t0 * (kPtTable / 4) + i];
+    for (int i = nG + tid; i < nT; i += nthr) T[i] = ((const uint4*)gT)[i];
+    if (tid < 2 * G) esum[tid] = 0ull;
+    int32_t slot = 0;
+    uint64_t* grow = nullptr;
+    uint32_t c0 = 0, c1 = 0;
+    PtTabRow a;
+    a.lds = lds;
+    a.cT = 4u * R0 * pt_tab_stride(LX);
+    a.cW = 4u * R0;
+    a.T = L.T + (live ? 4u * (q * H + h) * pt_tab_stride(LX) : 0u);
+    // words [G][2][class][q][H]
+    const uint32_t Wl = L.W + (live ? 8u * (2 * tl + rep) * R0 : 0u), Wo = Wl + 4u * (1 - q) * H;
+    a.W = Wl + (live ? 4u * (q * H + h) : 0u);
+    a.yp = Wo + (live ? 4u * (z * Y + (yp >> 1)) : 0u);
+    a.ym = Wo + (live ? 4u * (z * Y + (ym >> 1)) : 0u);
+    a.zp = Wo + (live ? 4u * (zp * Y + (y >> 1)) : 0u);
+    a.zm = Wo + (live ? 4u * (zm * Y + (y >> 1)) : 0u);
+    a.q = q;
+    if (live) {
+        slot = perm[((int64_t)run * 2 + rep) * g.M + t];
+        grow = spins + (((int64_t)run * 2 + rep) * g.M + slot) * R0 + r;
+        const uint32_t row = (uint32_t)*grow;
+        c0 = spread4(row >> q);
+        c1 = spread4(row >> (1 - q));
+        a.at(a.W) = c0;
+        a.at(a.W + a.cW) = c1;
+        if (HOUD && k < H)  // the first replica's rows of the first temperature
+            nbr[r] = make_ushort4((uint16_t)(yp + g.Ly * z), (uint16_t)(ym + g.Ly * z), (uint16_t)(y + g.Ly * zp),
+                                  (uint16_t)(y + g.Ly * zm));
+    }
+    __syncthreads();
+
+    const uint32_t* tab = tabs + (live ? tl : 0) * kPtTable;
+    int32_t rm[K], lm[K];
+#pragma unroll
+    for (int j = 0; j < K; ++j) rm[j] = lm[j] = 0;
+    if (live) {
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+#pragma unroll
+            for (int j = 0; j < K; ++j) {
+                const uint32_t i = (uint32_t)(2 * j + (c ^ q) + LX * r);
+                const u32x4 w = philox10(i, e, (uint32_t)(2 * t + rep), stream_word(kStreamPtWalker, (uint32_t)run),
+                                         g.key0, g.key1);
+                (c == 0 ? rm : lm)[j] = exp_draw4(tab, w);
+            }
+        }
+    }
+    __syncthreads();
+    for (int i = tid; i < min(nG, nT); i += nthr) T[i] = ((const uint4*)gT)[i];
+    __syncthreads();
+
+    const auto turn = [&] {  // RM to the next index, LM to the one before
+        const int32_t last = rm[K - 1], first = lm[0];
+#pragma unroll
+        for (int j = K - 1; j > 0; --j) rm[j] = rm[j - 1];
+        rm[0] = last;
+#pragma unroll
+        for (int j = 0; j + 1 < K; ++j) lm[j] = lm[j + 1];
+        lm[K - 1] = first;
+    };
+    for (int s = 0; s < g.S; s += 2) {
+        if (live) tab_half<LX, 0>(a, c0, c1, rm);
+        __syncthreads();
+        if (live) tab_half<LX, 1>(a, c1, c0, lm);
+        __syncthreads();
+        if (s + 1 == g.S) break;
+        if (q == 1) turn();
+        if (live) tab_half<LX, 0>(a, c0, c1, lm);
+        __syncthreads();
+        if (live) tab_half<LX, 1>(a, c1, c0, rm);
+        __syncthreads();
+        if (q == 0) turn();
+    }
+
+    if (HOUD) {
+        if (live && rep == 0) {
+            const uint32_t d0 = c0 ^ a.at(a.W + 2 * a.cW), d1 = c1 ^ a.at(a.W + 3 * a.cW);  // the other replica's row
+            diff[tl * R0 + r] = (gather2(d0) << q) | (gather2(d1) << (1 - q));
+            mark[tl * R0 + r] = 0u;
+        }
+        __syncthreads();
+        houdayer_grow<LX>(g, G, t0, (uint32_t)run, e, diff, mark, nbr);
+        __syncthreads();
+        if (live) {
+            const uint32_t m = mark[tl * R0 + r];
+            c0 ^= spread4(m >> q);
+            c1 ^= spread4(m >> (1 - q));
+            a.at(a.W) = c0;
+            a.at(a.W + a.cW) = c1;
+        }
+        __syncthreads();
+    }
+
+    if (live) {
+        const uint32_t x0 = q ? nib_next<K>(c1) : c1, x1 = q ? c0 : nib_next<K>(c0);  // sites one to the right
+        const uint32_t F0 = tab_index<K>(c0, x0, a.at(a.yp + a.cW), a.at(a.zp + a.cW));
+        const uint32_t F1 = tab_index<K>(c1, x1, a.at(a.yp), a.at(a.zp));
+        int32_t en = 0;
+#pragma unroll
+        for (int j = 0; j < K; ++j)
+            en += a.entry(a.T, F0, j, 0) + a.entry(a.T + a.cT, F1, j, 0);
+        atomicAdd(&esum[tl * 2 + rep], (unsigned long long)(int64_t)(en / 2));
+        *grow = (gather2(c0) << q) | (gather2(c1) << (1 - q));
+    }
+    __syncthreads();
+    if (live && q == 0 && h == 0) E[((int64_t)run * 2 + rep) * g.M + slot] = (int64_t)esum[tl * 2 + rep];
 }
 
 // Tempering step: one wave per replica group (run, replica); lane t decides
@@ -702,6 +1016,32 @@ __global__ __launch_bounds__(256) void k_pt_init_spins(PtGeom g, uint64_t* __res
         row |= (uint64_t)(ws[i & 3] >> 31) << x;
     }
     spins[k] = row;
+}
+
+// Reads of runs u0 .. u0 + gridDim.y, a wave per (temperature, run):
+// E [run][replica][temperature] through the permutation, and the overlap of
+// the two replicas, sum_x s^a s^b = N - 2 (number of differing sites).  The
+// rows themselves stay: copying 12.8 MB of them to the host took 2.2 of the
+// 3.8 ms of four EMCS and a read at 200 runs of 40 temperatures of 10^3.
+__global__ __launch_bounds__(64) void k_pt_read(PtGeom g, int u0, const int32_t* __restrict__ perm,
+                                                const int64_t* __restrict__ E, const uint64_t* __restrict__ spins,
+                                                int64_t* __restrict__ outE, int64_t* __restrict__ outQ)
+{
+    const int t = blockIdx.x, lane = threadIdx.x;
+    const int64_t b0 = (int64_t)(u0 + blockIdx.y) * 2 * g.M, b1 = b0 + g.M;
+    const int64_t s0 = b0 + perm[b0 + t], s1 = b1 + perm[b1 + t];
+    int32_t d = 0;
+    if (outQ)
+        for (int r = lane; r < g.R0; r += 64) d += __popcll((spins[s0 * g.R0 + r] ^ spins[s1 * g.R0 + r]) & g.xmask);
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) d += __shfl_xor(d, off, 64);
+    if (lane == 0) {
+        if (outE) {
+            outE[(int64_t)blockIdx.y * 2 * g.M + t] = E[s0];
+            outE[((int64_t)blockIdx.y * 2 + 1) * g.M + t] = E[s1];
+        }
+        if (outQ) outQ[(int64_t)blockIdx.y * g.M + t] = g.N - 2 * (int64_t)d;
+    }
 }
 
 // Energies of every slot from scratch: grid (M, runs * 2), one block per slot.
