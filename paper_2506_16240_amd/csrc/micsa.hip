@@ -7,6 +7,8 @@
 #include <hip/hip_runtime.h>
 #include <hip/hip_ext.h>
 
+#include <atomic>
+#include <chrono>
 #include <cmath>
 #include <cstdio>
 #include <cstring>
@@ -72,6 +74,7 @@ struct JobStore {
     std::mutex lock;
     std::vector<Block> idle;  // oldest first
     std::vector<std::pair<int, hipStream_t>> streams;
+    std::vector<void*> pins;  // pinned host buffers of kPinBytes
     size_t held = 0, limit = 0;  // bytes of idle, and their bound
 
     static constexpr size_t kStreams = 32;  // idle streams kept at most
@@ -89,6 +92,7 @@ struct JobStore {
     {
         trim(0);
         for (auto& s : streams) (void)hipStreamDestroy(s.second);
+        for (void* p : pins) (void)hipHostFree(p);
     }
 };
 
@@ -183,7 +187,11 @@ struct micsa_ctx {
     const void* gkey[kAlgos] = {};  // state buffer the graph was captured with
     unsigned long long* tally = nullptr;  // [L][kSlots]
     unsigned long long* red = nullptr;    // [max(L, S)][kSlots] reduction scratch
-    long long* sums = nullptr;            // [max(L, S)] slots summed for a read
+    // pinned host memory that kernels write the results of small reads to
+    // (allocated by the first read), and the last ticket given (fetch)
+    uint8_t* pin = nullptr;
+    bool pin_failed = false;
+    uint32_t ticket = 0;
     // device-pointer logging: one row of slots [2][L][kSlots] (energy, then
     // level sums), and the resident kernel's (U, sum m) pairs, grown on demand
     unsigned long long* logslots = nullptr;
@@ -465,23 +473,88 @@ int zero_slots(micsa_ctx* c, unsigned long long* p, int64_t n)
     return check_launch(c, "k_fill_i64");
 }
 
-// Copy the slots of n entities to the host and sum them per entity (on the
-// device first where they are many: 512 lattices' slots are 256 KiB, copied
-// through pageable memory).
+// A small read: its last kernel writes the result to pinned host memory, and a
+// single work-group also the ticket that the host waits for (at most 1 ms, then
+// it waits for the stream, which also reports errors).  A copy to pageable
+// memory and a stream synchronisation took 23 us for 512 bytes, a kernel that
+// writes pinned memory and a synchronisation 11.7, the ticket 6.4; at 256 KiB
+// 33 and 22, above that the copy is faster.
+constexpr size_t kPinBytes = (size_t)256 << 10, kPinHead = 64, kTicketBytes = (size_t)16 << 10;
+
+bool have_pin(micsa_ctx* c)
+{
+    if (c->pin) return true;
+    if (c->pin_failed) return false;
+    if (c->store) {
+        std::lock_guard<std::mutex> hold(c->store->lock);
+        if (!c->store->pins.empty()) {
+            c->pin = static_cast<uint8_t*>(c->store->pins.back());
+            c->store->pins.pop_back();
+        }
+    }
+    void* p = nullptr;
+    if (!c->pin && hipHostMalloc(&p, kPinHead + kPinBytes, hipHostMallocDefault) != hipSuccess) {
+        (void)hipGetLastError();
+        c->pin_failed = true;
+        return false;
+    }
+    if (!c->pin) c->pin = static_cast<uint8_t*>(p);
+    *reinterpret_cast<volatile uint32_t*>(c->pin) = c->ticket = 0;
+    return true;
+}
+
+// run(dst, ticket, value) launches it, as one work-group that ends with
+// give_ticket(ticket, value) where `one`.
+template <class Run>
+int fetch(micsa_ctx* c, size_t bytes, void* host, bool one, Run run)
+{
+    uint8_t* const dst = c->pin + kPinHead;
+    volatile uint32_t* const flag = reinterpret_cast<volatile uint32_t*>(c->pin);
+    const uint32_t value = ++c->ticket;
+    run(dst, one ? reinterpret_cast<uint32_t*>(c->pin) : nullptr, value);
+    if (int st = check_launch(c, "read")) return st;
+    bool done = false;
+    if (one) {
+        const auto limit = std::chrono::steady_clock::now() + std::chrono::milliseconds(1);
+        for (int i = 0; !done; ++i) {
+            done = *flag == value;
+            if ((i & 255) == 255 && std::chrono::steady_clock::now() > limit) break;
+        }
+        std::atomic_thread_fence(std::memory_order_acquire);
+    }
+    if (!done) HIP_TRY(c, hipStreamSynchronize(c->stream));
+    std::memcpy(host, dst, bytes);
+    return MICSA_OK;
+}
+
+// Device memory (a multiple of 8 bytes, as is its address) to the host.
+int read_device(micsa_ctx* c, const void* dev, void* host, size_t bytes)
+{
+    if (bytes <= kPinBytes && have_pin(c)) {
+        const bool one = bytes <= kTicketBytes;
+        return fetch(c, bytes, host, one, [&](void* dst, uint32_t* ticket, uint32_t value) {
+            k_to_host<<<one ? 1u : (unsigned)((bytes + 8191) / 8192), 1024, 0, c->stream>>>(
+                static_cast<const uint64_t*>(dev), (int64_t)(bytes / 8), static_cast<uint64_t*>(dst), ticket, value);
+        });
+    }
+    HIP_TRY(c, hipMemcpyAsync(host, dev, bytes, hipMemcpyDeviceToHost, c->stream));
+    HIP_TRY(c, hipStreamSynchronize(c->stream));
+    return MICSA_OK;
+}
+
+// The slots of n entities, summed per entity.
 int read_slots(micsa_ctx* c, const unsigned long long* dev, int64_t n, std::vector<int64_t>& out)
 {
-    if (n > 16 && n <= std::max(c->L, c->p.n_samples)) {
-        k_sum_slots<<<(unsigned)((n + 3) / 4), 256, 0, c->stream>>>(dev, n, c->sums);
-        if (int st = check_launch(c, "k_sum_slots")) return st;
-        out.resize((size_t)n);
-        HIP_TRY(c, hipMemcpyAsync(out.data(), c->sums, (size_t)n * 8, hipMemcpyDeviceToHost, c->stream));
-        HIP_TRY(c, hipStreamSynchronize(c->stream));
-        return MICSA_OK;
-    }
+    out.assign((size_t)n, 0);
+    if ((size_t)n * 8 <= kPinBytes && have_pin(c))
+        // (a wave per entity: up to eight rounds of one work-group)
+        return fetch(c, (size_t)n * 8, out.data(), n <= 128, [&](void* dst, uint32_t* ticket, uint32_t value) {
+            k_sum_slots<<<ticket ? 1u : (unsigned)((n + 15) / 16), 1024, 0, c->stream>>>(
+                dev, n, static_cast<long long*>(dst), ticket, value);
+        });
     std::vector<int64_t> raw((size_t)(n * kSlots));
     HIP_TRY(c, hipMemcpyAsync(raw.data(), dev, raw.size() * 8, hipMemcpyDeviceToHost, c->stream));
     HIP_TRY(c, hipStreamSynchronize(c->stream));
-    out.assign((size_t)n, 0);
     for (int64_t e = 0; e < n; ++e)
         for (int k = 0; k < kSlots; ++k) out[(size_t)e] += raw[(size_t)(e * kSlots + k)];
     return MICSA_OK;
@@ -2315,6 +2388,14 @@ void free_all(micsa_ctx* c)
             (void)hipEventDestroy(e.second);
         }
     for (const JobStore::Block& b : c->owned) drop_block(c, b);
+    if (c->pin && c->store) {
+        std::lock_guard<std::mutex> hold(c->store->lock);
+        if (c->store->pins.size() < JobStore::kStreams) {
+            c->store->pins.push_back(c->pin);
+            c->pin = nullptr;
+        }
+    }
+    if (c->pin) (void)hipHostFree(c->pin);
 }
 
 // tally <- energies recomputed from the state, on the device.
@@ -2433,7 +2514,7 @@ static int create_ctx(const micsa_params* p, hipStream_t stream, size_t draw_roo
     const bool cells = use_cells(c), msc = !cells && !c->bit && c->gamma == 1 && msc_eligible(c);
     // One allocation for all of it: nine took 90 us of the 230 us that a 16^3
     // context took to set up.
-    const size_t home = arena_size((size_t)c->L * kSlots * 8) + arena_size(nred * kSlots * 8) + arena_size(nred * 8) +
+    const size_t home = arena_size((size_t)c->L * kSlots * 8) + arena_size(nred * kSlots * 8) +
                         (c->bit ? 3 * arena_size(words * 8) + arena_size(bonds)
                                 : (alt ? 2 : 1) * (arena_size(state) + arena_size(dstate)));
     size_t work = 0;
@@ -2451,7 +2532,7 @@ static int create_ctx(const micsa_params* p, hipStream_t stream, size_t draw_roo
         c->arena_left = home;
     }
     bool ok = c->arena && ctx_alloc(c, c->tally, (size_t)c->L * kSlots * 8) &&
-              ctx_alloc(c, c->red, nred * kSlots * 8) && ctx_alloc(c, c->sums, nred * 8);
+              ctx_alloc(c, c->red, nred * kSlots * 8);
     if (ok && !c->bit) {
         ok = ctx_alloc(c, c->spin, state) && ctx_alloc(c, c->dem, dstate);
         if (ok && alt) ok = need_alt(c) == MICSA_OK;
@@ -2652,10 +2733,7 @@ int micsa_sweep_logged(micsa_ctx* ctx, int32_t algo, int64_t n, int64_t stride, 
             return fail(ctx, MICSA_ENOMEM, "log buffer");
         int st = sweep_logging(ctx, algo, n, rows > 0 ? rlog : nullptr, stride);
         std::vector<int64_t> h((size_t)rows * L * 2);
-        if (!st && rows > 0 &&
-            hipMemcpyAsync(h.data(), rlog, h.size() * 8, hipMemcpyDeviceToHost, ctx->stream) != hipSuccess)
-            st = fail(ctx, MICSA_EHIP, "log copy");
-        if (!st && hipStreamSynchronize(ctx->stream) != hipSuccess) st = fail(ctx, MICSA_EHIP, "sync");
+        if (!st && rows > 0) st = read_device(ctx, rlog, h.data(), h.size() * 8);
         ctx_free(ctx, rlog);
         if (st) return st;
         const int64_t N = n_sites(ctx);
@@ -2883,7 +2961,7 @@ int micsa_read_c4_static(micsa_ctx* ctx, int64_t* G)
                      ctx->stream>>>(ctx->g, cg, (int)sp0, Q, dD);
         if ((st = check_launch(ctx, "k_c4_count"))) return st;
     }
-    k_sum_slots<<<(unsigned)((ent + 3) / 4), 256, 0, ctx->stream>>>(dD, ent, sums);
+    k_sum_slots<<<(unsigned)((ent + 15) / 16), 1024, 0, ctx->stream>>>(dD, ent, sums, nullptr, 0u);
     if ((st = check_launch(ctx, "k_sum_slots"))) return st;
     HIP_TRY(ctx, hipMemcpyAsync(G, sums, (size_t)ent * 8, hipMemcpyDeviceToHost, ctx->stream));
     HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
@@ -2965,18 +3043,46 @@ int micsa_read_overlap(micsa_ctx* ctx, int32_t a, int32_t b, int64_t* Q)
 // spins, or the daemons with count = L * gamma) -> host [count][N].
 static int read_state(micsa_ctx* ctx, const uint8_t* dev, uint8_t* host, int64_t count, uint8_t mask = 0xFF)
 {
-    const int64_t N = n_sites(ctx);
-    std::vector<uint8_t> buf((size_t)count * 2 * (size_t)ctx->g.Nh);
-    HIP_TRY(ctx, hipMemcpyAsync(buf.data(), dev, buf.size(), hipMemcpyDeviceToHost, ctx->stream));
-    HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
-    for (int64_t l = 0; l < count; ++l)
-        for (int64_t i = 0; i < N; ++i) {
-            int par;
-            int64_t h;
-            split_index(ctx, i, par, h);
-            host[(int64_t)l * N + i] = buf[((size_t)l * 2 + par) * ctx->g.Nh + h] & mask;
-        }
-    return MICSA_OK;
+    // in natural order by the device: small states to pinned memory, larger
+    // ones by way of a buffer of at most 32 MiB
+    const int64_t words = count * n_sites(ctx) / 8;
+    const auto launch = [&](int64_t w0, int64_t n, void* dst, unsigned blocks, uint32_t* ticket, uint32_t value) {
+        k_natural<<<blocks, 1024, 0, ctx->stream>>>(ctx->g, dev, w0, n, 0x01010101u * mask, static_cast<uint2*>(dst),
+                                                   ticket, value);
+    };
+    if ((size_t)words * 8 <= kPinBytes && have_pin(ctx)) {
+        const bool one = (size_t)words * 8 <= kTicketBytes;
+        return fetch(ctx, (size_t)words * 8, host, one, [&](void* dst, uint32_t* ticket, uint32_t value) {
+            launch(0, words, dst, one ? 1u : (unsigned)((words + 1023) / 1024), ticket, value);
+        });
+    }
+    const int64_t chunk = std::min<int64_t>(words, (int64_t)4 << 20);
+    uint2* buf = nullptr;
+    if (!ctx_alloc(ctx, buf, (size_t)chunk * 8)) {  // no room: as it lies, put in order here
+        const int64_t N = n_sites(ctx);
+        std::vector<uint8_t> raw((size_t)count * 2 * (size_t)ctx->g.Nh);
+        HIP_TRY(ctx, hipMemcpyAsync(raw.data(), dev, raw.size(), hipMemcpyDeviceToHost, ctx->stream));
+        HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
+        for (int64_t l = 0; l < count; ++l)
+            for (int64_t i = 0; i < N; ++i) {
+                int par;
+                int64_t h;
+                split_index(ctx, i, par, h);
+                host[(int64_t)l * N + i] = raw[((size_t)l * 2 + par) * ctx->g.Nh + h] & mask;
+            }
+        return MICSA_OK;
+    }
+    int st = MICSA_OK;
+    for (int64_t w0 = 0; w0 < words && !st; w0 += chunk) {
+        const int64_t n = std::min(chunk, words - w0);
+        launch(w0, n, buf, (unsigned)((n + 1023) / 1024), nullptr, 0u);
+        st = check_launch(ctx, "k_natural");
+        if (!st && (hipMemcpyAsync(host + w0 * 8, buf, (size_t)n * 8, hipMemcpyDeviceToHost, ctx->stream) != hipSuccess ||
+                    hipStreamSynchronize(ctx->stream) != hipSuccess))
+            st = fail(ctx, MICSA_EHIP, "state copy");
+    }
+    ctx_free(ctx, buf);
+    return st;
 }
 
 // Bit-plane words [WL][2][Nh] -> host values [S][R][N]; with two planes

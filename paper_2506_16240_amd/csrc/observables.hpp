@@ -115,14 +115,54 @@ __global__ void __launch_bounds__(256) k_c4_count(Geom g, C4Geom cg, int sp0, co
     block_add(D + ((int64_t)(s * 3 + mu) * (cg.rmax + 1) + r) * kSlots, cnt);
 }
 
-// Slots of n entities summed, a wave per entity.
-__global__ void __launch_bounds__(256) k_sum_slots(const unsigned long long* __restrict__ slots, int64_t n,
-                                                   long long* __restrict__ out)
+// The end of a work-group whose results are in host memory: the ticket, once
+// all of them are visible there.
+__device__ __forceinline__ void give_ticket(uint32_t* ticket, uint32_t value)
 {
-    const int64_t e = blockIdx.x * 4ll + (threadIdx.x >> 6);
-    if (e >= n) return;
-    const long long v = wave_sum64((long long)slots[e * kSlots + (threadIdx.x & 63)]);
-    if ((threadIdx.x & 63) == 0) out[e] = v;
+    if (!ticket) return;
+    __threadfence_system();
+    __syncthreads();
+    if (threadIdx.x == 0) __hip_atomic_store(ticket, value, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+// Slots of n entities summed, a wave per entity (work-groups of 16 waves).
+__global__ void __launch_bounds__(1024) k_sum_slots(const unsigned long long* __restrict__ slots, int64_t n,
+                                                    long long* __restrict__ out, uint32_t* ticket, uint32_t value)
+{
+    for (int64_t e = blockIdx.x * 16ll + (threadIdx.x >> 6); e < n; e += gridDim.x * 16ll) {
+        const long long v = wave_sum64((long long)slots[e * kSlots + (threadIdx.x & 63)]);
+        if ((threadIdx.x & 63) == 0) out[e] = v;
+    }
+    give_ticket(ticket, value);
+}
+
+// Words to host memory.
+__global__ void __launch_bounds__(1024) k_to_host(const uint64_t* __restrict__ src, int64_t n,
+                                                  uint64_t* __restrict__ dst, uint32_t* ticket, uint32_t value)
+{
+    for (int64_t i = blockIdx.x * 1024ll + threadIdx.x; i < n; i += gridDim.x * 1024ll) dst[i] = src[i];
+    give_ticket(ticket, value);
+}
+
+// Bytes of the checkerboard halves in natural order: words [w0, w0 + n) of 8
+// consecutive sites of a row, four from each half, with `mask` applied.
+__global__ void __launch_bounds__(1024) k_natural(Geom g, const uint8_t* __restrict__ halves, int64_t w0, int64_t n,
+                                                  uint32_t mask, uint2* __restrict__ out, uint32_t* ticket,
+                                                  uint32_t value)
+{
+    const int per_row = g.Lx / 8;
+    for (int64_t i = blockIdx.x * 1024ll + threadIdx.x; i < n; i += gridDim.x * 1024ll) {
+        const int64_t row = (w0 + i) / per_row;  // of all lattices
+        const int w = (int)(w0 + i - row * per_row);
+        const int64_t l = row / g.rows;
+        const int r = (int)(row - l * g.rows), q = (r / g.Ly + r % g.Ly) & 1;
+        const uint8_t* at = halves + l * 2 * g.Nh + (int64_t)r * g.Kx + 4 * w;
+        const uint32_t e = *reinterpret_cast<const uint32_t*>(at + q * g.Nh) & mask;        // even x
+        const uint32_t o = *reinterpret_cast<const uint32_t*>(at + (1 - q) * g.Nh) & mask;  // odd x
+        // bytes e0 o0 e1 o1 | e2 o2 e3 o3 (selectors 0-3: second operand, 4-7: first)
+        out[i] = make_uint2(__builtin_amdgcn_perm(o, e, 0x05010400u), __builtin_amdgcn_perm(o, e, 0x07030602u));
+    }
+    give_ticket(ticket, value);
 }
 
 // Energy tally of lattice blockIdx.x from its unsatisfied bonds U (slots):

@@ -36,7 +36,7 @@ struct micsa_pt {
     int32_t* perm = nullptr;     // [runs][2][M]
     int64_t* E = nullptr;        // [runs][2][M] by slot
     int64_t* swaps = nullptr;    // [runs][2][M-1]
-    int64_t* out = nullptr;      // [kPtReadWords] results of a read
+    int64_t* out = nullptr;      // [kPtReadWords] results of a read, in pinned host memory
     uint32_t* wtab = nullptr;    // [M][kPtTable] device form (thresholds - 1, guides)
     uint32_t* ptab = nullptr;    // [M-1][kPtTable]
     std::vector<int32_t> Jq;     // [3][N]
@@ -120,8 +120,9 @@ void free_pt(micsa_pt* c)
 {
     if (!c) return;
     for (void* ptr : {(void*)c->rec, (void*)c->spins, (void*)c->perm, (void*)c->E, (void*)c->swaps, (void*)c->wtab,
-                      (void*)c->ptab, (void*)c->out, (void*)c->ftab})
+                      (void*)c->ptab, (void*)c->ftab})
         if (ptr) (void)hipFree(ptr);
+    if (c->out) (void)hipHostFree(c->out);
     for (auto& ev : c->events)
         for (hipEvent_t x : ev) (void)hipEventDestroy(x);
 }
@@ -343,7 +344,7 @@ int micsa_pt_create(const micsa_pt_params* p, const double* J, const double* T, 
               hipMalloc(&c->spins, nslot * g.R0 * 8) == hipSuccess && hipMalloc(&c->perm, nslot * 4) == hipSuccess &&
               hipMalloc(&c->E, nslot * 8) == hipSuccess &&
               hipMalloc(&c->swaps, (size_t)g.runs * 2 * (M - 1) * 8) == hipSuccess &&
-              hipMalloc(&c->out, (size_t)kPtReadWords * 8) == hipSuccess &&
+              hipHostMalloc(&c->out, (size_t)kPtReadWords * 8) == hipSuccess &&
               hipMalloc(&c->wtab, dw.size() * 4) == hipSuccess && hipMalloc(&c->ptab, std::max<size_t>(dp.size(), 1) * 4) == hipSuccess;
     if (!ok) {
         (void)hipGetLastError();
@@ -495,10 +496,9 @@ int micsa_pt_read(micsa_pt* pt, int64_t* E, int64_t* Q)
         k_pt_read<<<dim3((unsigned)g.M, (unsigned)n), 64, 0, pt->stream>>>(g, (int)u, pt->perm, pt->E, pt->spins, dE,
                                                                           dQ);
         PT_TRY(pt, hipGetLastError());
-        if (E)
-            PT_TRY(pt, hipMemcpyAsync(E + u * 2 * g.M, dE, (size_t)n * 2 * g.M * 8, hipMemcpyDeviceToHost, pt->stream));
-        if (Q) PT_TRY(pt, hipMemcpyAsync(Q + u * g.M, dQ, (size_t)n * g.M * 8, hipMemcpyDeviceToHost, pt->stream));
         PT_TRY(pt, hipStreamSynchronize(pt->stream));
+        if (E) std::memcpy(E + u * 2 * g.M, dE, (size_t)n * 2 * g.M * 8);
+        if (Q) std::memcpy(Q + u * g.M, dQ, (size_t)n * g.M * 8);
     }
     return MICSA_OK;
 }
