@@ -288,8 +288,7 @@ struct CellSweep {
     const uint32_t *dr0, *dr1;          // drawn levels of the launch's first refresh
     int64_t dr_stride;              // words from one refresh's levels to the next's
     unsigned long long* tally;
-    long long* log;      // [row][lattices][2]: unsatisfied bonds and level sum, or null
-    int64_t log_row0;
+    uint32_t* log;       // logged launches: [row][lattices][lanes], see k_cells_log_rows; or null
     int64_t k0;          // first sweep index
     int32_t n;           // sweeps
     int32_t ref0;        // first refresh sweep of the launch, counted from k0 (>= n: none)
@@ -332,7 +331,7 @@ __device__ __forceinline__ uint32_t wave_sum_dpp(uint32_t v)
 // one per site; 4: daemons or walkers in several families (F).
 template <int NR, int XM, int ALG>
 __device__ __forceinline__ void cells_body(const CellSweep& J, const CellFamilies* F, int l, int ty, int tz,
-                                           uint32_t* lds, uint32_t* red)
+                                           uint32_t* lds)
 {
     constexpr int CAP = NR * kCellLanes;  // LDS words of one parity's plane
     constexpr bool LEVELS = ALG == 0 || ALG == 3;  // one family, in registers for the whole launch
@@ -441,7 +440,6 @@ __device__ __forceinline__ void cells_body(const CellSweep& J, const CellFamilie
         lds[c] = s[0][i];
         lds[CAP + c] = s[1][i];
     }
-    if (t < 4) red[t] = 0;
     auto levels = [&]() {
         int v = 0;
 #pragma unroll
@@ -615,8 +613,29 @@ __device__ __forceinline__ void cells_body(const CellSweep& J, const CellFamilie
         u[0] = xor3(S, s[1 - p][i], j[p][i][0]);
         u[1] = xor3(S, shifted(i, p), j[p][i][1]);
     };
+    // Logged sweeps: a lane stores its unsatisfied bonds (each counted at its even
+    // end) and, above bit 16, its level sum; k_cells_log_rows adds the lanes.
+    // The bonds are those that the next even half finds before it moves anything,
+    // so a logged sweep costs a few counts and a store: 0.36 us at 16^3, 0.30 not
+    // logged (0.69 with the fields formed once more and the lanes summed here).
+    uint32_t* logto = J.log ? J.log + (int64_t)l * B + t : nullptr;
+    uint32_t logD = 0;
+    bool pend = false;  // a sweep has ended whose row is not yet written
+    int to_log = J.log_first;
+    auto bonds = [&](int i, const uint32_t (&u)[6]) {
+        uint32_t n = 0;
+#pragma unroll
+        for (int d = 0; d < 6; ++d) n += (uint32_t)__popc(u[d] & msk(i));
+        return (valid >> i) & 1u ? n : 0u;
+    };
+    auto write_row = [&](uint32_t U) {
+        *logto = U | logD;
+        logto += (int64_t)J.lattices * B;
+        pend = false;
+    };
     auto half = [&](auto pc) {
         constexpr int p = decltype(pc)::value;
+        uint32_t U = 0;
         uint32_t cur[NR][K];
         if (CANON) {
 #pragma unroll
@@ -629,6 +648,7 @@ __device__ __forceinline__ void cells_body(const CellSweep& J, const CellFamilie
         for (int i = 0; i < NR; ++i) {
             uint32_t u[6];
             unsat(i, p, u);
+            if (p == 0 && pend) U += bonds(i, u);
             if (!CANON) {
                 s[p][i] ^= cell_move(u, m0[p][i], m1[p][i]);
             } else {
@@ -660,20 +680,10 @@ __device__ __forceinline__ void cells_body(const CellSweep& J, const CellFamilie
             }
             lds[p * CAP + t + i * B] = s[p][i];
         }
+        if (p == 0 && pend) write_row(U);
         lds_barrier();
     };
-    int64_t row = J.log_row0;
-    int pend = -1;  // buffer of `red` holding a logged row not yet written
-    auto flush = [&]() {
-        if (pend >= 0 && t == 0) {
-            J.log[(row * J.lattices + l) * 2 + 0] = (long long)red[2 * pend];
-            J.log[(row * J.lattices + l) * 2 + 1] = (long long)red[2 * pend + 1];
-            red[2 * pend] = red[2 * pend + 1] = 0;
-        }
-        if (pend >= 0) ++row;
-        pend = -1;
-    };
-    int to_log = J.log_first, buf = 0;
+
     for (int it = 0; it < J.n; ++it) {
         if (ALG == 3 && it > 0 && it != ref) wander_parity((int)((J.k0 + it - 1) & 1));
         if (ALG == 4) {
@@ -698,7 +708,6 @@ __device__ __forceinline__ void cells_body(const CellSweep& J, const CellFamilie
             if (AHEAD) fetch();
         }
         half(std::integral_constant<int, 0>{});
-        flush();
         half(std::integral_constant<int, 1>{});
         if (ALG == 4) {
             taken -= levels();
@@ -714,32 +723,25 @@ __device__ __forceinline__ void cells_body(const CellSweep& J, const CellFamilie
         }
         if (J.log && --to_log == 0) {
             to_log = J.log_stride;
-            // from-scratch energy (every bond once, at its even end) and the
-            // level sum; a wave's sums stay below 2^16
-            uint32_t U = 0, D0 = 0, D1 = 0;
+            uint32_t D = 0;
 #pragma unroll
             for (int i = 0; i < NR; ++i) {
-                uint32_t u[6];
-                unsat(i, 0, u);
-                uint32_t n = 0;
-#pragma unroll
-                for (int d = 0; d < 6; ++d) n += (uint32_t)__popc(u[d] & msk(i));
-                U += (valid >> i) & 1u ? n : 0u;
-                D0 += (valid >> i) & 1u ? (uint32_t)(__popc(m0[0][i]) + __popc(m0[1][i])) : 0u;
-                D1 += (valid >> i) & 1u ? (uint32_t)(__popc(m1[0][i]) + __popc(m1[1][i])) : 0u;
+                const int n = __popc(m0[0][i]) + __popc(m0[1][i]) + 2 * (__popc(m1[0][i]) + __popc(m1[1][i]));
+                D += (valid >> i) & 1u ? (uint32_t)n : 0u;
             }
-            const uint32_t v = wave_sum_dpp(U | ((D0 + 2 * D1) << 16));
-            if ((t & 63) == 63) {
-                atomicAdd(&red[2 * buf], v & 0xFFFFu);
-                atomicAdd(&red[2 * buf + 1], v >> 16);
-            }
-            pend = buf;
-            buf ^= 1;
+            logD = D << 16;
+            pend = true;
         }
     }
-    if (J.log) {
-        lds_barrier();
-        flush();
+    if (pend) {
+        uint32_t U = 0;
+#pragma unroll
+        for (int i = 0; i < NR; ++i) {
+            uint32_t u[6];
+            unsat(i, 0, u);
+            U += bonds(i, u);
+        }
+        write_row(U);
     }
     if (LEVELS) taken -= levels();
 #pragma unroll
@@ -764,16 +766,39 @@ template <int NR, int XM, int ALG>
 __global__ void __launch_bounds__(kCellLanes) k_cells_sweep(CellSweep J)
 {
     __shared__ uint32_t lds[(ALG == 3 && XM > 0 ? 3 : 2) * NR * kCellLanes];
-    __shared__ uint32_t red[4];
-    cells_body<NR, XM, ALG>(J, nullptr, blockIdx.z, blockIdx.x, blockIdx.y, lds, red);
+    cells_body<NR, XM, ALG>(J, nullptr, blockIdx.z, blockIdx.x, blockIdx.y, lds);
 }
 
 template <int NR, int XM>
 __global__ void __launch_bounds__(kCellLanes) k_cells_sweep_families(CellSweep J, CellFamilies F)
 {
     __shared__ uint32_t lds[2 * NR * kCellLanes];
-    __shared__ uint32_t red[4];
-    cells_body<NR, XM, 4>(J, &F, blockIdx.z, blockIdx.x, blockIdx.y, lds, red);
+    cells_body<NR, XM, 4>(J, &F, blockIdx.z, blockIdx.x, blockIdx.y, lds);
+}
+
+// Rows of a logged launch: entry e = row * lattices + lattice of `out` gets the
+// unsatisfied bonds and the level sum from its lanes' words; the baselines,
+// which neither hold nor change the levels, get the sum from its slots.  A wave
+// per entry.
+__global__ void __launch_bounds__(256) k_cells_log_rows(const uint32_t* __restrict__ raw, int64_t n, int lanes,
+                                                        const unsigned long long* __restrict__ levels, int lattices,
+                                                        long long* __restrict__ out)
+{
+    const int64_t e = blockIdx.x * 4ll + (threadIdx.x >> 6);
+    if (e >= n) return;
+    const int lane = threadIdx.x & 63;
+    long long U = 0, D = levels ? (long long)levels[(e % lattices) * kSlots + lane] : 0;
+    for (int k = lane; k < lanes; k += 64) {
+        const uint32_t v = raw[e * lanes + k];
+        U += v & 0xFFFFu;
+        D += v >> 16;
+    }
+    U = wave_sum64(U);
+    D = wave_sum64(D);
+    if (lane == 0) {
+        out[2 * e] = U;
+        out[2 * e + 1] = D;
+    }
 }
 
 // The batched launches of the serving pool: whole lattices of different jobs,
@@ -788,10 +813,9 @@ __global__ void __launch_bounds__(kCellLanes) k_cells_sweep_batch(const CellSwee
                                                                   const CellItem* __restrict__ items)
 {
     __shared__ uint32_t lds[2 * NR * kCellLanes];
-    __shared__ uint32_t red[4];
     const CellItem it = items[blockIdx.x];
     const CellSweep J = jobs[it.job];
-    cells_body<NR, XM, 0>(J, nullptr, it.lattice, 0, 0, lds, red);
+    cells_body<NR, XM, 0>(J, nullptr, it.lattice, 0, 0, lds);
 }
 
 __global__ void __launch_bounds__(256) k_cells_draw_batch(const CellDraw* __restrict__ jobs,

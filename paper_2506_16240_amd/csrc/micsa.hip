@@ -197,6 +197,12 @@ struct micsa_ctx {
     unsigned long long* logslots = nullptr;
     long long* rlog = nullptr;
     size_t rlog_cap = 0;  // entries of rlog
+    // workspace of one call on the context's stream (host logs, C4, large
+    // states), kept up to 16 MiB: a free waits for the device, 50 us and more
+    void* work = nullptr;
+    size_t work_cap = 0;
+    uint32_t* lograw = nullptr;  // lanes' words of a logged launch of cell sweeps, and its room in rows
+    int64_t lograw_rows = 0;
     Schedule sched;
     // device tables of the installed schedule, one entry per refresh index
     DaemonThresholds* d_dth = nullptr;
@@ -326,6 +332,28 @@ void ctx_free(micsa_ctx* c, void* p)
             c->owned.erase(c->owned.begin() + (long)i);
             return;
         }
+}
+
+// The workspace, or a block of its own where that would be too large to keep;
+// given back before the call ends, its work finished.
+void* work_take(micsa_ctx* c, size_t bytes)
+{
+    if (bytes > (size_t)16 << 20) return ctx_alloc(c, bytes);
+    if (c->work_cap < bytes) {
+        if (c->work) {
+            (void)hipStreamSynchronize(c->stream);
+            ctx_free(c, c->work);
+        }
+        const size_t n = std::max<size_t>(bytes, (size_t)64 << 10);
+        c->work = ctx_alloc(c, n);
+        c->work_cap = c->work ? n : 0;
+    }
+    return c->work;
+}
+
+void work_give(micsa_ctx* c, void* p)
+{
+    if (p != c->work) ctx_free(c, p);
 }
 
 // A stream of default priority, and its end (its work has finished).
@@ -2038,13 +2066,45 @@ int launch_cells(micsa_ctx* c, int alg, CellSweep& J, const CellFamilies* F = nu
 
 // Logging fields of a launch of the sweeps from done on, in a call that logs
 // every stride sweeps to dlog.
-void cell_log(CellSweep& J, long long* dlog, int64_t done, int64_t stride)
+void cell_log(micsa_ctx* c, CellSweep& J, bool logged, int64_t done, int64_t stride)
 {
-    J.log = dlog;
-    if (!dlog) return;
-    J.log_row0 = done / stride;
+    J.log = logged ? c->lograw : nullptr;
+    if (!logged) return;
     J.log_stride = (int32_t)std::min<int64_t>(stride, INT32_MAX);
     J.log_first = (int32_t)std::min<int64_t>(stride - done % stride, INT32_MAX);
+}
+
+// Room for the lanes' words of `rows` logged rows, or for as many as fit 8 MiB
+// (launches are cut accordingly).
+bool log_room(micsa_ctx* c, int64_t rows)
+{
+    const int64_t row = (int64_t)c->L * c->plan.block;
+    const int64_t want = std::max<int64_t>(1, std::min<int64_t>(rows, ((int64_t)2 << 20) / row));
+    if (c->lograw_rows >= want) return true;
+    if (c->lograw) {
+        (void)hipStreamSynchronize(c->stream);
+        ctx_free(c, c->lograw);
+        c->lograw_rows = 0;
+    }
+    if (!ctx_alloc(c, c->lograw, (size_t)(want * row) * 4)) return false;
+    c->lograw_rows = want;
+    return true;
+}
+
+// Sweeps of a logged launch at most.
+int64_t log_most(const micsa_ctx* c, int64_t most, int64_t stride)
+{
+    return stride >= most ? most : std::min(most, c->lograw_rows * stride);
+}
+
+// The rows that sweeps [done, done + n) of the call ended.
+int write_log(micsa_ctx* c, int64_t done, int64_t n, int64_t stride, const unsigned long long* levels, long long* dlog)
+{
+    const int64_t r0 = done / stride, e = ((done + n) / stride - r0) * c->L;
+    if (e == 0) return MICSA_OK;
+    k_cells_log_rows<<<(unsigned)((e + 3) / 4), 256, 0, c->stream>>>(c->lograw, e, (int)c->plan.block, levels, c->L,
+                                                                   dlog + r0 * c->L * 2);
+    return check_launch(c, "k_cells_log_rows");
 }
 
 // The next launch of MicSA sweeps from sweep k on, in a run to k_end: its
@@ -2091,7 +2151,8 @@ int sweep_cells(micsa_ctx* c, int64_t n, long long* dlog, int64_t stride, bool w
         const int64_t k = c->k;
         bool draw;
         CellDraw D;
-        CellSweep J = cells_next(c, k, k_end, c->plan.sweeps > 0 ? c->plan.sweeps : kResidentChunk, &draw, &D);
+        const int64_t most = c->plan.sweeps > 0 ? c->plan.sweeps : kResidentChunk;
+        CellSweep J = cells_next(c, k, k_end, dlog ? log_most(c, most, stride) : most, &draw, &D);
         if (draw) {
             {
                 TimedLaunch t(c, kTimeRefresh);
@@ -2099,9 +2160,10 @@ int sweep_cells(micsa_ctx* c, int64_t n, long long* dlog, int64_t stride, bool w
             }
             if ((st = check_launch(c, "k_cells_draw"))) return st;
         }
-        cell_log(J, dlog, k - k_first, stride);
+        cell_log(c, J, dlog, k - k_first, stride);
         J.wander0 = walkers && J.ref0 > 0 ? c->pend_wander : -1;
         if ((st = launch_cells(c, walkers ? 3 : 0, J))) return st;
+        if (dlog && (st = write_log(c, k - k_first, J.n, stride, nullptr, dlog))) return st;
         c->k = k + J.n;
         c->pend_wander = walkers ? (int32_t)((c->k - 1) & 1) : -1;
     }
@@ -2223,6 +2285,7 @@ int sweep_cells_canonical(micsa_ctx* c, int32_t algo, int64_t n, long long* dlog
     const int64_t k_first = c->k, k_end = c->k + n, plane = (int64_t)c->L * cg.plane;
     c->home_ok = false;
     c->cdr_n = 0;  // the buffer holds the baselines' draws from here on
+    if (dlog && (st = enqueue_level_sum(c, c->red))) return st;  // the levels of every logged row
     const int64_t room = std::min<int64_t>(4 * plane * c->cdr_cap / (2 * K * plane), 4096);  // sweeps drawn at once
     while (c->k < k_end) {
         const int64_t len = std::min<int64_t>(k_end - c->k, room), k_draw = c->k;
@@ -2245,13 +2308,15 @@ int sweep_cells_canonical(micsa_ctx* c, int32_t algo, int64_t n, long long* dlog
         }
         if ((st = check_launch(c, "k_cells_draw_canonical"))) return st;
         while (c->k < k_draw + len) {
-            const int64_t m = std::min<int64_t>(k_draw + len - c->k, c->plan.sweeps > 0 ? c->plan.sweeps : len);
+            const int64_t most = c->plan.sweeps > 0 ? c->plan.sweeps : len;
+            const int64_t m = std::min(k_draw + len - c->k, dlog ? log_most(c, most, stride) : most);
             CellSweep J{};
             J.dr0 = c->cdr0 + (c->k - k_draw) * 2 * K * plane;
-            cell_log(J, dlog, c->k - k_first, stride);
+            cell_log(c, J, dlog, c->k - k_first, stride);
             J.k0 = c->k;
             J.n = (int32_t)m;
             if ((st = launch_cells(c, alg, J))) return st;
+            if (dlog && (st = write_log(c, c->k - k_first, m, stride, c->red, dlog))) return st;
             c->k += m;
         }
     }
@@ -2678,7 +2743,7 @@ int micsa_sweep_logged_d(micsa_ctx* ctx, int32_t algo, int64_t n, int64_t stride
     int st = check_sweep(ctx, algo, n);
     if (st) return st;
     if (rows == 0 || (!E_log && !D_log)) return sweep_impl(ctx, algo, n);
-    if (logs_in_kernel(ctx, algo, n)) {
+    if (logs_in_kernel(ctx, algo, n) && log_room(ctx, rows)) {
         const size_t need = (size_t)rows * L * 2;
         if (need > ctx->rlog_cap) {
             // the old buffer may still be in use by enqueued work
@@ -2726,15 +2791,15 @@ int micsa_sweep_logged(micsa_ctx* ctx, int32_t algo, int64_t n, int64_t stride, 
     const int L = ctx->L;
     int st0 = check_sweep(ctx, algo, n);
     if (st0) return st0;
-    if (logs_in_kernel(ctx, algo, n)) {
+    if (logs_in_kernel(ctx, algo, n) && log_room(ctx, rows)) {
         if (algo != MICSA_ALGO_WALKERS && (st0 = settle_wander(ctx))) return st0;
         long long* rlog = nullptr;
-        if (rows > 0 && !ctx_alloc(ctx, rlog, (size_t)rows * L * 2 * 8))
+        if (rows > 0 && !(rlog = static_cast<long long*>(work_take(ctx, (size_t)rows * L * 2 * 8))))
             return fail(ctx, MICSA_ENOMEM, "log buffer");
         int st = sweep_logging(ctx, algo, n, rows > 0 ? rlog : nullptr, stride);
         std::vector<int64_t> h((size_t)rows * L * 2);
         if (!st && rows > 0) st = read_device(ctx, rlog, h.data(), h.size() * 8);
-        ctx_free(ctx, rlog);
+        work_give(ctx, rlog);
         if (st) return st;
         const int64_t N = n_sites(ctx);
         for (int64_t r = 0; r < rows; ++r)
@@ -2746,7 +2811,8 @@ int micsa_sweep_logged(micsa_ctx* ctx, int32_t algo, int64_t n, int64_t stride, 
     }
     unsigned long long* dlog = nullptr;
     const size_t row_len = (size_t)L * 2 * kSlots;
-    if (rows > 0 && !ctx_alloc(ctx, dlog, (size_t)rows * row_len * 8)) return fail(ctx, MICSA_ENOMEM, "log buffer");
+    if (rows > 0 && !(dlog = static_cast<unsigned long long*>(work_take(ctx, (size_t)rows * row_len * 8))))
+        return fail(ctx, MICSA_ENOMEM, "log buffer");
     int st = MICSA_OK;
     int64_t done = 0;
     for (int64_t r = 0; r < rows && !st; ++r) {
@@ -2759,7 +2825,7 @@ int micsa_sweep_logged(micsa_ctx* ctx, int32_t algo, int64_t n, int64_t stride, 
     std::vector<int64_t> h;
     if (!st && rows > 0) st = read_slots(ctx, dlog, rows * L * 2, h);
     if (!st && hipStreamSynchronize(ctx->stream) != hipSuccess) st = fail(ctx, MICSA_EHIP, "sync");
-    ctx_free(ctx, dlog);
+    work_give(ctx, dlog);
     if (st) return st;
     const int64_t N = n_sites(ctx);
     for (int64_t r = 0; r < rows; ++r)
@@ -2822,12 +2888,10 @@ static int c4_counts(micsa_ctx* c, const C4Geom& cg, std::vector<int64_t>& D)
     const int64_t total = (int64_t)c->p.n_samples * cg.npair;
     const int64_t budget_words = ((int64_t)256 << 20) / 4;  // at most 256 MiB of packed pairs at a time
     const int64_t chunk = std::max<int64_t>(1, std::min<int64_t>({total, budget_words / per_pair, 65535}));
-    unsigned long long* dD = nullptr;
-    uint32_t* Q = nullptr;
-    if (!ctx_alloc(c, dD, (size_t)ent * kSlots * 8) || !ctx_alloc(c, Q, (size_t)(chunk * per_pair) * 4)) {
-        ctx_free(c, dD);
-        return fail(c, MICSA_ENOMEM, "correlation buffers");
-    }
+    uint8_t* const buf = static_cast<uint8_t*>(work_take(c, (size_t)ent * kSlots * 8 + (size_t)(chunk * per_pair) * 4));
+    if (!buf) return fail(c, MICSA_ENOMEM, "correlation buffers");
+    unsigned long long* dD = reinterpret_cast<unsigned long long*>(buf);
+    uint32_t* Q = reinterpret_cast<uint32_t*>(buf + (size_t)ent * kSlots * 8);
     int st = zero_slots(c, dD, ent);
     const int64_t valid = (int64_t)2 * c->g.rows * cg.Wv;
     for (int64_t sp0 = 0; sp0 < total && !st; sp0 += chunk) {
@@ -2850,8 +2914,7 @@ static int c4_counts(micsa_ctx* c, const C4Geom& cg, std::vector<int64_t>& D)
         st = check_launch(c, "k_c4_count");
     }
     if (!st) st = read_slots(c, dD, ent, D);
-    ctx_free(c, Q);
-    ctx_free(c, dD);
+    work_give(c, buf);
     return st;
 }
 
@@ -3057,8 +3120,8 @@ static int read_state(micsa_ctx* ctx, const uint8_t* dev, uint8_t* host, int64_t
         });
     }
     const int64_t chunk = std::min<int64_t>(words, (int64_t)4 << 20);
-    uint2* buf = nullptr;
-    if (!ctx_alloc(ctx, buf, (size_t)chunk * 8)) {  // no room: as it lies, put in order here
+    uint2* const buf = static_cast<uint2*>(work_take(ctx, (size_t)chunk * 8));
+    if (!buf) {  // no room: as it lies, put in order here
         const int64_t N = n_sites(ctx);
         std::vector<uint8_t> raw((size_t)count * 2 * (size_t)ctx->g.Nh);
         HIP_TRY(ctx, hipMemcpyAsync(raw.data(), dev, raw.size(), hipMemcpyDeviceToHost, ctx->stream));
@@ -3081,7 +3144,7 @@ static int read_state(micsa_ctx* ctx, const uint8_t* dev, uint8_t* host, int64_t
                     hipStreamSynchronize(ctx->stream) != hipSuccess))
             st = fail(ctx, MICSA_EHIP, "state copy");
     }
-    ctx_free(ctx, buf);
+    work_give(ctx, buf);
     return st;
 }
 

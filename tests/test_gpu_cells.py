@@ -138,6 +138,23 @@ def test_canonical_sweeps_on_cells(shape, algo):
     g.close()
 
 
+@pytest.mark.parametrize("algo", [M.ALGO_MICSA, M.ALGO_WALKERS, M.ALGO_HEATBATH, M.ALGO_METROPOLIS])
+@pytest.mark.parametrize("shape", [SHAPES[0], SHAPES[2], SHAPES[4], SHAPES[6], SHAPES[7], (16, 16, 16, 1, 700)])
+def test_logs_of_lattices_in_one_work_group(shape, algo):
+    """Energies and levels of every sweep and of every third, in calls that end
+    between rows, with refreshes in between and levels that a baseline leaves as
+    they are; the last shape cuts its launches (11 rows of lanes' words fit)."""
+    g, o = M.Lattice(*shape, 0x10C5), O.Lattice(*shape, 0x10C5)
+    g.set_schedule(M.Schedule(M.SCHED_LINEAR, 2.5, 0.5, 60, 4))
+    os_ = O.Schedule(O.SCHED_LINEAR, 2.5, 0.5, 60, 4)
+    for a, n, stride in ((M.ALGO_MICSA, 9, 1), (algo, 13, 1), (algo, 11, 3), (M.ALGO_MICSA, 4, 4), (algo, 2, 5)):
+        E, D = g.sweep_logged(a, n, stride)
+        Eo, Do = o.run(a, os_, n, stride)
+        assert np.array_equal(E, Eo) and np.array_equal(D, Do)
+    state(g, o)
+    g.close()
+
+
 @pytest.mark.parametrize("algo", [M.ALGO_MICSA, M.ALGO_WALKERS])
 @pytest.mark.parametrize("gamma", [1, 2, 6])
 @pytest.mark.parametrize("shape", [s for s in SHAPES if s[0] * s[1] * s[2] * s[4] < 600_000])
