@@ -1998,15 +1998,21 @@ CellDraw cells_draw_slice(micsa_ctx* c, int64_t kr, int64_t k_end)
 int64_t cells_draw_blocks(const CellDraw& D) { return std::min<int64_t>((D.n * D.cg.plane + 63) / 64, 16384); }
 
 using CellKernel = void (*)(CellSweep);
-template <int ALG>
+template <int ALG, bool RING>
 CellKernel cell_kernel(int nr, int xm)
 {
     static const CellKernel k[kCellMaxNR][3] = {
-        {k_cells_sweep<1, 0, ALG>, k_cells_sweep<1, 1, ALG>, k_cells_sweep<1, 2, ALG>},
-        {k_cells_sweep<2, 0, ALG>, k_cells_sweep<2, 1, ALG>, k_cells_sweep<2, 2, ALG>},
-        {k_cells_sweep<3, 0, ALG>, k_cells_sweep<3, 1, ALG>, k_cells_sweep<3, 2, ALG>},
-        {k_cells_sweep<4, 0, ALG>, k_cells_sweep<4, 1, ALG>, nullptr}};
+        {k_cells_sweep<1, 0, ALG, RING>, k_cells_sweep<1, 1, ALG, RING>, k_cells_sweep<1, 2, ALG, RING>},
+        {k_cells_sweep<2, 0, ALG, RING>, k_cells_sweep<2, 1, ALG, RING>, k_cells_sweep<2, 2, ALG, RING>},
+        {k_cells_sweep<3, 0, ALG, RING>, k_cells_sweep<3, 1, ALG, RING>, k_cells_sweep<3, 2, ALG, RING>},
+        {k_cells_sweep<4, 0, ALG, RING>, k_cells_sweep<4, 1, ALG, RING>, nullptr}};
     return k[nr - 1][xm];
+}
+
+template <int ALG>
+CellKernel cell_kernel(const CellPlan& p)
+{
+    return p.sweeps > 0 ? cell_kernel<ALG, true>(p.nr, p.xm) : cell_kernel<ALG, false>(p.nr, p.xm);
 }
 
 // The launch's planes and shape (J holds its sweeps, draws and logging).
@@ -2046,10 +2052,10 @@ int launch_cells(micsa_ctx* c, int alg, CellSweep& J, const CellFamilies* F = nu
                 {k_cells_sweep_families<3, 0>, k_cells_sweep_families<3, 1>, k_cells_sweep_families<3, 2>}};
             k[pl.nr - 1][pl.xm]<<<grid, pl.block, 0, c->stream>>>(J, *F);
         } else {
-            const CellKernel k = alg == 0   ? cell_kernel<0>(pl.nr, pl.xm)
-                                 : alg == 1 ? cell_kernel<1>(pl.nr, pl.xm)
-                                 : alg == 2 ? cell_kernel<2>(pl.nr, pl.xm)
-                                            : cell_kernel<3>(pl.nr, pl.xm);
+            const CellKernel k = alg == 0   ? cell_kernel<0>(pl)
+                                 : alg == 1 ? cell_kernel<1>(pl)
+                                 : alg == 2 ? cell_kernel<2>(pl)
+                                            : cell_kernel<3>(pl);
             k<<<grid, pl.block, 0, c->stream>>>(J);
         }
     }
