@@ -126,9 +126,9 @@ const char* micsa_last_error(const micsa_ctx* ctx);
    hipStream_t (NULL = the null stream) on which every later call enqueues
    its work.  On success *out owns all device memory; on failure *out is
    NULL and nothing is leaked.  The working buffers of the sweep path the
-   lattice takes by default (the multispin planes, the slab sweep's drawn
-   levels) are allocated here when they fit, else by the first sweep call
-   that needs them.
+   lattice takes by default (bit planes and drawn levels) are allocated here
+   when they fit, else by the first sweep call that needs them.  The initial
+   state is enqueued on the stream; the call does not wait for it.
    Errors: EINVAL (bad sides/counts/layout/gamma), ENOMEM, EHIP. */
 int micsa_create(const micsa_params* p, void* hip_stream, micsa_ctx** out);
 
@@ -163,9 +163,10 @@ int micsa_sweep_logged(micsa_ctx* ctx, int32_t algo, int64_t n, int64_t stride, 
    for a kernel the caller launched on the same stream.  The arrays stay the
    caller's and must stay allocated until then.  The library keeps one
    device row of reduction slots per context, allocated on the first call;
-   on lattices swept by the resident kernel it keeps a buffer of the whole
-   log that grows (after synchronising the stream) when a call logs more
-   rows than any call before it.  Errors as micsa_sweep_logged. */
+   on lattices that a work-group holds whole it keeps a buffer of the whole
+   log, and of up to 8 MiB (or one row) of what the lanes log, that grow
+   (after synchronising the stream) when a call logs more rows than any call
+   before it.  Errors as micsa_sweep_logged. */
 int micsa_sweep_logged_d(micsa_ctx* ctx, int32_t algo, int64_t n, int64_t stride, int64_t* E_log,
                          int64_t* D_log);
 
@@ -261,7 +262,10 @@ int micsa_load(micsa_ctx* ctx, const void* buf, size_t len);
 int micsa_set_timing(micsa_ctx* ctx, int32_t enable);
 int micsa_get_timing(micsa_ctx* ctx, int32_t kind, double* total_ms, int64_t* launches);
 
-/* Name of the sweep kernel variant the context uses (static string). */
+/* Name of the sweep kernel variant that a call of eight sweeps or more uses
+   (static string).  The resident and slab variants keep their names; they,
+   and the bit-plane layout's kb_sweep without a launch shape of its own, run
+   the cell sweep ("k_cells_sweep" where no variant is named). */
 const char* micsa_kernel_name(const micsa_ctx* ctx, int32_t algo);
 
 /* Launch-shape options (results never depend on them; they exist for the
@@ -299,16 +303,16 @@ const char* micsa_kernel_name(const micsa_ctx* ctx, int32_t algo);
      by 8, else it falls back to 1), and acts as 1 on the fused byte sweeps.
      0 is the plain order.
    MICSA_OPT_GRAPHS: 1 replays the per-half paths (bit-plane layout; byte
-     lattices using neither the resident nor the fused sweep) as captured
+     lattices that are neither of resident size nor swept fused) as captured
      HIP graphs of 16 sweeps; 0 (default) launches every kernel, which is
      faster for these kernels on MI355X (the graph form adds a refresh-check
      and a counter kernel to every sweep).  Per-launch timing
      (micsa_set_timing) always launches every kernel.
    MICSA_OPT_TEMPORAL: MicSA sweeps per pass over memory on the fused byte
-     sweep and the slab sweep: 2 (default) runs sweeps k and k + 1 in one
-     launch wherever a call
+     sweep: 2 (default) runs sweeps k and k + 1 in one launch wherever a call
      sweeps at least two (the state is read and written once per pair); 1
-     runs one sweep per launch.  Results are identical.
+     runs one sweep per launch.  (The slab variant's name depends on it, its
+     launches do not.)  Results are identical.
    MICSA_OPT_MSC_PASS: MicSA sweeps per pass on the one-launch multispin
      sweep: 2 (default: sweeps k and k + 1 in one launch, rings of 8 rows
      and planes, the state read and written once per pair; a pass whose
@@ -316,18 +320,17 @@ const char* micsa_kernel_name(const micsa_ctx* ctx, int32_t algo);
      two refreshes, a refresh with DRAW_AHEAD 0, the last odd sweep of a
      call, walkers, or a tile whose work-group does not fit runs one sweep
      per launch) or 1 (one sweep per launch).  Results are identical; at
-     512^3 on MI355X the pair takes 36 us against 2 x 27 us.
+     512^3 on MI355X the pair takes 30 us against 2 x 27 us.
    MICSA_OPT_MSC_FUSED: the multispin sweep in one launch per sweep marching
      along z (1, default) or one launch per half sweep (0).
    MICSA_OPT_PREFETCH: steps of global loads in flight in the fused MicSA
      sweep, 1 (default) or 2 (used for work-groups of at most 640 lanes,
      i.e. (tile_y + 4) * Lx / 32 <= 640; larger tiles run with 1).
-   MICSA_OPT_DRAW_AHEAD: one-launch multispin, slab and bit-plane sweeps.  On
-     two-sweep slab launches, 1 (default) has a launch without a refresh of
-     its own draw the levels of the schedule's next refresh for its planes,
-     kept across calls until the schedule changes, and 0 draws them inside
-     the refresh launch.  Elsewhere, 1 (default for the multispin sweep;
-     the bit-plane layout defaults to 0) draws
+   MICSA_OPT_DRAW_AHEAD: one-launch multispin and bit-plane sweeps (the cell
+     sweep always reads levels drawn for many refreshes at once, kept across
+     calls until the schedule changes).  1 (default for the multispin sweep;
+     the bit-plane layout defaults to 0, and takes its own sweep in place of
+     the cell sweep where it is 1) draws
      the daemon levels of each refresh (Sec. 2.3; they depend on the refresh
      index and temperature, not on the state) in a kernel of their own on a
      second stream of the library, while the sweeps before the refresh run;
@@ -354,17 +357,14 @@ enum micsa_option {
     MICSA_OPT_MSC_PASS = 10
 };
 enum micsa_kernel_choice {
-    MICSA_KERNEL_AUTO = 0,    /* resident if the lattice fits; else, for MicSA calls of >= 8 sweeps, multispin
-                                 if Lx % 128 == 0; else fused if Lx >= 128, else simple */
+    MICSA_KERNEL_AUTO = 0,    /* the cell sweep, or, if Lx % 128 == 0, the two-sweep multispin pass where it is
+                                 estimated faster (MicSA and walkers; heat bath and Metropolis on large
+                                 lattices: the fused sweep) */
     MICSA_KERNEL_SIMPLE = 1,  /* one launch per half sweep (bit-plane layout: instead of its one-launch sweep) */
     MICSA_KERNEL_FUSED = 2,   /* one launch per sweep, refresh fused in (Lx % 32 == 0) */
-    MICSA_KERNEL_RESIDENT = 3, /* one work-group per lattice keeps it in LDS for many sweeps (<= 102400 sites) */
+    MICSA_KERNEL_RESIDENT = 3, /* the cell sweep (<= 102400 sites, byte layout) */
     MICSA_KERNEL_MULTISPIN = 4, /* MicSA daemon sweeps on bit planes, 64 sites of a row per word (Lx % 128 == 0) */
-    MICSA_KERNEL_SLAB = 5       /* MicSA, a z plane per work-group with its neighbour planes recomputed (byte
-                                   layout, gamma = 1, Ly * Lx / 8 <= 1024): two sweeps per launch while the
-                                   lattices have fewer planes than the device has compute units (and two per
-                                   pass are set, the default), else one; AUTO takes it for lattices too large
-                                   for the resident sweep with Lx < 128 (e.g. L = 64) */
+    MICSA_KERNEL_SLAB = 5       /* the cell sweep (byte layout, gamma = 1, Ly * Lx / 8 <= 1024) */
 };
 int micsa_set_option(micsa_ctx* ctx, int32_t option, int64_t value);
 

@@ -72,7 +72,7 @@ __device__ __forceinline__ uint32_t maj32(uint32_t a, uint32_t b, uint32_t c)
     return __builtin_amdgcn_bitop3_b32(a, b, c, 0xE8);
 }
 
-// The move of msc_move_fused on 32 sites: u[0..5] are the unsatisfied-bond
+// The Creutz move on 32 sites: u[0..5] are the unsatisfied-bond
 // bits; returns the accepted flips and updates the level bits.
 __device__ __forceinline__ uint32_t cell_move(const uint32_t (&u)[6], uint32_t& m0, uint32_t& m1)
 {

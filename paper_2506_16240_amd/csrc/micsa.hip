@@ -170,6 +170,7 @@ struct micsa_ctx {
     MscTile tile2{};  // tile of the two-sweep multispin pass (follows the tile options)
     uint32_t *cdr0 = nullptr, *cdr1 = nullptr;
     int64_t cdr_rho0 = 0, cdr_n = 0, cdr_cap = 0;
+    bool captured = false;  // a sweep call was captured into a graph (see sweep_impl)
     size_t draw_room = 0;  // bytes for them (0: chosen by size)
     // several daemon (walker) families: level planes of each in two copies,
     // the copy that is current, and the parity of the wandering the planes of
@@ -193,7 +194,7 @@ struct micsa_ctx {
     bool pin_failed = false;
     uint32_t ticket = 0;
     // device-pointer logging: one row of slots [2][L][kSlots] (energy, then
-    // level sums), and the resident kernel's (U, sum m) pairs, grown on demand
+    // level sums), and the cell sweep's (U, sum m) pairs, grown on demand
     unsigned long long* logslots = nullptr;
     long long* rlog = nullptr;
     size_t rlog_cap = 0;  // entries of rlog
@@ -823,7 +824,7 @@ int launch_refresh(micsa_ctx* c, int64_t rho, double T)
 // sweeps per launch: the cell sweep) is asked for, and taken by default before
 // every other path, up to this size.
 constexpr size_t kResidentLdsMax = 150 * 1024;
-constexpr int64_t kResidentChunk = 2048;  // sweeps per resident launch
+constexpr int64_t kResidentChunk = 2048;  // sweeps per launch of a whole lattice
 
 bool resident_eligible(const micsa_ctx* c)
 {
@@ -2329,6 +2330,33 @@ int sweep_cells_canonical(micsa_ctx* c, int32_t algo, int64_t n, long long* dlog
     return MICSA_OK;
 }
 
+// A finished job of a pool that sweeps again does so on the pool's stream.
+void run_stream(micsa_ctx* c)
+{
+    if (!c || !c->sweep_stream || c->stream == c->sweep_stream) return;
+    (void)hipStreamSynchronize(c->stream);
+    c->stream = c->sweep_stream;
+}
+
+// A sweep call that is captured into a graph runs whenever the graph is
+// replayed, so it must find the state where every call leaves it, and may not
+// rely on levels that an earlier call drew into buffers a replay overwrites.
+// From the first captured call on, each one packs the planes from the state's
+// own arrays, draws what it needs, and unpacks the planes again.
+int begin_sweeps(micsa_ctx* c)
+{
+    run_stream(c);
+    hipStreamCaptureStatus on = hipStreamCaptureStatusNone;
+    if (!c->captured && c->stream && hipStreamIsCapturing(c->stream, &on) != hipSuccess) (void)hipGetLastError();
+    c->captured |= on != hipStreamCaptureStatusNone;
+    if (!c->captured) return MICSA_OK;
+    c->cdr_n = 0;
+    c->msc_drawn = -1;
+    return own_home(c);
+}
+
+int end_sweeps(micsa_ctx* c, int st) { return st || !c->captured ? st : need_home(c); }
+
 // A sweep call of this algorithm logs inside its launches (one work-group
 // per lattice).
 bool logs_in_kernel(const micsa_ctx* c, int32_t algo, int64_t n)
@@ -2342,23 +2370,24 @@ bool logs_in_kernel(const micsa_ctx* c, int32_t algo, int64_t n)
 int sweep_logging(micsa_ctx* c, int32_t algo, int64_t n, long long* dlog, int64_t stride)
 {
     if (n <= 0) return MICSA_OK;
-    if (algo == MICSA_ALGO_MICSA || algo == MICSA_ALGO_WALKERS)
-        return sweep_cells(c, n, dlog, stride, algo == MICSA_ALGO_WALKERS);
-    return sweep_cells_canonical(c, algo, n, dlog, stride);
+    if (int st = begin_sweeps(c)) return st;
+    return end_sweeps(c, algo == MICSA_ALGO_MICSA || algo == MICSA_ALGO_WALKERS
+                             ? sweep_cells(c, n, dlog, stride, algo == MICSA_ALGO_WALKERS)
+                             : sweep_cells_canonical(c, algo, n, dlog, stride));
 }
 
-// A finished job of a pool that sweeps again does so on the pool's stream.
-void run_stream(micsa_ctx* c)
-{
-    if (!c || !c->sweep_stream || c->stream == c->sweep_stream) return;
-    (void)hipStreamSynchronize(c->stream);
-    c->stream = c->sweep_stream;
-}
+int sweep_run(micsa_ctx* c, int32_t algo, int64_t n);
 
 int sweep_impl(micsa_ctx* c, int32_t algo, int64_t n)
 {
-    run_stream(c);
     if (!c) return MICSA_EINVAL;
+    if (int st = check_sweep(c, algo, n)) return st;
+    if (int st = begin_sweeps(c)) return st;
+    return end_sweeps(c, sweep_run(c, algo, n));
+}
+
+int sweep_run(micsa_ctx* c, int32_t algo, int64_t n)
+{
     int st0 = check_sweep(c, algo, n);
     if (st0) return st0;
     // walkers (gamma = 1) on the fused sweep carry their wandering into the
@@ -2696,7 +2725,7 @@ int micsa_set_schedule(micsa_ctx* ctx, const micsa_schedule* s)
     } else {
         return fail(ctx, MICSA_EINVAL, "unknown schedule kind");
     }
-    // threshold tables for every refresh of the schedule (used by the resident sweeps)
+    // threshold tables for every refresh of the schedule (read by the draws)
     const int64_t nrho = std::max<int64_t>(refresh_count(n), 1);
     const size_t o_h = (size_t)nrho * sizeof(DaemonThresholds), o_m = o_h + (size_t)nrho * sizeof(HeatBathThresholds);
     std::vector<uint8_t> tab(o_m + (size_t)nrho * sizeof(MetropolisThresholds));
@@ -3556,8 +3585,13 @@ const char* micsa_kernel_name(const micsa_ctx* ctx, int32_t algo)
                    ? (bp_one_launch(ctx) && !use_graph(ctx) ? (bp_rows(bp_launch(ctx)) ? "kb_sweep_rows" : "kb_sweep")
                                                             : "kb_micsa_half")
                    : "";
+    if (ctx && algo == MICSA_ALGO_MICSA && !use_resident(ctx) && !use_slab(ctx) && use_cells(ctx))
+        return "k_cells_sweep";
     if (ctx && algo == MICSA_ALGO_MICSA && use_msc(ctx))  // a long call runs its sweeps in pairs where it can
         return msc_one_launch(ctx) ? (msc2_fits(ctx) ? "k_msc_sweep_multi" : "k_msc_sweep") : "k_msc_half";
+    // (the names of the forms that callers ask for by option stay: lattices of
+    // the resident and slab forms run the cell sweep too)
+    if (ctx && algo == MICSA_ALGO_WALKERS && use_cells_walkers(ctx, kMscMinSweeps)) return "k_cells_sweep";
     // walkers on the fused sweeps wander on the next sweep's loads
     if (ctx && algo == MICSA_ALGO_WALKERS && use_msc(ctx, kMscMinSweeps, algo))
         return msc_one_launch(ctx) && msc2_fits(ctx) && 64 % (ctx->p.Lx / 64) == 0 ? "k_msc_sweep_multi"
@@ -3566,9 +3600,10 @@ const char* micsa_kernel_name(const micsa_ctx* ctx, int32_t algo)
         return ctx && use_fused(ctx) && ctx->gamma == 1
                    ? (ctx->temporal == 2 && sweep2_walk_eligible(ctx) ? "k_micsa_sweep2_fused" : "k_micsa_sweep_fused")
                    : "k_micsa_half+k_wander";
-    // gamma > 1 runs the per-half kernels (never resident or fused)
     if (ctx && use_resident(ctx))
         return algo == MICSA_ALGO_HEATBATH ? "k_resident<1>" : (algo == MICSA_ALGO_METROPOLIS ? "k_resident<2>" : "k_resident<0>");
+    if (ctx && (algo == MICSA_ALGO_HEATBATH || algo == MICSA_ALGO_METROPOLIS) && use_cells_canonical(ctx))
+        return "k_cells_sweep";
     if (algo == MICSA_ALGO_HEATBATH)
         return ctx && use_fused(ctx) ? "k_heatbath_sweep_fused<0>" : "k_heatbath_half<0>";
     if (algo == MICSA_ALGO_METROPOLIS)

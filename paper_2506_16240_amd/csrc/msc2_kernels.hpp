@@ -25,7 +25,7 @@
 // barrier per step.  Half h is needed from step 2h on; the step count is
 // TZ + 4T - 2.
 //
-// Refresh: the levels of a refresh sweep are drawn ahead (k_msc_draw) and
+// Refresh: the levels of a refresh sweep are drawn ahead (k_cells_draw) and
 // read in place of the stored ones -- by the host passing the drawn planes
 // as the input levels when the first sweep of the pass refreshes, and by
 // the kernel loading them for halves 2 RJ and 2 RJ + 1 when sweep RJ >= 1 of

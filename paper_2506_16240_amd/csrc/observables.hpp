@@ -194,7 +194,7 @@ __global__ void __launch_bounds__(256) k_log_from_slots(const unsigned long long
     if (D) D[l] = 4 * (long long)m;
 }
 
-// The same from the resident kernel's log of (U, sum m) pairs, n = rows x L.
+// The same from the cell sweep's log of (U, sum m) pairs, n = rows x L.
 __global__ void __launch_bounds__(256) k_log_from_pairs(const long long* __restrict__ raw, int64_t n, int64_t N,
                                                         long long* __restrict__ E, long long* __restrict__ D)
 {

@@ -403,15 +403,13 @@ int micsa_pt_create(const micsa_pt_params* p, const double* J, const double* T, 
             if (lds > 65536u && hipFuncSetAttribute((const void*)tab_kernel(g.Lx, p->houdayer != 0),
                                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
                 return fin(MICSA_EHIP);
-            if (hipMalloc(&c->ftab, T.size() * 4) != hipSuccess) {
+            if (hipMalloc(&c->ftab, T.size() * 4) != hipSuccess) {  // the records do without
                 (void)hipGetLastError();
                 c->ftab = nullptr;
-                return fin(MICSA_ENOMEM);
-            }
-            if (hipMemcpyAsync(c->ftab, T.data(), T.size() * 4, hipMemcpyHostToDevice, c->stream) != hipSuccess ||
+            } else if (hipMemcpyAsync(c->ftab, T.data(), T.size() * 4, hipMemcpyHostToDevice, c->stream) != hipSuccess ||
                 hipStreamSynchronize(c->stream) != hipSuccess)
                 return fin(MICSA_EHIP);
-            c->Gt = Gt;
+            c->Gt = c->ftab ? Gt : 0;
             c->tab_lds = lds;
         }
     }

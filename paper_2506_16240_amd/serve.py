@@ -66,11 +66,10 @@ def job_layout(spec: "JobSpec") -> tuple[int, int]:
     """(layout, lane mode) a job runs in.  L = 64 jobs of many replicas take
     the bit-plane layout with lanes = replicas: a word holds one site of up
     to 64 replicas of the instance, the couplings broadcast to every lane
-    (multispin coding of replicas, Sec. 2.5).  There it beats the byte
-    slab sweep from about 16 replicas on (1.2x at 20, 1.8x at 37, 2.4x at
-    53 on one MI355X), and loses below.  Every other job keeps the byte
-    layout: the batched resident launch for L <= 32, the multispin planes
-    for L = 128 (faster than bit planes at every replica count there).
+    (multispin coding of replicas, Sec. 2.5).  Both layouts sweep on the same
+    cell planes; the words share one set of couplings among the replicas.
+    Every other job keeps the byte layout: batched cell sweeps for L <= 32,
+    the multispin planes for L = 128.
     Results do not depend on the layout."""
     if spec.L == 64 and spec.R >= BITPLANE_MIN_REPLICAS:
         return M.LAYOUT_BITPLANE, M.LANES_REPLICAS

@@ -220,8 +220,9 @@ class BitplaneResult:
 
 def tune_bitplane(Lx: int, Ly: int, Lz: int, S: int, R: int, lane_mode: int = 0, sweeps: int = 40,
                   use_cache: bool = True, verbose: bool = False) -> BitplaneResult:
-    """Fastest bit-exact launch of the one-launch bit-plane sweep: one or two
-    planes per work-group, refresh levels drawn ahead or in place."""
+    """Fastest bit-exact launch of the bit-plane layout: the library's choice, or
+    the one-launch sweep with one or two planes per work-group, refresh levels
+    drawn ahead or in place."""
     shape = (Lx, Ly, Lz, S, R)
     key = f"{_device_name()}|bitplane|{Lx}x{Ly}x{Lz}|S{S}|R{R}|lanes{lane_mode}"
     if use_cache and (hit := _cached(key)):
@@ -230,18 +231,18 @@ def tune_bitplane(Lx: int, Ly: int, Lz: int, S: int, R: int, lane_mode: int = 0,
     ref, _ = _run(shape, seed, M.KERNEL_SIMPLE, 0, 0, sweeps, warm, False, layout=M.LAYOUT_BITPLANE,
                   lane_mode=lane_mode)
     best = None
-    for tz in (1, 2):
-        if Lz % tz:
+    # (0, 0): the library's choice, the cell sweep where it takes the lattice
+    for tz, ahead in ((0, 0), (1, 1), (1, 0), (2, 1), (2, 0)):
+        if tz and Lz % tz:
             continue
-        for ahead in (1, 0):
-            digest, us = _timed(shape, seed, M.KERNEL_AUTO, 0, tz, sweeps, warm, True, layout=M.LAYOUT_BITPLANE,
-                                opts=((M.OPT_DRAW_AHEAD, ahead),), lane_mode=lane_mode)
-            if digest != ref:
-                raise RuntimeError(f"bit-plane TZ={tz} draw-ahead {ahead} changed the result for {shape}")
-            if verbose:
-                print(f"  TZ={tz} ahead={ahead}: {us:9.2f} us/sweep", flush=True)
-            if best is None or us < best.us_per_sweep:
-                best = BitplaneResult(tz, ahead, us)
+        digest, us = _timed(shape, seed, M.KERNEL_AUTO, 0, tz, sweeps, warm, True, layout=M.LAYOUT_BITPLANE,
+                            opts=((M.OPT_DRAW_AHEAD, ahead),), lane_mode=lane_mode)
+        if digest != ref:
+            raise RuntimeError(f"bit-plane TZ={tz} draw-ahead {ahead} changed the result for {shape}")
+        if verbose:
+            print(f"  TZ={tz} ahead={ahead}: {us:9.2f} us/sweep", flush=True)
+        if best is None or us < best.us_per_sweep:
+            best = BitplaneResult(tz, ahead, us)
     if use_cache:
         _store(key, best.__dict__)
     return best

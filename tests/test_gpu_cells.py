@@ -2,6 +2,7 @@
 oracle, at the shapes where its tiles, word forms and launch lengths change."""
 import numpy as np
 import pytest
+import torch
 
 from oracle import oracle as O
 from paper_2506_16240_amd import micsa as M
@@ -221,3 +222,42 @@ def test_jobs_one_after_another(jobs_at_once):
             pool.release(j)
     assert not jobs
     pool.close()
+
+
+@pytest.mark.parametrize("algo", [M.ALGO_MICSA, M.ALGO_HEATBATH])
+@pytest.mark.parametrize("shape", [(16, 16, 16, 1, 2), (64, 64, 64, 1, 2), (128, 64, 64, 1, 40)])
+def test_captured_sweeps_replay(shape, algo):
+    """A call captured into a graph and replayed, with eager calls (which draw
+    levels of their own and move the state between its buffers) and written
+    spins in between."""
+    stream = torch.cuda.Stream()
+    g, o = M.Lattice(*shape, 0x6AF, stream=stream), O.Lattice(*shape, 0x6AF)
+    g.set_schedule(M.Schedule(M.SCHED_LINEAR, 2.5, 0.5, 60, 4))
+    os_ = O.Schedule(O.SCHED_LINEAR, 2.5, 0.5, 60, 4)
+
+    def eager(n):
+        g.sweep(algo, n)
+        o.run(algo, os_, n, 0)
+
+    def replay(k):
+        graph.replay()
+        torch.cuda.synchronize()
+        after, o.k = o.k, k
+        o.run(algo, os_, 9, 0)
+        o.k = max(after, o.k)
+        state(g, o)
+
+    eager(10)
+    state(g, o)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=stream):
+        g.sweep(algo, 9)
+    replay(10)
+    eager(8)
+    replay(10)
+    eager(8)
+    state(g, o)
+    g.write_spins(1 - o.sigma)
+    o.sigma = 1 - o.sigma
+    replay(10)
+    g.close()
