@@ -219,7 +219,7 @@ __global__ void __launch_bounds__(64) k_cells_draw_canonical(CellCanon D)
     }
     const bool some_never = th.tau[6] == 0;  // the smallest (the scalar unit is near its rate: no masks without it)
     for (int64_t cell = (int64_t)blockIdx.x * 64 + threadIdx.x; cell < cg.plane; cell += (int64_t)gridDim.x * 64) {
-        const int64_t row = cell / cg.W;
+        const int64_t row = cg.W == 1 ? cell : cell / cg.W;  // (a division is a good part of a short row's work)
         const int w = (int)(cell - row * cg.W), n4 = min(32, cg.g.Kx - 32 * w) >> 2;
         const uint32_t base = (uint32_t)((row * cg.g.Kx + 32 * w) >> 2);
         uint32_t b[K] = {};

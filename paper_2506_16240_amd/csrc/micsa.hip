@@ -170,6 +170,8 @@ struct micsa_ctx {
     MscTile tile2{};  // tile of the two-sweep multispin pass (follows the tile options)
     uint32_t *cdr0 = nullptr, *cdr1 = nullptr;
     int64_t cdr_rho0 = 0, cdr_n = 0, cdr_cap = 0;
+    uint32_t* cdc = nullptr;  // the baselines' drawn comparisons, where the levels' buffer holds too few sweeps
+    size_t cdc_bytes = 0;
     bool captured = false;  // a sweep call was captured into a graph (see sweep_impl)
     size_t draw_room = 0;  // bytes for them (0: chosen by size)
     // several daemon (walker) families: level planes of each in two copies,
@@ -2293,12 +2295,31 @@ int sweep_cells_canonical(micsa_ctx* c, int32_t algo, int64_t n, long long* dlog
     c->home_ok = false;
     c->cdr_n = 0;  // the buffer holds the baselines' draws from here on
     if (dlog && (st = enqueue_level_sum(c, c->red))) return st;  // the levels of every logged row
-    const int64_t room = std::min<int64_t>(4 * plane * c->cdr_cap / (2 * K * plane), 4096);  // sweeps drawn at once
+    // Sweeps drawn at once: those that fit the levels' buffer, or one of its own
+    // of up to 128 MiB where that gives more and a launch could use them (512
+    // lattices of 32^3: one sweep per draw and launch 26 us per sweep, ten 15).
+    const size_t per = (size_t)2 * K * (size_t)plane * 4;
+    int64_t room = std::min<int64_t>((int64_t)((size_t)4 * plane * c->cdr_cap * 4 / per), 4096);
+    const int64_t useful = std::min<int64_t>({n, c->plan.sweeps > 0 ? c->plan.sweeps : 20, (int64_t)(((size_t)128 << 20) / per)});
+    uint32_t* draws = c->cdr0;
+    if (useful > room) {
+        if (c->cdc_bytes < per * (size_t)useful) {
+            if (c->cdc) {
+                (void)hipStreamSynchronize(c->stream);
+                ctx_free(c, c->cdc);
+            }
+            c->cdc_bytes = ctx_alloc(c, c->cdc, per * (size_t)useful) ? per * (size_t)useful : 0;
+        }
+        if (c->cdc_bytes) {
+            draws = c->cdc;
+            room = useful;
+        }
+    }
     while (c->k < k_end) {
         const int64_t len = std::min<int64_t>(k_end - c->k, room), k_draw = c->k;
         CellCanon D{};
         D.cg = cg;
-        D.dr = c->cdr0;
+        D.dr = draws;
         D.tab = canonical_table(c, algo);
         D.k0 = k_draw;
         D.n = (int32_t)len;
@@ -2318,7 +2339,7 @@ int sweep_cells_canonical(micsa_ctx* c, int32_t algo, int64_t n, long long* dlog
             const int64_t most = c->plan.sweeps > 0 ? c->plan.sweeps : len;
             const int64_t m = std::min(k_draw + len - c->k, dlog ? log_most(c, most, stride) : most);
             CellSweep J{};
-            J.dr0 = c->cdr0 + (c->k - k_draw) * 2 * K * plane;
+            J.dr0 = draws + (c->k - k_draw) * 2 * K * plane;
             cell_log(c, J, dlog, c->k - k_first, stride);
             J.k0 = c->k;
             J.n = (int32_t)m;
