@@ -70,6 +70,7 @@ struct JobStore {
         int device;
         size_t bytes;
         void* p;
+        bool kept = false;  // a captured graph may hold its address
     };
     std::mutex lock;
     std::vector<Block> idle;  // oldest first
@@ -172,7 +173,9 @@ struct micsa_ctx {
     int64_t cdr_rho0 = 0, cdr_n = 0, cdr_cap = 0;
     uint32_t* cdc = nullptr;  // the baselines' drawn comparisons, where the levels' buffer holds too few sweeps
     size_t cdc_bytes = 0;
-    bool captured = false;  // a sweep call was captured into a graph (see sweep_impl)
+    bool captured = false;   // a sweep call was captured into a graph (see begin_sweeps)
+    bool capturing = false;  // the sweep call under way is being captured
+    int depth = 0;           // begin_sweeps not yet ended
     size_t draw_room = 0;  // bytes for them (0: chosen by size)
     // several daemon (walker) families: level planes of each in two copies,
     // the copy that is current, and the parity of the wandering the planes of
@@ -262,7 +265,7 @@ constexpr size_t arena_size(size_t bytes) { return (bytes + 255) / 256 * 256; }
 // at most a quarter larger, else a new one, for which idle ones make room.
 void* own_block(micsa_ctx* c, size_t bytes)
 {
-    JobStore::Block b{c->device, arena_size(std::max<size_t>(bytes, 1)), nullptr};
+    JobStore::Block b{c->device, arena_size(std::max<size_t>(bytes, 1)), nullptr, false};
     if (JobStore* s = c->store) {
         std::lock_guard<std::mutex> hold(s->lock);
         size_t best = s->idle.size();
@@ -309,8 +312,9 @@ bool ctx_alloc(micsa_ctx* c, T*& p, size_t bytes)
     return (p = static_cast<T*>(ctx_alloc(c, bytes))) != nullptr;
 }
 
-void drop_block(micsa_ctx* c, const JobStore::Block& b)
+void drop_block(micsa_ctx* c, JobStore::Block b)
 {
+    b.kept = false;
     if (JobStore* s = c->store) {
         std::lock_guard<std::mutex> hold(s->lock);
         s->idle.push_back(b);
@@ -322,11 +326,13 @@ void drop_block(micsa_ctx* c, const JobStore::Block& b)
 }
 
 // Free a block before its context (work on it may be queued; a part of the
-// arena stays until the context goes).
+// arena, and a block that a captured graph may hold, stay until the context
+// goes).
 void ctx_free(micsa_ctx* c, void* p)
 {
     for (size_t i = 0; p && i < c->owned.size(); ++i)
         if (c->owned[i].p == p) {
+            if (c->owned[i].kept || c->capturing) return;
             if (c->store) {  // the next owner does not wait for this one's streams
                 (void)hipStreamSynchronize(c->stream);
                 if (c->draw_stream) (void)hipStreamSynchronize(c->draw_stream);
@@ -337,16 +343,23 @@ void ctx_free(micsa_ctx* c, void* p)
         }
 }
 
+// The same for a buffer of the sweeps that a larger one replaces: what is
+// queued on it ends first (nothing is waited for in a captured call, whose
+// blocks all stay).
+void ctx_retire(micsa_ctx* c, void* p)
+{
+    if (!p || c->capturing) return;
+    (void)hipStreamSynchronize(c->stream);
+    ctx_free(c, p);
+}
+
 // The workspace, or a block of its own where that would be too large to keep;
 // given back before the call ends, its work finished.
 void* work_take(micsa_ctx* c, size_t bytes)
 {
     if (bytes > (size_t)16 << 20) return ctx_alloc(c, bytes);
     if (c->work_cap < bytes) {
-        if (c->work) {
-            (void)hipStreamSynchronize(c->stream);
-            ctx_free(c, c->work);
-        }
+        ctx_retire(c, c->work);
         const size_t n = std::max<size_t>(bytes, (size_t)64 << 10);
         c->work = ctx_alloc(c, n);
         c->work_cap = c->work ? n : 0;
@@ -2090,11 +2103,8 @@ bool log_room(micsa_ctx* c, int64_t rows)
     const int64_t row = (int64_t)c->L * c->plan.block;
     const int64_t want = std::max<int64_t>(1, std::min<int64_t>(rows, ((int64_t)2 << 20) / row));
     if (c->lograw_rows >= want) return true;
-    if (c->lograw) {
-        (void)hipStreamSynchronize(c->stream);
-        ctx_free(c, c->lograw);
-        c->lograw_rows = 0;
-    }
+    ctx_retire(c, c->lograw);
+    c->lograw_rows = 0;
     if (!ctx_alloc(c, c->lograw, (size_t)(want * row) * 4)) return false;
     c->lograw_rows = want;
     return true;
@@ -2304,10 +2314,7 @@ int sweep_cells_canonical(micsa_ctx* c, int32_t algo, int64_t n, long long* dlog
     uint32_t* draws = c->cdr0;
     if (useful > room) {
         if (c->cdc_bytes < per * (size_t)useful) {
-            if (c->cdc) {
-                (void)hipStreamSynchronize(c->stream);
-                ctx_free(c, c->cdc);
-            }
+            ctx_retire(c, c->cdc);
             c->cdc_bytes = ctx_alloc(c, c->cdc, per * (size_t)useful) ? per * (size_t)useful : 0;
         }
         if (c->cdc_bytes) {
@@ -2359,24 +2366,49 @@ void run_stream(micsa_ctx* c)
     c->stream = c->sweep_stream;
 }
 
+bool stream_captured(hipStream_t s)
+{
+    hipStreamCaptureStatus on = hipStreamCaptureStatusNone;
+    if (s && hipStreamIsCapturing(s, &on) != hipSuccess) (void)hipGetLastError();
+    return on != hipStreamCaptureStatusNone;
+}
+
+// Every block that the context has now stays until the context goes.
+void keep_blocks(micsa_ctx* c)
+{
+    for (JobStore::Block& b : c->owned) b.kept = true;
+}
+
 // A sweep call that is captured into a graph runs whenever the graph is
 // replayed, so it must find the state where every call leaves it, and may not
 // rely on levels that an earlier call drew into buffers a replay overwrites.
 // From the first captured call on, each one packs the planes from the state's
-// own arrays, draws what it needs, and unpacks the planes again.
+// own arrays, draws what it needs, and unpacks the planes again.  The graph
+// holds the addresses of the call's buffers: none of them is freed before the
+// context, also where a later call needs a larger one.
 int begin_sweeps(micsa_ctx* c)
 {
+    if (c->depth++) return MICSA_OK;
     run_stream(c);
-    hipStreamCaptureStatus on = hipStreamCaptureStatusNone;
-    if (!c->captured && c->stream && hipStreamIsCapturing(c->stream, &on) != hipSuccess) (void)hipGetLastError();
-    c->captured |= on != hipStreamCaptureStatusNone;
+    c->capturing = stream_captured(c->stream);
+    if (c->capturing) {
+        c->captured = true;
+        keep_blocks(c);
+    }
     if (!c->captured) return MICSA_OK;
     c->cdr_n = 0;
     c->msc_drawn = -1;
     return own_home(c);
 }
 
-int end_sweeps(micsa_ctx* c, int st) { return st || !c->captured ? st : need_home(c); }
+int end_sweeps(micsa_ctx* c, int st)
+{
+    if (--c->depth) return st;
+    if (!st && c->captured) st = need_home(c);
+    if (c->capturing) keep_blocks(c);
+    c->capturing = false;
+    return st;
+}
 
 // A sweep call of this algorithm logs inside its launches (one work-group
 // per lattice).
@@ -2391,7 +2423,7 @@ bool logs_in_kernel(const micsa_ctx* c, int32_t algo, int64_t n)
 int sweep_logging(micsa_ctx* c, int32_t algo, int64_t n, long long* dlog, int64_t stride)
 {
     if (n <= 0) return MICSA_OK;
-    if (int st = begin_sweeps(c)) return st;
+    if (int st = begin_sweeps(c)) return end_sweeps(c, st);
     return end_sweeps(c, algo == MICSA_ALGO_MICSA || algo == MICSA_ALGO_WALKERS
                              ? sweep_cells(c, n, dlog, stride, algo == MICSA_ALGO_WALKERS)
                              : sweep_cells_canonical(c, algo, n, dlog, stride));
@@ -2403,7 +2435,7 @@ int sweep_impl(micsa_ctx* c, int32_t algo, int64_t n)
 {
     if (!c) return MICSA_EINVAL;
     if (int st = check_sweep(c, algo, n)) return st;
-    if (int st = begin_sweeps(c)) return st;
+    if (int st = begin_sweeps(c)) return end_sweeps(c, st);
     return end_sweeps(c, sweep_run(c, algo, n));
 }
 
@@ -2785,32 +2817,21 @@ int micsa_set_schedule(micsa_ctx* ctx, const micsa_schedule* s)
 
 int micsa_sweep(micsa_ctx* ctx, int32_t algo, int64_t n) { return sweep_impl(ctx, algo, n); }
 
-int micsa_sweep_logged_d(micsa_ctx* ctx, int32_t algo, int64_t n, int64_t stride, int64_t* E_log,
-                         int64_t* D_log)
+static int sweep_logged_d(micsa_ctx* ctx, int32_t algo, int64_t n, int64_t stride, int64_t* E_log, int64_t* D_log)
 {
-    if (!ctx) return MICSA_EINVAL;
-    if (stride < 1) return fail(ctx, MICSA_EINVAL, "stride must be >= 1");
-    if (!ctx->sched.set) return fail(ctx, MICSA_ESTATE, "no schedule installed");
-    if (n < 0 || ctx->k + n > ctx->sched.n_sweeps) return fail(ctx, MICSA_ERANGE, "sweeps beyond the schedule");
-    run_stream(ctx);
     const int64_t rows = n / stride;
     const int L = ctx->L;
     const int64_t N = n_sites(ctx);
-    int st = check_sweep(ctx, algo, n);
-    if (st) return st;
-    if (rows == 0 || (!E_log && !D_log)) return sweep_impl(ctx, algo, n);
+    int st;
     if (logs_in_kernel(ctx, algo, n) && log_room(ctx, rows)) {
         const size_t need = (size_t)rows * L * 2;
         if (need > ctx->rlog_cap) {
-            // the old buffer may still be in use by enqueued work
-            if (ctx->rlog) {
-                HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
-                ctx_free(ctx, ctx->rlog);
-                ctx->rlog = nullptr;
-                ctx->rlog_cap = 0;
-            }
-            if (!ctx_alloc(ctx, ctx->rlog, need * 8)) return fail(ctx, MICSA_ENOMEM, "log buffer");
-            ctx->rlog_cap = need;
+            // (by a factor of two where the old one stays)
+            const size_t cap = ctx->captured ? std::max(need, 2 * ctx->rlog_cap) : need;
+            ctx_retire(ctx, ctx->rlog);  // enqueued work may still use it
+            ctx->rlog_cap = 0;
+            if (!ctx_alloc(ctx, ctx->rlog, cap * 8)) return fail(ctx, MICSA_ENOMEM, "log buffer");
+            ctx->rlog_cap = cap;
         }
         if ((algo != MICSA_ALGO_WALKERS && (st = settle_wander(ctx))) ||
             (st = sweep_logging(ctx, algo, n, ctx->rlog, stride)))
@@ -2834,6 +2855,20 @@ int micsa_sweep_logged_d(micsa_ctx* ctx, int32_t algo, int64_t n, int64_t stride
         if ((st = check_launch(ctx, "k_log_from_slots"))) return st;
     }
     return n > rows * stride ? sweep_impl(ctx, algo, n - rows * stride) : MICSA_OK;
+}
+
+int micsa_sweep_logged_d(micsa_ctx* ctx, int32_t algo, int64_t n, int64_t stride, int64_t* E_log,
+                         int64_t* D_log)
+{
+    if (!ctx) return MICSA_EINVAL;
+    if (stride < 1) return fail(ctx, MICSA_EINVAL, "stride must be >= 1");
+    if (!ctx->sched.set) return fail(ctx, MICSA_ESTATE, "no schedule installed");
+    if (n < 0 || ctx->k + n > ctx->sched.n_sweeps) return fail(ctx, MICSA_ERANGE, "sweeps beyond the schedule");
+    if (int st = check_sweep(ctx, algo, n)) return st;
+    if (n / stride == 0 || (!E_log && !D_log)) return sweep_impl(ctx, algo, n);
+    // (the buffers of the logs belong to the call: see begin_sweeps)
+    const int st = begin_sweeps(ctx);
+    return end_sweeps(ctx, st ? st : sweep_logged_d(ctx, algo, n, stride, E_log, D_log));
 }
 
 int micsa_sweep_logged(micsa_ctx* ctx, int32_t algo, int64_t n, int64_t stride, int64_t* E_log, int64_t* D_log)
