@@ -146,6 +146,15 @@ int micsa_set_schedule(micsa_ctx* ctx, const micsa_schedule* s);
    MICSA the daemons are refreshed before every refresh-point sweep at the
    temperature of that refresh; a sweep is the even half then the odd half.
    Asynchronous: returns once the work is enqueued.
+   A call on a stream that is being captured becomes part of the graph, with
+   its sweep indices and temperatures: every replay sweeps the state that the
+   last call or replay left (order them as any work on one stream), at those
+   indices.  k advances once, at the capture.  What a captured call uses of
+   the context's memory stays allocated until the context is destroyed, also
+   where later calls need larger buffers or install another schedule.  Calls
+   that wait for the device (reads, writes, micsa_save, micsa_load,
+   micsa_set_schedule, micsa_sweep_logged) are refused with ESTATE while the
+   context's stream is captured; nothing is changed then.
    Errors: ESTATE (no schedule), ERANGE (k+n > n_sweeps), EINVAL. */
 int micsa_sweep(micsa_ctx* ctx, int32_t algo, int64_t n);
 

@@ -47,6 +47,19 @@ struct Schedule {
     std::vector<double> table;
 };
 
+// Where the state of a captured context lies between calls (see rest_state):
+// in the planes or in the layout's own arrays, in which copies, and the
+// wanderings that the levels there owe.
+struct Rest {
+    bool planes = false;
+    uint8_t *spin = nullptr, *dem = nullptr;
+    uint64_t *bspin = nullptr, *bdm0 = nullptr, *bdm1 = nullptr;
+    uint64_t *ms = nullptr, *md0 = nullptr, *md1 = nullptr;
+    uint8_t fcur[6] = {};
+    int32_t fowed[6] = {};
+    int32_t pend = -1;
+};
+
 // How the cell sweep runs a context's lattices.
 struct CellPlan {
     bool ok = false;
@@ -176,6 +189,7 @@ struct micsa_ctx {
     bool captured = false;   // a sweep call was captured into a graph (see begin_sweeps)
     bool capturing = false;  // the sweep call under way is being captured
     int depth = 0;           // begin_sweeps not yet ended
+    Rest rest;
     size_t draw_room = 0;  // bytes for them (0: chosen by size)
     // several daemon (walker) families: level planes of each in two copies,
     // the copy that is current, and the parity of the wandering the planes of
@@ -234,6 +248,7 @@ int fail(micsa_ctx* c, int status, const std::string& msg)
 
 int need_home(micsa_ctx* c);
 int own_home(micsa_ctx* c);
+int rest_state(micsa_ctx* c);
 
 #define HIP_TRY(ctx, call)                                                                       \
     do {                                                                                         \
@@ -1502,7 +1517,9 @@ CellLevels cell_levels(const micsa_ctx* c)
 // anything reads them).
 int need_home(micsa_ctx* c)
 {
-    if (c->home_ok) return MICSA_OK;
+    // (between calls of a captured context a replay may have moved on the planes)
+    const bool replayed = c->captured && c->rest.planes && c->planes_ok && c->depth == 0;
+    if (c->home_ok && !replayed) return MICSA_OK;
     const CellGeom cg = cell_geom(c);
     {
         TimedLaunch t(c, kTimeReduce);
@@ -1993,7 +2010,7 @@ CellDraw cells_draw_slice(micsa_ctx* c, int64_t kr, int64_t k_end)
     const int32_t P = c->sched.period;
     const int64_t rho = refresh_index(kr, P);
     const int64_t in_call = refresh_index(k_end - 1, P) - rho + 1;
-    const int64_t fill = 32768 / std::max<int64_t>(1, cg.plane * c->L);
+    const int64_t fill = c->capturing ? 0 : 32768 / std::max<int64_t>(1, cg.plane * c->L);
     const int64_t n = std::max<int64_t>(
         1, std::min<int64_t>({std::max(in_call, fill), c->cdr_cap, refresh_count(c->sched) - rho}));
     CellDraw D{};
@@ -2373,6 +2390,13 @@ bool stream_captured(hipStream_t s)
     return on != hipStreamCaptureStatusNone;
 }
 
+// Calls that wait for the stream: refused before they change anything.
+int refuse_capture(micsa_ctx* c)
+{
+    return stream_captured(c->stream) ? fail(c, MICSA_ESTATE, "this call waits for its stream, which is being captured")
+                                      : MICSA_OK;
+}
+
 // Every block that the context has now stays until the context goes.
 void keep_blocks(micsa_ctx* c)
 {
@@ -2380,34 +2404,117 @@ void keep_blocks(micsa_ctx* c)
 }
 
 // A sweep call that is captured into a graph runs whenever the graph is
-// replayed, so it must find the state where every call leaves it, and may not
-// rely on levels that an earlier call drew into buffers a replay overwrites.
-// From the first captured call on, each one packs the planes from the state's
-// own arrays, draws what it needs, and unpacks the planes again.  The graph
-// holds the addresses of the call's buffers: none of them is freed before the
-// context, also where a later call needs a larger one.
+// replayed: it must find the state where every call and every replay leaves
+// it, may not rely on levels that an earlier call drew into buffers a replay
+// overwrites, and the buffers it holds the addresses of must live as long as
+// the context.  So the place where the state lies when the first call is
+// captured (the planes if they are current, else the layout's own arrays: no
+// settling of earlier work becomes part of the graph), with the copies it lies
+// in and the wanderings it owes, is where every later call that changes the
+// state puts it back (rest_state), every sweep call draws what it needs, and
+// no buffer is freed before the context.
 int begin_sweeps(micsa_ctx* c)
 {
     if (c->depth++) return MICSA_OK;
     run_stream(c);
     c->capturing = stream_captured(c->stream);
     if (c->capturing) {
-        c->captured = true;
         keep_blocks(c);
+        if (!c->captured) {
+            Rest& x = c->rest;
+            x.planes = c->planes_ok;
+            x.spin = c->spin, x.dem = c->dem;
+            x.bspin = c->bspin, x.bdm0 = c->bdm0, x.bdm1 = c->bdm1;
+            x.ms = c->ms, x.md0 = c->md0, x.md1 = c->md1;
+            std::copy_n(c->fcur, 6, x.fcur);
+            std::copy_n(c->fowed, 6, x.fowed);
+            x.pend = c->pend_wander;
+            (x.planes ? c->home_ok : c->planes_ok) = false;
+            c->captured = true;
+        }
     }
     if (!c->captured) return MICSA_OK;
     c->cdr_n = 0;
     c->msc_drawn = -1;
-    return own_home(c);
+    if (c->rest.planes) c->home_ok = false;  // (read before a replay)
+    return MICSA_OK;
 }
 
 int end_sweeps(micsa_ctx* c, int st)
 {
     if (--c->depth) return st;
-    if (!st && c->captured) st = need_home(c);
+    if (!st) st = rest_state(c);
     if (c->capturing) keep_blocks(c);
     c->capturing = false;
     return st;
+}
+
+// The state of a captured context back to where it rests: copied where it
+// ended in the other copy of its arrays; by way of the layout's own arrays
+// where its levels owe other wanderings (which are exchanges: applied once
+// more, they are owed again) or where it has to change its layout.
+template <class T>
+int rest_copy(micsa_ctx* c, T*& now, T*& other, T* place, size_t bytes)
+{
+    if (now == place) return MICSA_OK;
+    k_copy_u64<<<(unsigned)std::min<size_t>((bytes / 8 + 255) / 256, 4096), 256, 0, c->stream>>>(
+        reinterpret_cast<const uint64_t*>(now), (int64_t)(bytes / 8), reinterpret_cast<uint64_t*>(place));
+    other = now;
+    now = place;
+    return check_launch(c, "k_copy_u64");
+}
+
+// The end of a synchronous call that has changed the state.
+int rest_and_wait(micsa_ctx* c)
+{
+    if (int st = rest_state(c)) return st;
+    HIP_TRY(c, hipStreamSynchronize(c->stream));
+    return MICSA_OK;
+}
+
+int rest_state(micsa_ctx* c)
+{
+    if (!c->captured) return MICSA_OK;
+    const Rest& x = c->rest;
+    const size_t plane_bytes = (size_t)c->L * 2 * (size_t)cell_geom(c).plane * 4;
+    int st;
+    if (x.planes && c->planes_ok && c->pend_wander == x.pend &&
+        (c->gamma == 1 || (std::equal(x.fcur, x.fcur + 6, c->fcur) && std::equal(x.fowed, x.fowed + 6, c->fowed)))) {
+        c->home_ok = false;
+        if ((st = rest_copy(c, c->ms, c->ms_alt, x.ms, plane_bytes))) return st;
+        if ((st = rest_copy(c, c->md0, c->md0_alt, x.md0, plane_bytes))) return st;
+        return rest_copy(c, c->md1, c->md1_alt, x.md1, plane_bytes);
+    }
+    if ((st = own_home(c))) return st;
+    if (c->pend_wander != x.pend) {
+        if (c->pend_wander >= 0 && (st = launch_wander(c, c->pend_wander))) return st;
+        c->pend_wander = -1;
+        if (x.pend >= 0 && (st = launch_wander(c, x.pend))) return st;
+        c->pend_wander = x.pend;
+    }
+    if (x.planes) {
+        WanderParity wp{{-1, -1, -1, -1, -1, -1}};
+        bool owes = false;
+        for (int a = 0; a < c->gamma && c->gamma > 1; ++a) owes = (wp.p[a] = x.fowed[a]) >= 0 || owes;
+        if (owes && (st = launch_wander_families(c, wp))) return st;
+        if (c->ms != x.ms) std::swap(c->ms, c->ms_alt);
+        if (c->md0 != x.md0) std::swap(c->md0, c->md0_alt);
+        if (c->md1 != x.md1) std::swap(c->md1, c->md1_alt);
+        std::copy_n(x.fcur, 6, c->fcur);
+        if ((st = need_planes(c))) return st;
+        std::copy_n(x.fowed, 6, c->fowed);
+        c->home_ok = false;
+        return MICSA_OK;
+    }
+    if (c->bit) {
+        const size_t bytes = (size_t)word_lattices(c) * 2 * (size_t)c->g.Nh * 8;
+        if ((st = rest_copy(c, c->bspin, c->bspin_alt, x.bspin, bytes))) return st;
+        if ((st = rest_copy(c, c->bdm0, c->bdm0_alt, x.bdm0, bytes))) return st;
+        return rest_copy(c, c->bdm1, c->bdm1_alt, x.bdm1, bytes);
+    }
+    const size_t bytes = (size_t)c->L * 2 * (size_t)c->g.Nh;
+    if ((st = rest_copy(c, c->spin, c->spin_alt, x.spin, bytes))) return st;
+    return rest_copy(c, c->dem, c->dem_alt, x.dem, bytes * (size_t)c->gamma);
 }
 
 // A sweep call of this algorithm logs inside its launches (one work-group
@@ -2651,6 +2758,10 @@ static int create_ctx(const micsa_params* p, hipStream_t stream, size_t draw_roo
         return st;
     }
     c->draw_room = draw_room;
+    if (stream_captured(stream)) {  // the initial state is no part of a graph
+        delete c;
+        return MICSA_EHIP;
+    }
     const Geom& g = c->g;
 
     c->store = store;
@@ -2753,6 +2864,7 @@ int micsa_destroy(micsa_ctx* ctx)
 int micsa_set_schedule(micsa_ctx* ctx, const micsa_schedule* s)
 {
     if (!ctx) return MICSA_EINVAL;
+    if (int st_ = refuse_capture(ctx)) return st_;
     if (!s) return fail(ctx, MICSA_EINVAL, "null schedule");
     if (s->refresh_period < 0) return fail(ctx, MICSA_EINVAL, "refresh_period < 0");
     if (s->n_sweeps < 0) return fail(ctx, MICSA_EINVAL, "n_sweeps < 0");
@@ -2874,6 +2986,7 @@ int micsa_sweep_logged_d(micsa_ctx* ctx, int32_t algo, int64_t n, int64_t stride
 int micsa_sweep_logged(micsa_ctx* ctx, int32_t algo, int64_t n, int64_t stride, int64_t* E_log, int64_t* D_log)
 {
     if (!ctx) return MICSA_EINVAL;
+    if (int st_ = refuse_capture(ctx)) return st_;
     if (stride < 1) return fail(ctx, MICSA_EINVAL, "stride must be >= 1");
     if (!ctx->sched.set) return fail(ctx, MICSA_ESTATE, "no schedule installed");
     if (n < 0 || ctx->k + n > ctx->sched.n_sweeps) return fail(ctx, MICSA_ERANGE, "sweeps beyond the schedule");
@@ -2939,6 +3052,7 @@ static int read_red(micsa_ctx* c, int64_t n, std::vector<int64_t>& out) { return
 int micsa_read_energy(micsa_ctx* ctx, int64_t* E)
 {
     if (!ctx || !E) return MICSA_EINVAL;
+    if (int st_ = refuse_capture(ctx)) return st_;
     int st = enqueue_energy(ctx, ctx->red);
     std::vector<int64_t> U;
     if (st || (st = read_red(ctx, ctx->L, U))) return st;
@@ -2950,6 +3064,7 @@ int micsa_read_energy(micsa_ctx* ctx, int64_t* E)
 int micsa_read_energy_tally(micsa_ctx* ctx, int64_t* E)
 {
     if (!ctx || !E) return MICSA_EINVAL;
+    if (int st_ = refuse_capture(ctx)) return st_;
     if (ctx->bit && !ctx->tally_ok)
         return fail(ctx, MICSA_ESTATE, "the bit-plane tally is kept by the one-launch sweep only (a per-half "
                                        "sweep ran since the spins were last set)");
@@ -2963,6 +3078,7 @@ int micsa_read_energy_tally(micsa_ctx* ctx, int64_t* E)
 int micsa_read_demon_energy(micsa_ctx* ctx, int64_t* D)
 {
     if (!ctx || !D) return MICSA_EINVAL;
+    if (int st_ = refuse_capture(ctx)) return st_;
     int st = enqueue_level_sum(ctx, ctx->red);
     std::vector<int64_t> v;
     if (st || (st = read_red(ctx, ctx->L, v))) return st;
@@ -3022,6 +3138,7 @@ static C4Geom c4_geom(const micsa_ctx* c)
 int micsa_read_c4(micsa_ctx* ctx, int64_t* G)
 {
     if (!ctx || !G) return MICSA_EINVAL;
+    if (int st_ = refuse_capture(ctx)) return st_;
     if (int st_ = need_home(ctx)) return st_;
     if (ctx->p.n_replicas < 2) return fail(ctx, MICSA_EINVAL, "C4 needs at least two replicas");
     const C4Geom cg = c4_geom(ctx);
@@ -3080,6 +3197,7 @@ size_t align256(size_t n) { return (n + 255) & ~(size_t)255; }
 int micsa_read_c4_static(micsa_ctx* ctx, int64_t* G)
 {
     if (!ctx || !G) return MICSA_EINVAL;
+    if (int st_ = refuse_capture(ctx)) return st_;
     if (int st_ = need_home(ctx)) return st_;
     if (ctx->p.n_replicas < 2) return fail(ctx, MICSA_EINVAL, "C4 needs at least two replicas");
     const C4Geom cg = c4_geom(ctx);
@@ -3133,6 +3251,7 @@ int micsa_read_c4_static(micsa_ctx* ctx, int64_t* G)
 int micsa_read_xi(micsa_ctx* ctx, double* xi12, double* xi23)
 {
     if (!ctx || !xi12 || !xi23) return MICSA_EINVAL;
+    if (int st_ = refuse_capture(ctx)) return st_;
     if (int st_ = need_home(ctx)) return st_;
     if (ctx->p.n_replicas < 2) return fail(ctx, MICSA_EINVAL, "xi needs at least two replicas");
     const C4Geom cg = c4_geom(ctx);
@@ -3168,6 +3287,7 @@ int micsa_read_xi(micsa_ctx* ctx, double* xi12, double* xi23)
 int micsa_read_overlap(micsa_ctx* ctx, int32_t a, int32_t b, int64_t* Q)
 {
     if (!ctx || !Q) return MICSA_EINVAL;
+    if (int st_ = refuse_capture(ctx)) return st_;
     if (a < 0 || b < 0 || a >= ctx->p.n_replicas || b >= ctx->p.n_replicas || a == b)
         return fail(ctx, MICSA_EINVAL, "replica indices out of range or equal");
     const int S = ctx->p.n_samples;
@@ -3269,6 +3389,7 @@ static int read_words(micsa_ctx* ctx, const uint64_t* w0, const uint64_t* w1, ui
 int micsa_read_spins(micsa_ctx* ctx, uint8_t* sigma)
 {
     if (!ctx || !sigma) return MICSA_EINVAL;
+    if (int st_ = refuse_capture(ctx)) return st_;
     if (int st_ = need_home(ctx)) return st_;
     if (ctx->bit) return read_words(ctx, ctx->bspin, nullptr, sigma);
     return read_state(ctx, ctx->spin, sigma, ctx->L, 1);  // bit 0: even bytes also hold their bonds
@@ -3277,16 +3398,18 @@ int micsa_read_spins(micsa_ctx* ctx, uint8_t* sigma)
 int micsa_read_demons(micsa_ctx* ctx, uint8_t* m)
 {
     if (!ctx || !m) return MICSA_EINVAL;
+    if (int st_ = refuse_capture(ctx)) return st_;
     if (int st_ = need_home(ctx)) return st_;
     if (ctx->bit) return read_words(ctx, ctx->bdm0, ctx->bdm1, m);
-    const int st = settle_wander(ctx);
-    if (st) return st;
-    return read_state(ctx, ctx->dem, m, (int64_t)ctx->L * ctx->gamma);
+    int st = settle_wander(ctx);
+    if (!st) st = read_state(ctx, ctx->dem, m, (int64_t)ctx->L * ctx->gamma);
+    return st || !ctx->captured ? st : rest_and_wait(ctx);
 }
 
 int micsa_read_couplings(micsa_ctx* ctx, uint8_t* j)
 {
     if (!ctx || !j) return MICSA_EINVAL;
+    if (int st_ = refuse_capture(ctx)) return st_;
     if (int st_ = need_home(ctx)) return st_;
     const Geom& g = ctx->g;
     const int S = ctx->p.n_samples;
@@ -3381,23 +3504,29 @@ static int write_words(micsa_ctx* ctx, uint64_t* w0, uint64_t* w1, const uint8_t
 int micsa_write_spins(micsa_ctx* ctx, const uint8_t* sigma)
 {
     if (!ctx || !sigma) return MICSA_EINVAL;
+    if (int st_ = refuse_capture(ctx)) return st_;
     if (int st_ = own_home(ctx)) return st_;
     int st = ctx->bit ? write_words(ctx, ctx->bspin, nullptr, sigma, 1) : write_state(ctx, ctx->spin, sigma, 1, ctx->L);
     if (!st && !ctx->bit) st = enqueue_bonds(ctx);  // the written bytes hold spins only: restore the bond bits
-    if (st) return st;
+    if (st) {
+        (void)rest_and_wait(ctx);
+        return st;
+    }
     if ((st = tally_from_state(ctx))) return st;
     ctx->tally_ok = true;
-    return MICSA_OK;
+    return ctx->captured ? rest_and_wait(ctx) : MICSA_OK;
 }
 
 int micsa_write_demons(micsa_ctx* ctx, const uint8_t* m)
 {
     if (!ctx || !m) return MICSA_EINVAL;
+    if (int st_ = refuse_capture(ctx)) return st_;
     if (int st_ = own_home(ctx)) return st_;
-    if (ctx->bit) return write_words(ctx, ctx->bdm0, ctx->bdm1, m, 3);
-    const int st = write_state(ctx, ctx->dem, m, 3, (int64_t)ctx->L * ctx->gamma);
+    const int st = ctx->bit ? write_words(ctx, ctx->bdm0, ctx->bdm1, m, 3)
+                            : write_state(ctx, ctx->dem, m, 3, (int64_t)ctx->L * ctx->gamma);
     if (!st) ctx->pend_wander = -1;  // the written daemons are where they are
-    return st;
+    const int back = rest_and_wait(ctx);
+    return st ? st : back;
 }
 
 // ------------------------------------------------------------- checkpoint
@@ -3448,6 +3577,7 @@ bool same_params(const micsa_params& a, const micsa_params& b)
 int micsa_save(micsa_ctx* ctx, void* buf, size_t* len)
 {
     if (!ctx || !len) return MICSA_EINVAL;
+    if (int st_ = refuse_capture(ctx)) return st_;
     if (int st_ = need_home(ctx)) return st_;
     const int64_t T_len = ctx->sched.set ? (int64_t)ctx->sched.table.size() : 0;
     const size_t total = ck_bytes(ctx, T_len);
@@ -3503,6 +3633,7 @@ int micsa_save(micsa_ctx* ctx, void* buf, size_t* len)
 int micsa_load(micsa_ctx* ctx, const void* buf, size_t len)
 {
     if (!ctx) return MICSA_EINVAL;
+    if (int st_ = refuse_capture(ctx)) return st_;
     if (int st_ = need_home(ctx)) return st_;
     if (!buf) return fail(ctx, MICSA_EINVAL, "null checkpoint");
     const uint8_t* in = static_cast<const uint8_t*>(buf);

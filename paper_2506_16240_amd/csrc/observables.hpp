@@ -136,6 +136,13 @@ __global__ void __launch_bounds__(1024) k_sum_slots(const unsigned long long* __
     give_ticket(ticket, value);
 }
 
+// Words from one device buffer to another.
+__global__ void __launch_bounds__(256) k_copy_u64(const uint64_t* __restrict__ src, int64_t n,
+                                                  uint64_t* __restrict__ dst)
+{
+    for (int64_t i = blockIdx.x * 256ll + threadIdx.x; i < n; i += gridDim.x * 256ll) dst[i] = src[i];
+}
+
 // Words to host memory.
 __global__ void __launch_bounds__(1024) k_to_host(const uint64_t* __restrict__ src, int64_t n,
                                                   uint64_t* __restrict__ dst, uint32_t* ticket, uint32_t value)

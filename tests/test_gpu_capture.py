@@ -40,7 +40,8 @@ class Run:
 
     def replay(self, algo, cap, stride=0):
         graph, k, n, sched = cap
-        graph.replay()
+        with torch.cuda.stream(self.stream):
+            graph.replay()
         torch.cuda.synchronize()
         after, self.o.k = self.o.k, k
         out = self.o.run(algo, sched, n, stride)
@@ -58,9 +59,11 @@ class Run:
         return torch.zeros((n, self.g.S * self.g.R), dtype=torch.int64, device="cuda")
 
     def same(self):
+        E, D = self.o.energy(), self.o.daemon_energy()
+        assert np.array_equal(self.g.energy(), E) and np.array_equal(self.g.daemon_energy(), D)
         assert np.array_equal(self.g.spins(), self.o.sigma), "spins differ"
         assert np.array_equal(self.g.daemons(), self.o.m), "daemons differ"
-        assert np.array_equal(self.g.energy_tally(), self.o.energy())
+        assert np.array_equal(self.g.energy(), E) and np.array_equal(self.g.energy_tally(), E)
 
 
 def same_logs(got, want):
@@ -106,4 +109,90 @@ def test_captured_logs_outlive_longer_logs(shape, algo):
         want = r.replay(algo, cap, 2)
         same_logs((E.cpu().numpy(), D.cpu().numpy()), want)
         r.same()
+    r.g.close()
+
+
+CASES = [  # shape, gamma, algorithm, kernel, layout, sweeps captured
+    ((16, 16, 16, 1, 3), 1, M.ALGO_MICSA, M.KERNEL_AUTO, M.LAYOUT_BYTE, 3),      # one work-group, in place
+    ((64, 64, 64, 1, 2), 1, M.ALGO_MICSA, M.KERNEL_AUTO, M.LAYOUT_BYTE, 3),      # tiles, one launch: the other copy
+    ((64, 64, 64, 1, 2), 1, M.ALGO_HEATBATH, M.KERNEL_AUTO, M.LAYOUT_BYTE, 3),   # the same, levels stay
+    ((16, 16, 16, 1, 3), 1, M.ALGO_WALKERS, M.KERNEL_AUTO, M.LAYOUT_BYTE, 3),    # a wandering owed, of either parity
+    ((64, 64, 64, 1, 1), 1, M.ALGO_WALKERS, M.KERNEL_AUTO, M.LAYOUT_BYTE, 4),
+    ((16, 16, 16, 1, 3), 3, M.ALGO_WALKERS, M.KERNEL_AUTO, M.LAYOUT_BYTE, 4),    # families owe, a call inside a timestep
+    ((72, 34, 34, 1, 2), 2, M.ALGO_WALKERS, M.KERNEL_AUTO, M.LAYOUT_BYTE, 6),
+    ((24, 4, 600, 1, 1), 2, M.ALGO_MICSA, M.KERNEL_AUTO, M.LAYOUT_BYTE, 3),      # families in the other copy, tiles
+    ((32, 16, 8, 1, 2), 1, M.ALGO_WALKERS, M.KERNEL_SIMPLE, M.LAYOUT_BYTE, 3),   # byte arrays
+    ((128, 16, 8, 1, 2), 1, M.ALGO_MICSA, M.KERNEL_FUSED, M.LAYOUT_BYTE, 5),     # byte arrays in the other copy
+    ((128, 16, 8, 1, 2), 1, M.ALGO_WALKERS, M.KERNEL_FUSED, M.LAYOUT_BYTE, 5),
+    ((128, 16, 8, 1, 2), 1, M.ALGO_METROPOLIS, M.KERNEL_FUSED, M.LAYOUT_BYTE, 3),
+    ((256, 16, 8, 1, 1), 1, M.ALGO_MICSA, M.KERNEL_MULTISPIN, M.LAYOUT_BYTE, 9),
+    ((256, 16, 8, 1, 1), 1, M.ALGO_WALKERS, M.KERNEL_MULTISPIN, M.LAYOUT_BYTE, 5),
+    ((16, 6, 10, 65, 2), 1, M.ALGO_MICSA, M.KERNEL_AUTO, M.LAYOUT_BITPLANE, 9),  # cell planes
+    ((16, 6, 10, 65, 2), 1, M.ALGO_MICSA, M.KERNEL_AUTO, M.LAYOUT_BITPLANE, 3),  # words, other copy, on a fresh state
+]
+
+
+@pytest.mark.parametrize("start", ["fresh", "swept", "read"])
+@pytest.mark.parametrize("case", CASES)
+def test_replays_start_where_the_state_is(case, start):
+    """Captured on a fresh state, after sweeps that nothing has read yet, and
+    after a read: reads before the first replay, two replays in a row, replays
+    after calls of other lengths and another algorithm, after written spins and
+    written daemons."""
+    shape, gamma, algo, kernel, layout, n = case
+    r = Run(shape, gamma=gamma, kernel=kernel, layout=layout)
+    if start != "fresh":
+        r.eager(algo, 2 * gamma + 3)
+    if start == "read":
+        r.same()
+    cap = r.capture(lambda g: g.sweep(algo, n), n)
+    r.same()
+    for before in (0, 0, 1, 2 * gamma + 2):
+        if before:
+            r.eager(algo, before)
+        r.replay(algo, cap)
+        if before != 1:
+            r.same()
+    if layout == M.LAYOUT_BYTE:
+        r.eager(M.ALGO_HEATBATH, 3)
+        r.replay(algo, cap)
+    r.g.write_spins(1 - r.o.sigma)
+    r.o.sigma = 1 - r.o.sigma
+    r.replay(algo, cap)
+    r.same()
+    m = np.ascontiguousarray(r.o.m[..., ::-1])
+    r.g.write_daemons(m)
+    r.o.m[...] = m
+    r.replay(algo, cap)
+    r.replay(algo, cap)
+    assert np.array_equal(r.g.energy(), r.o.energy())
+    image = r.g.save()
+    r.replay(algo, cap)
+    r.same()
+    r.g.load(image)
+    r.eager(algo, 2)
+    r.g.close()
+
+
+def test_calls_that_wait_are_refused_in_a_capture():
+    """Reads, writes, schedules and host logs inside a capture: ESTATE, nothing
+    changed, and the capture goes on."""
+    r = Run((16, 16, 16, 1, 2))
+    r.eager(M.ALGO_MICSA, 3)
+    state = r.o.sigma.copy()
+
+    def call(g):
+        for refused in (g.energy, g.daemon_energy, g.energy_tally, lambda: g.overlap(0, 1), g.spins, g.daemons, g.couplings,
+                        g.c4_sums, g.c4_sums_static, g.xi, g.save, lambda: g.write_spins(state),
+                        lambda: g.write_daemons(state), lambda: r.schedule(1.0, 1.0),
+                        lambda: g.sweep_logged(M.ALGO_MICSA, 4, 2)):
+            with pytest.raises(M.MicsaError) as e:
+                refused()
+            assert e.value.status == M.ESTATE
+        g.sweep(M.ALGO_MICSA, 3)
+
+    cap = r.capture(call, 3)
+    r.same()
+    r.replay(M.ALGO_MICSA, cap)
+    r.same()
     r.g.close()
