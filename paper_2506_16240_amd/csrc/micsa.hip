@@ -3514,7 +3514,7 @@ int micsa_write_spins(micsa_ctx* ctx, const uint8_t* sigma)
     }
     if ((st = tally_from_state(ctx))) return st;
     ctx->tally_ok = true;
-    return ctx->captured ? rest_and_wait(ctx) : MICSA_OK;
+    return rest_and_wait(ctx);
 }
 
 int micsa_write_demons(micsa_ctx* ctx, const uint8_t* m)
