@@ -967,13 +967,19 @@ CellGeom cell_geom(const micsa_ctx* c);
 uint32_t* w32(uint64_t* p);
 
 // The alternate byte arrays (allocated with the context where a path that
-// needs them is the default, else by the first call that takes one).
+// needs them is the default, else by the first call that takes one; walkers
+// need the daemons' for the wandering that a sweep leaves owed).
+int need_dem_alt(micsa_ctx* c)
+{
+    if (!c->dem_alt) ctx_alloc(c, c->dem_alt, (size_t)c->L * 2 * (size_t)c->g.Nh * (size_t)c->gamma);
+    return c->dem_alt ? MICSA_OK : fail(c, MICSA_ENOMEM, "alternate daemons");
+}
+
 int need_alt(micsa_ctx* c)
 {
-    const size_t state = (size_t)c->L * 2 * (size_t)c->g.Nh;
-    if (!c->spin_alt) ctx_alloc(c, c->spin_alt, state);
-    if (!c->dem_alt) ctx_alloc(c, c->dem_alt, state * (size_t)c->gamma);
-    return c->spin_alt && c->dem_alt ? MICSA_OK : fail(c, MICSA_ENOMEM, "alternate state buffers");
+    if (!c->spin_alt) ctx_alloc(c, c->spin_alt, (size_t)c->L * 2 * (size_t)c->g.Nh);
+    const int st = need_dem_alt(c);
+    return st || c->spin_alt ? st : fail(c, MICSA_ENOMEM, "alternate spins");
 }
 
 int launch_fused_sweep(micsa_ctx* c, bool refresh, int64_t rho, double T, int wander = -1)
@@ -1304,7 +1310,7 @@ int check_sweep(micsa_ctx* c, int32_t algo, int64_t n)
 // family along its own direction, the half of the cycle given by t's parity).
 int launch_wander_families(micsa_ctx* c, const WanderParity& wp)
 {
-    if (int st = need_alt(c)) return st;
+    if (int st = need_dem_alt(c)) return st;
     const int64_t words = (int64_t)c->g.rows * c->g.Wr;
     {
         TimedLaunch tl(c, kTimeSweep);
@@ -1810,9 +1816,9 @@ int settle_wander(micsa_ctx* c)
 {
     if (c->pend_wander < 0) return MICSA_OK;
     if (int st = own_home(c)) return st;  // the wandering kernel moves the byte arrays' levels
-    const int p = c->pend_wander;
-    c->pend_wander = -1;
-    return launch_wander(c, p);
+    const int st = launch_wander(c, c->pend_wander);
+    if (!st) c->pend_wander = -1;
+    return st;
 }
 
 // ------------------------------------------------------------- cell sweeps
@@ -2530,7 +2536,9 @@ bool logs_in_kernel(const micsa_ctx* c, int32_t algo, int64_t n)
 int sweep_logging(micsa_ctx* c, int32_t algo, int64_t n, long long* dlog, int64_t stride)
 {
     if (n <= 0) return MICSA_OK;
-    if (int st = begin_sweeps(c)) return end_sweeps(c, st);
+    int st = begin_sweeps(c);
+    if (!st && algo == MICSA_ALGO_WALKERS) st = need_dem_alt(c);
+    if (st) return end_sweeps(c, st);
     return end_sweeps(c, algo == MICSA_ALGO_MICSA || algo == MICSA_ALGO_WALKERS
                              ? sweep_cells(c, n, dlog, stride, algo == MICSA_ALGO_WALKERS)
                              : sweep_cells_canonical(c, algo, n, dlog, stride));
@@ -2550,6 +2558,7 @@ int sweep_run(micsa_ctx* c, int32_t algo, int64_t n)
 {
     int st0 = check_sweep(c, algo, n);
     if (st0) return st0;
+    if (algo == MICSA_ALGO_WALKERS && n > 0 && (st0 = need_dem_alt(c))) return st0;
     // walkers (gamma = 1) on the fused sweep carry their wandering into the
     // next sweep's loads; every other path needs the daemons in place
     const bool walk_cells = algo == MICSA_ALGO_WALKERS && use_cells_walkers(c, n);
@@ -2780,7 +2789,8 @@ static int create_ctx(const micsa_params* p, hipStream_t stream, size_t draw_roo
     // context took to set up.
     const size_t home = arena_size((size_t)c->L * kSlots * 8) + arena_size(nred * kSlots * 8) +
                         (c->bit ? 3 * arena_size(words * 8) + arena_size(bonds)
-                                : (alt ? 2 : 1) * (arena_size(state) + arena_size(dstate)));
+                                : (alt ? 2 : 1) * (arena_size(state) + arena_size(dstate)) +
+                                      (gamma > 1 ? arena_size(dstate) : 0));
     size_t work = 0;
     if (msc || (cells && msc_eligible(c))) {
         const size_t mw = (size_t)c->L * 2 * (size_t)msc_geom(c).plane * 8;
@@ -2800,6 +2810,7 @@ static int create_ctx(const micsa_params* p, hipStream_t stream, size_t draw_roo
     if (ok && !c->bit) {
         ok = ctx_alloc(c, c->spin, state) && ctx_alloc(c, c->dem, dstate);
         if (ok && alt) ok = need_alt(c) == MICSA_OK;
+        if (ok && gamma > 1) ok = need_dem_alt(c) == MICSA_OK;
     } else if (ok) {
         ok = ctx_alloc(c, c->bspin, words * 8) && ctx_alloc(c, c->bdm0, words * 8) &&
              ctx_alloc(c, c->bdm1, words * 8) && ctx_alloc(c, c->bJ, bonds);

@@ -1,9 +1,15 @@
 """What calls promise beside their results: what has ended when they return,
 and what they do where device memory is short."""
+import ctypes
+import os
+import shutil
+import subprocess
+
 import numpy as np
 import pytest
 import torch
 
+from oracle import oracle as O
 from paper_2506_16240_amd import micsa as M
 
 pytestmark = pytest.mark.gpu
@@ -23,3 +29,65 @@ def test_writes_have_ended_when_they_return(layout):
         assert stream.query()
     assert np.array_equal(g.energy(), g.energy_tally())
     g.close()
+
+
+class Memory:
+    """What the library holds of device memory, and a bound on it."""
+
+    def __init__(self, shim):
+        self.shim = shim
+        shim.alloc_live.restype = ctypes.c_size_t
+        shim.alloc_limit.argtypes = [ctypes.c_size_t]
+
+    def held(self):
+        return self.shim.alloc_live()
+
+    def bound(self, more=None):
+        """At most `more` bytes beyond what is held now; None: no bound."""
+        self.shim.alloc_limit(2 ** 64 - 1 if more is None else self.held() + more)
+
+
+@pytest.fixture(scope="module")
+def counted(tmp_path_factory):
+    """A copy of the library whose device allocations can be counted and bounded."""
+    d = tmp_path_factory.mktemp("alloc")
+    M.lib()
+    subprocess.check_call(["gcc", "-O1", "-shared", "-fPIC", "-o", str(d / "alloc.so"),
+                           os.path.join(os.path.dirname(__file__), "alloc_limit.c"), "-ldl", "-lpthread"])
+    shim = ctypes.CDLL(str(d / "alloc.so"), ctypes.RTLD_GLOBAL)
+    shutil.copy(M.LIB_PATH, d / "libmicsa.so")
+    return Memory(shim), str(d / "libmicsa.so")
+
+
+@pytest.fixture
+def memory(counted, monkeypatch):
+    mem, path = counted
+    monkeypatch.setattr(M, "LIB_PATH", path)
+    monkeypatch.setattr(M, "_lib", None)
+    before = mem.held()
+    yield mem
+    mem.bound()
+    assert mem.held() == before
+
+
+@pytest.mark.parametrize("shape,gamma", [((16, 16, 16, 1, 3), 1), ((64, 64, 64, 1, 1), 1), ((16, 16, 16, 1, 3), 3)])
+def test_walkers_without_room_for_their_wandering(memory, shape, gamma):
+    """A walker call takes the room that its wandering will need before it
+    changes anything, so that a read never lacks it."""
+    with M.Lattice(*shape, 5, gamma=gamma) as g:
+        o = O.Lattice(*shape, 5, gamma=gamma)
+        g.set_schedule(M.Schedule(M.SCHED_CONST, 0.9, 0.9, 200, 4))
+        os_ = O.Schedule(O.SCHED_CONST, 0.9, 0.9, 200, 4)
+        for n in (2 * gamma + 1, 3 * gamma):
+            memory.bound(0)
+            try:
+                g.sweep(M.ALGO_WALKERS, n)
+            except M.MicsaError as e:
+                assert e.status == M.ENOMEM and g.counters() == (o.k, o.k // gamma // 4)
+                memory.bound()
+                g.sweep(M.ALGO_WALKERS, n)
+            o.run(O.ALGO_WALKERS, os_, n, 0)
+            memory.bound(0)
+            assert np.array_equal(g.daemon_energy(), o.daemon_energy())
+            assert np.array_equal(g.daemons(), o.m) and np.array_equal(g.spins(), o.sigma)
+            memory.bound()
