@@ -127,7 +127,9 @@ const char* micsa_last_error(const micsa_ctx* ctx);
    its work.  On success *out owns all device memory; on failure *out is
    NULL and nothing is leaked.  The working buffers of the sweep path the
    lattice takes by default (bit planes and drawn levels) are allocated here
-   when they fit, else by the first sweep call that needs them.  The initial
+   when they fit, else by the first sweep call that needs them; where they do
+   not fit then either, sweeps that can run on the state's own arrays do so
+   until a schedule is installed.  The initial
    state is enqueued on the stream; the call does not wait for it.
    Errors: EINVAL (bad sides/counts/layout/gamma), ENOMEM, EHIP. */
 int micsa_create(const micsa_params* p, void* hip_stream, micsa_ctx** out);

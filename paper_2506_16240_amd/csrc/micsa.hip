@@ -181,6 +181,7 @@ struct micsa_ctx {
     // cell sweeps (cells.hpp): launch plan, and the levels of cdr_n refreshes
     // from index cdr_rho0 on, drawn ahead (room for cdr_cap of them)
     CellPlan plan;
+    bool no_room = false;  // there was none for the planes: the paths on the layout's own arrays, until a new schedule
     MscTile tile2{};  // tile of the two-sweep multispin pass (follows the tile options)
     uint32_t *cdr0 = nullptr, *cdr1 = nullptr;
     int64_t cdr_rho0 = 0, cdr_n = 0, cdr_cap = 0;
@@ -1932,7 +1933,7 @@ double msc_cost(const micsa_ctx* c) { return c->tile2.TY > 0 ? msc2_cost(c, c->t
 // word-wise sweep 8.7.
 bool use_cells(const micsa_ctx* c, int64_t n = kMscMinSweeps)
 {
-    if (!c->plan.ok) return false;
+    if (!c->plan.ok || c->no_room) return false;
     if (c->bit)
         return c->kernel_opt == MICSA_KERNEL_AUTO && !c->tile_y && !c->tile_z && !c->use_graphs && !c->draw_ahead &&
                (n >= kMscMinSweeps || c->planes_ok);
@@ -1965,10 +1966,22 @@ size_t cells_plane_words(const micsa_ctx* c)
     return words * ((alt ? 2 : 1) + levels) + (size_t)(c->L / c->g.R) * 6 * (size_t)cg.plane;
 }
 
+// Give back planes that hold no state.
+void planes_free(micsa_ctx* c)
+{
+    if (msc_eligible(c))
+        for (uint64_t* q : {c->ms, c->md0, c->md1, c->mb, c->ms_alt, c->md0_alt, c->md1_alt}) ctx_free(c, q);
+    else
+        ctx_free(c, c->ms);  // one block
+    c->ms = c->md0 = c->md1 = c->mb = c->ms_alt = c->md0_alt = c->md1_alt = nullptr;
+    for (auto& copy : c->fl) std::fill(copy, copy + 6, nullptr);
+}
+
 int cells_alloc(micsa_ctx* c)
 {
     const CellGeom cg = cell_geom(c);
     const size_t words = (size_t)c->L * 2 * (size_t)cg.plane;
+    const bool fresh = !c->ms;
     if (!c->ms || (c->plan.sweeps > 0 && !c->ms_alt)) {
         if (msc_eligible(c)) {
             if (int st = msc_alloc(c, true, false)) return st;
@@ -1995,9 +2008,15 @@ int cells_alloc(micsa_ctx* c)
         }
     }
     if (!c->cdr0) {
-        const int64_t cap = cells_draw_cap(c);
+        int64_t cap = cells_draw_cap(c);
         uint32_t* a = nullptr;
-        if (!ctx_alloc(c, a, words * 8 * (size_t)cap)) return fail(c, MICSA_ENOMEM, "drawn levels");
+        while (!ctx_alloc(c, a, words * 8 * (size_t)cap)) {  // fewer refreshes where memory is short
+            if (cap <= 2) {
+                if (fresh) planes_free(c);
+                return fail(c, MICSA_ENOMEM, "drawn levels");
+            }
+            cap = std::max<int64_t>(2, cap / 4);
+        }
         c->cdr0 = a;
         c->cdr1 = a + words * (size_t)cap;
         c->cdr_cap = cap;
@@ -2291,7 +2310,7 @@ int sweep_cells_families(micsa_ctx* c, int64_t n, bool walkers)
 // site) where those leave the device idle (us per sweep, cells against them).
 bool use_cells_walkers(const micsa_ctx* c, int64_t n)
 {
-    if (!c->plan.ok || c->bit) return false;
+    if (!c->plan.ok || c->no_room || c->bit) return false;
     if (c->kernel_opt != MICSA_KERNEL_AUTO && c->kernel_opt != MICSA_KERNEL_RESIDENT &&
         c->kernel_opt != MICSA_KERNEL_SLAB)
         return false;
@@ -2310,7 +2329,7 @@ bool use_cells_walkers(const micsa_ctx* c, int64_t n)
 // for the fused kernel pay two launches per sweep there.
 bool use_cells_canonical(const micsa_ctx* c)
 {
-    if (!c->plan.ok || c->bit) return false;
+    if (!c->plan.ok || c->no_room || c->bit) return false;
     if (c->kernel_opt == MICSA_KERNEL_RESIDENT) return true;
     if (c->kernel_opt != MICSA_KERNEL_AUTO || use_graph(c)) return false;
     if (!use_fused(c)) return true;
@@ -2523,10 +2542,24 @@ int rest_state(micsa_ctx* c)
     return rest_copy(c, c->dem, c->dem_alt, x.dem, bytes * (size_t)c->gamma);
 }
 
+// Room for the planes of a call that takes the cell sweep.  Without it the call
+// runs on the layout's own arrays, and so do those that follow until a schedule
+// is installed (each would wait for an allocation to fail).
+void find_room(micsa_ctx* c, int32_t algo, int64_t n)
+{
+    const bool cells = algo == MICSA_ALGO_MICSA     ? use_cells(c, n)
+                       : algo == MICSA_ALGO_WALKERS ? use_cells_walkers(c, n)
+                                                    : use_cells_canonical(c);
+    if (n <= 0 || !cells || cells_alloc(c) == MICSA_OK) return;
+    c->no_room = true;
+    c->err.clear();
+}
+
 // A sweep call of this algorithm logs inside its launches (one work-group
 // per lattice).
-bool logs_in_kernel(const micsa_ctx* c, int32_t algo, int64_t n)
+bool logs_in_kernel(micsa_ctx* c, int32_t algo, int64_t n)
 {
+    find_room(c, algo, n);
     if (c->plan.sweeps > 0) return false;
     if (algo == MICSA_ALGO_WALKERS) return c->gamma == 1 && use_cells_walkers(c, n);
     if (algo == MICSA_ALGO_MICSA) return c->gamma == 1 && use_cells(c, n);
@@ -2559,6 +2592,7 @@ int sweep_run(micsa_ctx* c, int32_t algo, int64_t n)
     int st0 = check_sweep(c, algo, n);
     if (st0) return st0;
     if (algo == MICSA_ALGO_WALKERS && n > 0 && (st0 = need_dem_alt(c))) return st0;
+    find_room(c, algo, n);
     // walkers (gamma = 1) on the fused sweep carry their wandering into the
     // next sweep's loads; every other path needs the daemons in place
     const bool walk_cells = algo == MICSA_ALGO_WALKERS && use_cells_walkers(c, n);
@@ -2933,6 +2967,7 @@ int micsa_set_schedule(micsa_ctx* ctx, const micsa_schedule* s)
     ctx->d_hth = reinterpret_cast<HeatBathThresholds*>(d + o_h);
     ctx->d_mth = reinterpret_cast<MetropolisThresholds*>(d + o_m);
     ctx->sched = std::move(n);
+    ctx->no_room = false;
     ctx->cdr_n = 0;  // levels drawn ahead under the old temperatures
     ctx->msc_drawn = -1;
     return MICSA_OK;

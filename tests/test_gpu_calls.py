@@ -91,3 +91,46 @@ def test_walkers_without_room_for_their_wandering(memory, shape, gamma):
             assert np.array_equal(g.daemon_energy(), o.daemon_energy())
             assert np.array_equal(g.daemons(), o.m) and np.array_equal(g.spins(), o.sigma)
             memory.bound()
+
+
+def _home_bytes(shape, layout):
+    """The state's own arrays and the slots of the reductions."""
+    N, L, S, R = shape[0] * shape[1] * shape[2], shape[3] * shape[4], shape[3], shape[4]
+    G = (S + 63) // 64
+    state = 2 * L * N if layout == M.LAYOUT_BYTE else 3 * G * R * N * 8 + G * 6 * N // 2 * 8
+    return state + 2 * 512 * max(L, S) + 2048
+
+
+@pytest.mark.parametrize("part", [0.0, 0.3, 0.7])
+@pytest.mark.parametrize("shape,layout", [((32, 32, 32, 1, 16), M.LAYOUT_BYTE), ((64, 64, 64, 1, 2), M.LAYOUT_BYTE),
+                                          ((8, 64, 60, 1, 4), M.LAYOUT_BYTE), ((32, 16, 16, 70, 2), M.LAYOUT_BITPLANE)])
+def test_sweeps_without_room_for_planes(memory, shape, layout, part):
+    """Room for the state alone, or for a part of the planes and drawn levels:
+    every call runs, on fewer drawn refreshes or on the state's own arrays."""
+    start = memory.held()
+    with M.Lattice(*shape, 5, layout=layout) as g:
+        full = memory.held() - start
+    home = _home_bytes(shape, layout)
+    assert full > home
+    # 192 KiB for the schedule's tables and small workspaces
+    memory.bound(int(home + part * (full - home)) + (192 << 10))
+    if layout == M.LAYOUT_BITPLANE:  # the word-wise sweep goes from one copy to the other
+        memory.bound(int(home + part * (full - home)) + (192 << 10) + home)
+    with M.Lattice(*shape, 5, layout=layout) as g:
+        o = O.Lattice(*shape, 5)
+        g.set_schedule(M.Schedule(M.SCHED_LINEAR, 2.5, 0.5, 100, 3))
+        os_ = O.Schedule(O.SCHED_LINEAR, 2.5, 0.5, 100, 3)
+        algos = (M.ALGO_MICSA, M.ALGO_HEATBATH, M.ALGO_METROPOLIS) if layout == M.LAYOUT_BYTE else (M.ALGO_MICSA,)
+        for algo in algos:
+            g.sweep(algo, 11)
+            o.run(algo, os_, 11, 0)
+            E, D = g.sweep_logged(algo, 4, 2)
+            Eo, Do = o.run(algo, os_, 4, 2)
+            assert np.array_equal(E, Eo) and np.array_equal(D, Do)
+        memory.bound()  # room again: the next schedule finds it
+        g.set_schedule(M.Schedule(M.SCHED_CONST, 0.9, 0.9, 100, 5))
+        os_ = O.Schedule(O.SCHED_CONST, 0.9, 0.9, 100, 5)
+        g.sweep(M.ALGO_MICSA, 12)
+        o.run(O.ALGO_MICSA, os_, 12, 0)
+        assert np.array_equal(g.energy(), o.energy())
+        assert np.array_equal(g.spins(), o.sigma) and np.array_equal(g.daemons(), o.m)
