@@ -398,7 +398,10 @@ int micsa_set_option(micsa_ctx* ctx, int32_t option, int64_t value);
    in a loop keeps the device busy while new jobs are submitted and
    admitted.  A job whose every sweep has been enqueued and has finished on
    the device is DONE; its state stays readable through
-   micsa_pool_job_context until micsa_pool_release frees it.
+   micsa_pool_job_context until micsa_pool_release gives it back.  Where the
+   device itself has less room than the budget says, a job waits for those that
+   run; one that runs alone sweeps on fewer drawn levels, or on the state's own
+   arrays.
    Results never depend on the other jobs in the pool: every random number
    is keyed by the job's own seed, sample, replica, site and time.
    ------------------------------------------------------------------------ */
@@ -406,10 +409,17 @@ typedef struct micsa_pool micsa_pool;
 
 enum micsa_job_state { MICSA_JOB_QUEUED = 0, MICSA_JOB_RUNNING = 1, MICSA_JOB_DONE = 2, MICSA_JOB_RELEASED = 3 };
 
-/* Device bytes a job with these parameters occupies while admitted. */
+/* Device bytes a job with these parameters needs to be admitted, beside the
+   tables of its schedule (136 bytes per refresh) and 512 bytes per further
+   replica for reductions.  A job may hold more (planes of
+   short rows, levels drawn for up to 16 refreshes) from what the queued jobs
+   leave of the budget, and counts with what it holds then; a job whose planes
+   find no room beside the others sweeps on the state's own arrays. */
 int micsa_pool_footprint(const micsa_params* p, size_t* bytes);
 
-/* hbm_budget: bytes the pool may hold for admitted jobs; max_running >= 1.
+/* hbm_budget: bytes the pool may hold for admitted jobs (what the jobs'
+   contexts allocate beyond their footprint when the caller reads large states,
+   logs, or sweeps them with another algorithm comes on top); max_running >= 1.
    hip_stream as in micsa_create.  Errors: EINVAL, ENOMEM. */
 int micsa_pool_create(size_t hbm_budget, int32_t max_running, void* hip_stream, micsa_pool** out);
 int micsa_pool_destroy(micsa_pool* pool); /* frees every job; NULL accepted */
@@ -435,7 +445,9 @@ int micsa_pool_job_state(micsa_pool* pool, int64_t job, int32_t* state, int64_t*
    release); read results through the micsa_read_* calls. */
 int micsa_pool_job_context(micsa_pool* pool, int64_t job, micsa_ctx** ctx);
 
-/* Free a DONE job's device memory (EINVAL for an unknown or unfinished job). */
+/* Give a DONE job's device memory back (EINVAL for an unknown or unfinished
+   job).  The pool keeps it for later jobs, within the budget, and frees it when
+   it holds no job any more. */
 int micsa_pool_release(micsa_pool* pool, int64_t job);
 
 /* ------------------------------------------------------------------------

@@ -75,9 +75,10 @@ struct CellPlan {
 // a free waits for everything the device has in flight, of other jobs too, and
 // the device then idles until the host has fed it again.  A block is given
 // back once its job's streams have finished, so the next job may write it at
-// once.  What lies idle is bounded by limit (the budget less the footprints of
-// the running jobs) and freed with the pool.  Contexts of one pool may be used
-// from several threads: every access holds the lock.
+// once, if it is at most a quarter larger than the job needs and within what
+// the job may hold.  What lies idle is bounded by limit (the budget less what the
+// admitted jobs are charged) and freed when the pool holds no job.  Contexts of
+// one pool may be used from several threads: every access holds the lock.
 struct JobStore {
     struct Block {
         int device;
@@ -121,6 +122,7 @@ struct micsa_ctx {
     // device memory: blocks of this context, from the pool's store if it has
     // one; what is known at creation lies in the first, filled from its start
     JobStore* store = nullptr;
+    bool pooled = false;  // (a job's shape too, which has no store)
     std::vector<JobStore::Block> owned;
     uint8_t* arena = nullptr;
     size_t arena_left = 0;
@@ -277,24 +279,30 @@ void* dev_alloc(size_t bytes)
 
 constexpr size_t arena_size(size_t bytes) { return (bytes + 255) / 256 * 256; }
 
-// A block of the context's own.  From a store: the smallest idle one that is
-// at most a quarter larger, else a new one, for which idle ones make room.
-void* own_block(micsa_ctx* c, size_t bytes)
+// A block of the context's own, of at most `most` bytes (0: of its size).  From a
+// store: the smallest idle one that fits, else a new one (of four sizes per factor
+// of two, so that it fits other jobs too), for which idle ones make room.
+void* own_block(micsa_ctx* c, size_t bytes, size_t most = 0)
 {
     JobStore::Block b{c->device, arena_size(std::max<size_t>(bytes, 1)), nullptr, false};
     if (JobStore* s = c->store) {
+        const size_t need = b.bytes;
+        most = std::min(std::max(most, need), need + need / 4);
+        size_t step = 256;
+        while (7 * step < need) step *= 2;
+        b.bytes = std::min((need + step - 1) / step * step, most);
         std::lock_guard<std::mutex> hold(s->lock);
-        size_t best = s->idle.size();
+        size_t at = s->idle.size();
         for (size_t i = 0; i < s->idle.size(); ++i) {
             const JobStore::Block& q = s->idle[i];
-            if (q.device == b.device && q.bytes >= b.bytes && q.bytes - b.bytes <= b.bytes / 4 &&
-                (best == s->idle.size() || q.bytes < s->idle[best].bytes))
-                best = i;
+            if (q.device == b.device && q.bytes >= need && q.bytes <= most &&
+                (at == s->idle.size() || q.bytes < s->idle[at].bytes))
+                at = i;
         }
-        if (best < s->idle.size()) {
-            b = s->idle[best];
+        if (at < s->idle.size()) {
+            b = s->idle[at];
             s->held -= b.bytes;
-            s->idle.erase(s->idle.begin() + (long)best);
+            s->idle.erase(s->idle.begin() + (long)at);
         } else {
             s->trim(s->limit);
             b.p = dev_alloc(b.bytes);
@@ -385,7 +393,12 @@ void* work_take(micsa_ctx* c, size_t bytes)
 
 void work_give(micsa_ctx* c, void* p)
 {
-    if (p != c->work) ctx_free(c, p);
+    if (p == c->work && !c->store) return;
+    if (p == c->work) {  // (a pool's job keeps what it is charged for)
+        c->work = nullptr;
+        c->work_cap = 0;
+    }
+    ctx_free(c, p);
 }
 
 // A stream of default priority, and its end (its work has finished).
@@ -2744,16 +2757,19 @@ const char* micsa_status_string(int status)
 
 const char* micsa_last_error(const micsa_ctx* ctx) { return ctx ? ctx->err.c_str() : "null context"; }
 
-// Parameters, geometry and launch plans (no device memory).
-static int setup_ctx(micsa_ctx* c, const micsa_params* p, hipStream_t stream)
+// Parameters, geometry and launch plans (no device memory); the plans are those
+// of `like` if that is a context of the same parameters and device.
+static int setup_ctx(micsa_ctx* c, const micsa_params* p, hipStream_t stream, const micsa_ctx* like = nullptr)
 {
     const int64_t N = (int64_t)p->Lx * p->Ly * p->Lz;
     const int gamma = p->gamma == 0 ? 1 : p->gamma;
+    int st = MICSA_OK;
     if (hipGetDevice(&c->device) != hipSuccess) {
         (void)hipGetLastError();
-        return MICSA_EHIP;
+        c->device = 0;
+        st = MICSA_EHIP;
     }
-    if (hipDeviceGetAttribute(&c->cus, hipDeviceAttributeMultiprocessorCount, c->device) != hipSuccess) {
+    if (st || hipDeviceGetAttribute(&c->cus, hipDeviceAttributeMultiprocessorCount, c->device) != hipSuccess) {
         (void)hipGetLastError();
         c->cus = 0;
     }
@@ -2781,12 +2797,53 @@ static int setup_ctx(micsa_ctx* c, const micsa_params* p, hipStream_t stream)
     g.key1 = (uint32_t)(p->seed >> 32);
     g.gamma = gamma;
 
-    c->plan = cell_plan(c);
-    c->tile2 = msc2_plan(c);
-    return MICSA_OK;
+    const bool same = like && like->device == c->device && like->cus == c->cus;
+    c->plan = same ? like->plan : cell_plan(c);
+    c->tile2 = same ? like->tile2 : msc2_plan(c);
+    return st;
 }
 
-static int create_ctx(const micsa_params* p, hipStream_t stream, size_t draw_room, JobStore* store, micsa_ctx** out)
+// Device memory that a context takes when it is created: the state's own arrays
+// with the reductions' slots, and the working buffers of the sweep path that the
+// lattice takes by default.
+struct CtxBytes {
+    bool alt, cells, msc;  // the fused sweeps' second copies; which planes
+    size_t state, dstate, words, bonds, nred;
+    size_t home, work;
+};
+
+static CtxBytes ctx_bytes(const micsa_ctx* c)
+{
+    CtxBytes b{};
+    const Geom& g = c->g;
+    b.nred = (size_t)std::max(c->L, c->p.n_samples);
+    b.state = (size_t)c->L * 2 * (size_t)g.Nh;
+    b.dstate = b.state * (size_t)c->gamma;  // every daemon family
+    b.words = (size_t)word_lattices(c) * 2 * (size_t)g.Nh;
+    b.bonds = c->bit ? (size_t)bp_coupling_sets(geomb(c)) * 6 * (size_t)g.Nh * 8 : 0;
+    // the fused sweeps go from one copy to the other
+    b.alt = !c->bit && fused_eligible(c) && c->p.Lx >= 128;
+    b.cells = use_cells(c);
+    b.msc = !b.cells && !c->bit && c->gamma == 1 && msc_eligible(c);
+    b.home = arena_size((size_t)c->L * kSlots * 8) + arena_size(b.nred * kSlots * 8) +
+             (c->bit ? 3 * arena_size(b.words * 8) + arena_size(b.bonds)
+                     : (b.alt ? 2 : 1) * (arena_size(b.state) + arena_size(b.dstate)) +
+                           (c->gamma > 1 && !c->pooled ? arena_size(b.dstate) : 0));
+    if (b.msc || (b.cells && msc_eligible(c))) {
+        const size_t mw = (size_t)c->L * 2 * (size_t)msc_geom(c).plane * 8;
+        b.work = (b.msc ? 8 : 6) * arena_size(mw) + arena_size(3 * mw);
+    } else if (b.cells) {
+        b.work = arena_size(cells_plane_words(c) * 4);
+    }
+    if (b.cells)
+        b.work += arena_size((size_t)c->L * 2 * (size_t)cell_geom(c).plane * 8 * (size_t)cells_draw_cap(c));
+    return b;
+}
+
+// most: size of its block at most (0: what it needs); spare: whether it may do
+// without the working buffers for now.
+static int create_ctx(const micsa_params* p, hipStream_t stream, const micsa_ctx* like, size_t most, bool spare,
+                      JobStore* store, micsa_ctx** out)
 {
     if (!out) return MICSA_EINVAL;
     *out = nullptr;
@@ -2796,46 +2853,27 @@ static int create_ctx(const micsa_params* p, hipStream_t stream, size_t draw_roo
 
     micsa_ctx* c = new (std::nothrow) micsa_ctx();
     if (!c) return MICSA_ENOMEM;
-    if (const int st = setup_ctx(c, p, stream)) {
+    if (const int st = setup_ctx(c, p, stream, like)) {
         delete c;
         return st;
     }
-    c->draw_room = draw_room;
+    c->draw_room = like ? like->draw_room : 0;
+    c->store = store;
+    c->pooled = store != nullptr;
     if (stream_captured(stream)) {  // the initial state is no part of a graph
         delete c;
         return MICSA_EHIP;
     }
     const Geom& g = c->g;
 
-    c->store = store;
-    const size_t nred = (size_t)std::max(c->L, p->n_samples);
-    const size_t state = (size_t)c->L * 2 * (size_t)g.Nh;
-    const size_t dstate = state * (size_t)gamma;  // every daemon family
-    const size_t words = (size_t)word_lattices(c) * 2 * (size_t)g.Nh;
-    const size_t bonds = c->bit ? (size_t)bp_coupling_sets(geomb(c)) * 6 * (size_t)g.Nh * 8 : 0;
-    // the fused sweeps go from one copy to the other
-    const bool alt = !c->bit && fused_eligible(c) && p->Lx >= 128;
-    // Working buffers of the sweep path the lattice takes by default (counted
-    // in the pool footprint), so that the first sweep call does not allocate;
-    // if they do not fit now, that call tries again.
-    const bool cells = use_cells(c), msc = !cells && !c->bit && c->gamma == 1 && msc_eligible(c);
+    const CtxBytes B = ctx_bytes(c);
+    const auto [alt, cells, msc, state, dstate, words, bonds, nred, home, work] = B;
     // One allocation for all of it: nine took 90 us of the 230 us that a 16^3
-    // context took to set up.
-    const size_t home = arena_size((size_t)c->L * kSlots * 8) + arena_size(nred * kSlots * 8) +
-                        (c->bit ? 3 * arena_size(words * 8) + arena_size(bonds)
-                                : (alt ? 2 : 1) * (arena_size(state) + arena_size(dstate)) +
-                                      (gamma > 1 ? arena_size(dstate) : 0));
-    size_t work = 0;
-    if (msc || (cells && msc_eligible(c))) {
-        const size_t mw = (size_t)c->L * 2 * (size_t)msc_geom(c).plane * 8;
-        work = (msc ? 8 : 6) * arena_size(mw) + arena_size(3 * mw);
-    } else if (cells) {
-        work = arena_size(cells_plane_words(c) * 4);
-    }
-    if (cells) work += arena_size((size_t)c->L * 2 * (size_t)cell_geom(c).plane * 8 * (size_t)cells_draw_cap(c));
-    c->arena = static_cast<uint8_t*>(own_block(c, home + work));
+    // context took to set up.  Working buffers that do not fit now are tried
+    // again by the first sweep call.
+    c->arena = static_cast<uint8_t*>(own_block(c, home + work, most));
     c->arena_left = home + work;
-    if (!c->arena) {
+    if (!c->arena && spare) {
         c->arena = static_cast<uint8_t*>(own_block(c, home));
         c->arena_left = home;
     }
@@ -2844,7 +2882,7 @@ static int create_ctx(const micsa_params* p, hipStream_t stream, size_t draw_roo
     if (ok && !c->bit) {
         ok = ctx_alloc(c, c->spin, state) && ctx_alloc(c, c->dem, dstate);
         if (ok && alt) ok = need_alt(c) == MICSA_OK;
-        if (ok && gamma > 1) ok = need_dem_alt(c) == MICSA_OK;
+        if (ok && gamma > 1 && !c->pooled) ok = need_dem_alt(c) == MICSA_OK;
     } else if (ok) {
         ok = ctx_alloc(c, c->bspin, words * 8) && ctx_alloc(c, c->bdm0, words * 8) &&
              ctx_alloc(c, c->bdm1, words * 8) && ctx_alloc(c, c->bJ, bonds);
@@ -2893,7 +2931,7 @@ static int create_ctx(const micsa_params* p, hipStream_t stream, size_t draw_roo
 
 int micsa_create(const micsa_params* p, void* hip_stream, micsa_ctx** out) 
 {
-    return create_ctx(p, (hipStream_t)hip_stream, 0, nullptr, out);
+    return create_ctx(p, (hipStream_t)hip_stream, nullptr, 0, true, nullptr, out);
 }
 
 
@@ -3932,6 +3970,15 @@ struct PoolJob {
     hipEvent_t ev[2] = {nullptr, nullptr};  // end of the last two chunks of sweeps
     int64_t chunks = 0;                     // chunks enqueued so far
     int64_t last_batch = -1;                // batched jobs: the batch that holds their latest chunk
+    // from submission on: launch plans; and what the job may hold, the most
+    // first: planes and levels drawn for up to 16 refreshes, planes and two
+    // refreshes, the state's own arrays alone
+    CellPlan plan;
+    MscTile tile2{};
+    int device = 0, cus = 0;
+    size_t draw_room[2] = {0, 0};
+    size_t need[3] = {0, 0, 0};
+    size_t charged = 0;  // while admitted
 };
 
 size_t footprint(const micsa_params* p)
@@ -3947,20 +3994,51 @@ size_t footprint(const micsa_params* p)
         return 2 * WL * N * 8 * 3 + NJ * 6 * (N / 2) * 8 + slots;  // state and its alternate
     }
     const size_t gamma = p->gamma == 0 ? 1 : (size_t)p->gamma;
-    // 2 state buffers x (spin + gamma daemons); the couplings live in the even spin bytes
+    // spin and daemon bytes, and as much again: second copies, or planes and drawn levels
     size_t bytes = 2 * L * N * (1 + gamma) + slots;
-    // lattices the multispin sweep can take allocate its planes on their first
-    // long MicSA call: spins and two level planes, their alternates, the drawn
-    // levels (2) and the six coupling planes of the even sites (3 words per
-    // word of sites), each 1 bit per site: 11/8 B per site per lattice
+    // the multispin planes beside both copies: spins and two level planes, their
+    // alternates, the drawn levels (2) and the six coupling planes of the even
+    // sites (3 words per word of sites), each 1 bit per site: 11/8 B per site
+    // per lattice
     if (gamma == 1 && p->Lx % 128 == 0) bytes += 11 * L * N / 8;
-    // lattices the slab sweep takes (too large for the resident sweep,
-    // narrower than the fused one) draw refresh levels ahead into two
-    // buffers of a byte per site per lattice
+    // lattices in tiles have second copies of the planes too, and longer calls to
+    // draw levels for
     else if (gamma == 1 && (size_t)p->Ly * (p->Lx / 8) <= (size_t)kSlabLanes && N / 2 * 3 > kResidentLdsMax &&
              p->Lx < 128)
         bytes += 2 * L * N;
     return bytes;
+}
+
+// What a job of this shape (setup_ctx, draw_room set, pooled) holds.  A bit-plane
+// job, whose chunks may be too short for the planes, has second copies of its
+// words then.
+size_t job_need(const micsa_ctx* shape)
+{
+    const CtxBytes b = ctx_bytes(shape);
+    return b.home + b.work + (bp_one_launch(shape) ? 3 * arena_size(b.words * 8) : 0);
+}
+
+// Plans and needs of a job (without a device: as for 256 compute units).  Drawn
+// levels at most: 16 refreshes (a chunk of sweeps seldom has more) within 1 MiB or
+// 2.5 bytes per site and lattice, whichever is more.
+void plan_job(PoolJob& j)
+{
+    micsa_ctx shape;
+    (void)setup_ctx(&shape, &j.p, nullptr);
+    shape.pooled = true;
+    j.plan = shape.plan;
+    j.tile2 = shape.tile2;
+    j.device = shape.device;
+    j.cus = shape.cus;
+    const size_t one = (size_t)shape.L * 2 * (size_t)cell_geom(&shape).plane * 8;
+    const size_t sites = (size_t)shape.L * 2 * (size_t)shape.g.Nh;
+    j.draw_room[0] = std::min(16 * one, std::max((size_t)1 << 20, sites * 5 / 2));
+    j.draw_room[1] = 1;  // (at least two)
+    for (int v = 0; v < 3; ++v) {
+        shape.draw_room = v < 2 ? j.draw_room[v] : 1;
+        shape.plan.ok = shape.plan.ok && v < 2;
+        j.need[v] = job_need(&shape);
+    }
 }
 
 }  // namespace
@@ -4086,12 +4164,14 @@ int micsa_pool_submit(micsa_pool* pool, const micsa_params* p, const micsa_sched
     j.sched.T0 = s->T0;
     j.sched.T1 = s->T1;
     j.sched.n_sweeps = s->n_sweeps;
+    j.sched.n_steps = (s->n_sweeps + std::max(p->gamma, 1) - 1) / std::max(p->gamma, 1);
     if (s->kind == MICSA_SCHED_TABLE) {
         if (!s->T_table || s->T_len < refresh_count(j.sched)) return MICSA_EINVAL;
         j.sched.table.assign(s->T_table, s->T_table + s->T_len);
     }
     j.bytes = footprint(p);
     if (j.bytes > pool->budget) return MICSA_EINVAL;
+    plan_job(j);
     j.id = pool->next_id++;
     *job = j.id;
     pool->jobs.push_back(std::move(j));
@@ -4129,8 +4209,7 @@ static int enqueue_batch(micsa_pool* pool, int64_t sweeps)
         micsa_ctx* c = j.ctx;
         const int64_t n = std::min<int64_t>(sweeps, c->sched.n_sweeps - c->k);
         if (n <= 0) continue;
-        int st;
-        if ((st = cells_alloc(c)) || (st = need_planes(c))) return st;
+        if (const int st = need_planes(c)) return st;  // (a batched job has had its planes since it was admitted)
         c->home_ok = false;
         parts.push_back(Part{&j, c->k, c->k + n});
     }
@@ -4262,19 +4341,36 @@ int micsa_pool_step(micsa_pool* pool, int64_t sweeps, int32_t* running, int32_t*
     // 2. admit queued jobs in arrival order while they fit
     int32_t nrun = 0;
     for (auto& j : pool->jobs) nrun += j.state == MICSA_JOB_RUNNING;
+    // what the queued jobs that fit now leave of the budget: from it a job may hold
+    // more than its footprint
+    size_t spare = pool->budget - std::min(pool->budget, pool->used);
+    int64_t places = (int64_t)pool->max_running - nrun;
+    for (const auto& j : pool->jobs) {
+        if (j.state != MICSA_JOB_QUEUED) continue;
+        if (places-- <= 0 || j.bytes > spare) break;
+        spare -= j.bytes;
+    }
     for (auto& j : pool->jobs) {
         if (j.state != MICSA_JOB_QUEUED) continue;
         if (nrun >= pool->max_running || pool->used + j.bytes > pool->budget) break;
         micsa_params pr = j.p;
         micsa_ctx* probe = nullptr;
-        micsa_ctx shape;
-        if (const int st = setup_ctx(&shape, &pr, nullptr)) return st;
-        const bool batched = batches(&shape);
-        // what the footprint leaves beside the home arrays and the planes, or 1 MiB
-        const size_t sites = (size_t)shape.L * 2 * (size_t)shape.g.Nh;
-        const size_t words = (size_t)shape.L * 2 * (size_t)cell_geom(&shape).plane * 4;
-        const size_t taken = (shape.bit ? j.bytes : 2 * sites) + words * (shape.plan.sweeps > 0 ? 6 : 3) + words * 3;
-        const size_t room = std::max<size_t>(j.bytes > taken ? j.bytes - taken : 0, (size_t)1 << 20);
+        micsa_ctx like, shape;
+        like.device = j.device;
+        like.cus = j.cus;
+        like.plan = j.plan;
+        like.tile2 = j.tile2;
+        if (const int st = setup_ctx(&shape, &pr, nullptr, &like)) return st;
+        // as much as fits; the state's own arrays always do.  (The footprint has
+        // reduction slots for one replica of each sample and no padding.)
+        const size_t most = j.bytes + spare + (size_t)(shape.L - shape.p.n_samples) * kSlots * 8 + 4096;
+        int fit = 0;
+        while (fit < 2 && j.need[fit] > most) ++fit;
+        shape.pooled = true;
+        shape.draw_room = j.draw_room[std::min(fit, 1)];
+        shape.plan.ok = shape.plan.ok && fit < 2;
+        const size_t charge = std::max(j.bytes, j.need[fit]);
+        bool batched = batches(&shape);
         const int device = shape.device;
         if (batched && pool->side && pool->side_device != device) {
             if (hipStreamSynchronize(pool->side) != hipSuccess) return MICSA_EHIP;
@@ -4291,31 +4387,65 @@ int micsa_pool_step(micsa_pool* pool, int64_t sweeps, int32_t* running, int32_t*
             }
             pool->side_device = device;
         }
-        if (!batched && (take_stream(&pool->store, device, &j.stream) != hipSuccess ||
-                         hipEventCreateWithFlags(&j.ev[0], hipEventDisableTiming) != hipSuccess ||
-                         hipEventCreateWithFlags(&j.ev[1], hipEventDisableTiming) != hipSuccess)) {
+        const auto own_stream = [&] {
+            if (take_stream(&pool->store, device, &j.stream) == hipSuccess &&
+                hipEventCreateWithFlags(&j.ev[0], hipEventDisableTiming) == hipSuccess &&
+                hipEventCreateWithFlags(&j.ev[1], hipEventDisableTiming) == hipSuccess)
+                return (int)MICSA_OK;
             (void)hipGetLastError();
+            return (int)MICSA_EHIP;
+        };
+        if (!batched && own_stream() != MICSA_OK) {
             free_job_stream(pool, j, device);
             return MICSA_EHIP;
         }
-        limit_store(pool, pool->used + j.bytes);
-        int st = create_ctx(&pr, batched ? pool->side : j.stream, room, &pool->store, &probe);
-        if (st) {
+        limit_store(pool, pool->used + charge);
+        // A device that is fuller than the budget says: the job waits for those
+        // that run, and alone does without what it lacks.
+        const auto drop = [&] {
+            if (j.ctx) micsa_destroy(j.ctx);
+            j.ctx = nullptr;
             free_job_stream(pool, j, device);
-            if (st == MICSA_ENOMEM) break;  // the device is fuller than the budget says: retry next step
+            limit_store(pool, pool->used);
+        };
+        int st = create_ctx(&pr, batched ? pool->side : j.stream, &shape, most - std::min(most, j.need[fit] - ctx_bytes(&shape).home - ctx_bytes(&shape).work),
+                            nrun == 0, &pool->store, &probe);
+        if (st) {
+            drop();
+            if (st == MICSA_ENOMEM) break;  // retry next step
             return st;
         }
         j.ctx = probe;
-        j.batched = batched;
         micsa_schedule cs{j.sched.kind, j.sched.period, j.sched.T0, j.sched.T1, j.sched.n_sweeps,
                           j.sched.table.empty() ? nullptr : j.sched.table.data(), (int64_t)j.sched.table.size()};
-        if ((st = micsa_set_schedule(j.ctx, &cs))) return st;
+        if ((st = micsa_set_schedule(j.ctx, &cs))) {
+            drop();
+            if (st == MICSA_ENOMEM) break;
+            return st;
+        }
         if (batched) {
             if (hipStreamSynchronize(pool->side) != hipSuccess) return MICSA_EHIP;
-            j.ctx->stream = j.ctx->sweep_stream = pool->stream;
+            find_room(j.ctx, MICSA_ALGO_MICSA, kMscMinSweeps);
+            batched = !j.ctx->no_room;
+            if (batched) {
+                j.ctx->stream = j.ctx->sweep_stream = pool->stream;
+            } else {
+                if (own_stream() != MICSA_OK) {
+                    drop();
+                    return MICSA_EHIP;
+                }
+                j.ctx->stream = j.stream;
+            }
         }
+        j.batched = batched;
         j.state = MICSA_JOB_RUNNING;
-        pool->used += j.bytes;
+        size_t holds = j.need[fit] - ctx_bytes(&shape).home - ctx_bytes(&shape).work;
+        for (const JobStore::Block& b : j.ctx->owned)
+            if (b.p != j.ctx->d_dth) holds += b.bytes;
+        j.charged = std::max(j.bytes, holds);
+        spare -= std::min(spare, j.charged - j.bytes);
+        pool->used += j.charged;
+        limit_store(pool, pool->used);
         ++nrun;
     }
     // 3. enqueue the next chunk of sweeps of every running job with a free
@@ -4377,11 +4507,12 @@ int micsa_pool_release(micsa_pool* pool, int64_t job)
         if (j.id != job) continue;
         if (j.state != MICSA_JOB_DONE) return MICSA_EINVAL;
         const int device = j.ctx->device;
-        limit_store(pool, pool->used - j.bytes);
+        limit_store(pool, pool->used - j.charged);
         micsa_destroy(j.ctx);  // synchronises the job's stream
         free_job_stream(pool, j, device);
-        pool->used -= j.bytes;
+        pool->used -= j.charged;
         pool->jobs.erase(pool->jobs.begin() + (long)i);
+        if (pool->jobs.empty()) limit_store(pool, pool->budget);
         return MICSA_OK;
     }
     return MICSA_EINVAL;

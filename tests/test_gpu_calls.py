@@ -4,6 +4,7 @@ import ctypes
 import os
 import shutil
 import subprocess
+import threading
 
 import numpy as np
 import pytest
@@ -134,3 +135,157 @@ def test_sweeps_without_room_for_planes(memory, shape, layout, part):
         o.run(O.ALGO_MICSA, os_, 12, 0)
         assert np.array_equal(g.energy(), o.energy())
         assert np.array_equal(g.spins(), o.sigma) and np.array_equal(g.daemons(), o.m)
+
+
+JOBS = [(8, 1, M.LAYOUT_BYTE), (16, 1, M.LAYOUT_BYTE), (16, 64, M.LAYOUT_BYTE), (32, 5, M.LAYOUT_BYTE),
+        (64, 1, M.LAYOUT_BYTE), (64, 3, M.LAYOUT_BYTE), (128, 1, M.LAYOUT_BYTE), (128, 20, M.LAYOUT_BYTE),
+        (64, 37, M.LAYOUT_BITPLANE), (16, 100, M.LAYOUT_BITPLANE)]
+
+
+def _lanes(layout):
+    return M.LANES_REPLICAS if layout == M.LAYOUT_BITPLANE else M.LANES_SAMPLES
+
+
+def _footprint(L, R, layout):
+    size = ctypes.c_size_t()
+    p = M._params(L, L, L, 1, R, layout, 0, 1, _lanes(layout))
+    assert M.lib().micsa_pool_footprint(ctypes.byref(p), ctypes.byref(size)) == M.OK
+    return size.value
+
+
+def _finish(pool, jobs, sweeps, check=lambda: None):
+    left = set(jobs)
+    for _ in range(100_000):
+        pool.step(sweeps)
+        check()
+        for j in [j for j in left if pool.state(j)[0] == M.JOB_DONE]:
+            left.discard(j)
+            yield j
+        if not left:
+            return
+    raise AssertionError("jobs left")
+
+
+def _beside(R, refreshes):
+    """Tables, slots of further replicas, padding."""
+    return 136 * refreshes + 512 * (R - 1) + 8192
+
+
+@pytest.mark.parametrize("times", [1, 1.4, 10])
+@pytest.mark.parametrize("L,R,layout", JOBS)
+def test_a_job_keeps_to_the_budget(memory, L, R, layout, times):
+    """Alone in a pool whose budget is its footprint, little more, or plenty, with
+    chunks too short for the planes and long ones: never more than the budget is
+    held, and nothing once the pool holds no job; the job ends as it does alone."""
+    budget = int(_footprint(L, R, layout) * times)
+    pool = M.Pool(budget)
+    base = memory.held()
+    for n, period, sweeps in ((40, 10, 20), (12, 4, 3), (60, 1, 60)):
+        sched = M.Schedule(M.SCHED_LINEAR, 2.0, 0.5, n, period)
+        memory.bound()
+        with M.Lattice(L, L, L, 1, R, 7, layout=layout, lane_mode=_lanes(layout)) as g:
+            g.set_schedule(sched)
+            g.sweep(M.ALGO_MICSA, n)
+            want = g.energy()
+        tables = 1 << 20  # of the batched launches, the pool's own (two of them)
+        job = pool.submit(L, L, L, 1, R, 7, sched, layout=layout, lane_mode=_lanes(layout))
+        most = []
+        for j in _finish(pool, [job], sweeps, lambda: most.append(memory.held() - base)):
+            assert np.array_equal(pool.lattice(j).energy(), want)
+            pool.release(j)
+        assert max(most) <= budget + _beside(R, n // period) + 2 * tables
+        assert memory.held() - base in (0, tables, 2 * tables)
+    pool.close()
+
+
+def test_a_pool_keeps_to_its_budget(memory):
+    """Jobs of many sizes through a budget of a few: what they hold, with what
+    lies idle between them, stays within it."""
+    budget = int(2.3 * max(_footprint(*j) for j in JOBS))
+    pool = M.Pool(budget)
+    rng = np.random.default_rng(5)
+    specs = [JOBS[k] for k in rng.integers(0, len(JOBS), 40)]
+    sched = M.Schedule(M.SCHED_LINEAR, 2.0, 0.5, 30, 10)
+    jobs = [pool.submit(L, L, L, 1, R, 7 + i, sched, layout=lay, lane_mode=_lanes(lay))
+            for i, (L, R, lay) in enumerate(specs)]
+    beside = sum(_beside(R, 3) for _, R, _ in specs) + (2 << 20)
+
+    def check():
+        assert memory.held() <= budget + beside
+
+    for j in _finish(pool, jobs, 10, check):
+        pool.release(j)
+        check()
+    pool.close()
+
+
+@pytest.mark.parametrize("room", [1.05, 0.5])
+def test_a_device_with_less_room_than_the_budget(memory, room):
+    """Room for little more than one job at a time, and for less than one job's
+    planes: every job ends as it does alone."""
+    specs = [(32, 6, M.LAYOUT_BYTE), (64, 2, M.LAYOUT_BYTE), (32, 6, M.LAYOUT_BYTE), (64, 2, M.LAYOUT_BYTE)]
+    sched = M.Schedule(M.SCHED_LINEAR, 2.0, 0.5, 30, 10)
+    alone = []
+    for i, (L, R, _) in enumerate(specs):
+        with M.Lattice(L, L, L, 1, R, 7 + i) as g:
+            g.set_schedule(sched)
+            g.sweep(M.ALGO_MICSA, 30)
+            alone.append((g.energy(), g.daemon_energy()))
+    pool = M.Pool(1 << 34)
+    for j in _finish(pool, [pool.submit(8, 8, 8, 1, 1, 1, sched)], 5):
+        pool.release(j)
+    memory.bound(int(room * max(_footprint(*s) for s in specs)))
+    jobs = {pool.submit(L, L, L, 1, R, 7 + i, sched): i for i, (L, R, _) in enumerate(specs)}
+    for j in _finish(pool, jobs, 10):
+        lat = pool.lattice(j)
+        for got, want in zip((lat.energy(), lat.daemon_energy()), alone[jobs[j]]):
+            assert np.array_equal(got, want)
+        pool.release(j)
+    pool.close()
+
+
+def test_contexts_of_a_pool_in_several_threads():
+    """Finished jobs read, swept on and released from threads of their own
+    (releases under the pool's caller's lock) while the pool admits others."""
+    pool, lock = M.Pool(1 << 30), threading.Lock()
+    s1, s2 = M.Schedule(M.SCHED_LINEAR, 2.0, 0.5, 30, 10), M.Schedule(M.SCHED_CONST, 0.8, 0.8, 40, 5)
+    specs = [(16, 3), (64, 1), (32, 2), (16, 40), (64, 2), (32, 1)] * 4
+    jobs = {pool.submit(L, L, L, 1, R, 50 + i, s1): (L, R, 50 + i) for i, (L, R) in enumerate(specs)}
+    got, threads = {}, []
+
+    def use(j, lat):
+        a = lat.energy()
+        lat.set_schedule(s2)
+        lat.sweep(M.ALGO_HEATBATH, 3)
+        lat.sweep(M.ALGO_MICSA, 7)
+        got[j] = a, lat.energy(), lat.spins(), lat.daemons()
+        with lock:
+            pool.release(j)
+
+    left = set(jobs)
+    for _ in range(100_000):
+        with lock:
+            pool.step(10)
+            done = [j for j in left if pool.state(j)[0] == M.JOB_DONE]
+            views = {j: pool.lattice(j) for j in done}
+        for j in done:
+            left.discard(j)
+            threads.append(threading.Thread(target=use, args=(j, views[j])))
+            threads[-1].start()
+        if not left:
+            break
+    for t in threads:
+        t.join(60)
+    assert sorted(got) == sorted(jobs)
+    pool.close()
+    for j, (L, R, seed) in jobs.items():
+        with M.Lattice(L, L, L, 1, R, seed) as g:
+            g.set_schedule(s1)
+            g.sweep(M.ALGO_MICSA, 30)
+            want = [g.energy()]
+            g.set_schedule(s2)
+            g.sweep(M.ALGO_HEATBATH, 3)
+            g.sweep(M.ALGO_MICSA, 7)
+            want += [g.energy(), g.spins(), g.daemons()]
+        for a, b in zip(got[j], want):
+            assert np.array_equal(a, b)
