@@ -89,7 +89,6 @@ struct JobStore {
     std::mutex lock;
     std::vector<Block> idle;  // oldest first
     std::vector<std::pair<int, hipStream_t>> streams;
-    std::vector<void*> pins;  // pinned host buffers of kPinBytes
     size_t held = 0, limit = 0;  // bytes of idle, and their bound
 
     static constexpr size_t kStreams = 32;  // idle streams kept at most
@@ -107,7 +106,6 @@ struct JobStore {
     {
         trim(0);
         for (auto& s : streams) (void)hipStreamDestroy(s.second);
-        for (void* p : pins) (void)hipHostFree(p);
     }
 };
 
@@ -554,24 +552,53 @@ int zero_slots(micsa_ctx* c, unsigned long long* p, int64_t n)
 // 33 and 22, above that the copy is faster.
 constexpr size_t kPinBytes = (size_t)256 << 10, kPinHead = 64, kTicketBytes = (size_t)16 << 10;
 
+// Buffers of contexts that are gone, kept for the next ones of their device (at
+// most kIdlePins, 2 MiB of host memory, until the process ends): allocating one
+// took 32 us of a context's first read, and freeing it 45 us of its end.
+constexpr size_t kIdlePins = 8;
+std::mutex g_pin_lock;
+struct {
+    int device;
+    uint8_t* p;
+} g_pins[kIdlePins];
+size_t g_pin_count = 0;
+
+uint8_t* idle_pin(int device)
+{
+    std::lock_guard<std::mutex> hold(g_pin_lock);
+    for (size_t i = 0; i < g_pin_count; ++i)
+        if (g_pins[i].device == device) {
+            uint8_t* p = g_pins[i].p;
+            g_pins[i] = g_pins[--g_pin_count];
+            return p;
+        }
+    return nullptr;
+}
+
+// (no kernel writes to it any more)
+void give_pin(int device, uint8_t* p)
+{
+    {
+        std::lock_guard<std::mutex> hold(g_pin_lock);
+        if (g_pin_count < kIdlePins) {
+            g_pins[g_pin_count++] = {device, p};
+            return;
+        }
+    }
+    (void)hipHostFree(p);
+}
+
 bool have_pin(micsa_ctx* c)
 {
     if (c->pin) return true;
     if (c->pin_failed) return false;
-    if (c->store) {
-        std::lock_guard<std::mutex> hold(c->store->lock);
-        if (!c->store->pins.empty()) {
-            c->pin = static_cast<uint8_t*>(c->store->pins.back());
-            c->store->pins.pop_back();
-        }
-    }
-    void* p = nullptr;
-    if (!c->pin && hipHostMalloc(&p, kPinHead + kPinBytes, hipHostMallocDefault) != hipSuccess) {
+    void* p = idle_pin(c->device);
+    if (!p && hipHostMalloc(&p, kPinHead + kPinBytes, hipHostMallocDefault) != hipSuccess) {
         (void)hipGetLastError();
         c->pin_failed = true;
         return false;
     }
-    if (!c->pin) c->pin = static_cast<uint8_t*>(p);
+    c->pin = static_cast<uint8_t*>(p);
     *reinterpret_cast<volatile uint32_t*>(c->pin) = c->ticket = 0;
     return true;
 }
@@ -1957,14 +1984,18 @@ bool use_cells(const micsa_ctx* c, int64_t n = kMscMinSweeps)
 
 // Planes (with their alternates where tiles read what others write) and room
 // for drawn levels.  Drawn levels: as many refreshes as fit 8 MiB or the
-// lattices' spins in bytes, whichever is more (a pool's job: 1 MiB, or what its
-// footprint leaves), at least two (a sweep of a baseline draws the words of one
+// lattices' spins in bytes, whichever is more (1.25 MiB where that holds 256: a
+// context below 2 MiB is made and freed in 50 us less; a pool's job: see
+// plan_job), at least two (a sweep of a baseline draws the words of one
 // and a half).
 int64_t cells_draw_cap(const micsa_ctx* c)
 {
     const size_t one = (size_t)c->L * 2 * (size_t)cell_geom(c).plane * 4 * 2;
-    const size_t room =
-        c->draw_room ? c->draw_room : std::max<size_t>((size_t)8 << 20, (size_t)c->L * 2 * (size_t)c->g.Nh);
+    const size_t few = (size_t)5 << 18;
+    const size_t room = c->draw_room ? c->draw_room
+                        : few / one >= 256
+                            ? few
+                            : std::max<size_t>((size_t)8 << 20, (size_t)c->L * 2 * (size_t)c->g.Nh);
     return std::max<int64_t>(2, std::min<int64_t>((int64_t)(room / one), 1024));
 }
 
@@ -2704,14 +2735,7 @@ void free_all(micsa_ctx* c)
             (void)hipEventDestroy(e.second);
         }
     for (const JobStore::Block& b : c->owned) drop_block(c, b);
-    if (c->pin && c->store) {
-        std::lock_guard<std::mutex> hold(c->store->lock);
-        if (c->store->pins.size() < JobStore::kStreams) {
-            c->store->pins.push_back(c->pin);
-            c->pin = nullptr;
-        }
-    }
-    if (c->pin) (void)hipHostFree(c->pin);
+    if (c->pin) give_pin(c->device, c->pin);
 }
 
 // tally <- energies recomputed from the state, on the device.

@@ -1,5 +1,6 @@
-/* Device allocations counted, and refused above a limit: loaded globally before
-   a copy of the library, whose hipMalloc and hipFree then are these. */
+/* Device allocations counted, and refused above a limit, and those of pinned
+   memory counted: loaded globally before a copy of the library, whose hipMalloc,
+   hipFree and hipHostMalloc then are these. */
 #define _GNU_SOURCE
 #include <dlfcn.h>
 #include <link.h>
@@ -58,5 +59,16 @@ int hipFree(void* p)
     return f(p);
 }
 
+static long pinned;
+
+int hipHostMalloc(void** p, size_t n, unsigned flags)
+{
+    static int (*f)(void**, size_t, unsigned);
+    if (!f) f = (int (*)(void**, size_t, unsigned))real("hipHostMalloc");
+    __atomic_add_fetch(&pinned, 1, __ATOMIC_RELAXED);
+    return f(p, n, flags);
+}
+
+long pinned_calls(void) { return __atomic_load_n(&pinned, __ATOMIC_RELAXED); }
 size_t alloc_live(void) { return live; }
 void alloc_limit(size_t n) { limit = n; }

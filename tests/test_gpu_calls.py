@@ -38,7 +38,11 @@ class Memory:
     def __init__(self, shim):
         self.shim = shim
         shim.alloc_live.restype = ctypes.c_size_t
+        shim.pinned_calls.restype = ctypes.c_long
         shim.alloc_limit.argtypes = [ctypes.c_size_t]
+
+    def pinned(self):
+        return self.shim.pinned_calls()
 
     def held(self):
         return self.shim.alloc_live()
@@ -289,3 +293,32 @@ def test_contexts_of_a_pool_in_several_threads():
             want += [g.energy(), g.spins(), g.daemons()]
         for a, b in zip(got[j], want):
             assert np.array_equal(a, b)
+
+
+def test_contexts_one_after_another_share_what_is_dear_to_allocate(memory):
+    """A short life costs no pinned allocation after the first, and little device
+    memory; contexts that live at once read through buffers of their own."""
+    def life(seed, L=16):
+        g = M.Lattice(L, L, L, 1, 1, seed)
+        g.set_schedule(M.Schedule(M.SCHED_CONST, 1.5, 1.5, 100, 10))
+        g.sweep(M.ALGO_MICSA, 10)
+        return g
+
+    life(1).energy()
+    before = memory.pinned()
+    for seed in range(6):
+        with life(seed) as g:
+            o = O.Lattice(16, 16, 16, 1, 1, seed)
+            o.run(O.ALGO_MICSA, O.Schedule(O.SCHED_CONST, 1.5, 1.5, 100, 10), 10, 0)
+            assert np.array_equal(g.energy(), o.energy()) and np.array_equal(g.spins(), o.sigma)
+            assert memory.held() < 2 << 20
+    assert memory.pinned() == before
+    many = [life(s) for s in range(12)]
+    for _ in range(2):
+        for g, want in zip(many, [M.Lattice(16, 16, 16, 1, 1, s) for s in range(12)]):
+            want.set_schedule(M.Schedule(M.SCHED_CONST, 1.5, 1.5, 100, 10))
+            want.sweep(M.ALGO_MICSA, 10)
+            assert np.array_equal(g.energy(), want.energy()) and np.array_equal(g.daemons(), want.daemons())
+            want.close()
+    for g in many:
+        g.close()
