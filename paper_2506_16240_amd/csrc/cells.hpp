@@ -196,6 +196,55 @@ __device__ __forceinline__ int64_t cell_refresh_index(int64_t k, int32_t P)
     return P >= 1 ? k / P : 63 - __clzll((unsigned long long)(k + 1));
 }
 
+// The table of a half sweep: u < t as u <= t - 1, or never for t = 0 (t may be 2^32).
+struct CellTable {
+    uint32_t t[7];
+    uint64_t on[7];
+    bool some_never;  // the smallest is 0 (the scalar unit is near its rate: no masks without it)
+};
+
+__device__ __forceinline__ void cell_table(const HeatBathThresholds& th, CellTable& T)
+{
+#pragma unroll
+    for (int v = 0; v < 7; ++v) {
+        T.t[v] = (uint32_t)(th.tau[v] - (th.tau[v] ? 1u : 0u));
+        T.on[v] = th.tau[v] ? ~0ull : 0ull;
+    }
+    T.some_never = th.tau[6] == 0;
+}
+
+// The comparisons of a cell's 4 n4 sites, the words of base + n4 - 1 .. base.
+template <int ALG, int K>
+__device__ __forceinline__ void cell_compare(const CellTable& T, uint32_t base, int n4, uint32_t time, uint32_t rep,
+                                             uint32_t sw, uint32_t key0, uint32_t key1, uint32_t (&b)[K])
+{
+#pragma unroll
+    for (int i = 0; i < K; ++i) b[i] = 0;
+    auto push = [&](uint32_t u) {
+        uint64_t M[7];
+#pragma unroll
+        for (int v = ALG == 1 ? 0 : 4; v < 7; ++v) M[v] = __ballot(u <= T.t[v]);
+        if (T.some_never)
+#pragma unroll
+            for (int v = ALG == 1 ? 0 : 4; v < 7; ++v) M[v] &= T.on[v];
+        if (ALG == 1) {
+            cell_push(b[0], M[0] ^ M[1] ^ M[2] ^ M[3] ^ M[4] ^ M[5] ^ M[6]);
+            cell_push(b[1], (M[1] & ~M[3]) | M[5]);
+            cell_push(b[K - 1], M[3]);
+        } else {
+            cell_push(b[0], M[4] ^ M[5] ^ M[6]);
+            cell_push(b[1], M[5]);
+        }
+    };
+    for (int c = n4 - 1; c >= 0; --c) {
+        const u32x4 o = philox10(base + (uint32_t)c, time, rep, sw, key0, key1);
+        push(o.v3);
+        push(o.v2);
+        push(o.v1);
+        push(o.v0);
+    }
+}
+
 // Thread per cell of lattice blockIdx.y and half sweep blockIdx.z (uniform, so
 // that its table is too), grid-stride.
 template <int ALG>
@@ -208,44 +257,13 @@ __global__ void __launch_bounds__(64) k_cells_draw_canonical(CellCanon D)
     const uint32_t sw = stream_word(ALG == 1 ? kStreamHeatBath : kStreamMetropolis, (uint32_t)(l / cg.g.R));
     const int64_t k = D.k0 + (blockIdx.z >> 1);
     const uint32_t time = (uint32_t)(2 * k + (blockIdx.z & 1));
-    const HeatBathThresholds& th = D.tab[cell_refresh_index(k / D.gamma, D.period)];
-    // u < t as u <= t - 1, or never for t = 0 (t may be 2^32)
-    uint32_t t[7];
-    uint64_t on[7];
-#pragma unroll
-    for (int v = 0; v < 7; ++v) {
-        t[v] = (uint32_t)(th.tau[v] - (th.tau[v] ? 1u : 0u));
-        on[v] = th.tau[v] ? ~0ull : 0ull;
-    }
-    const bool some_never = th.tau[6] == 0;  // the smallest (the scalar unit is near its rate: no masks without it)
+    CellTable T;
+    cell_table(D.tab[cell_refresh_index(k / D.gamma, D.period)], T);
     for (int64_t cell = (int64_t)blockIdx.x * 64 + threadIdx.x; cell < cg.plane; cell += (int64_t)gridDim.x * 64) {
         const int64_t row = cg.W == 1 ? cell : cell / cg.W;  // (a division is a good part of a short row's work)
         const int w = (int)(cell - row * cg.W), n4 = min(32, cg.g.Kx - 32 * w) >> 2;
-        const uint32_t base = (uint32_t)((row * cg.g.Kx + 32 * w) >> 2);
-        uint32_t b[K] = {};
-        auto push = [&](uint32_t u) {
-            uint64_t M[7];
-#pragma unroll
-            for (int v = ALG == 1 ? 0 : 4; v < 7; ++v) M[v] = __ballot(u <= t[v]);
-            if (some_never)
-#pragma unroll
-                for (int v = ALG == 1 ? 0 : 4; v < 7; ++v) M[v] &= on[v];
-            if (ALG == 1) {
-                cell_push(b[0], M[0] ^ M[1] ^ M[2] ^ M[3] ^ M[4] ^ M[5] ^ M[6]);
-                cell_push(b[1], (M[1] & ~M[3]) | M[5]);
-                cell_push(b[K - 1], M[3]);
-            } else {
-                cell_push(b[0], M[4] ^ M[5] ^ M[6]);
-                cell_push(b[1], M[5]);
-            }
-        };
-        for (int c = n4 - 1; c >= 0; --c) {
-            const u32x4 o = philox10(base + (uint32_t)c, time, rep, sw, cg.g.key0, cg.g.key1);
-            push(o.v3);
-            push(o.v2);
-            push(o.v1);
-            push(o.v0);
-        }
+        uint32_t b[K];
+        cell_compare<ALG, K>(T, (uint32_t)((row * cg.g.Kx + 32 * w) >> 2), n4, time, rep, sw, cg.g.key0, cg.g.key1, b);
 #pragma unroll
         for (int i = 0; i < K; ++i)
             D.dr[((int64_t)blockIdx.z * K + i) * D.L * cg.plane + (int64_t)l * cg.plane + cell] = b[i];
@@ -298,6 +316,8 @@ struct CellSweep {
     int32_t lattices;
     float inv_bdiv;      // 1 / cg.bdiv
     int32_t wander0;     // walkers, one per site: parity of the wandering owed at the start, or -1
+    const HeatBathThresholds* tab;  // baselines that draw in place: the schedule's table (ref0: its next entry)
+    int32_t gamma;                  // and the sweeps of a timestep
 };
 
 // Several families: the levels of each sweep of the launch (in and out), the
@@ -342,7 +362,8 @@ __device__ __forceinline__ int wave_max_dpp(int v)
 // ALG 0: MicSA; 1, 2: the heat bath and Metropolis on drawn planes; 3: walkers,
 // one per site; 4: daemons or walkers in several families (F).
 // RING: tiles with rings (a branch per half sweep costs a whole lattice 5 %).
-template <int NR, int XM, int ALG, bool RING>
+// DRAW: a baseline that draws its comparisons in the half sweep that uses them.
+template <int NR, int XM, int ALG, bool RING, bool DRAW = false>
 __device__ __forceinline__ void cells_body(const CellSweep& J, const CellFamilies* F, int l, int ty, int tz,
                                            uint32_t* lds)
 {
@@ -499,9 +520,10 @@ __device__ __forceinline__ void cells_body(const CellSweep& J, const CellFamilie
     constexpr int K = ALG == 1 ? 3 : 2;
     uint32_t nx[NR][K];
     const int64_t lplane = (int64_t)J.lattices * cg.plane;
-    const uint32_t* cd = CANON ? J.dr0 + (int64_t)l * cg.plane : nullptr;
+    const uint32_t* cd = CANON && !DRAW ? J.dr0 + (int64_t)l * cg.plane : nullptr;
     int halves = 2 * J.n;
     auto fetch_half = [&](int h) {
+        if (DRAW) return;
 #pragma unroll
         for (int i = 0; i < NR; ++i) {
             if (RING && last[i] < h) continue;
@@ -512,6 +534,9 @@ __device__ __forceinline__ void cells_body(const CellSweep& J, const CellFamilie
         cd += halves > 0 ? K * lplane : 0;  // (past the last half: the same addresses again)
     };
     if (CANON) fetch_half(1);
+    CellTable table{};  // of the sweep under way, where the comparisons are drawn here
+    const uint32_t rep = (uint32_t)(l % g.R);
+    const uint32_t stream = stream_word(ALG == 1 ? kStreamHeatBath : kStreamMetropolis, (uint32_t)(l / g.R));
     // families: the next sweep's levels at the places they come from (and the
     // adjacent words of the same row, for a move along x), loaded a sweep ahead
     uint32_t n0[2][NR], n1[2][NR], a0[2][NR], a1[2][NR];
@@ -662,7 +687,12 @@ __device__ __forceinline__ void cells_body(const CellSweep& J, const CellFamilie
         constexpr int p = decltype(pc)::value;
         uint32_t U = 0;
         uint32_t cur[NR][K];
-        if (CANON) {
+        if (CANON && DRAW) {
+#pragma unroll
+            for (int i = 0; i < NR; ++i)  // (gi: the cell's byte offset; one word per row)
+                cell_compare<ALG, K>(table, (gi[i] >> 2) * (uint32_t)(g.Kx >> 2), g.Kx >> 2,
+                                     (uint32_t)(2 * J.k0) + (uint32_t)(h - 1), rep, stream, g.key0, g.key1, cur[i]);
+        } else if (CANON) {
 #pragma unroll
             for (int i = 0; i < NR; ++i)
 #pragma unroll
@@ -733,6 +763,10 @@ __device__ __forceinline__ void cells_body(const CellSweep& J, const CellFamilie
             dr += ref < J.n ? J.dr_stride : 0;
             if (AHEAD) fetch();
         }
+        if (CANON && DRAW && (it == 0 || it == ref || J.period < 1)) {
+            cell_table(J.tab[cell_refresh_index((J.k0 + it) / J.gamma, J.period)], table);
+            if (it == ref) ref += (int64_t)J.period * J.gamma;
+        }
         half(std::integral_constant<int, 0>{}, 2 * it + 1);
         half(std::integral_constant<int, 1>{}, 2 * it + 2);
         if (ALG == 4) {
@@ -793,6 +827,14 @@ __global__ void __launch_bounds__(kCellLanes) k_cells_sweep(CellSweep J)
 {
     __shared__ uint32_t lds[(ALG == 3 && XM > 0 ? 3 : 2) * NR * kCellLanes];
     cells_body<NR, XM, ALG, RING>(J, nullptr, blockIdx.z, blockIdx.x, blockIdx.y, lds);
+}
+
+// The baselines on whole lattices of one word per row, drawing as they go.
+template <int NR, int ALG>
+__global__ void __launch_bounds__(kCellLanes) k_cells_sweep_drawing(CellSweep J)
+{
+    __shared__ uint32_t lds[2 * NR * kCellLanes];
+    cells_body<NR, 0, ALG, false, true>(J, nullptr, blockIdx.z, 0, 0, lds);
 }
 
 template <int NR, int XM>

@@ -1884,12 +1884,31 @@ bool cells_shape_ok(const micsa_ctx* c)
     return cg.plane < ((int64_t)1 << 30) && cg.W <= kCellCap / 25 && c->p.Ly < (1 << 22) && c->p.Lz < (1 << 22);
 }
 
+// Work-groups of a plan on one unit: held at once (by the waves per SIMD that the
+// registers allow) and in rounds, and the cycles of a half sweep of those.
+struct CellLoad {
+    double m, rounds, half;
+    int waves;
+};
+
+CellLoad cell_load(const micsa_ctx* c, int nr, int xm, unsigned block, double wgs)
+{
+    CellLoad d;
+    d.waves = (int)block / 64;
+    const double issue = kCellIssue * (xm == 0 ? 1.0 : (xm == 1 ? 1.15 : 1.2)) * nr;  // of one wave and half
+    const int fit = std::max(1, (nr == 1 ? 32 : (nr == 2 ? 20 : 16)) / d.waves);
+    const double per_cu = std::ceil(wgs / (c->cus > 0 ? c->cus : 256));
+    d.m = std::min<double>(per_cu, fit);
+    d.rounds = per_cu / d.m;
+    d.half = std::max(kCellChain + issue, std::ceil(d.m * d.waves / 4.0) * issue + 100.0);
+    return d;
+}
+
 CellPlan cell_plan(const micsa_ctx* c)
 {
     CellPlan best;
     if (!cells_shape_ok(c)) return best;
     const int W = (c->g.Kx + 31) / 32, Ly = c->p.Ly, Lz = c->p.Lz;
-    const int cus = c->cus > 0 ? c->cus : 256;
     const int xm = W == 1 ? 0 : (c->g.Kx % 32 == 0 ? 1 : 2);
     auto consider = [&](int TY, int TZ, int T) {
         CellTile f{};
@@ -1912,17 +1931,12 @@ CellPlan cell_plan(const micsa_ctx* c)
         // not fit the registers)
         if (nr > (xm == 2 || c->gamma > 1 ? 3 : kCellMaxNR) || f.ntz > 65535) return;
         const bool whole = f.nty * f.ntz == 1;
-        const int block = (int)(((cells + nr - 1) / nr + 63) / 64 * 64), waves = block / 64;
-        const double issue = kCellIssue * (xm == 0 ? 1.0 : (xm == 1 ? 1.15 : 1.2)) * nr;  // of one wave and half
-        // work-groups a unit holds at once: waves per SIMD by registers
-        const int fit = std::max(1, (nr == 1 ? 32 : (nr == 2 ? 20 : 16)) / waves);
+        const int block = (int)(((cells + nr - 1) / nr + 63) / 64 * 64);
         const double wgs = (double)f.nty * f.ntz * c->L;
-        const double per_cu = std::ceil(wgs / cus);
-        const double m = std::min<double>(per_cu, fit), rounds = per_cu / m;
-        const double half = std::max(kCellChain + issue, std::ceil(m * waves / 4.0) * issue + 100.0);
-        const double load = kCellLaunch * rounds + (double)cells * wgs * 72.0 / kCellBytes;
+        const CellLoad d = cell_load(c, nr, xm, (unsigned)block, wgs);
+        const double load = kCellLaunch * d.rounds + (double)cells * wgs * 72.0 / kCellBytes;
         // (several families: at most one sweep of each per launch)
-        const double t = rounds * half * 2.0 + (whole ? (c->gamma > 1 ? load / c->gamma : 0.0) : load / T);
+        const double t = d.rounds * d.half * 2.0 + (whole ? (c->gamma > 1 ? load / c->gamma : 0.0) : load / T);
         if (!best.ok || t < best.cost) {
             best.ok = true;
             best.f = f;
@@ -2154,7 +2168,13 @@ int launch_cells(micsa_ctx* c, int alg, CellSweep& J, const CellFamilies* F = nu
                 {k_cells_sweep_families<3, 0>, k_cells_sweep_families<3, 1>, k_cells_sweep_families<3, 2>}};
             k[pl.nr - 1][pl.xm]<<<grid, pl.block, 0, c->stream>>>(J, *F);
         } else {
-            const CellKernel k = alg == 0   ? cell_kernel<0>(pl)
+            static const CellKernel drawing[2][kCellMaxNR] = {
+                {k_cells_sweep_drawing<1, 1>, k_cells_sweep_drawing<2, 1>, k_cells_sweep_drawing<3, 1>,
+                 k_cells_sweep_drawing<4, 1>},
+                {k_cells_sweep_drawing<1, 2>, k_cells_sweep_drawing<2, 2>, k_cells_sweep_drawing<3, 2>,
+                 k_cells_sweep_drawing<4, 2>}};
+            const CellKernel k = J.tab      ? drawing[alg - 1][pl.nr - 1]
+                                 : alg == 0 ? cell_kernel<0>(pl)
                                  : alg == 1 ? cell_kernel<1>(pl)
                                  : alg == 2 ? cell_kernel<2>(pl)
                                             : cell_kernel<3>(pl);
@@ -2381,6 +2401,30 @@ bool use_cells_canonical(const micsa_ctx* c)
     return c->plan.cost / 2.4e3 + sites / 1.5e6 < sites / 0.68e6;
 }
 
+// The baselines on a whole lattice of one word per row, n sweeps: drawn in the
+// sweep itself (one launch, no words through memory, but a lattice's draws on its
+// own unit) or ahead on the whole device.  Cycles of either: a Philox call with
+// its comparisons takes a wave 510 where a SIMD has several and 800 alone; ahead,
+// a wave draws a word of 4 n4 sites in 650 + 305 n4, and the words go out and in
+// at 4 TB/s; a launch costs 8000.  Heat bath, us per sweep in the sweep / ahead,
+// calls of 60 sweeps: 256 of 8 x 64 x 64 9.5 / 21.5, 1024 of them 38 / 113, 16 of
+// them 9.5 / 5.1, 4096 of 8^3 3.0 / 4.8, 512 of 32^3 14.8 / 14.4, 64^3 x 64 49 /
+// 14; calls of one sweep: 8^3 4.2 / 7.9, 512 of 16^3 6.4 / 10.0, 32^3 10.7 / 7.5.
+bool cells_draw_in_place(const micsa_ctx* c, int alg, int64_t n)
+{
+    const CellPlan& pl = c->plan;
+    if (pl.sweeps > 0 || pl.xm != 0) return false;
+    const CellLoad d = cell_load(c, pl.nr, pl.xm, pl.block, c->L);
+    const double cells = (double)c->L * (double)cell_geom(c).plane, n4 = c->g.Kx / 4;
+    const double simds = 4.0 * (c->cus > 0 ? c->cus : 256);
+    const double call = std::max(800.0, 510.0 * std::ceil(d.m * d.waves / 4.0)) * pl.nr * n4;
+    const double here = 8000.0 + (double)n * 2.0 * d.rounds * (d.half + 500.0 + call);
+    const double draw = cells * 2.0 / 64.0 * std::max(1100.0, 650.0 + 305.0 * n4) / simds;
+    const double words = cells * 2.0 * (alg == 1 ? 3.0 : 2.0) * 4.0 / 1750.0;
+    const double ahead = 16000.0 * std::ceil((double)n / 20.0) + (double)n * (pl.cost + draw + words);
+    return here * 1.1 < ahead;
+}
+
 int sweep_cells_canonical(micsa_ctx* c, int32_t algo, int64_t n, long long* dlog, int64_t stride)
 {
     int st;
@@ -2389,8 +2433,26 @@ int sweep_cells_canonical(micsa_ctx* c, int32_t algo, int64_t n, long long* dlog
     const int alg = algo == MICSA_ALGO_METROPOLIS ? 2 : 1, K = alg == 1 ? 3 : 2;
     const int64_t k_first = c->k, k_end = c->k + n, plane = (int64_t)c->L * cg.plane;
     c->home_ok = false;
-    c->cdr_n = 0;  // the buffer holds the baselines' draws from here on
     if (dlog && (st = enqueue_level_sum(c, c->red))) return st;  // the levels of every logged row
+    if (cells_draw_in_place(c, alg, n)) {
+        while (c->k < k_end) {
+            const int64_t m = std::min(k_end - c->k, dlog ? log_most(c, kResidentChunk, stride) : kResidentChunk);
+            CellSweep J{};
+            J.tab = canonical_table(c, algo);
+            J.gamma = c->gamma;
+            // sweeps to the table's next entry
+            const int64_t step = (int64_t)c->sched.period * c->gamma;
+            J.ref0 = (int32_t)std::min<int64_t>(step > 0 ? (step - c->k % step) % step : 0, INT32_MAX);
+            cell_log(c, J, dlog, c->k - k_first, stride);
+            J.k0 = c->k;
+            J.n = (int32_t)m;
+            if ((st = launch_cells(c, alg, J))) return st;
+            if (dlog && (st = write_log(c, c->k - k_first, m, stride, c->red, dlog))) return st;
+            c->k += m;
+        }
+        return MICSA_OK;
+    }
+    c->cdr_n = 0;  // the buffer holds the baselines' draws from here on
     // Sweeps drawn at once: those that fit the levels' buffer, or one of its own
     // of up to 128 MiB where that gives more and a launch could use them (512
     // lattices of 32^3: one sweep per draw and launch 26 us per sweep, ten 15).

@@ -261,3 +261,29 @@ def test_captured_sweeps_replay(shape, algo):
     o.sigma = 1 - o.sigma
     replay(10)
     g.close()
+
+
+@pytest.mark.parametrize("algo", [M.ALGO_HEATBATH, M.ALGO_METROPOLIS])
+@pytest.mark.parametrize("shape,gamma", [((8, 2, 2, 1, 1), 1), ((8, 8, 8, 3, 2), 2), ((16, 34, 32, 1, 260), 1),
+                                         ((8, 64, 48, 1, 130), 1), ((40, 8, 6, 2, 2), 3), ((64, 32, 32, 1, 300), 1)])
+def test_baselines_that_draw_in_the_sweep(shape, gamma, algo):
+    """Whole lattices of one word per row in calls of one sweep and, where many
+    lattices fill the device, of many: one to four cells per lane, tables that
+    change inside a call, at every timestep and at powers of two, certain and
+    impossible moves, logs; calls that draw ahead in between."""
+    g, o = M.Lattice(*shape, 0xD12A, gamma=gamma), O.Lattice(*shape, 0xD12A, gamma=gamma)
+    big = shape[0] * shape[1] * shape[2] * shape[4] > 1_000_000
+    for P, calls in ((2, (1, 1) if big else (1, 1, 2, 30)), (M.REFRESH_LOG2, (2, 5)), (1, (3,))):
+        g.set_schedule(M.Schedule(M.SCHED_LINEAR, 3.0, 0.05, 60, P))
+        os_ = O.Schedule(O.SCHED_LINEAR, 3.0, 0.05, 60, P)
+        for n in calls:
+            g.sweep(algo, n)
+            o.run(algo, os_, n, 0)
+        assert np.array_equal(g.energy_tally(), o.energy()) and np.array_equal(g.spins(), o.sigma)
+    E, D = g.sweep_logged(algo, 3, 1)
+    Eo, Do = o.run(algo, os_, 3, 1)
+    assert np.array_equal(E, Eo) and np.array_equal(D, Do)
+    g.sweep(M.ALGO_MICSA, 2)
+    o.run(O.ALGO_MICSA, os_, 2, 0)
+    assert np.array_equal(g.daemons(), o.m) and np.array_equal(g.spins(), o.sigma)
+    g.close()
