@@ -535,8 +535,8 @@ __device__ __forceinline__ void cells_body(const CellSweep& J, const CellFamilie
     };
     if (CANON) fetch_half(1);
     CellTable table{};  // of the sweep under way, where the comparisons are drawn here
-    const uint32_t rep = (uint32_t)(l % g.R);
-    const uint32_t stream = stream_word(ALG == 1 ? kStreamHeatBath : kStreamMetropolis, (uint32_t)(l / g.R));
+    const uint32_t rep = DRAW ? (uint32_t)(l % g.R) : 0u;
+    const uint32_t stream = DRAW ? stream_word(ALG == 1 ? kStreamHeatBath : kStreamMetropolis, (uint32_t)(l / g.R)) : 0u;
     // families: the next sweep's levels at the places they come from (and the
     // adjacent words of the same row, for a move along x), loaded a sweep ahead
     uint32_t n0[2][NR], n1[2][NR], a0[2][NR], a1[2][NR];

@@ -68,6 +68,17 @@ struct CellPlan {
     unsigned block = 64;
     int sweeps = 0;   // sweeps per launch of a tiled lattice; 0: the tile is the lattice, any number
     double cost = 0;  // estimated cycles per sweep of every lattice
+    double load = 0;  // of a launch's operands
+    double brief = 0;  // of a short call (CellPlans): of the whole call
+};
+
+// The plan of long calls and, where that has tiles, of what a call's last n <=
+// kBriefSweeps sweeps run on: rings for six sweeps cost a launch of one sweep
+// several times the lattice (8 x 400 x 400 x 8 28.7 us, 19.0 per byte half).
+constexpr int kBriefSweeps = 8;
+struct CellPlans {
+    CellPlan main, brief[kBriefSweeps + 1];
+    CellPlan walk;  // of long calls of one walker per site, whose kernels hold more in registers
 };
 
 // Device blocks and streams that a serving pool hands from one job to the next.
@@ -181,6 +192,12 @@ struct micsa_ctx {
     // cell sweeps (cells.hpp): launch plan, and the levels of cdr_n refreshes
     // from index cdr_rho0 on, drawn ahead (room for cdr_cap of them)
     CellPlan plan;
+    CellPlan brief[kBriefSweeps + 1];
+    CellPlan walk;
+    // what the sweep call under way runs on against the rule for long calls, and
+    // the us that short calls have lost where they are (see choose_arrays)
+    bool off_cells = false, on_cells = false;
+    double lag = 0;
     bool no_room = false;  // there was none for the planes: the paths on the layout's own arrays, until a new schedule
     MscTile tile2{};  // tile of the two-sweep multispin pass (follows the tile options)
     uint32_t *cdr0 = nullptr, *cdr1 = nullptr;
@@ -1904,10 +1921,11 @@ CellLoad cell_load(const micsa_ctx* c, int nr, int xm, unsigned block, double wg
     return d;
 }
 
-CellPlan cell_plan(const micsa_ctx* c)
+CellPlans cell_plans(const micsa_ctx* c)
 {
-    CellPlan best;
-    if (!cells_shape_ok(c)) return best;
+    CellPlans plans;
+    CellPlan& best = plans.main;
+    if (!cells_shape_ok(c)) return plans;
     const int W = (c->g.Kx + 31) / 32, Ly = c->p.Ly, Lz = c->p.Lz;
     const int xm = W == 1 ? 0 : (c->g.Kx % 32 == 0 ? 1 : 2);
     auto consider = [&](int TY, int TZ, int T) {
@@ -1928,27 +1946,39 @@ CellPlan cell_plan(const micsa_ctx* c)
         const int64_t cells = (int64_t)f.EY * f.EZ * W;
         const int nr = (int)((cells + kCellLanes - 1) / kCellLanes);
         // (four cells of rows with a short last word, or of several families, do
-        // not fit the registers)
-        if (nr > (xm == 2 || c->gamma > 1 ? 3 : kCellMaxNR) || f.ntz > 65535) return;
+        // not fit the registers; nor do three of several families with more than
+        // a word per row: 4 x 160^3 with two daemons 20.8 us per sweep, on two 9.5)
+        if (nr > (c->gamma > 1 ? (xm == 0 ? 3 : 2) : (xm == 2 ? 3 : kCellMaxNR)) || f.ntz > 65535) return;
         const bool whole = f.nty * f.ntz == 1;
         const int block = (int)(((cells + nr - 1) / nr + 63) / 64 * 64);
         const double wgs = (double)f.nty * f.ntz * c->L;
         const CellLoad d = cell_load(c, nr, xm, (unsigned)block, wgs);
         const double load = kCellLaunch * d.rounds + (double)cells * wgs * 72.0 / kCellBytes;
         // (several families: at most one sweep of each per launch)
-        const double t = d.rounds * d.half * 2.0 + (whole ? (c->gamma > 1 ? load / c->gamma : 0.0) : load / T);
-        if (!best.ok || t < best.cost) {
-            best.ok = true;
-            best.f = f;
-            best.nr = nr;
-            best.xm = xm;
-            best.block = (unsigned)block;
-            best.sweeps = whole ? 0 : T;
-            best.cost = t;
+        const double sweep = d.rounds * d.half * 2.0;
+        const double t = sweep + (whole ? (c->gamma > 1 ? load / c->gamma : 0.0) : load / T);
+        CellPlan p;
+        p.ok = true;
+        p.f = f;
+        p.nr = nr;
+        p.xm = xm;
+        p.block = (unsigned)block;
+        p.sweeps = whole ? 0 : T;
+        p.cost = t;
+        p.load = load;
+        if (!best.ok || t < best.cost) best = p;
+        // (with four cells of rows of several words their kernel spills 56 registers)
+        if (nr <= (xm == 1 ? 3 : kCellMaxNR) && (!plans.walk.ok || t < plans.walk.cost)) plans.walk = p;
+        for (int n = 1; n <= kBriefSweeps; ++n) {
+            p.brief = std::ceil((double)n / (whole ? std::max(n, 1) : T)) * load + n * sweep;
+            if (!plans.brief[n].ok || p.brief < plans.brief[n].brief) plans.brief[n] = p;
         }
     };
     if ((int64_t)Ly * Lz * W <= kCellCap) consider(Ly, Lz, 1);
-    if (best.ok && best.nr <= 2) return best;  // no tile makes up for its launches here
+    if (best.ok && best.nr <= 2) {  // no tile makes up for its launches here
+        plans.walk = best;
+        return plans;
+    }
     // tiles that divide a side about evenly, a few per factor of two
     auto sides = [](int L) {
         std::vector<int> v;
@@ -1971,7 +2001,15 @@ CellPlan cell_plan(const micsa_ctx* c)
                     consider(ty, tz, T);
             }
     }
-    return best;
+    return plans;
+}
+
+// The plan of the next launch of a call with `left` sweeps to go.  (A whole
+// lattice has no second copy of its planes, so that its walkers take its plan.)
+const CellPlan& plan_for(const micsa_ctx* c, int64_t left, bool walkers = false)
+{
+    if (c->plan.sweeps > 0 && left <= kBriefSweeps) return c->brief[left];
+    return walkers && c->plan.sweeps > 0 && c->walk.ok ? c->walk : c->plan;
 }
 
 // Estimated cycles per sweep of the two-sweep multispin pass.
@@ -1987,10 +2025,10 @@ double msc_cost(const micsa_ctx* c) { return c->tile2.TY > 0 ? msc2_cost(c, c->t
 // word-wise sweep 8.7.
 bool use_cells(const micsa_ctx* c, int64_t n = kMscMinSweeps)
 {
-    if (!c->plan.ok || c->no_room) return false;
+    if (!c->plan.ok || c->no_room || c->off_cells) return false;
     if (c->bit)
         return c->kernel_opt == MICSA_KERNEL_AUTO && !c->tile_y && !c->tile_z && !c->use_graphs && !c->draw_ahead &&
-               (n >= kMscMinSweeps || c->planes_ok);
+               (n >= kMscMinSweeps || c->planes_ok || c->on_cells);
     if (c->kernel_opt == MICSA_KERNEL_RESIDENT || c->kernel_opt == MICSA_KERNEL_SLAB) return true;
     if (c->kernel_opt != MICSA_KERNEL_AUTO || use_graph(c)) return false;
     return !msc_eligible(c) || resident_eligible(c) || c->plan.cost < msc_cost(c);
@@ -2132,9 +2170,8 @@ CellKernel cell_kernel(const CellPlan& p)
 }
 
 // The launch's planes and shape (J holds its sweeps, draws and logging).
-void fill_cells(const micsa_ctx* c, CellSweep& J)
+void fill_cells(const micsa_ctx* c, CellSweep& J, const CellPlan& pl)
 {
-    const CellPlan& pl = c->plan;
     J.cg = cell_geom(c);
     J.f = pl.f;
     J.s_in = w32(c->ms);
@@ -2153,10 +2190,9 @@ void fill_cells(const micsa_ctx* c, CellSweep& J)
 
 // One launch of the cell kernel on the planes; tiles go from one copy to the
 // other.
-int launch_cells(micsa_ctx* c, int alg, CellSweep& J, const CellFamilies* F = nullptr)
+int launch_cells(micsa_ctx* c, int alg, CellSweep& J, const CellPlan& pl, const CellFamilies* F = nullptr)
 {
-    const CellPlan& pl = c->plan;
-    fill_cells(c, J);
+    fill_cells(c, J, pl);
     {
         TimedLaunch t(c, alg == 1 ? kTimeHeatBath : (alg == 2 ? kTimeMetropolis : kTimeSweep));
         const dim3 grid((unsigned)pl.f.nty, (unsigned)pl.f.ntz, (unsigned)c->L);
@@ -2276,7 +2312,8 @@ int sweep_cells(micsa_ctx* c, int64_t n, long long* dlog, int64_t stride, bool w
         const int64_t k = c->k;
         bool draw;
         CellDraw D;
-        const int64_t most = c->plan.sweeps > 0 ? c->plan.sweeps : kResidentChunk;
+        const CellPlan& pl = plan_for(c, k_end - k, walkers);
+        const int64_t most = pl.sweeps > 0 ? pl.sweeps : kResidentChunk;
         CellSweep J = cells_next(c, k, k_end, dlog ? log_most(c, most, stride) : most, &draw, &D);
         if (draw) {
             {
@@ -2287,7 +2324,7 @@ int sweep_cells(micsa_ctx* c, int64_t n, long long* dlog, int64_t stride, bool w
         }
         cell_log(c, J, dlog, k - k_first, stride);
         J.wander0 = walkers && J.ref0 > 0 ? c->pend_wander : -1;
-        if ((st = launch_cells(c, walkers ? 3 : 0, J))) return st;
+        if ((st = launch_cells(c, walkers ? 3 : 0, J, pl))) return st;
         if (dlog && (st = write_log(c, k - k_first, J.n, stride, nullptr, dlog))) return st;
         c->k = k + J.n;
         c->pend_wander = walkers ? (int32_t)((c->k - 1) & 1) : -1;
@@ -2332,7 +2369,8 @@ int sweep_cells_families(micsa_ctx* c, int64_t n, bool walkers)
         }
         CellSweep J{};
         CellFamilies F{};
-        const int64_t most = std::min<int64_t>(k_end - c->k, c->plan.sweeps > 0 ? std::min(c->plan.sweeps, gamma) : gamma);
+        const CellPlan& pl = plan_for(c, k_end - c->k);
+        const int64_t most = std::min<int64_t>(k_end - c->k, pl.sweeps > 0 ? std::min(pl.sweeps, gamma) : gamma);
         J.k0 = c->k;
         int64_t len = 0;
         bool settle = false;  // a family would owe a second wandering
@@ -2358,7 +2396,7 @@ int sweep_cells_families(micsa_ctx* c, int64_t n, bool walkers)
         }
         J.n = (int32_t)len;
         J.ref0 = J.n;
-        if ((st = launch_cells(c, 4, J, &F))) return st;
+        if ((st = launch_cells(c, 4, J, pl, &F))) return st;
         c->k += len;
         if (settle) {  // (other algorithms ran the sweeps that would have used the family's levels)
             if ((st = own_home(c)) || (st = need_planes(c))) return st;
@@ -2374,14 +2412,15 @@ int sweep_cells_families(micsa_ctx* c, int64_t n, bool walkers)
 // site) where those leave the device idle (us per sweep, cells against them).
 bool use_cells_walkers(const micsa_ctx* c, int64_t n)
 {
-    if (!c->plan.ok || c->no_room || c->bit) return false;
+    if (!c->plan.ok || c->no_room || c->off_cells || c->bit) return false;
     if (c->kernel_opt != MICSA_KERNEL_AUTO && c->kernel_opt != MICSA_KERNEL_RESIDENT &&
         c->kernel_opt != MICSA_KERNEL_SLAB)
         return false;
     if (c->gamma > 1 || c->kernel_opt != MICSA_KERNEL_AUTO) return true;
-    if (use_msc(c, n, MICSA_ALGO_WALKERS)) return c->plan.cost < msc_cost(c);
+    const CellPlan& pl = plan_for(c, n, true);
+    if (use_msc(c, n, MICSA_ALGO_WALKERS)) return pl.cost < msc_cost(c);
     const double sites = (double)c->L * 2.0 * (double)c->g.Nh;
-    return !use_fused(c) || c->plan.cost * 1.2 / 2.4e3 < std::max(8.0, sites / 1.4e6);
+    return !use_fused(c) || pl.cost * 1.2 / 2.4e3 < std::max(8.0, sites / 1.4e6);
 }
 
 // The heat bath and Metropolis on the cell kernel: their comparisons drawn
@@ -2393,7 +2432,7 @@ bool use_cells_walkers(const micsa_ctx* c, int64_t n)
 // for the fused kernel pay two launches per sweep there.
 bool use_cells_canonical(const micsa_ctx* c)
 {
-    if (!c->plan.ok || c->no_room || c->bit) return false;
+    if (!c->plan.ok || c->no_room || c->off_cells || c->bit) return false;
     if (c->kernel_opt == MICSA_KERNEL_RESIDENT) return true;
     if (c->kernel_opt != MICSA_KERNEL_AUTO || use_graph(c)) return false;
     if (!use_fused(c)) return true;
@@ -2446,7 +2485,7 @@ int sweep_cells_canonical(micsa_ctx* c, int32_t algo, int64_t n, long long* dlog
             cell_log(c, J, dlog, c->k - k_first, stride);
             J.k0 = c->k;
             J.n = (int32_t)m;
-            if ((st = launch_cells(c, alg, J))) return st;
+            if ((st = launch_cells(c, alg, J, c->plan))) return st;
             if (dlog && (st = write_log(c, c->k - k_first, m, stride, c->red, dlog))) return st;
             c->k += m;
         }
@@ -2491,14 +2530,15 @@ int sweep_cells_canonical(micsa_ctx* c, int32_t algo, int64_t n, long long* dlog
         }
         if ((st = check_launch(c, "k_cells_draw_canonical"))) return st;
         while (c->k < k_draw + len) {
-            const int64_t most = c->plan.sweeps > 0 ? c->plan.sweeps : len;
+            const CellPlan& pl = plan_for(c, k_end - c->k);
+            const int64_t most = pl.sweeps > 0 ? pl.sweeps : len;
             const int64_t m = std::min(k_draw + len - c->k, dlog ? log_most(c, most, stride) : most);
             CellSweep J{};
             J.dr0 = draws + (c->k - k_draw) * 2 * K * plane;
             cell_log(c, J, dlog, c->k - k_first, stride);
             J.k0 = c->k;
             J.n = (int32_t)m;
-            if ((st = launch_cells(c, alg, J))) return st;
+            if ((st = launch_cells(c, alg, J, pl))) return st;
             if (dlog && (st = write_log(c, c->k - k_first, m, stride, c->red, dlog))) return st;
             c->k += m;
         }
@@ -2573,6 +2613,7 @@ int begin_sweeps(micsa_ctx* c)
 
 int end_sweeps(micsa_ctx* c, int st)
 {
+    c->off_cells = c->on_cells = false;
     if (--c->depth) return st;
     if (!st) st = rest_state(c);
     if (c->capturing) keep_blocks(c);
@@ -2648,15 +2689,66 @@ int rest_state(micsa_ctx* c)
     return rest_copy(c, c->dem, c->dem_alt, x.dem, bytes * (size_t)c->gamma);
 }
 
+bool takes_cells(const micsa_ctx* c, int32_t algo, int64_t n)
+{
+    return algo == MICSA_ALGO_MICSA     ? use_cells(c, n)
+           : algo == MICSA_ALGO_WALKERS ? use_cells_walkers(c, n)
+                                        : use_cells_canonical(c);
+}
+
+// Calls that the cell sweep takes but that the word-wise or per-half kernels do
+// faster: of one or two sweeps on large lattices in bit planes (every launch
+// loads and stores the planes of each lattice apart), and on rows of few sites
+// (planes of mostly empty words).  Estimates in us, fitted to 50 shapes: a call on
+// cells costs its plan and 3 us; the kernels on the words (per site of 64 lanes)
+// and bytes as below.  One sweep, on cells / on its own arrays: bit planes 64 x
+// 128^3 58 / 37, 64 x 104^3 31 / 24, 64 x 8 x 64 x 64 11.8 / 7.9; bytes, 8 of 8 x
+// 400 x 400, MicSA 26 / 23, heat bath 45 / 30 (60 sweeps: 30.3 / 28.6).
+// The state moves from the planes to those arrays, and back for the next long
+// call: a short call stays where its state is until such calls have lost what the
+// move costs.
+void choose_arrays(micsa_ctx* c, int32_t algo, int64_t n)
+{
+    if (!c->bit && (c->g.Kx > 12 || c->plan.sweeps == 0)) return;
+    if (c->captured || c->no_room || !c->plan.ok || algo == MICSA_ALGO_WALKERS || !takes_cells(c, algo, kMscMinSweeps)) return;
+    const double sites = (double)c->L * 2.0 * (double)c->g.Nh;
+    const CellPlan& pl = plan_for(c, n);
+    // (the cost of a tiled plan has its launches in it)
+    double cells = (pl.cost * (double)n + (pl.sweeps > 0 ? 0.0 : pl.load)) / 2.4e3 + 3.0, home, move;
+    if (c->bit) {
+        const double lanes = 64.0 * (double)word_lattices(c) * 2.0 * (double)c->g.Nh;
+        home = (bp_one_launch(c) ? std::max(8.0, 4.0 + lanes / 2.4e6) : std::max(18.0, lanes / 3.6e6)) * (double)n;
+        move = 20.0 + lanes / 2e6;
+    } else if (algo == MICSA_ALGO_MICSA) {
+        home = std::max(10.0, 3.0 + sites / 0.62e6) * (double)n;
+        move = 20.0 + sites / 1e6;
+    } else {
+        const double words = (double)c->L * (double)cell_geom(c).plane, heat = algo == MICSA_ALGO_HEATBATH ? 1.0 : 0.85;
+        const double simds = 4.0 * (c->cus > 0 ? c->cus : 256);
+        const double draw = words * 2.0 / 64.0 * std::max(1100.0, 650.0 + 305.0 * c->g.Kx / 4) / simds;
+        cells += (double)n * heat * (draw + words * 48.0 / 1750.0) / 2.4e3 + 3.0;
+        home = std::max(12.0, 4.0 + sites / 0.40e6) * (double)n;
+        move = 20.0 + sites / 1e6;
+    }
+    const bool on = c->planes_ok && !c->home_ok, off = c->home_ok && !c->planes_ok;
+    if (home * 1.25 < cells) {
+        c->off_cells = !on || (c->lag += cells - home) >= move;
+        if (c->off_cells) c->lag = 0;
+    } else if (off && c->bit && n < kMscMinSweeps && cells * 1.1 < home) {
+        c->on_cells = (c->lag += home - cells) >= move;
+        if (c->on_cells) c->lag = 0;
+    } else {
+        c->lag = 0;
+    }
+}
+
 // Room for the planes of a call that takes the cell sweep.  Without it the call
 // runs on the layout's own arrays, and so do those that follow until a schedule
 // is installed (each would wait for an allocation to fail).
 void find_room(micsa_ctx* c, int32_t algo, int64_t n)
 {
-    const bool cells = algo == MICSA_ALGO_MICSA     ? use_cells(c, n)
-                       : algo == MICSA_ALGO_WALKERS ? use_cells_walkers(c, n)
-                                                    : use_cells_canonical(c);
-    if (n <= 0 || !cells || cells_alloc(c) == MICSA_OK) return;
+    if (c->ms && c->cdr0 && (c->plan.sweeps == 0 || c->ms_alt)) return;  // there
+    if (n <= 0 || !takes_cells(c, algo, n) || cells_alloc(c) == MICSA_OK) return;
     c->no_room = true;
     c->err.clear();
 }
@@ -2698,6 +2790,7 @@ int sweep_run(micsa_ctx* c, int32_t algo, int64_t n)
     int st0 = check_sweep(c, algo, n);
     if (st0) return st0;
     if (algo == MICSA_ALGO_WALKERS && n > 0 && (st0 = need_dem_alt(c))) return st0;
+    if (n > 0) choose_arrays(c, algo, n);
     find_room(c, algo, n);
     // walkers (gamma = 1) on the fused sweep carry their wandering into the
     // next sweep's loads; every other path needs the daemons in place
@@ -2884,7 +2977,16 @@ static int setup_ctx(micsa_ctx* c, const micsa_params* p, hipStream_t stream, co
     g.gamma = gamma;
 
     const bool same = like && like->device == c->device && like->cus == c->cus;
-    c->plan = same ? like->plan : cell_plan(c);
+    if (same) {
+        c->plan = like->plan;
+        c->walk = like->walk;
+        std::copy(std::begin(like->brief), std::end(like->brief), c->brief);
+    } else {
+        const CellPlans plans = cell_plans(c);
+        c->plan = plans.main;
+        c->walk = plans.walk;
+        std::copy(std::begin(plans.brief), std::end(plans.brief), c->brief);
+    }
     c->tile2 = same ? like->tile2 : msc2_plan(c);
     return st;
 }
@@ -4059,7 +4161,7 @@ struct PoolJob {
     // from submission on: launch plans; and what the job may hold, the most
     // first: planes and levels drawn for up to 16 refreshes, planes and two
     // refreshes, the state's own arrays alone
-    CellPlan plan;
+    CellPlans plans;
     MscTile tile2{};
     int device = 0, cus = 0;
     size_t draw_room[2] = {0, 0};
@@ -4112,7 +4214,9 @@ void plan_job(PoolJob& j)
     micsa_ctx shape;
     (void)setup_ctx(&shape, &j.p, nullptr);
     shape.pooled = true;
-    j.plan = shape.plan;
+    j.plans.main = shape.plan;
+    j.plans.walk = shape.walk;
+    std::copy(std::begin(shape.brief), std::end(shape.brief), j.plans.brief);
     j.tile2 = shape.tile2;
     j.device = shape.device;
     j.cus = shape.cus;
@@ -4320,7 +4424,7 @@ static int enqueue_batch(micsa_pool* pool, int64_t sweeps)
             bool draw;
             CellDraw D;
             CellSweep J = cells_next(c, p.k, p.end, kResidentChunk, &draw, &D);
-            fill_cells(c, J);
+            fill_cells(c, J, c->plan);
             if (draw) {
                 for (int l = 0; l < c->L; ++l) items.push_back(CellItem{(int32_t)draws.size(), l});
                 draws.push_back(D);
@@ -4444,7 +4548,9 @@ int micsa_pool_step(micsa_pool* pool, int64_t sweeps, int32_t* running, int32_t*
         micsa_ctx like, shape;
         like.device = j.device;
         like.cus = j.cus;
-        like.plan = j.plan;
+        like.plan = j.plans.main;
+        like.walk = j.plans.walk;
+        std::copy(std::begin(j.plans.brief), std::end(j.plans.brief), like.brief);
         like.tile2 = j.tile2;
         if (const int st = setup_ctx(&shape, &pr, nullptr, &like)) return st;
         // as much as fits; the state's own arrays always do.  (The footprint has

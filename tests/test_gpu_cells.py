@@ -287,3 +287,38 @@ def test_baselines_that_draw_in_the_sweep(shape, gamma, algo):
     o.run(O.ALGO_MICSA, os_, 2, 0)
     assert np.array_equal(g.daemons(), o.m) and np.array_equal(g.spins(), o.sigma)
     g.close()
+
+
+@pytest.mark.parametrize("shape,gamma", [((64, 64, 64, 1, 2), 1), ((104, 46, 38, 2, 2), 1), ((24, 4, 600, 1, 1), 2),
+                                         ((160, 48, 48, 1, 2), 2), ((128, 64, 64, 1, 3), 1)])
+@pytest.mark.parametrize("algo", [M.ALGO_MICSA, M.ALGO_WALKERS, M.ALGO_METROPOLIS])
+def test_short_calls_in_tiles(shape, gamma, algo):
+    """Calls of one to nine sweeps, each on tiles of its own length, between long
+    ones; refreshes inside and at the ends."""
+    g, o = M.Lattice(*shape, 0x5407, gamma=gamma), O.Lattice(*shape, 0x5407, gamma=gamma)
+    g.set_schedule(M.Schedule(M.SCHED_LINEAR, 2.0, 0.6, 100, 4))
+    os_ = O.Schedule(O.SCHED_LINEAR, 2.0, 0.6, 100, 4)
+    for n in (1, 2, 3, 11, 4, 5, 1, 6, 7, 8, 9):
+        g.sweep(algo, n)
+        o.run(algo, os_, n, 0)
+        assert np.array_equal(g.energy_tally(), o.energy()) and np.array_equal(g.energy(), o.energy())
+    assert np.array_equal(g.daemons(), o.m) and np.array_equal(g.spins(), o.sigma)
+    g.close()
+
+
+@pytest.mark.parametrize("shape,layout,algo", [((8, 64, 64, 64, 1), M.LAYOUT_BITPLANE, M.ALGO_MICSA),
+                                               ((8, 400, 400, 1, 4), M.LAYOUT_BYTE, M.ALGO_MICSA),
+                                               ((8, 400, 400, 1, 4), M.LAYOUT_BYTE, M.ALGO_HEATBATH)])
+def test_calls_that_move_between_planes_and_the_layouts_arrays(shape, layout, algo):
+    """Runs of single sweeps (which leave the planes once that pays), of a few
+    and of many, with reads in between and without."""
+    g, o = M.Lattice(*shape, 0x3071, layout=layout), O.Lattice(*shape, 0x3071)
+    g.set_schedule(M.Schedule(M.SCHED_LINEAR, 2.0, 0.6, 100, 4))
+    os_ = O.Schedule(O.SCHED_LINEAR, 2.0, 0.6, 100, 4)
+    for times, n in ((1, 9), (14, 1), (1, 1), (6, 3), (1, 10), (2, 1)):
+        for _ in range(times):
+            g.sweep(algo, n)
+        o.run(algo, os_, times * n, 0)
+        assert np.array_equal(g.energy(), o.energy()) and np.array_equal(g.energy_tally(), o.energy())
+    assert np.array_equal(g.daemons(), o.m) and np.array_equal(g.spins(), o.sigma)
+    g.close()
