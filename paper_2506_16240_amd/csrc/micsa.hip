@@ -26,9 +26,50 @@
 #include "msc_kernels.hpp"
 #include "msc2_kernels.hpp"
 #include "observables.hpp"
+#include "pins.hpp"
 #include "micsa.h"
 
 using namespace micsa;
+
+namespace micsa {
+
+static std::mutex g_pin_lock;
+static struct {
+    int device;
+    uint8_t* p;
+} g_pins[kIdlePins];
+static size_t g_pin_count = 0;
+
+uint8_t* take_pin(int device)
+{
+    {
+        std::lock_guard<std::mutex> hold(g_pin_lock);
+        for (size_t i = 0; i < g_pin_count; ++i)
+            if (g_pins[i].device == device) {
+                uint8_t* p = g_pins[i].p;
+                g_pins[i] = g_pins[--g_pin_count];
+                return p;
+            }
+    }
+    void* p = nullptr;
+    if (hipHostMalloc(&p, kPinHead + kPinBytes, hipHostMallocDefault) == hipSuccess) return static_cast<uint8_t*>(p);
+    (void)hipGetLastError();
+    return nullptr;
+}
+
+void give_pin(int device, uint8_t* pin)
+{
+    {
+        std::lock_guard<std::mutex> hold(g_pin_lock);
+        if (g_pin_count < kIdlePins) {
+            g_pins[g_pin_count++] = {device, pin};
+            return;
+        }
+    }
+    (void)hipHostFree(pin);
+}
+
+}  // namespace micsa
 
 namespace {
 
@@ -567,55 +608,17 @@ int zero_slots(micsa_ctx* c, unsigned long long* p, int64_t n)
 // memory and a stream synchronisation took 23 us for 512 bytes, a kernel that
 // writes pinned memory and a synchronisation 11.7, the ticket 6.4; at 256 KiB
 // 33 and 22, above that the copy is faster.
-constexpr size_t kPinBytes = (size_t)256 << 10, kPinHead = 64, kTicketBytes = (size_t)16 << 10;
-
-// Buffers of contexts that are gone, kept for the next ones of their device (at
-// most kIdlePins, 2 MiB of host memory, until the process ends): allocating one
-// took 32 us of a context's first read, and freeing it 45 us of its end.
-constexpr size_t kIdlePins = 8;
-std::mutex g_pin_lock;
-struct {
-    int device;
-    uint8_t* p;
-} g_pins[kIdlePins];
-size_t g_pin_count = 0;
-
-uint8_t* idle_pin(int device)
-{
-    std::lock_guard<std::mutex> hold(g_pin_lock);
-    for (size_t i = 0; i < g_pin_count; ++i)
-        if (g_pins[i].device == device) {
-            uint8_t* p = g_pins[i].p;
-            g_pins[i] = g_pins[--g_pin_count];
-            return p;
-        }
-    return nullptr;
-}
-
-// (no kernel writes to it any more)
-void give_pin(int device, uint8_t* p)
-{
-    {
-        std::lock_guard<std::mutex> hold(g_pin_lock);
-        if (g_pin_count < kIdlePins) {
-            g_pins[g_pin_count++] = {device, p};
-            return;
-        }
-    }
-    (void)hipHostFree(p);
-}
+constexpr size_t kTicketBytes = (size_t)16 << 10;
 
 bool have_pin(micsa_ctx* c)
 {
     if (c->pin) return true;
     if (c->pin_failed) return false;
-    void* p = idle_pin(c->device);
-    if (!p && hipHostMalloc(&p, kPinHead + kPinBytes, hipHostMallocDefault) != hipSuccess) {
-        (void)hipGetLastError();
+    c->pin = take_pin(c->device);
+    if (!c->pin) {
         c->pin_failed = true;
         return false;
     }
-    c->pin = static_cast<uint8_t*>(p);
     *reinterpret_cast<volatile uint32_t*>(c->pin) = c->ticket = 0;
     return true;
 }
@@ -1947,7 +1950,7 @@ CellPlans cell_plans(const micsa_ctx* c)
         const int nr = (int)((cells + kCellLanes - 1) / kCellLanes);
         // (four cells of rows with a short last word, or of several families, do
         // not fit the registers; nor do three of several families with more than
-        // a word per row: 4 x 160^3 with two daemons 20.8 us per sweep, on two 9.5)
+        // a word per row: 4 x 160^3 with two daemons 20.8 us per sweep, on two 13.3)
         if (nr > (c->gamma > 1 ? (xm == 0 ? 3 : 2) : (xm == 2 ? 3 : kCellMaxNR)) || f.ntz > 65535) return;
         const bool whole = f.nty * f.ntz == 1;
         const int block = (int)(((cells + nr - 1) / nr + 63) / 64 * 64);
@@ -2702,7 +2705,7 @@ bool takes_cells(const micsa_ctx* c, int32_t algo, int64_t n)
 // (planes of mostly empty words).  Estimates in us, fitted to 50 shapes: a call on
 // cells costs its plan and 3 us; the kernels on the words (per site of 64 lanes)
 // and bytes as below.  One sweep, on cells / on its own arrays: bit planes 64 x
-// 128^3 58 / 37, 64 x 104^3 31 / 24, 64 x 8 x 64 x 64 11.8 / 7.9; bytes, 8 of 8 x
+// 128^3 58 / 47, 64 x 104^3 31 / 27, 64 x 8 x 64 x 64 11.8 / 7.2; bytes, 8 of 8 x
 // 400 x 400, MicSA 26 / 23, heat bath 45 / 30 (60 sweeps: 30.3 / 28.6).
 // The state moves from the planes to those arrays, and back for the next long
 // call: a short call stays where its state is until such calls have lost what the

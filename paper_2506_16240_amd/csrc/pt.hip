@@ -14,6 +14,7 @@
 #include <vector>
 
 #include "micsa.h"
+#include "pins.hpp"
 #include "pt_kernels.hpp"
 
 using namespace micsa;
@@ -36,7 +37,8 @@ struct micsa_pt {
     int32_t* perm = nullptr;     // [runs][2][M]
     int64_t* E = nullptr;        // [runs][2][M] by slot
     int64_t* swaps = nullptr;    // [runs][2][M-1]
-    int64_t* out = nullptr;      // [kPtReadWords] results of a read, in pinned host memory
+    uint8_t* pin = nullptr;      // pinned host buffer of the reads (pins.hpp), from the first one on
+    int device = 0;
     uint32_t* wtab = nullptr;    // [M][kPtTable] device form (thresholds - 1, guides)
     uint32_t* ptab = nullptr;    // [M-1][kPtTable]
     std::vector<int32_t> Jq;     // [3][N]
@@ -53,7 +55,7 @@ namespace {
 
 constexpr uint32_t kPtLds = 160u * 1024u;  // of a compute unit
 constexpr uint32_t kPtLdsMax = 150u * 1024u;
-constexpr int64_t kPtReadWords = 1 << 16;  // buffer of a read's results
+constexpr int64_t kPtReadWords = kPinBytes / 8;  // results of a read at a time
 
 int pt_fail(micsa_pt* c, int st, const std::string& m)
 {
@@ -122,7 +124,7 @@ void free_pt(micsa_pt* c)
     for (void* ptr : {(void*)c->rec, (void*)c->spins, (void*)c->perm, (void*)c->E, (void*)c->swaps, (void*)c->wtab,
                       (void*)c->ptab, (void*)c->ftab})
         if (ptr) (void)hipFree(ptr);
-    if (c->out) (void)hipHostFree(c->out);
+    if (c->pin) give_pin(c->device, c->pin);
     for (auto& ev : c->events)
         for (hipEvent_t x : ev) (void)hipEventDestroy(x);
 }
@@ -296,6 +298,7 @@ int micsa_pt_create(const micsa_pt_params* p, const double* J, const double* T, 
     if (!c) return MICSA_ENOMEM;
     c->p = *p;
     c->stream = (hipStream_t)hip_stream;
+    if (hipGetDevice(&c->device) != hipSuccess) (void)hipGetLastError();
     c->Jq = std::move(Jq);
     c->hw = std::move(hw);
     c->hp = std::move(hp);
@@ -344,7 +347,6 @@ int micsa_pt_create(const micsa_pt_params* p, const double* J, const double* T, 
               hipMalloc(&c->spins, nslot * g.R0 * 8) == hipSuccess && hipMalloc(&c->perm, nslot * 4) == hipSuccess &&
               hipMalloc(&c->E, nslot * 8) == hipSuccess &&
               hipMalloc(&c->swaps, (size_t)g.runs * 2 * (M - 1) * 8) == hipSuccess &&
-              hipHostMalloc(&c->out, (size_t)kPtReadWords * 8) == hipSuccess &&
               hipMalloc(&c->wtab, dw.size() * 4) == hipSuccess && hipMalloc(&c->ptab, std::max<size_t>(dp.size(), 1) * 4) == hipSuccess;
     if (!ok) {
         (void)hipGetLastError();
@@ -392,9 +394,7 @@ int micsa_pt_create(const micsa_pt_params* p, const double* J, const double* T, 
         }
         // with field tables (64 bytes per site in LDS, twice the records) where they fit
         int cus = 0;
-        int device = 0;
-        if (hipGetDevice(&device) != hipSuccess ||
-            hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess)
+        if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, c->device) != hipSuccess)
             return fin(MICSA_EHIP);
         const int Gt = walkers ? tab_temperatures(g, G, std::max(cus, 1)) : 0;
         if (Gt > 0) {
@@ -486,18 +486,35 @@ int micsa_pt_read(micsa_pt* pt, int64_t* E, int64_t* Q)
         PT_TRY(pt, hipStreamSynchronize(pt->stream));
         return MICSA_OK;
     }
-    // as many runs at a time as the read buffer holds
+    // as many runs at a time as the buffer holds: pinned host memory, or device
+    // memory and a copy where there is none
+    if (!pt->pin) pt->pin = take_pin(pt->device);
+    int64_t* buf = reinterpret_cast<int64_t*>(pt->pin ? pt->pin + kPinHead : nullptr);
+    if (!buf && hipMalloc(&buf, (size_t)kPtReadWords * 8) != hipSuccess) {
+        (void)hipGetLastError();
+        return pt_fail(pt, MICSA_ENOMEM, "read buffer");
+    }
     const int64_t per = (int64_t)3 * g.M, chunk = std::min<int64_t>(kPtReadWords / per, 65535);
-    for (int64_t u = 0; u < g.runs; u += chunk) {
+    hipError_t err = hipSuccess;
+    for (int64_t u = 0; u < g.runs && err == hipSuccess; u += chunk) {
         const int64_t n = std::min<int64_t>(chunk, g.runs - u);
-        int64_t *dE = E ? pt->out : nullptr, *dQ = Q ? pt->out + (size_t)chunk * 2 * g.M : nullptr;
+        int64_t *dE = E ? buf : nullptr, *dQ = Q ? buf + (size_t)chunk * 2 * g.M : nullptr;
         k_pt_read<<<dim3((unsigned)g.M, (unsigned)n), 64, 0, pt->stream>>>(g, (int)u, pt->perm, pt->E, pt->spins, dE,
                                                                           dQ);
-        PT_TRY(pt, hipGetLastError());
-        PT_TRY(pt, hipStreamSynchronize(pt->stream));
+        err = hipGetLastError();
+        const auto get = [&](int64_t* to, const int64_t* from, size_t words) {
+            if (to && err == hipSuccess && !pt->pin)
+                err = hipMemcpyAsync(to, from, words * 8, hipMemcpyDeviceToHost, pt->stream);
+        };
+        get(E ? E + u * 2 * g.M : nullptr, dE, (size_t)n * 2 * g.M);
+        get(Q ? Q + u * g.M : nullptr, dQ, (size_t)n * g.M);
+        if (err == hipSuccess) err = hipStreamSynchronize(pt->stream);
+        if (err != hipSuccess || !pt->pin) continue;
         if (E) std::memcpy(E + u * 2 * g.M, dE, (size_t)n * 2 * g.M * 8);
         if (Q) std::memcpy(Q + u * g.M, dQ, (size_t)n * g.M * 8);
     }
+    if (!pt->pin) (void)hipFree(buf);
+    PT_TRY(pt, err);
     return MICSA_OK;
 }
 

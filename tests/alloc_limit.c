@@ -60,15 +60,17 @@ int hipFree(void* p)
 }
 
 static long pinned;
+static int refuse_pinned;
 
 int hipHostMalloc(void** p, size_t n, unsigned flags)
 {
     static int (*f)(void**, size_t, unsigned);
     if (!f) f = (int (*)(void**, size_t, unsigned))real("hipHostMalloc");
     __atomic_add_fetch(&pinned, 1, __ATOMIC_RELAXED);
-    return f(p, n, flags);
+    return refuse_pinned ? OUT_OF_MEMORY : f(p, n, flags);
 }
 
 long pinned_calls(void) { return __atomic_load_n(&pinned, __ATOMIC_RELAXED); }
 size_t alloc_live(void) { return live; }
 void alloc_limit(size_t n) { limit = n; }
+void pinned_refuse(int on) { refuse_pinned = on; }

@@ -12,6 +12,7 @@ import torch
 
 from oracle import oracle as O
 from paper_2506_16240_amd import micsa as M
+from paper_2506_16240_amd import workloads as W
 
 pytestmark = pytest.mark.gpu
 
@@ -72,6 +73,7 @@ def memory(counted, monkeypatch):
     before = mem.held()
     yield mem
     mem.bound()
+    mem.shim.pinned_refuse(0)
     assert mem.held() == before
 
 
@@ -322,3 +324,28 @@ def test_contexts_one_after_another_share_what_is_dear_to_allocate(memory):
             want.close()
     for g in many:
         g.close()
+
+
+def test_tempering_reads_with_and_without_pinned_memory(memory):
+    """Contexts one after another read through one buffer (runs in several pieces);
+    where there is no pinned memory a read goes by way of the device."""
+    dims, T = (4, 4, 4), np.linspace(0.3, 2.0, 64)
+    J = W.gaussian_couplings(*dims, 3)
+    o = O.PTLattice(*dims, runs=200, T=T, J=J, seed=9, sweeps=2, algo=O.PT_WALKERS, houdayer=False)
+    o.run(2)
+    want = o.energies(), o.overlaps()
+    pinned = []
+    for refuse in (0, 0, 1, 0):
+        memory.shim.pinned_refuse(refuse)
+        held = [M.PT(*dims, 1, T, J, 1, 2, M.PT_WALKERS, False) for _ in range(9 if refuse else 0)]
+        for h in held:
+            h.read()  # (idle buffers go to these)
+        g = M.PT(*dims, 200, T, J, 9, 2, M.PT_WALKERS, False)
+        g.step(2)
+        E, Q = g.read()
+        assert np.array_equal(E, want[0]) and np.array_equal(Q, want[1])
+        g.close()
+        for h in held:
+            h.close()
+        pinned.append(memory.pinned())
+    assert pinned[1] == pinned[0]
