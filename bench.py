@@ -453,7 +453,7 @@ def main() -> int:
     algo_name = args.algo
     period = M.REFRESH_LOG2 if args.refresh == "log2" else None
     if args.gamma != 1 and (layout or tile):
-        tile = None  # gamma > 1 runs the per-half kernels
+        tile = None  # no launch shape applies to gamma > 1
     log(f"{algo_name}: {w.name}, {sweeps} sweeps, gamma {args.gamma}, refresh {args.refresh}")
     kern = {"auto": 0, "fused": M.KERNEL_FUSED, "multispin": M.KERNEL_MULTISPIN, "slab": M.KERNEL_SLAB,
             "simple": M.KERNEL_SIMPLE}[args.kernel]
@@ -498,19 +498,23 @@ def main() -> int:
     per_update = BYTES_PER_UPDATE_BITPLANE if layout else BYTES_PER_UPDATE[algo_name]
     if "k_wander" in mi["kernel"]:  # a separate wandering kernel moves every daemon byte once more
         per_update += 2.0
-    if mi["kernel"] in ("k_msc_half", "k_msc_sweep", "k_msc_sweep_multi"):
+    # byte-layout forms whose sweeps the cell sweep runs, on the same bit planes
+    cells = not layout and mi["kernel"].startswith(("k_cells", "k_resident", "k_micsa_slab"))
+    if cells or mi["kernel"] in ("k_msc_half", "k_msc_sweep", "k_msc_sweep_multi"):
         per_update = BYTES_PER_UPDATE_MULTISPIN
     bytes_launch = per_update * w.N * w.lattices * min(1.0, sweeps_per_launch)
     achieved = bytes_launch / (avg_ms * 1e6)  # GB/s
     traffic = measured_traffic(mi["kernel"])
-    # what the timed kernel computes on: the multispin sweep holds 1-bit
-    # spin and coupling planes and 2-bit daemons as two planes (64 sites per
-    # 64-bit word); the bit-plane layout the same with 64 samples per word;
+    # what the timed kernel computes on: the multispin and cell sweeps hold 1-bit
+    # spin and coupling planes and 2-bit daemons as two planes (32 sites per
+    # word); the bit-plane layout the same with 64 samples per word;
     # the byte kernels one byte per spin and per daemon
     if mi["kernel"].startswith("k_msc"):
         layout_name, dtype = "multispin", "u1 bit planes (2-bit daemons)"
     elif layout:
         layout_name, dtype = "bitplane", "u1 bit planes (2-bit daemons)"
+    elif cells:
+        layout_name, dtype = "byte", "u1 bit planes (2-bit daemons)"
     else:
         layout_name, dtype = "byte", "u8"
     out = {
