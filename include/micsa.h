@@ -200,8 +200,9 @@ int micsa_read_overlap(micsa_ctx* ctx, int32_t a, int32_t b, int64_t* Q);
    (periodic), mu = x, y, z, for r = 0 .. rmax with rmax = max(Lx, Ly, Lz)/2;
    entries with r > L_mu / 2 are 0.  C4(r) is the mean of G over the three
    axes divided by N R (R - 1) / 2 (so C4(0) = 1).  Host array
-   [S][3][rmax + 1]; EINVAL unless R >= 2.  Allocates and frees a device
-   buffer of at most 256 MiB for the packed overlap fields. */
+   [S][3][rmax + 1]; EINVAL unless R >= 2.  Takes a device buffer of at most
+   256 MiB for the packed overlap fields; up to 16 MiB of it stay with the
+   context as its workspace (a pool's job gives all of it back). */
 int micsa_read_c4(micsa_ctx* ctx, int64_t* G);
 /* micsa_read_c4 without allocation, for callers that cannot allocate
    device memory (code under HIP graph capture, tight serving loops,
@@ -287,12 +288,13 @@ const char* micsa_kernel_name(const micsa_ctx* ctx, int32_t algo);
      the one-launch sweep with its per-lane tally, which AUTO takes where a
      plane has at most 1024 words and which on larger planes runs in row
      tiles only on this request, the per-half kernels being faster there),
-     MICSA_KERNEL_RESIDENT (whole
-     lattice in LDS for many sweeps per launch; byte layout, N <= 102400),
+     MICSA_KERNEL_RESIDENT (the cell sweep: bit planes of 32 sites per word,
+     whole lattices of up to 4096 words per parity for many sweeps per launch,
+     larger ones in tiles; byte layout, N <= 102400),
      MICSA_KERNEL_MULTISPIN (MicSA with daemons, gamma = 1, Lx % 128 == 0:
      multispin coding, Sec. 2.5 -- a sweep call packs the state into bit
-     planes of 64 sites per word, sweeps there with one launch per sweep
-     (or per half sweep, MICSA_OPT_MSC_FUSED) and the refresh fused in; the
+     planes, sweeps there with one launch per two sweeps (MICSA_OPT_MSC_PASS;
+     or per half sweep, MICSA_OPT_MSC_FUSED); the
      planes stay the working state after the call and are unpacked only
      when an entry point next reads or writes the state or sweeps it on
      another path, so consecutive multispin calls pack once; walkers
@@ -329,9 +331,10 @@ const char* micsa_kernel_name(const micsa_ctx* ctx, int32_t algo);
      and planes, the state read and written once per pair; a pass whose
      sweeps include a refresh takes the levels drawn ahead, and a pair with
      two refreshes, a refresh with DRAW_AHEAD 0, the last odd sweep of a
-     call, walkers, or a tile whose work-group does not fit runs one sweep
-     per launch) or 1 (one sweep per launch).  Results are identical; at
-     512^3 on MI355X the pair takes 30 us against 2 x 27 us.
+     call, walkers whose rows do not divide a wave, or a tile whose
+     work-group does not fit runs one sweep per launch) or 1 (one sweep per
+     launch).  Results are identical; at 512^3 on MI355X the pair takes 31 us
+     against 2 x 27 us.
    MICSA_OPT_MSC_FUSED: the multispin sweep in one launch per sweep marching
      along z (1, default) or one launch per half sweep (0).
    MICSA_OPT_PREFETCH: steps of global loads in flight in the fused MicSA
@@ -368,9 +371,9 @@ enum micsa_option {
     MICSA_OPT_MSC_PASS = 10
 };
 enum micsa_kernel_choice {
-    MICSA_KERNEL_AUTO = 0,    /* the cell sweep, or, if Lx % 128 == 0, the two-sweep multispin pass where it is
-                                 estimated faster (MicSA and walkers; heat bath and Metropolis on large
-                                 lattices: the fused sweep) */
+    MICSA_KERNEL_AUTO = 0,    /* the cell sweep; if Lx % 128 == 0, MicSA and walkers take the two-sweep multispin
+                                 pass, and if Lx >= 128, walkers, heat bath and Metropolis the fused sweep, where
+                                 that is estimated faster */
     MICSA_KERNEL_SIMPLE = 1,  /* one launch per half sweep (bit-plane layout: instead of its one-launch sweep) */
     MICSA_KERNEL_FUSED = 2,   /* one launch per sweep, refresh fused in (Lx % 32 == 0) */
     MICSA_KERNEL_RESIDENT = 3, /* the cell sweep (<= 102400 sites, byte layout) */
@@ -539,7 +542,9 @@ int micsa_pt_get_couplings(micsa_pt* pt, int32_t* Jq); /* [3][N] mesh units */
    identical. */
 enum micsa_pt_kernel { MICSA_PT_KERNEL_AUTO = 0, MICSA_PT_KERNEL_ROWS = 1, MICSA_PT_KERNEL_REGISTER = 2 };
 int micsa_pt_set_kernel(micsa_pt* pt, int32_t kernel);
-const char* micsa_pt_kernel_name(const micsa_pt* pt); /* kernel the next step launches */
+const char* micsa_pt_kernel_name(const micsa_pt* pt); /* variant the next step runs: "k_pt_emcs_reg" is the
+                                                         register form, of which walkers whose field tables fit
+                                                         LDS launch k_pt_emcs_tab */
 
 /* Per-kernel timing with HIP events on the stream: kind 0 = EMCS kernel,
    1 = exchange kernel. */

@@ -44,10 +44,15 @@
 // about 36 VALU instructions per wave, 24 of them the move), else the chain
 // of one half: LDS reads, the move, the write, a barrier, 0.12 us with one
 // wave and 0.25 us with sixteen.  Measured against the byte-wise LDS sweeps
-// this replaced (us per sweep, refreshes left out, one MI355X): 8^3 0.24
-// (4.5), 16^3 0.30 (4.2 with a logged row), 64 x 32^3 0.51 (9.9), 256 x 64^3
-// 2.0 = 33700 updates/ns; against one or two byte sweeps per launch: 64^3 x 2
-// 1.4 (3.6), 104 x 90 x 70 x 4 2.8 (10.5).
+// this replaced (us per sweep, refreshes left out, one MI355X): 8^3 0.25
+// (4.5), 16^3 0.32, with a logged row 0.36 (4.2), 64 x 32^3 0.52 (9.9), 256 x
+// 64^3 1.7 = 39600 updates/ns; against one or two byte sweeps per launch: 64^3 x
+// 2 1.19 (3.6), 104 x 90 x 70 x 4 2.56 (10.5).  The VALU is busy 67 % of a launch
+// of 512 lattices of 32^3, 39 % of 256^3 (where waves wait 64 % of their time
+// for memory, LDS and barriers) and 19 % of 64^3 x 2 (128 work-groups of short
+// launches).  Four cells per thread do not fit 128 registers: 1 to 21 spill,
+// up to 57 with a walker per site, so that plans take three there for long calls
+// of rows of several words (three spill 10 to 23).
 #pragma once
 #include "bitplane_kernels.hpp"
 #include "byte_kernels.hpp"
@@ -666,7 +671,7 @@ __device__ __forceinline__ void cells_body(const CellSweep& J, const CellFamilie
     // Logged sweeps: a lane stores its unsatisfied bonds (each counted at its even
     // end) and, above bit 16, its level sum; k_cells_log_rows adds the lanes.
     // The bonds are those that the next even half finds before it moves anything,
-    // so a logged sweep costs a few counts and a store: 0.36 us at 16^3, 0.30 not
+    // so a logged sweep costs a few counts and a store: 0.36 us at 16^3, 0.32 not
     // logged (0.69 with the fields formed once more and the lanes summed here).
     uint32_t* logto = J.log ? J.log + (int64_t)l * B + t : nullptr;
     uint32_t logD = 0;
@@ -829,7 +834,8 @@ __global__ void __launch_bounds__(kCellLanes) k_cells_sweep(CellSweep J)
     cells_body<NR, XM, ALG, RING>(J, nullptr, blockIdx.z, blockIdx.x, blockIdx.y, lds);
 }
 
-// The baselines on whole lattices of one word per row, drawing as they go.
+// The baselines on whole lattices of one word per row, drawing as they go
+// (with four cells per thread 12 or 13 registers spill).
 template <int NR, int ALG>
 __global__ void __launch_bounds__(kCellLanes) k_cells_sweep_drawing(CellSweep J)
 {
@@ -871,7 +877,8 @@ __global__ void __launch_bounds__(256) k_cells_log_rows(const uint32_t* __restri
 
 // The batched launches of the serving pool: whole lattices of different jobs,
 // each with its own shape, schedule and sweep index, a work-group per item.
-// Table entries are uniform per work-group.
+// Table entries are uniform per work-group.  (The draw keeps its copy of an
+// entry, whose family pointers it indexes, in 232 B of scratch per lane.)
 struct CellItem {
     int32_t job, lattice;
 };

@@ -954,9 +954,9 @@ bool use_msc(const micsa_ctx* c, int64_t n = kMscMinSweeps, int32_t algo = MICSA
     return c->kernel_opt == MICSA_KERNEL_AUTO && !use_resident(c) && n >= kMscMinSweeps;
 }
 
-// The slab variant (a lattice too large for one work-group and too narrow
-// for the fused sweep) is asked for where a plane has at most this many
-// 4-site words.
+// The slab form (a lattice too large for one work-group and too narrow for
+// the fused sweep; the cell sweep runs it) may be asked for where a plane has at
+// most this many 4-site words.
 constexpr int kSlabLanes = 1024;
 bool slab_eligible(const micsa_ctx* c)
 {
@@ -1067,7 +1067,6 @@ int launch_fused_sweep(micsa_ctx* c, bool refresh, int64_t rho, double T, int wa
     return MICSA_OK;
 }
 
-// Both halves with daemon family fam.
 // Tile of the two-sweep kernel: TY + 8 ring rows of NC lanes within
 // kSweep2Lanes; the tile options apply where they fit.
 FusedTile choose_tile2(const micsa_ctx* c)
@@ -1680,14 +1679,12 @@ constexpr int64_t kMscDrawWindow = 1024;
 int sweep_msc(micsa_ctx* c, int64_t n, bool walkers = false)
 {
     const MscGeom m = msc_geom(c);
-    const size_t words = (size_t)c->L * 2 * (size_t)m.plane;
     const MscTile f = msc_tile(c);
     const int lanes = (f.TY + 4) * m.W;
     const bool one = msc_one_launch(c);
     const bool ahead = one && c->draw_ahead;
     const bool fits2 = msc2_fits(c);
     const MscTile f2 = c->tile2;
-    (void)words;
     if (int st = msc_alloc(c, one, ahead)) return st;
     int st = MICSA_OK;
     const int64_t k_end = c->k + n;
@@ -2020,8 +2017,8 @@ double msc_cost(const micsa_ctx* c) { return c->tile2.TY > 0 ? msc2_cost(c, c->t
 
 // MicSA takes the cell sweep: on request for the resident and slab forms,
 // and by default unless the multispin pass is estimated faster (us per sweep,
-// cells against the pass: 128^3 2.9 and 12.8, 256^3 9.4 and 13.5, 128^3 x 32
-// 20.2 and 17.6, 512^3 73.5 and 17).
+// cells against the pass: 128^3 2.7 and 12.8, 256^3 9.4 and 5.4, 128^3 x 32
+// 20.2 and 9.0, 512^3 73.5 and 15.7).
 // The bit-plane layout takes it for calls of at least kMscMinSweeps sweeps
 // (a call packs the planes if they are stale) unless a launch shape of its
 // own sweep is asked for: 256 x 2 lattices of 32^3 take 0.8 us per sweep, the
@@ -2411,8 +2408,12 @@ int sweep_cells_families(micsa_ctx* c, int64_t n, bool walkers)
 }
 
 // Walkers on the cell kernel: against the per-half kernels and their wandering
-// pass always; against the multispin and fused byte sweeps (one walker per
-// site) where those leave the device idle (us per sweep, cells against them).
+// pass always; against the multispin pass (one walker per site) by the two
+// estimates; against the fused byte sweeps where the plan's estimate (a fifth
+// more for the wandering) stays below theirs, 8 us for the launches or 1400
+// updates/ns, twice what they reach.  us per sweep, cells against fused: 160^3
+// 5.5 and 12.4, 160^3 x 16 29 and 73, 192^3 x 4 10.8 and 35, 224 x 64 x 64 3.5
+// and 11.9, 320^3 21 and 44, 352^3 32 and 49.
 bool use_cells_walkers(const micsa_ctx* c, int64_t n)
 {
     if (!c->plan.ok || c->no_room || c->off_cells || c->bit) return false;
@@ -2432,7 +2433,9 @@ bool use_cells_walkers(const micsa_ctx* c, int64_t n)
 // per four updates and about as much again for the comparisons, in the sweep
 // itself: at most 700 updates/ns on a full device, where the draws alone run
 // at about 1550 and the sweep adds its plan's estimate.  Lattices too narrow
-// for the fused kernel pay two launches per sweep there.
+// for the fused kernel pay two launches per sweep there.  us per sweep of the
+// heat bath (Metropolis), cells against fused: 128^3 5.6 (4.7) and 20 (21), 128^3 x
+// 32 60 (57) and 138 (154), 256^3 21 (19) and 34 (37), 512^3 136 (120) and 190 (210).
 bool use_cells_canonical(const micsa_ctx* c)
 {
     if (!c->plan.ok || c->no_room || c->off_cells || c->bit) return false;

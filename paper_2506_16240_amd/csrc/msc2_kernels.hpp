@@ -82,7 +82,12 @@
 // per unit spread evenly: 15.2 us per sweep at 512^3 (rows of eight words, 32 x
 // 16 tiles), of which 10.3 us with neither loads nor stores.  Where every row
 // of the lattice fits the lanes there is no ring along y (Lx = 128: 9.4 against
-// 15.5 us per sweep of 32 lattices of 128^3).
+// 15.5 us per sweep of 32 lattices of 128^3).  At 512^3 the VALU is busy 41 % of a
+// launch; 2.4 waves per SIMD spend 40 % of their time in waits for memory, LDS and
+// barriers and 25 % waiting to issue.  Walkers with a refresh in the pair's second
+// sweep (RJ = 1: odd periods, powers of two) spill 12 of 128 registers: 39.3 us per
+// sweep at a refresh every 5 sweeps, 30.5 at one every 6 (daemons, which do not
+// spill, 30.2 and 25.4).
 
 #pragma once
 #include <type_traits>

@@ -384,9 +384,9 @@ __global__ __launch_bounds__(kPtBlock) void k_pt_emcs(PtGeom g, const int4* __re
 // moving class with site j (or j + 1 when the class starts at x = 1) of the
 // other class, all within the row.
 // It runs the Metropolis sweeps, and the walkers of lattices whose field tables
-// (k_pt_emcs_tab) exceed LDS.  Metropolis stays within 64 registers, so that
+// (k_pt_emcs_tab) exceed LDS.  Metropolis is held to 64 registers, so that
 // two work-groups share a compute unit (10^3 with Houdayer moves: 605 us per
-// EMCS, 790 with one).
+// EMCS, 790 with one); with those moves 22 spill.
 // LDS: tables [G][kPtTable] u32 | records [N][2] int4 | rows [G][2][R0] u32 |
 //      mark, diff [G][R0] u32 | energies [G][2] u64; the Houdayer move
 //      keeps the neighbour rows [R0] 4 x u16 over the tables.
