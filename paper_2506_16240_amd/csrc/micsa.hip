@@ -2712,11 +2712,12 @@ bool takes_cells(const micsa_ctx* c, int32_t algo, int64_t n)
 // 400 x 400, MicSA 26 / 23, heat bath 45 / 30 (60 sweeps: 30.3 / 28.6).
 // The state moves from the planes to those arrays, and back for the next long
 // call: a short call stays where its state is until such calls have lost what the
-// move costs.
+// move costs, and on the planes as long as there is a tally to lose.
 void choose_arrays(micsa_ctx* c, int32_t algo, int64_t n)
 {
     if (!c->bit && (c->g.Kx > 12 || c->plan.sweeps == 0)) return;
     if (c->captured || c->no_room || !c->plan.ok || algo == MICSA_ALGO_WALKERS || !takes_cells(c, algo, kMscMinSweeps)) return;
+    if (c->bit && !bp_one_launch(c) && c->tally_ok) return;  // (the per-half kernels keep no tally)
     const double sites = (double)c->L * 2.0 * (double)c->g.Nh;
     const CellPlan& pl = plan_for(c, n);
     // (the cost of a tiled plan has its launches in it)

@@ -322,3 +322,15 @@ def test_calls_that_move_between_planes_and_the_layouts_arrays(shape, layout, al
         assert np.array_equal(g.energy(), o.energy()) and np.array_equal(g.energy_tally(), o.energy())
     assert np.array_equal(g.daemons(), o.m) and np.array_equal(g.spins(), o.sigma)
     g.close()
+
+
+def test_the_tally_of_bit_planes_outlives_short_calls():
+    """Planes of more words than the one-launch sweep takes: single sweeps after
+    a long call, which the per-half kernels would do faster, keep the tally."""
+    g = M.Lattice(8, 400, 64, 64, 1, 0x7A11, layout=M.LAYOUT_BITPLANE)
+    g.set_schedule(M.Schedule(M.SCHED_CONST, 0.8, 0.8, 100, 4))
+    g.sweep(M.ALGO_MICSA, 9)
+    for _ in range(12):
+        g.sweep(M.ALGO_MICSA, 1)
+    assert np.array_equal(g.energy_tally(), g.energy())
+    g.close()
