@@ -2715,7 +2715,7 @@ bool takes_cells(const micsa_ctx* c, int32_t algo, int64_t n)
 // move costs, and on the planes as long as there is a tally to lose.
 void choose_arrays(micsa_ctx* c, int32_t algo, int64_t n)
 {
-    if (!c->bit && (c->g.Kx > 12 || c->plan.sweeps == 0)) return;
+    if (!c->bit && (c->g.Kx > 12 || c->plan.sweeps == 0 || c->kernel_opt != MICSA_KERNEL_AUTO)) return;
     if (c->captured || c->no_room || !c->plan.ok || algo == MICSA_ALGO_WALKERS || !takes_cells(c, algo, kMscMinSweeps)) return;
     if (c->bit && !bp_one_launch(c) && c->tally_ok) return;  // (the per-half kernels keep no tally)
     const double sites = (double)c->L * 2.0 * (double)c->g.Nh;

@@ -334,3 +334,17 @@ def test_the_tally_of_bit_planes_outlives_short_calls():
         g.sweep(M.ALGO_MICSA, 1)
     assert np.array_equal(g.energy_tally(), g.energy())
     g.close()
+
+
+def test_short_calls_run_the_form_that_was_asked_for():
+    """One launch per single sweep on the cell sweep, also where the per-half
+    kernels (two launches) would be faster."""
+    g = M.Lattice(8, 400, 400, 1, 8, 0x0F0A)
+    g.set_option(M.OPT_SWEEP_KERNEL, M.KERNEL_SLAB)
+    g.set_schedule(M.Schedule(M.SCHED_CONST, 0.8, 0.8, 100, 50))
+    g.sweep(M.ALGO_MICSA, 9)
+    g.set_timing(True)
+    for _ in range(12):
+        g.sweep(M.ALGO_MICSA, 1)
+    assert g.timing(M.TIME_SWEEP)[1] == 12
+    g.close()
