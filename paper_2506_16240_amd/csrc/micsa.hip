@@ -1908,16 +1908,16 @@ struct CellLoad {
     int waves;
 };
 
-CellLoad cell_load(const micsa_ctx* c, int nr, int xm, unsigned block, double wgs)
+CellLoad cell_load(const micsa_ctx* c, int nr, int xm, unsigned block, int64_t wgs)
 {
     CellLoad d;
     d.waves = (int)block / 64;
     const double issue = kCellIssue * (xm == 0 ? 1.0 : (xm == 1 ? 1.15 : 1.2)) * nr;  // of one wave and half
-    const int fit = std::max(1, (nr == 1 ? 32 : (nr == 2 ? 20 : 16)) / d.waves);
-    const double per_cu = std::ceil(wgs / (c->cus > 0 ? c->cus : 256));
-    d.m = std::min<double>(per_cu, fit);
-    d.rounds = per_cu / d.m;
-    d.half = std::max(kCellChain + issue, std::ceil(d.m * d.waves / 4.0) * issue + 100.0);
+    const int fit = std::max(1, (nr == 1 ? 32 : (nr == 2 ? 20 : 16)) / d.waves), cus = c->cus > 0 ? c->cus : 256;
+    const int64_t per_cu = (wgs + cus - 1) / cus, m = std::min<int64_t>(per_cu, fit);
+    d.m = (double)m;
+    d.rounds = (double)per_cu / d.m;
+    d.half = std::max(kCellChain + issue, (double)((m * d.waves + 3) / 4) * issue + 100.0);
     return d;
 }
 
@@ -1928,53 +1928,52 @@ CellPlans cell_plans(const micsa_ctx* c)
     if (!cells_shape_ok(c)) return plans;
     const int W = (c->g.Kx + 31) / 32, Ly = c->p.Ly, Lz = c->p.Lz;
     const int xm = W == 1 ? 0 : (c->g.Kx % 32 == 0 ? 1 : 2);
-    auto consider = [&](int TY, int TZ, int T) {
-        CellTile f{};
-        const int G = 2 * T;
-        f.TY = TY;
-        f.TZ = TZ;
-        f.GY = TY < Ly ? G : 0;
-        f.GZ = TZ < Lz ? G : 0;
-        f.EY = TY + 2 * f.GY;
-        f.EZ = TZ + 2 * f.GZ;
-        f.nty = (Ly + TY - 1) / TY;
-        f.ntz = (Lz + TZ - 1) / TZ;
-        f.inv_EYW = 1.0f / (float)(f.EY * W);
-        f.inv_W = 1.0f / (float)W;
-        f.inv_Ly = 1.0f / (float)Ly;
-        f.inv_Lz = 1.0f / (float)Lz;
-        const int64_t cells = (int64_t)f.EY * f.EZ * W;
-        const int nr = (int)((cells + kCellLanes - 1) / kCellLanes);
+    // (a context of a tiled lattice weighs over a thousand tiles when it is made, in
+    // a few us: few divisions, and a plan put together only where it is the best)
+    double brief[kBriefSweeps];  // us of a call of n + 1 sweeps, and the launches of it
+    double launches[kBriefSweeps];
+    std::fill_n(brief, kBriefSweeps, 1e300);
+    auto consider = [&](int TY, int TZ, int nty, int ntz, int T) {
+        const int G = 2 * T, GY = TY < Ly ? G : 0, GZ = TZ < Lz ? G : 0, EY = TY + 2 * GY, EZ = TZ + 2 * GZ;
+        const int cells = EY * EZ * W;  // (at most kCellCap)
+        const int nr = (cells + kCellLanes - 1) / kCellLanes;
         // (four cells of rows with a short last word, or of several families, do
         // not fit the registers; nor do three of several families with more than
         // a word per row: 4 x 160^3 with two daemons 20.8 us per sweep, on two 13.3)
-        if (nr > (c->gamma > 1 ? (xm == 0 ? 3 : 2) : (xm == 2 ? 3 : kCellMaxNR)) || f.ntz > 65535) return;
-        const bool whole = f.nty * f.ntz == 1;
-        const int block = (int)(((cells + nr - 1) / nr + 63) / 64 * 64);
-        const double wgs = (double)f.nty * f.ntz * c->L;
+        if (nr > (c->gamma > 1 ? (xm == 0 ? 3 : 2) : (xm == 2 ? 3 : kCellMaxNR)) || ntz > 65535) return;
+        const bool whole = nty == 1 && ntz == 1;
+        const int block = ((cells + nr - 1) / nr + 63) / 64 * 64;
+        const int64_t wgs = (int64_t)nty * ntz * c->L;
         const CellLoad d = cell_load(c, nr, xm, (unsigned)block, wgs);
-        const double load = kCellLaunch * d.rounds + (double)cells * wgs * 72.0 / kCellBytes;
+        const double load = kCellLaunch * d.rounds + (double)cells * (double)wgs * 72.0 / kCellBytes;
         // (several families: at most one sweep of each per launch)
         const double sweep = d.rounds * d.half * 2.0;
         const double t = sweep + (whole ? (c->gamma > 1 ? load / c->gamma : 0.0) : load / T);
-        CellPlan p;
-        p.ok = true;
-        p.f = f;
-        p.nr = nr;
-        p.xm = xm;
-        p.block = (unsigned)block;
-        p.sweeps = whole ? 0 : T;
-        p.cost = t;
-        p.load = load;
-        if (!best.ok || t < best.cost) best = p;
+        auto put = [&](CellPlan& p, double call) {
+            p.ok = true;
+            p.f = CellTile{TY, TZ, GY, GZ, EY, EZ, nty, ntz, 1.0f / (float)(EY * W), 1.0f / (float)W, 1.0f / (float)Ly,
+                           1.0f / (float)Lz};
+            p.nr = nr;
+            p.xm = xm;
+            p.block = (unsigned)block;
+            p.sweeps = whole ? 0 : T;
+            p.cost = t;
+            p.load = load;
+            p.brief = call;
+        };
+        if (!best.ok || t < best.cost) put(best, 0);
         // (with four cells of rows of several words their kernel spills 56 registers)
-        if (nr <= (xm == 1 ? 3 : kCellMaxNR) && (!plans.walk.ok || t < plans.walk.cost)) plans.walk = p;
-        for (int n = 1; n <= kBriefSweeps; ++n) {
-            p.brief = std::ceil((double)n / (whole ? std::max(n, 1) : T)) * load + n * sweep;
-            if (!plans.brief[n].ok || p.brief < plans.brief[n].brief) plans.brief[n] = p;
-        }
+        if (nr <= (xm == 1 ? 3 : kCellMaxNR) && (!plans.walk.ok || t < plans.walk.cost)) put(plans.walk, 0);
+        bool better = false;
+        for (int i = 0; i < kBriefSweeps; ++i) better |= launches[i] * load + (i + 1) * sweep < brief[i];
+        for (int i = 0; better && i < kBriefSweeps; ++i)
+            if (launches[i] * load + (i + 1) * sweep < brief[i]) {
+                brief[i] = launches[i] * load + (i + 1) * sweep;
+                put(plans.brief[i + 1], brief[i]);
+            }
     };
-    if ((int64_t)Ly * Lz * W <= kCellCap) consider(Ly, Lz, 1);
+    std::fill_n(launches, kBriefSweeps, 1.0);
+    if ((int64_t)Ly * Lz * W <= kCellCap) consider(Ly, Lz, 1, 1, 1);
     if (best.ok && best.nr <= 2) {  // no tile makes up for its launches here
         plans.walk = best;
         return plans;
@@ -1994,12 +1993,15 @@ CellPlans cell_plans(const micsa_ctx* c)
     const std::vector<int> ys = sides(Ly), zs = sides(Lz);
     for (int T : {1, 2, 3, 4, 6, 8}) {
         if (c->gamma > 1 && T > c->gamma) break;
-        for (int ty : ys)
+        for (int i = 0; i < kBriefSweeps; ++i) launches[i] = (i + T) / T;
+        for (int ty : ys) {
+            const int nty = (Ly + ty - 1) / ty;
             for (int tz : zs) {
                 if (ty == Ly && tz == Lz) continue;
                 if ((int64_t)(ty + (ty < Ly ? 4 * T : 0)) * (tz + (tz < Lz ? 4 * T : 0)) * W <= kCellCap)
-                    consider(ty, tz, T);
+                    consider(ty, tz, nty, (Lz + tz - 1) / tz, T);
             }
+        }
     }
     return plans;
 }
