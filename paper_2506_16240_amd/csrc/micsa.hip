@@ -172,7 +172,6 @@ struct micsa_ctx {
     // device memory: blocks of this context, from the pool's store if it has
     // one; what is known at creation lies in the first, filled from its start
     JobStore* store = nullptr;
-    bool pooled = false;  // (a job's shape too, which has no store)
     std::vector<JobStore::Block> owned;
     uint8_t* arena = nullptr;
     size_t arena_left = 0;
@@ -3024,8 +3023,7 @@ static CtxBytes ctx_bytes(const micsa_ctx* c)
     b.msc = !b.cells && !c->bit && c->gamma == 1 && msc_eligible(c);
     b.home = arena_size((size_t)c->L * kSlots * 8) + arena_size(b.nred * kSlots * 8) +
              (c->bit ? 3 * arena_size(b.words * 8) + arena_size(b.bonds)
-                     : (b.alt ? 2 : 1) * (arena_size(b.state) + arena_size(b.dstate)) +
-                           (c->gamma > 1 && !c->pooled ? arena_size(b.dstate) : 0));
+                     : (b.alt ? 2 : 1) * (arena_size(b.state) + arena_size(b.dstate)));
     if (b.msc || (b.cells && msc_eligible(c))) {
         const size_t mw = (size_t)c->L * 2 * (size_t)msc_geom(c).plane * 8;
         b.work = (b.msc ? 8 : 6) * arena_size(mw) + arena_size(3 * mw);
@@ -3056,7 +3054,6 @@ static int create_ctx(const micsa_params* p, hipStream_t stream, const micsa_ctx
     }
     c->draw_room = like ? like->draw_room : 0;
     c->store = store;
-    c->pooled = store != nullptr;
     if (stream_captured(stream)) {  // the initial state is no part of a graph
         delete c;
         return MICSA_EHIP;
@@ -3079,7 +3076,6 @@ static int create_ctx(const micsa_params* p, hipStream_t stream, const micsa_ctx
     if (ok && !c->bit) {
         ok = ctx_alloc(c, c->spin, state) && ctx_alloc(c, c->dem, dstate);
         if (ok && alt) ok = need_alt(c) == MICSA_OK;
-        if (ok && gamma > 1 && !c->pooled) ok = need_dem_alt(c) == MICSA_OK;
     } else if (ok) {
         ok = ctx_alloc(c, c->bspin, words * 8) && ctx_alloc(c, c->bdm0, words * 8) &&
              ctx_alloc(c, c->bdm1, words * 8) && ctx_alloc(c, c->bJ, bonds);
@@ -4206,7 +4202,7 @@ size_t footprint(const micsa_params* p)
     return bytes;
 }
 
-// What a job of this shape (setup_ctx, draw_room set, pooled) holds.  A bit-plane
+// What a job of this shape (setup_ctx, draw_room set) holds.  A bit-plane
 // job, whose chunks may be too short for the planes, has second copies of its
 // words then.
 size_t job_need(const micsa_ctx* shape)
@@ -4222,7 +4218,6 @@ void plan_job(PoolJob& j)
 {
     micsa_ctx shape;
     (void)setup_ctx(&shape, &j.p, nullptr);
-    shape.pooled = true;
     j.plans.main = shape.plan;
     j.plans.walk = shape.walk;
     std::copy(std::begin(shape.brief), std::end(shape.brief), j.plans.brief);
@@ -4567,7 +4562,6 @@ int micsa_pool_step(micsa_pool* pool, int64_t sweeps, int32_t* running, int32_t*
         const size_t most = j.bytes + spare + (size_t)(shape.L - shape.p.n_samples) * kSlots * 8 + 4096;
         int fit = 0;
         while (fit < 2 && j.need[fit] > most) ++fit;
-        shape.pooled = true;
         shape.draw_room = j.draw_room[std::min(fit, 1)];
         shape.plan.ok = shape.plan.ok && fit < 2;
         const size_t charge = std::max(j.bytes, j.need[fit]);
