@@ -339,65 +339,62 @@ __global__ void __launch_bounds__(256) k_heatbath_half(Geom g, uint8_t* __restri
 // ------------------------------------------------------------- wandering
 // Walkers (Sec. 2.6): the wandering step along direction dir (+x, -x, +y,
 // -y, +z, -z) exchanges the level of every site s of parity p with that of
-// s + e_dir.  Written as two gathers into the other buffer: a site of parity
-// p takes the level at s + e_dir, a site of parity 1-p the level at t - e_dir
-// (both sites of the other parity).  Thread per word position (row, c) of
-// both parity arrays; grid.y over (lattice, family) pairs d = l*gamma + a.
+// s + e_dir, a site of the other parity: disjoint pairs, so in place, and no
+// second copy of the levels is needed by contexts that only now and then put an
+// owed wandering into these arrays.  Thread per word position (row, c) of
+// parity p's array; grid.y over (lattice, family) pairs d = l*gamma + a.
 // Family a wanders along kWalkerDir[a] (Sec. 2.8: forward X, Y, Z, then
 // backward X, Y, Z).
+// Bound: HBM; every level read and written once.  Partners are whole words
+// but for the x rows where they lie a site further, which go by bytes (a word
+// there is two threads', each with bytes of its own).  Measured against two
+// gathers into a second copy (us per wandering): 512 x 512 x 128, one family 17
+// both, six along each axis 12 (23); 16 of 64^3, which L2 holds, 5.0 (3.8).
 __constant__ const int kWalkerDir[6] = {kPx, kPy, kPz, kMx, kMy, kMz};
 
-// Parity of each family's wandering; a family with -1 stays (is copied).
+// Parity of each family's wandering; a family with -1 stays.
 struct WanderParity {
     int32_t p[6];
 };
 
-__global__ void __launch_bounds__(256) k_wander(Geom g, const uint8_t* __restrict__ dem_in,
-                                                uint8_t* __restrict__ dem_out, WanderParity wp)
+__global__ void __launch_bounds__(256) k_wander(Geom g, uint8_t* dem, WanderParity wp)
 {
     const int l = blockIdx.y;  // (lattice, family) pair
     const int dir = kWalkerDir[l % g.gamma];
     const int p = wp.p[l % g.gamma];
     const uint32_t w = blockIdx.x * blockDim.x + threadIdx.x;
-    if (w >= (uint32_t)g.rows * (uint32_t)g.Wr) return;
-    if (p < 0) {
-        for (int par = 0; par < 2; ++par)
-            reinterpret_cast<uint32_t*>(dem_out + ((int64_t)l * 2 + par) * g.Nh)[w] =
-                reinterpret_cast<const uint32_t*>(dem_in + ((int64_t)l * 2 + par) * g.Nh)[w];
-        return;
-    }
+    if (p < 0 || w >= (uint32_t)g.rows * (uint32_t)g.Wr) return;
     const int row = (int)(w / (uint32_t)g.Wr), c = (int)(w - (uint32_t)row * (uint32_t)g.Wr);
-    const int z = row / g.Ly, y = row - z * g.Ly;
-    const int sgn = (dir & 1) ? -1 : 1;  // even dir index: forward
+    int z = row / g.Ly, y = row - z * g.Ly;
+    const bool fwd = !(dir & 1);  // even dir index: forward
     const int axis = dir >> 1;
-    const int qp = (p + y + z) & 1;      // sites of parity p sit at x = 2k + qp
-    const int64_t wr = g.Wr;
-    for (int a = 0; a < 2; ++a) {  // destination parity array: a == 0 -> parity p
-        const int par = a == 0 ? p : 1 - p;
-        const uint32_t* src = reinterpret_cast<const uint32_t*>(dem_in + ((int64_t)l * 2 + (1 - par)) * g.Nh);
-        uint32_t* dst = reinterpret_cast<uint32_t*>(dem_out + ((int64_t)l * 2 + par) * g.Nh);
-        const int toward = a == 0 ? sgn : -sgn;  // partner offset along the axis
-        uint32_t v;
-        if (axis == 0) {
-            // x +- 1 of a site at x = 2k + q of this parity is at index k + shift in the other array
-            const int q = a == 0 ? qp : 1 - qp;
-            const int shift = toward > 0 ? q : q - 1;  // 0 or +1, or -1 or 0
-            const uint32_t A = src[row * wr + c];
-            if (shift == 0) {
-                v = A;
-            } else {
-                const int cs = shift > 0 ? (c + 1 == g.Wr ? 0 : c + 1) : (c == 0 ? g.Wr - 1 : c - 1);
-                v = shift_word(A, src[row * wr + cs], shift);
+    uint32_t* own = reinterpret_cast<uint32_t*>(dem + ((int64_t)l * 2 + p) * g.Nh) + w;
+    uint8_t* oth = dem + ((int64_t)l * 2 + 1 - p) * g.Nh;
+    if (axis == 0) {
+        // x +- 1 of a site at x = 2k + q of this parity is at index k + shift in the other array
+        const int q = (p + y + z) & 1, shift = fwd ? q : q - 1;  // 0 or +1, or -1 or 0
+        if (shift != 0) {
+            uint8_t* r = oth + (int64_t)row * g.Kx;
+            const uint32_t v = *own;
+            uint32_t got = 0;
+            for (int i = 0; i < 4; ++i) {
+                int k = 4 * c + i + shift;
+                k = k == g.Kx ? 0 : (k < 0 ? g.Kx - 1 : k);
+                got |= (uint32_t)r[k] << (8 * i);
+                r[k] = (uint8_t)(v >> (8 * i));
             }
-        } else if (axis == 1) {
-            const int yy = toward > 0 ? (y + 1 == g.Ly ? 0 : y + 1) : (y == 0 ? g.Ly - 1 : y - 1);
-            v = src[(int64_t)(yy + g.Ly * z) * wr + c];
-        } else {
-            const int zz = toward > 0 ? (z + 1 == g.Lz ? 0 : z + 1) : (z == 0 ? g.Lz - 1 : z - 1);
-            v = src[(int64_t)(y + g.Ly * zz) * wr + c];
+            *own = got;
+            return;
         }
-        dst[w] = v;
+    } else if (axis == 1) {
+        y = fwd ? (y + 1 == g.Ly ? 0 : y + 1) : (y == 0 ? g.Ly - 1 : y - 1);
+    } else {
+        z = fwd ? (z + 1 == g.Lz ? 0 : z + 1) : (z == 0 ? g.Lz - 1 : z - 1);
     }
+    uint32_t* o = reinterpret_cast<uint32_t*>(oth) + (int64_t)(y + g.Ly * z) * g.Wr + c;
+    const uint32_t v = *own;
+    *own = *o;
+    *o = v;
 }
 
 // -------------------------------------------------------------- reductions

@@ -1027,19 +1027,13 @@ CellGeom cell_geom(const micsa_ctx* c);
 uint32_t* w32(uint64_t* p);
 
 // The alternate byte arrays (allocated with the context where a path that
-// needs them is the default, else by the first call that takes one; walkers
-// need the daemons' for the wandering that a sweep leaves owed).
-int need_dem_alt(micsa_ctx* c)
-{
-    if (!c->dem_alt) ctx_alloc(c, c->dem_alt, (size_t)c->L * 2 * (size_t)c->g.Nh * (size_t)c->gamma);
-    return c->dem_alt ? MICSA_OK : fail(c, MICSA_ENOMEM, "alternate daemons");
-}
-
+// needs them is the default, else by the first call that takes one).
 int need_alt(micsa_ctx* c)
 {
-    if (!c->spin_alt) ctx_alloc(c, c->spin_alt, (size_t)c->L * 2 * (size_t)c->g.Nh);
-    const int st = need_dem_alt(c);
-    return st || c->spin_alt ? st : fail(c, MICSA_ENOMEM, "alternate spins");
+    const size_t state = (size_t)c->L * 2 * (size_t)c->g.Nh;
+    if (!c->spin_alt) ctx_alloc(c, c->spin_alt, state);
+    if (!c->dem_alt) ctx_alloc(c, c->dem_alt, state * (size_t)c->gamma);
+    return c->spin_alt && c->dem_alt ? MICSA_OK : fail(c, MICSA_ENOMEM, "alternate state buffers");
 }
 
 int launch_fused_sweep(micsa_ctx* c, bool refresh, int64_t rho, double T, int wander = -1)
@@ -1369,16 +1363,12 @@ int check_sweep(micsa_ctx* c, int32_t algo, int64_t n)
 // family along its own direction, the half of the cycle given by t's parity).
 int launch_wander_families(micsa_ctx* c, const WanderParity& wp)
 {
-    if (int st = need_dem_alt(c)) return st;
     const int64_t words = (int64_t)c->g.rows * c->g.Wr;
     {
         TimedLaunch tl(c, kTimeSweep);
-        k_wander<<<grid_for(words, c->L * c->gamma), kBlock, 0, c->stream>>>(c->g, c->dem, c->dem_alt, wp);
+        k_wander<<<grid_for(words, c->L * c->gamma), kBlock, 0, c->stream>>>(c->g, c->dem, wp);
     }
-    const int st = check_launch(c, "k_wander");
-    if (st) return st;
-    std::swap(c->dem, c->dem_alt);
-    return MICSA_OK;
+    return check_launch(c, "k_wander");
 }
 
 int launch_wander(micsa_ctx* c, int64_t t)
@@ -2775,9 +2765,7 @@ bool logs_in_kernel(micsa_ctx* c, int32_t algo, int64_t n)
 int sweep_logging(micsa_ctx* c, int32_t algo, int64_t n, long long* dlog, int64_t stride)
 {
     if (n <= 0) return MICSA_OK;
-    int st = begin_sweeps(c);
-    if (!st && algo == MICSA_ALGO_WALKERS) st = need_dem_alt(c);
-    if (st) return end_sweeps(c, st);
+    if (int st = begin_sweeps(c)) return end_sweeps(c, st);
     return end_sweeps(c, algo == MICSA_ALGO_MICSA || algo == MICSA_ALGO_WALKERS
                              ? sweep_cells(c, n, dlog, stride, algo == MICSA_ALGO_WALKERS)
                              : sweep_cells_canonical(c, algo, n, dlog, stride));
@@ -2797,7 +2785,6 @@ int sweep_run(micsa_ctx* c, int32_t algo, int64_t n)
 {
     int st0 = check_sweep(c, algo, n);
     if (st0) return st0;
-    if (algo == MICSA_ALGO_WALKERS && n > 0 && (st0 = need_dem_alt(c))) return st0;
     if (n > 0) choose_arrays(c, algo, n);
     find_room(c, algo, n);
     // walkers (gamma = 1) on the fused sweep carry their wandering into the

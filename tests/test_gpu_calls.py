@@ -79,8 +79,8 @@ def memory(counted, monkeypatch):
 
 @pytest.mark.parametrize("shape,gamma", [((16, 16, 16, 1, 3), 1), ((64, 64, 64, 1, 1), 1), ((16, 16, 16, 1, 3), 3)])
 def test_walkers_without_room_for_their_wandering(memory, shape, gamma):
-    """A walker call takes the room that its wandering will need before it
-    changes anything, so that a read never lacks it."""
+    """A walker call without memory changes nothing or is made, and leaves
+    nothing owed that a read would lack room for."""
     with M.Lattice(*shape, 5, gamma=gamma) as g:
         o = O.Lattice(*shape, 5, gamma=gamma)
         g.set_schedule(M.Schedule(M.SCHED_CONST, 0.9, 0.9, 200, 4))
@@ -98,6 +98,17 @@ def test_walkers_without_room_for_their_wandering(memory, shape, gamma):
             assert np.array_equal(g.daemon_energy(), o.daemon_energy())
             assert np.array_equal(g.daemons(), o.m) and np.array_equal(g.spins(), o.sigma)
             memory.bound()
+
+
+@pytest.mark.parametrize("shape,gamma", [((16, 16, 16, 1, 3), 1), ((96, 40, 20, 1, 1), 1), ((16, 16, 16, 1, 3), 6),
+                                         ((128, 64, 8, 1, 1), 1)])
+def test_walker_calls_allocate_nothing(memory, shape, gamma):
+    """The wandering that a call leaves owed needs no second copy of the levels."""
+    with M.Lattice(*shape, 5, gamma=gamma) as g:
+        g.set_schedule(M.Schedule(M.SCHED_CONST, 0.9, 0.9, 200, 4))
+        held = memory.held()
+        g.sweep(M.ALGO_WALKERS, 2 * gamma + 1)
+        assert memory.held() == held
 
 
 def _home_bytes(shape, layout):

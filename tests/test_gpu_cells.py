@@ -348,3 +348,19 @@ def test_short_calls_run_the_form_that_was_asked_for():
         g.sweep(M.ALGO_MICSA, 1)
     assert g.timing(M.TIME_SWEEP)[1] == 12
     g.close()
+
+
+@pytest.mark.parametrize("dims", [(8, 2, 2), (8, 4, 6), (24, 2, 10), (40, 6, 4), (72, 10, 2)])
+@pytest.mark.parametrize("gamma", [1, 6])
+def test_the_wandering_in_place(dims, gamma):
+    """On the byte arrays, timestep by timestep: rows of one word and more, whose
+    ends meet, sides of two, every direction, several lattices."""
+    g, o = M.Lattice(*dims, 2, 2, 0x3A1D, gamma=gamma), O.Lattice(*dims, 2, 2, 0x3A1D, gamma=gamma)
+    g.set_option(M.OPT_SWEEP_KERNEL, M.KERNEL_SIMPLE)
+    g.set_schedule(M.Schedule(M.SCHED_CONST, 1.1, 1.1, 60, 3))
+    os_ = O.Schedule(O.SCHED_CONST, 1.1, 1.1, 60, 3)
+    for n in (gamma, 2 * gamma, 1, gamma + 1):
+        g.sweep(M.ALGO_WALKERS, n)
+        o.run(O.ALGO_WALKERS, os_, n, 0)
+        assert np.array_equal(g.daemons(), o.m) and np.array_equal(g.spins(), o.sigma)
+    g.close()
